@@ -68,15 +68,16 @@ struct Ws {
   size_t total;
   int64_t PB;   // primaries per pair-block
   int spill_cap;  // spill-list entries per wave (0: none)
+  int parts;    // partial Gram products of a pair-block
   Grid grid;
   RowLayout lay;
 };
 
 // Workspace layout.  pb_max caps the primaries of a pair-block (the a_lm rows
-// held at once); spill = false leaves out the spill lists (a multi-chunk basis
-// then repeats its search per chunk).
+// held at once); compact = true leaves out the spill lists (a multi-chunk basis
+// then repeats its search per chunk) and keeps the Gram partials to four.
 Ws plan(const g3pcf_problem& p, int backward, int64_t pb_max = kPairBlockMax,
-        bool spill = true) {
+        bool compact = false) {
   Ws w{};
   const int64_t n = p.n;
   const int fp64 = (p.pair_prec == G3PCF_PREC_FP64);
@@ -108,11 +109,13 @@ Ws plan(const g3pcf_problem& p, int backward, int64_t pb_max = kPairBlockMax,
   w.scan = take(w.scan_bytes);
   w.counters = take(kCountersBytes);
   // per-wave spill lists for bases accumulated in several register chunks
-  const bool multi = spill && (fp64 || p.basis == G3PCF_BASIS_CARTESIAN);
+  const bool multi = !compact && (fp64 || p.basis == G3PCF_BASIS_CARTESIAN);
   w.spill = take(multi ? size_t(kPairWaves) * kSpillCap * 4 : 0);
   w.spill_cap = multi ? kSpillCap : 0;
   w.A = take(size_t(w.PB) * w.lay.W * 8);
-  w.C = take(zeta_partial_doubles(w.lay, w.PB) * 8);
+  // the compact layout's pair-blocks are one block of kZetaBlock rows
+  w.parts = compact ? 4 : zeta_parts(w.lay, w.PB);
+  w.C = take(size_t(w.parts) * sum_wm2(w.lay) * 8);
   // degenerate triangles: per-shell Legendre sums and their per-workgroup partials
   const bool deg = !backward && p.distinct;
   w.degD = take(deg ? size_t(p.nbins) * (2 * p.lmax + 1) * 8 : 0);
@@ -388,10 +391,10 @@ int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, i
       z.plist = a.plist;
       z.nprim = &c->nprim;
       z.row_begin = b0;
-      z.sub_begin = 0;
       z.K = a.p_count;
       z.lay = w.lay;
       z.C64 = at<double>(ws, w.C);
+      z.parts = w.parts;
       z.zeta = zeta;
       z.prec = p.zeta_prec;
       if ((e = launch_zeta_pairblock(z, st)) != hipSuccess) return hip_fail(e, "zeta");
@@ -588,7 +591,7 @@ int g3pcf_forward_noalloc(const g3pcf_problem* prob, double* zeta, void* stream)
   int rc = validate(prob);
   if (rc) return rc;
   if (!zeta) return fail(G3PCF_EINVAL, "zeta is NULL");
-  const Ws w = plan(*prob, 0, kScratchPairBlock, false);
+  const Ws w = plan(*prob, 0, kScratchPairBlock, true);
   if (w.total > kScratchBytes)
     return fail(G3PCF_EINVAL, "g3pcf_forward_noalloc: this problem needs " +
                                   std::to_string(w.total) + " bytes of scratch, the library "

@@ -32,10 +32,10 @@ constexpr int kWave = 64;
 constexpr int kSentinel = kWave;
 constexpr int kOutPerBin = (kDeg + 1) * (kDeg + 1);  // real a_lm outputs per shell (121)
 
-// Rows of A (primaries) reduced per Gram product on MFMA.
+// Rows of A (primaries) reduced per Gram product on MFMA: at most, and (where
+// few rows would leave CUs idle) at least.
 constexpr int kZetaBlock = 4096;
-// Split-K slices of the Gram product (partials summed in order in FP64).
-constexpr int kZetaSplitK = 4;
+constexpr int kZetaRowsMin = 128;
 // Primary queues of the pair kernel: one per XCD (workgroups are dispatched to
 // the 8 XCDs round-robin), each counter on its own 64-byte line.
 constexpr int kQueues = 8;
@@ -191,19 +191,17 @@ struct ZetaArgs {
   const int* plist;
   const long long* nprim;
   long long row_begin;       // global primary index of A row 0
-  long long sub_begin;       // first row of this sub-block (relative to A)
-  long long K;               // rows in this sub-block (upper bound)
+  long long K;               // rows of the pair-block (upper bound)
   RowLayout lay;
-  double* C64;               // per-block partial Gram products (FP64)
+  double* C64;               // [parts][sum W_m^2] per-block Gram products (FP64)
+  int parts;                 // blocks the partials have room for (>= K / kZetaBlock)
   double* zeta;
   int prec;
 };
-// Every block of kZetaBlock primaries of a pair-block: z.sub_begin = 0 and
-// z.K = rows of the pair-block.
+// Every block of a pair-block.
 hipError_t launch_zeta_pairblock(const ZetaArgs& z, hipStream_t st);
-// Doubles of the partial-Gram buffer (per-block partials of a pair-block of
-// at most PB primaries).
-size_t zeta_partial_doubles(const RowLayout& L, long long PB);
+// Blocks (partial Gram products) of a pair-block of at most PB primaries.
+int zeta_parts(const RowLayout& L, long long PB);
 
 // Adjoint helpers
 struct AdjArgs {

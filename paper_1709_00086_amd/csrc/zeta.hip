@@ -25,24 +25,34 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ long long valid_rows(const ZetaArgs& z) {
-  // primaries in the pair-block, then rows of this sub-block
-  const long long in_block = (long long)(*z.nprim) - z.row_begin;
-  long long kv = in_block - z.sub_begin;
+  // primaries in the pair-block
+  long long kv = (long long)(*z.nprim) - z.row_begin;
   if (kv > z.K) kv = z.K;
   return kv < 0 ? 0 : kv;
 }
 
+// Rows per Gram block: the valid rows spread over the workspace's partials, a
+// multiple of kZetaRowsMin.  Only the device knows how
+// many primaries there are (a mask or a region may leave few of the rows the
+// launch covers), so the blocks choose it; the ones past the rows leave at once.
+__device__ __forceinline__ long long block_rows(long long kv, int parts) {
+  const long long r = (kv + parts - 1) / parts;
+  return max(r + kZetaRowsMin - 1, (long long)kZetaRowsMin) / kZetaRowsMin * kZetaRowsMin;
+}
+
 // ---- FP32 / FP64: one workgroup per (m, 64 x 64 macro tile of C_m on or
-// above the diagonal, block of 4096 primaries).  Each step stages 32 rows of
+// above the diagonal, block of at most 4096 primaries).  Each step stages 32 rows of
 // the two column ranges in LDS (weights applied to the left operand, FP64 rows
 // converted to the working precision on the way), and each wave accumulates a
 // 32 x 32 quadrant as 2 x 2 MFMA tiles over the block's rows.  The next step's
 // rows are loaded into registers while the current step is multiplied.  In
-// FP32 the MFMA accumulators are added into FP64 ones every 512 rows, so the
+// FP32 the MFMA accumulators are added into FP64 ones every kFlush rows, so the
 // block's partial is FP64 like the sum across blocks.
 constexpr int kMT = 64;     // macro tile
 constexpr int kKS = 32;     // rows per step
-constexpr int kFlush = 512; // rows per FP32 accumulation before the FP64 sum
+// Rows per FP32 accumulation before the FP64 sum: blocks hold whole ones, so
+// the FP32 sums do not depend on how many blocks the rows are cut into.
+constexpr int kFlush = kZetaRowsMin;
 
 struct MDims {
   int nm;
@@ -121,9 +131,10 @@ __global__ __launch_bounds__(256) void k_gram_mt(ZetaArgs z, MDims d, double* __
   macro_tile_of(d, blockIdx.x, m, ti, tj);
   const int W = d.W[m];
   const bool diag = (ti == tj);
-  const long long Kv = valid_rows(z);
-  const long long r0 = (long long)s * kZetaBlock;
-  const long long r1 = min(Kv, r0 + kZetaBlock);
+  const long long Kv = valid_rows(z), rows = block_rows(Kv, z.parts);
+  const long long r0 = s * rows;
+  const long long r1 = min(Kv, r0 + rows);
+  if (r0 >= r1) return;
   const double* A = z.A + d.off[m];
   const int* plist = z.plist + z.row_begin;
 
@@ -178,10 +189,8 @@ __global__ __launch_bounds__(256) void k_gram_mt(ZetaArgs z, MDims d, double* __
   };
 
   int buf = 0;
-  if (r0 < r1) {
-    load(r0);
-    store(0);
-  }
+  load(r0);
+  store(0);
   __syncthreads();
   for (long long kb = r0; kb < r1; kb += kKS) {
     const bool more = kb + kKS < r1;
@@ -243,9 +252,10 @@ __global__ __launch_bounds__(256) void k_gram_bf16x3_mt(ZetaArgs z, MDims d,
   macro_tile_of(d, blockIdx.x, m, ti, tj);
   const int W = d.W[m];
   const bool diag = (ti == tj);
-  const long long Kv = valid_rows(z);
-  const long long r0 = (long long)s * kZetaBlock;
-  const long long r1 = min(Kv, r0 + kZetaBlock);
+  const long long Kv = valid_rows(z), rows = block_rows(Kv, z.parts);
+  const long long r0 = s * rows;
+  const long long r1 = min(Kv, r0 + rows);
+  if (r0 >= r1) return;
   const double* A = z.A + d.off[m];
   const int* plist = z.plist + z.row_begin;
   const int ci = ti * kMT + lane, cj = tj * kMT + lane;
@@ -323,10 +333,8 @@ __global__ __launch_bounds__(256) void k_gram_bf16x3_mt(ZetaArgs z, MDims d,
   const int li = lane % 16, g = lane / 16;
 
   int buf = 0;
-  if (r0 < r1) {
-    load(r0);
-    store(0);
-  }
+  load(r0);
+  store(0);
   __syncthreads();
   for (long long kb = r0; kb < r1; kb += kKS) {
     const bool more = kb + kKS < r1;
@@ -367,23 +375,31 @@ __global__ __launch_bounds__(256) void k_gram_bf16x3_mt(ZetaArgs z, MDims d,
       }
 }
 
-// zeta[m][l][l'][b1][b2] += sum over the pair-block's 4096-primary blocks (in
-// order, FP64) of the block Gram products.  Only macro tiles on or above the
-// diagonal are stored; C_m is symmetric.
-template <typename CT>
-__global__ void k_zeta_accum_mt(const CT* __restrict__ C, int nsub, MDims d, RowLayout L,
-                                double* __restrict__ zeta) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+// zeta[m][l][l'][b1][b2] += sum over the pair-block's blocks (in order, FP64)
+// of the block Gram products.  Only macro tiles on or above the diagonal are
+// stored; C_m is symmetric.  One workgroup per 16 x 16 tile of one m's (l, b1)
+// x (l', b2) entries, so that the partials are read in 128-byte pieces whether
+// an entry is stored as it is or transposed; only the blocks that hold primaries
+// are read.  Reading the partials bounds it: 166,100 doubles per block (lmax 10,
+// 10 shells).
+constexpr int kAT = 16;
+
+__global__ __launch_bounds__(kAT * kAT) void k_zeta_accum_mt(ZetaArgs z, MDims d,
+                                                             double* __restrict__ zeta) {
+  const RowLayout& L = z.lay;
   const int nb = L.nb, nm = L.lmax + 1;
-  const long long per_m = (long long)nm * nm * nb * nb;
-  if (idx >= per_m * nm) return;
-  long long t = idx;
-  const int b2 = int(t % nb); t /= nb;
-  const int b1 = int(t % nb); t /= nb;
-  const int lp = int(t % nm); t /= nm;
-  const int l = int(t % nm); t /= nm;
-  const int m = int(t);
-  if (l < m || lp < m) return;
+  int t = blockIdx.x, m = 0;
+  for (; m < nm; ++m) {
+    const int nt = (L.d[m] + kAT - 1) / kAT;
+    if (t < nt * nt) break;
+    t -= nt * nt;
+  }
+  const int dm = L.d[m], nt = (dm + kAT - 1) / kAT, nl = nm - m;
+  const int P = (t / nt) * kAT + int(threadIdx.x) / kAT, Pp = (t % nt) * kAT + int(threadIdx.x) % kAT;
+  const long long Kv = valid_rows(z);
+  if (P >= dm || Pp >= dm || Kv == 0) return;
+  const long long rows = block_rows(Kv, z.parts);
+  const int nsub = int((Kv + rows - 1) / rows);
   const int W = d.W[m];
   auto at = [&](int i, int j) {
     if (i / kMT > j / kMT) {
@@ -393,23 +409,24 @@ __global__ void k_zeta_accum_mt(const CT* __restrict__ C, int nsub, MDims d, Row
     }
     return d.cw[m] + i * W + j;
   };
-  const int P = L.pos(m, l, b1), Pp = L.pos(m, lp, b2);
-  const int dm = L.d[m];
   const int Q = dm + P, Qp = dm + Pp;
   const int iPP = at(P, Pp);
   const int iQQ = (m > 0) ? at(Q, Qp) : 0, iQP = (m > 0) ? at(Q, Pp) : 0,
             iPQ = (m > 0) ? at(P, Qp) : 0;
   double re = 0.0, im = 0.0;
-  for (int s = 0; s < nsub; ++s) {
-    const CT* c = C + (long long)s * d.csize;
-    if (m == 0) {
-      re += double(c[iPP]);
-    } else {
-      re += double(c[iPP]) + double(c[iQQ]);
-      im += double(c[iQP]) - double(c[iPQ]);
+  const double* c = z.C64;
+  if (m == 0) {
+#pragma unroll 4
+    for (int s = 0; s < nsub; ++s, c += d.csize) re += c[iPP];
+  } else {
+#pragma unroll 4
+    for (int s = 0; s < nsub; ++s, c += d.csize) {
+      re += c[iPP] + c[iQQ];
+      im += c[iQP] - c[iPQ];
     }
   }
-  double* o = zeta + idx * 2;
+  const int l = m + P % nl, b1 = P / nl, lp = m + Pp % nl, b2 = Pp / nl;
+  double* o = zeta + ((((long long)m * nm + l) * nm + lp) * nb + b1) * (2LL * nb) + 2 * b2;
   o[0] += re;
   o[1] += im;
 }
@@ -438,16 +455,26 @@ RowLayout make_layout(int lmax, int nb) {
   return L;
 }
 
-size_t zeta_partial_doubles(const RowLayout& L, long long PB) {
-  const long long nsub_max = (PB + kZetaBlock - 1) / kZetaBlock;
-  return size_t(std::max<long long>(nsub_max, kZetaSplitK)) * size_t(sum_wm2(L));
+// Partials of a pair-block of at most PB primaries.  4096 rows a block keep the
+// partials few where there are many rows; a small pair-block is cut into more,
+// until the macro tiles times the blocks give every CU about five workgroups
+// (a tile's 4096 rows are one serial chain of 128 steps: the Gram products of 16
+// catalogues of 8192 took 4.55 ms in blocks of 4096 rows and take 1.20 ms in 32
+// blocks; 27 regions of 3700 primaries 6.97 and 1.02 ms).
+int zeta_parts(const RowLayout& L, long long PB) {
+  const long long tiles = make_mdims(L).mt[L.lmax + 1];
+  const long long fill = (5 * 256 + tiles - 1) / tiles;
+  const long long least = (PB + kZetaBlock - 1) / kZetaBlock;
+  return int(std::max(least, std::min(fill, (PB + kZetaRowsMin - 1) / kZetaRowsMin)));
 }
 
-// All blocks of 4096 primaries of a pair-block (z.sub_begin = 0, z.K = rows).
+// All blocks of a pair-block (z.K rows at most).
 hipError_t launch_zeta_pairblock(const ZetaArgs& z, hipStream_t st) {
   const MDims d = make_mdims(z.lay);
-  const int nsub = int((z.K + kZetaBlock - 1) / kZetaBlock);
-  if (nsub <= 0) return hipSuccess;
+  if (z.K <= 0) return hipSuccess;
+  // at most `parts` blocks, each of at least kZetaRowsMin rows
+  const long long nsub =
+      std::min<long long>(z.parts, (z.K + kZetaRowsMin - 1) / kZetaRowsMin);
   const dim3 grid(unsigned(d.mt[d.nm]), unsigned(nsub));
   if (z.prec == G3PCF_PREC_FP32)
     hipLaunchKernelGGL((k_gram_mt<float>), grid, dim3(256), 0, st, z, d, z.C64);
@@ -457,11 +484,12 @@ hipError_t launch_zeta_pairblock(const ZetaArgs& z, hipStream_t st) {
     hipLaunchKernelGGL((k_gram_mt<double>), grid, dim3(256), 0, st, z, d, z.C64);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const long long entries = (long long)(z.lay.lmax + 1) * (z.lay.lmax + 1) * (z.lay.lmax + 1) *
-                            z.lay.nb * z.lay.nb;
-  const unsigned ab = unsigned((entries + 255) / 256);
-  hipLaunchKernelGGL((k_zeta_accum_mt<double>), dim3(ab), dim3(256), 0, st, z.C64, nsub, d,
-                     z.lay, z.zeta);
+  unsigned ab = 0;
+  for (int m = 0; m <= z.lay.lmax; ++m) {
+    const unsigned nt = unsigned((z.lay.d[m] + kAT - 1) / kAT);
+    ab += nt * nt;
+  }
+  hipLaunchKernelGGL(k_zeta_accum_mt, dim3(ab), dim3(kAT * kAT), 0, st, z, d, z.zeta);
   return hipGetLastError();
 }
 

@@ -1,0 +1,55 @@
+"""How the work is cut up must not change the results: Gram blocks of few rows,
+against the FP64 oracle with the tolerances of test_gpu_parity.py (FP64 1e-10,
+FP32 pair stage 1e-5 of max|zeta|)."""
+import sys
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from paper_1709_00086_amd import api, catalogues as C
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-10, "fp32": 1e-5, "bf16x3": 1e-5}
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def cfg_of(cat, precision, basis="spin", **kw):
+    return api.Config(box=cat.box, rmax=cat.rmax, nbins=cat.nbins, lmax=cat.lmax, los=cat.los,
+                      observer=cat.observer, periodic=cat.periodic, box_lo=cat.box_lo,
+                      precision=precision, basis=basis, **kw)
+
+
+def on(dev, cat):
+    return (torch.from_numpy(np.ascontiguousarray(cat.pos)).to(dev),
+            torch.from_numpy(np.ascontiguousarray(cat.w)).to(dev))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("count", [1, 127, 128, 129, 2100, 6000])
+def test_gram_blocks_hold_any_number_of_primaries(dev, precision, count):
+    """Primaries fewer than, just over and many times the least rows of a block
+    (128), of a catalogue whose launch covers 6000."""
+    say(f"case gram blocks {count} {precision}")
+    cat = C.uniform(6000, 300.0, seed=71, dtype=np.float64, weights="uniform", rmax=40.0)
+    mask = C.primary_mask(cat.n, count, seed=72)
+    pos, w = on(dev, cat)
+    z = api.zeta(pos, w, cfg_of(cat, precision), primary_mask=torch.from_numpy(mask).to(dev))
+    ref = oracle.zeta(cat, primary_mask=mask)
+    e = np.abs(z.cpu().numpy() - ref).max() / np.abs(ref).max()
+    say(f"  max|dz|/max|z| = {e:.2e}")
+    assert e <= TOL[precision]
