@@ -1,6 +1,6 @@
-"""How the work is cut up must not change the results: Gram blocks of few rows,
-against the FP64 oracle with the tolerances of test_gpu_parity.py (FP64 1e-10,
-FP32 pair stage 1e-5 of max|zeta|)."""
+"""How the work is cut up must not change the results: Gram blocks of few rows.
+FP64 against the oracle (1e-10 of max|zeta|); the FP32 and BF16x3 zeta stages
+against the FP64 zeta stage on the same FP32 pairs (1e-5)."""
 import sys
 
 import numpy as np
@@ -43,13 +43,20 @@ def on(dev, cat):
 @pytest.mark.parametrize("count", [1, 127, 128, 129, 2100, 6000])
 def test_gram_blocks_hold_any_number_of_primaries(dev, precision, count):
     """Primaries fewer than, just over and many times the least rows of a block
-    (128), of a catalogue whose launch covers 6000."""
+    (128), of a catalogue whose launch covers 6000.  (The oracle is no reference
+    for FP32 pairs here: with 59 pairs a primary, a pair or two that FP32 puts
+    into the next shell already moves zeta by 4e-5.)"""
     say(f"case gram blocks {count} {precision}")
     cat = C.uniform(6000, 300.0, seed=71, dtype=np.float64, weights="uniform", rmax=40.0)
     mask = C.primary_mask(cat.n, count, seed=72)
     pos, w = on(dev, cat)
-    z = api.zeta(pos, w, cfg_of(cat, precision), primary_mask=torch.from_numpy(mask).to(dev))
-    ref = oracle.zeta(cat, primary_mask=mask)
-    e = np.abs(z.cpu().numpy() - ref).max() / np.abs(ref).max()
+    mt = torch.from_numpy(mask).to(dev)
+    z = api.zeta(pos, w, cfg_of(cat, precision), primary_mask=mt).cpu().numpy()
+    if precision == "fp64":
+        ref = oracle.zeta(cat, primary_mask=mask)
+    else:
+        ref = api.zeta(pos, w, cfg_of(cat, precision, zeta_precision="fp64"),
+                       primary_mask=mt).cpu().numpy()
+    e = np.abs(z - ref).max() / np.abs(ref).max()
     say(f"  max|dz|/max|z| = {e:.2e}")
     assert e <= TOL[precision]
