@@ -69,7 +69,7 @@ WORKLOADS = {
     "c5": "config5",
 }
 PROFILE = os.path.join(ROOT, "profiles", "pair_kernel_uniform_n1048576_traffic.json")
-PAIR_KERNEL_SOURCES = ["paper_1709_00086_amd/csrc/pairs.hip",
+PAIR_KERNEL_SOURCES = ["paper_1709_00086_amd/csrc/pair_kernel.h",
                        "paper_1709_00086_amd/csrc/monomials.h",
                        "paper_1709_00086_amd/csrc/internal.h"]
 
@@ -366,7 +366,7 @@ def main():
                     help="summarise rocprofv3 CSV output instead of running (no GPU)")
     ap.add_argument("--counters", nargs="*", default=[])
     ap.add_argument("--kernel-stats", nargs="*", default=[])
-    ap.add_argument("--kernel-regex", default=r"k_pairs<float, 1, false, false, false>")
+    ap.add_argument("--kernel-regex", default=r"k_pairs<float, 1, false, 10, false, false>")
     ap.add_argument("--label", default=None)
     ap.add_argument("--copy-mib", type=int, default=0)
     ap.add_argument("--commands", nargs="*", default=None)

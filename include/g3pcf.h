@@ -181,8 +181,10 @@ size_t g3pcf_zeta_len(int lmax, int nbins);
 
 /* Monomial sums accumulated per (primary, shell) by the pair stage:
  * 286 for the cartesian basis (the paper's count (l+1)(l+2)(l+3)/6 at
- * l = 10, vectorisation section), 121 for the spin basis.  The kernels always
- * accumulate to degree 10; lmax only selects which coefficients are kept.
+ * l = 10, vectorisation section), 121 for the spin basis, both to degree 10.
+ * The cartesian kernels always accumulate to degree 10 (lmax only selects which
+ * coefficients are kept); the spin kernels to the smallest of degrees 4, 6, 8
+ * and 10 that holds lmax.
  * Returns -1 for an unknown basis. */
 int g3pcf_num_terms(int basis);
 

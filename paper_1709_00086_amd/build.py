@@ -16,7 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libg3pcf.so")
-SOURCES = ["cells.hip", "pairs.hip", "zeta.hip", "adjoint.hip", "api.hip", "tables.cpp"]
+SOURCES = ["pairs_d10.hip", "pairs_d8.hip", "pairs_d6.hip", "pairs_d4.hip", "pairs.hip",
+           "cells.hip", "zeta.hip", "adjoint.hip", "api.hip", "tables.cpp"]
 ARCH = "gfx950"
 
 

@@ -19,9 +19,8 @@
 // Because conj(Y_lm(u)) = sum_t c_{lm,t} mono_t(u) with the same monomials the
 // forward pass accumulates, the secondary term is a polynomial in u with
 // coefficients g_t(b) = sum_lm (Re c_{lm,t} Re H_lm(b) - Im c_{lm,t} Im H_lm(b)),
-// evaluated per pair by the pair kernel's adjoint mode.  With FP64 pairs
-// k_adj_finish forms the primary terms and these coefficients here; with FP32
-// pairs the adjoint pair kernel forms both from the H rows itself.
+// evaluated per pair by the pair kernel's adjoint mode, which forms the primary
+// terms and these coefficients from the H rows itself.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -41,13 +40,12 @@ struct AdjDims {
   int nm;
   int W[kDeg + 1], off[kDeg + 1], d[kDeg + 1];
   int cw[kDeg + 2];     // offset of M_H^m in the matrix buffer
-  int rowW, nb, lmax;
+  int nb, lmax;
 };
 
 AdjDims make_adj_dims(const RowLayout& L) {
   AdjDims d{};
   d.nm = L.lmax + 1;
-  d.rowW = L.W;
   d.nb = L.nb;
   d.lmax = L.lmax;
   int cw = 0;
@@ -128,13 +126,17 @@ __global__ __launch_bounds__(256) void k_h_gemm(const double* __restrict__ A,
                                                 const double* __restrict__ MHt, HDims d,
                                                 const long long* __restrict__ nprim,
                                                 long long p_begin, long long p_count,
-                                                double* __restrict__ H) {
+                                                double* __restrict__ H,
+                                                int* __restrict__ queue) {
   // two stages: the next k slice's global loads are in flight (in
   // registers) while the MFMAs work on the current one, one barrier a step
   __shared__ double Xs[2][kHT][kHK + 1];   // odd row stride: rows spread over banks
   __shared__ double Ms[2][kHK][kHT + 8];
   const int tid = threadIdx.x;
   const int lane = tid % kWave, wv = tid / kWave;
+  // the pair kernels on either side of this one start from cleared counters
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid < 2 * kQueues)
+    queue[(tid / 2) * kQueueStride + (tid & 1) * kQueueAdjoint] = 0;
   const long long rows = min(p_count, (long long)(*nprim) - p_begin);
   const long long R0 = (long long)blockIdx.y * kHT;
   if (R0 >= rows) return;
@@ -198,66 +200,6 @@ __global__ __launch_bounds__(256) void k_h_gemm(const double* __restrict__ A,
       }
 }
 
-// Per primary: the primary term Re(a^T H) / 2 and the coefficients g_t(b).
-// One thread per monomial term: its conversion entries are read once and
-// applied to every shell.
-constexpr int kFinThreads = 128;
-constexpr int kFinShells = 8;   // shells per pass over a term's entries
-
-__global__ __launch_bounds__(kFinThreads) void k_adj_finish(AdjArgs a, AdjDims d) {
-  const long long row = blockIdx.x;
-  const long long valid = min(a.p_count, (long long)(*a.nprim) - a.p_begin);
-  if (row >= valid) return;
-  const int slot = a.plist[a.p_begin + row];
-  const double* x = a.A + row * (long long)d.rowW;
-  const double* h = a.H + row * (long long)d.rowW;
-  extern __shared__ double fin_smem[];
-  double* red = fin_smem;                // [kFinThreads]
-  double* hs = fin_smem + kFinThreads;   // [rowW]
-  double prim = 0.0;
-  for (int c = threadIdx.x; c < d.rowW; c += blockDim.x) {
-    const double hv = h[c];
-    hs[c] = hv;
-    // column c belongs to block m; the imaginary half enters with a minus sign
-    int m = 0;
-    while (m + 1 < d.nm && c >= d.off[m + 1]) ++m;
-    const bool imag = (m > 0) && (c - d.off[m] >= d.d[m]);
-    prim += imag ? -x[c] * hv : x[c] * hv;
-  }
-  red[threadIdx.x] = prim;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.grad_w[slot] += 0.5 * red[0];
-
-  const ConvTable& t = *a.table;
-  const int nb = d.nb;
-  const int T = (a.basis == G3PCF_BASIS_SPIN) ? kTermsSpin : kTermsCart;
-  double* gout = a.gcoef + row * (long long)nb * T;
-  for (int term = threadIdx.x; term < T; term += blockDim.x) {
-    const int e0 = t.trowptr[term], e1 = t.trowptr[term + 1];
-    for (int b0 = 0; b0 < nb; b0 += kFinShells) {
-      double sacc[kFinShells];
-      for (int q = 0; q < kFinShells; ++q) sacc[q] = 0.0;
-      for (int e = e0; e < e1; ++e) {
-        const int out = t.tout[e];
-        const int l = t.out_l[out];
-        if (l > d.lmax) continue;
-        const int m = t.out_m[out], part = t.out_part[out];
-        const int nl = d.lmax + 1 - m;  // column stride between shells
-        const int col = d.off[m] + (l - m) + (part ? d.d[m] : 0);
-        const double c = part ? -t.tcoef[e] : t.tcoef[e];
-        for (int q = 0; q < kFinShells; ++q)
-          if (b0 + q < nb) sacc[q] += c * hs[col + (b0 + q) * nl];
-      }
-      for (int q = 0; q < kFinShells; ++q)
-        if (b0 + q < nb) gout[(b0 + q) * T + term] = sacc[q];
-    }
-  }
-}
-
 __global__ void k_unpermute(const double* __restrict__ gs, const float* __restrict__ gs32,
                             const int* __restrict__ perm, int64_t n, int accumulate,
                             const unsigned long long* __restrict__ fp_saved,
@@ -288,14 +230,7 @@ hipError_t launch_h_gemm(const AdjArgs& a, hipStream_t st) {
   const HDims hd = make_hdims(a.lay);
   const long long row_tiles = (a.p_count + kHT - 1) / kHT;
   hipLaunchKernelGGL(k_h_gemm, dim3(unsigned(hd.ct[hd.nm]), unsigned(row_tiles)), dim3(256), 0,
-                     st, a.A, a.MHt, hd, a.nprim, a.p_begin, a.p_count, a.H);
-  return hipGetLastError();
-}
-
-hipError_t launch_adj_finish(const AdjArgs& a, hipStream_t st) {
-  const AdjDims d = make_adj_dims(a.lay);
-  const size_t shm = size_t(kFinThreads + d.rowW) * sizeof(double);
-  hipLaunchKernelGGL(k_adj_finish, dim3(unsigned(a.p_count)), dim3(kFinThreads), shm, st, a, d);
+                     st, a.A, a.MHt, hd, a.nprim, a.p_begin, a.p_count, a.H, a.queue);
   return hipGetLastError();
 }
 

@@ -63,12 +63,13 @@ size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Ws {
   size_t pos4, tmp4, cid, perm, tmp_perm, rkey, rhist, wsort, cell_start, cell_count, flags,
-      plist, scan, counters, spill, A, C, gcoef, gsort, gsort32, mht, hrows, degD, degP;
+      plist, scan, counters, spill, A, C, gsort, gsort32, mht, hrows, degD, degP, degX;
   size_t scan_bytes;
   size_t total;
   int64_t PB;   // primaries per pair-block
   int spill_cap;  // spill-list entries per wave (0: none)
   int parts;    // partial Gram products of a pair-block
+  bool deg_fused;  // distinct: the pair kernel also collects the degenerate sums
   Grid grid;
   RowLayout lay;
 };
@@ -108,8 +109,8 @@ Ws plan(const g3pcf_problem& p, int backward, int64_t pb_max = kPairBlockMax,
   w.plist = take(size_t(n) * 4);
   w.scan = take(w.scan_bytes);
   w.counters = take(kCountersBytes);
-  // per-wave spill lists for bases accumulated in several register chunks
-  const bool multi = !compact && (fp64 || p.basis == G3PCF_BASIS_CARTESIAN);
+  // per-wave spill lists for the basis accumulated in several register chunks
+  const bool multi = !compact && p.basis == G3PCF_BASIS_CARTESIAN;
   w.spill = take(multi ? size_t(kPairWaves) * kSpillCap * 4 : 0);
   w.spill_cap = multi ? kSpillCap : 0;
   w.A = take(size_t(w.PB) * w.lay.W * 8);
@@ -120,12 +121,12 @@ Ws plan(const g3pcf_problem& p, int backward, int64_t pb_max = kPairBlockMax,
   const bool deg = !backward && p.distinct;
   w.degD = take(deg ? size_t(p.nbins) * (2 * p.lmax + 1) * 8 : 0);
   w.degP = take(deg ? deg_partial_doubles(w.PB, p.nbins, p.lmax) * 8 : 0);
+  // the spin kernels collect the degenerate sums on the way, into rows of their
+  // own; the cartesian kernels have no registers left for them, and the
+  // compact layout no room: there a pass of its own writes over the a_lm rows
+  w.deg_fused = deg && !compact && p.basis == G3PCF_BASIS_SPIN;
+  if (w.deg_fused) w.degX = take(size_t(w.PB) * p.nbins * (2 * p.lmax + 1) * 8);
   if (backward) {
-    // adjoint coefficients per primary and shell in the forward's basis (FP64
-    // pair path only: the FP32 adjoint pair kernel forms its spin-Chebyshev
-    // coefficients from the H rows)
-    const int T = (p.basis == G3PCF_BASIS_SPIN) ? kTermsSpin : kTermsCart;
-    w.gcoef = take(fp64 ? size_t(w.PB) * p.nbins * T * 8 : 0);
     w.gsort = take(size_t(n) * 8);
     w.gsort32 = take(fp64 ? 0 : size_t(n) * 4);  // FP32 secondary terms (FP32 pair path)
     w.mht = take(adj_matrix_doubles(w.lay) * 8);
@@ -180,13 +181,17 @@ int validate(const g3pcf_problem* p) {
 std::mutex g_tab_mu;
 std::set<std::pair<int, int>> g_tab_done;
 
+// Uploads a table to the current device once: G3PCF_BASIS_CARTESIAN, _SPIN (the
+// spin-Chebyshev tables) or kBasisDeg.
 int ensure_tables(int basis) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   std::lock_guard<std::mutex> lk(g_tab_mu);
   if (g_tab_done.count({dev, basis})) return G3PCF_OK;
-  e = (basis == kBasisDeg) ? upload_deg_table() : upload_tables(basis);
+  e = (basis == kBasisDeg)          ? upload_deg_table()
+      : (basis == G3PCF_BASIS_SPIN) ? upload_spin_tables()
+                                    : upload_conv_table();
   if (e != hipSuccess) return hip_fail(e, "table upload");
   g_tab_done.insert({dev, basis});
   return G3PCF_OK;
@@ -197,14 +202,20 @@ T* at(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
 }
 
+// Counts of one XCD's waves, on a 64-byte line of their own.
+struct XcdCounters {
+  int queue[2];                  // next primary: of the forward, of the adjoint
+  unsigned long long pairs;      // accepted pairs
+  unsigned long long pairs_adj;
+  unsigned long long pad[5];
+};
+static_assert(sizeof(XcdCounters) == kQueueStride * 4, "one line each");
+
 struct Counters {
   long long nprim;
-  unsigned long long pairs;
-  unsigned long long pairs_adj;
-  unsigned long long pairs_deg;  // counted again by the degenerate-triangle pass
   unsigned long long inputs_hash;  // backward: fingerprint of its inputs (a_lm store check)
-  int pad[6];
-  int queue[kQueues * kQueueStride];  // one primary counter per XCD, 64 B apart
+  long long pad[6];
+  XcdCounters xcd[kQueues];
 };
 static_assert(sizeof(Counters) <= kCountersBytes, "counters block");
 
@@ -236,8 +247,9 @@ int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, hipStream_t s
   return G3PCF_OK;
 }
 
-PairArgs pair_args(const g3pcf_problem& p, const Ws& w, void* ws) {
-  PairArgs a{};
+int pair_args(const g3pcf_problem& p, const Ws& w, void* ws, PairArgs& a) {
+  const hipError_t e = table_addresses(&a.conv, &a.spin);
+  if (e != hipSuccess) return hip_fail(e, "table address");
   Counters* c = at<Counters>(ws, w.counters);
   a.pos4 = at<void>(ws, w.pos4);
   a.sentinel = int(p.n);
@@ -246,14 +258,14 @@ PairArgs pair_args(const g3pcf_problem& p, const Ws& w, void* ws) {
   a.nprim = &c->nprim;
   a.spill = at<int>(ws, w.spill);
   a.spill_cap = w.spill_cap;
-  a.queue = c->queue;
-  a.pairs = &c->pairs;
+  a.queue = c->xcd[0].queue;
   for (int k = 0; k < 3; ++k) {
     a.nc[k] = w.grid.nc[k];
     a.s[k] = w.grid.s[k];
     a.inv_s[k] = w.grid.inv_s[k];
     a.lo[k] = w.grid.lo[k];
     a.L[k] = w.grid.L[k];
+    a.inv_L[k] = 1.0 / w.grid.L[k];
     a.tight[k] = w.grid.tight[k];
     a.obs[k] = p.observer[k];
   }
@@ -275,7 +287,8 @@ PairArgs pair_args(const g3pcf_problem& p, const Ws& w, void* ws) {
   a.lay = w.lay;
   a.perm = at<int>(ws, w.perm);
   a.wsort = at<double>(ws, w.wsort);
-  return a;
+  a.deg = at<double>(ws, w.degX);
+  return G3PCF_OK;
 }
 
 int check_workspace(const Ws& w, void* ws, size_t ws_bytes) {
@@ -354,7 +367,7 @@ hipError_t fingerprint(const g3pcf_problem& p, const Ws& w, void* ws, unsigned l
 }
 
 int forward_tables(const g3pcf_problem& p) {
-  int rc = ensure_tables(conv_table_of(p.basis));
+  int rc = ensure_tables(p.basis);
   if (!rc && p.distinct) rc = ensure_tables(kBasisDeg);
   return rc;
 }
@@ -366,7 +379,8 @@ int forward_tables(const g3pcf_problem& p) {
 int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, int64_t cover,
                   double* rows, hipStream_t st) {
   hipError_t e;
-  PairArgs a = pair_args(p, w, ws);
+  PairArgs a{};
+  if (int rc = pair_args(p, w, ws, a)) return rc;
   const int fp64 = (p.pair_prec == G3PCF_PREC_FP64);
   Counters* c = at<Counters>(ws, w.counters);
   double* degD = at<double>(ws, w.degD);
@@ -376,11 +390,11 @@ int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, i
   for (int64_t b0 = 0; b0 < cover; b0 += w.PB) {
     a.p_begin = b0;
     a.p_count = std::min<int64_t>(w.PB, cover - b0);
-    a.pairs = &c->pairs;
+    a.pairs = p.pairs_out ? &c->xcd[0].pairs : nullptr;
     if (rows) a.A = rows + size_t(b0) * w.lay.W;
     {
       StageScope sc(p.trace, G3PCF_STAGE_PAIRS, st);
-      if ((e = launch_pair_forward(a, fp64, p.basis, st)) != hipSuccess)
+      if ((e = launch_pair_forward(a, fp64, p.basis, w.deg_fused, st)) != hipSuccess)
         return hip_fail(e, "pair kernel");
     }
     {
@@ -397,17 +411,22 @@ int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, i
       z.parts = w.parts;
       z.zeta = zeta;
       z.prec = p.zeta_prec;
+      z.queue = a.queue;
       if ((e = launch_zeta_pairblock(z, st)) != hipSuccess) return hip_fail(e, "zeta");
     }
     if (p.distinct) {
-      // the same pairs again for their sums w_j^2 P_n(u_z), written over the
-      // pair-block's A rows (already reduced into zeta), then summed with w_i
+      // the sums w_j^2 T_n(u_z) of each primary, summed with w_i; without rows
+      // of their own the same pairs again, written over the pair-block's A rows
+      // (already reduced into zeta)
       StageScope scd(p.trace, G3PCF_STAGE_DISTINCT, st);
-      a.pairs = &c->pairs_deg;
-      if ((e = launch_pair_distinct(a, fp64, st)) != hipSuccess)
+      a.pairs = nullptr;  // counted already
+      if (!w.deg_fused && (e = launch_pair_distinct(a, fp64, st)) != hipSuccess)
         return hip_fail(e, "degenerate-triangle pass");
-      if ((e = launch_deg_reduce(a.A, w.lay.W, p.nbins, p.lmax, a.wsort, a.plist, &c->nprim, b0,
-                                 a.p_count, at<double>(ws, w.degP), degD, st)) != hipSuccess)
+      const double* X = w.deg_fused ? a.deg : a.A;
+      const int rowW = w.deg_fused ? p.nbins * (2 * p.lmax + 1) : w.lay.W;
+      if ((e = launch_deg_reduce(X, rowW, p.nbins, p.lmax, a.wsort, a.plist, &c->nprim, b0,
+                                 a.p_count, at<double>(ws, w.degP), degD, a.queue, st)) !=
+          hipSuccess)
         return hip_fail(e, "degenerate-triangle sums");
     }
   }
@@ -423,13 +442,14 @@ int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, i
 int finish_pairs(const g3pcf_problem& p, const Ws& w, void* ws, hipStream_t st,
                  bool adj = false) {
   if (!p.pairs_out) return G3PCF_OK;
-  unsigned long long host = 0;
+  XcdCounters host[kQueues];
   Counters* c = at<Counters>(ws, w.counters);
-  hipError_t e = hipMemcpyAsync(&host, adj ? &c->pairs_adj : &c->pairs, sizeof(host),
-                                hipMemcpyDeviceToHost, st);
+  hipError_t e = hipMemcpyAsync(host, c->xcd, sizeof(host), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_fail(e, "pair count read-back");
-  *p.pairs_out = (int64_t)host;
+  int64_t sum = 0;
+  for (const XcdCounters& x : host) sum += int64_t(adj ? x.pairs_adj : x.pairs);
+  *p.pairs_out = sum;
   return G3PCF_OK;
 }
 
@@ -711,14 +731,9 @@ int g3pcf_backward(const g3pcf_problem* prob, const double* grad_zeta, double* g
   if ((rc = check_workspace(w, ws, ws_bytes))) return rc;
   if ((rc = check_alm(p, w))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // the FP32 adjoint (either basis) evaluates its per-pair polynomial in
-  // (x - i y)^m T_n(z) (coefficients from the spin-Chebyshev table); the
-  // FP64 adjoint in the forward's own basis
-  const bool fp32 = (p.pair_prec == G3PCF_PREC_FP32);
-  const int adj_table = fp32 ? int(G3PCF_BASIS_SPIN_T) : conv_table_of(p.basis);
-  const int adj_basis = fp32 ? int(G3PCF_BASIS_SPIN) : int(p.basis);
-  if ((rc = ensure_tables(conv_table_of(p.basis))) || (rc = ensure_tables(adj_table)))
-    return rc;
+  // the adjoint (either basis) evaluates its per-pair polynomial in
+  // (x - i y)^m T_n(z), coefficients from the spin-Chebyshev table
+  if ((rc = ensure_tables(p.basis)) || (rc = ensure_tables(G3PCF_BASIS_SPIN))) return rc;
   if (p.n == 0) {
     if (p.pairs_out) *p.pairs_out = 0;
     return G3PCF_OK;
@@ -743,54 +758,45 @@ int g3pcf_backward(const g3pcf_problem* prob, const double* grad_zeta, double* g
     if ((e = launch_adj_matrix(grad_zeta, w.lay, at<double>(ws, w.mht), st)) != hipSuccess)
       return hip_fail(e, "adjoint matrices");
   }
-  PairArgs a = pair_args(p, w, ws);
+  PairArgs a{};
+  if ((rc = pair_args(p, w, ws, a))) return rc;
   const int fp64 = (p.pair_prec == G3PCF_PREC_FP64);
-  const ConvTable* tab = nullptr;
-  if ((e = conv_table_device(adj_table, &tab)) != hipSuccess) return hip_fail(e, "table address");
-  a.gcoef = at<double>(ws, w.gcoef);
   a.H = at<double>(ws, w.hrows);
   a.grad_w = gsort;
   a.grad_w32 = gsort32;
   for (int64_t b0 = 0; b0 < p.n; b0 += w.PB) {
     a.p_begin = b0;
     a.p_count = std::min<int64_t>(w.PB, p.n - b0);
-    a.pairs = &c->pairs;
+    a.pairs = nullptr;  // the adjoint's are counted
     if (p.alm) {
       // the a_lm rows the forward pass kept
       a.A = alm_rows(p) + size_t(b0) * w.lay.W;
     } else {
       StageScope sc(p.trace, G3PCF_STAGE_PAIRS, st);
-      if ((e = launch_pair_forward(a, fp64, p.basis, st)) != hipSuccess)
+      if ((e = launch_pair_forward(a, fp64, p.basis, false, st)) != hipSuccess)
         return hip_fail(e, "pair kernel (recompute)");
     }
     AdjArgs j{};
     j.A = a.A;
-    j.gz = grad_zeta;
-    j.wsort = a.wsort;
-    j.plist = a.plist;
-    j.perm = a.perm;
     j.nprim = &c->nprim;
     j.p_begin = b0;
     j.p_count = a.p_count;
     j.lay = w.lay;
-    j.basis = adj_basis;
-    j.table = tab;
-    j.gcoef = at<double>(ws, w.gcoef);
-    j.grad_w = gsort;
     j.MHt = at<double>(ws, w.mht);
     j.H = at<double>(ws, w.hrows);
+    j.queue = c->xcd[0].queue;
     {
       StageScope sc(p.trace, G3PCF_STAGE_ADJ_COEF, st);
       if ((e = launch_h_gemm(j, st)) != hipSuccess) return hip_fail(e, "adjoint GEMM");
-      if (fp64 && (e = launch_adj_finish(j, st)) != hipSuccess)
-        return hip_fail(e, "adjoint coefficients");
     }
-    a.pairs = &c->pairs_adj;
+    a.pairs = p.pairs_out ? &c->xcd[0].pairs_adj : nullptr;
+    a.queue = c->xcd[0].queue + kQueueAdjoint;
     {
       StageScope sc(p.trace, G3PCF_STAGE_PAIR_ADJOINT, st);
-      if ((e = launch_pair_adjoint(a, fp64, p.basis, st)) != hipSuccess)
+      if ((e = launch_pair_adjoint(a, fp64, st)) != hipSuccess)
         return hip_fail(e, "pair adjoint kernel");
     }
+    a.queue = c->xcd[0].queue;
   }
   const unsigned long long* saved = p.alm ? static_cast<const unsigned long long*>(p.alm) : nullptr;
   if ((e = launch_unpermute(gsort, gsort32, a.perm, p.n, p.accumulate, saved, &c->inputs_hash, grad_w,
@@ -821,8 +827,7 @@ int g3pcf_degenerate_term(int lmax, double uz, double* out) {
   double pn[kTermsDeg];
   pn[0] = 1.0;
   pn[1] = uz;
-  for (int n = 1; n + 1 < kTermsDeg; ++n)
-    pn[n + 1] = ((2.0 * n + 1.0) * uz * pn[n] - n * pn[n - 1]) / (n + 1.0);
+  for (int n = 1; n + 1 < kTermsDeg; ++n) pn[n + 1] = 2.0 * uz * pn[n] - pn[n - 1];
   const int L1 = lmax + 1;
   for (int m = 0; m <= lmax; ++m)
     for (int l = 0; l <= lmax; ++l)

@@ -11,18 +11,25 @@
 
 namespace g3 {
 
-// The pair kernels always accumulate monomials up to this total degree; a
-// smaller lmax only drops coefficients at conversion time.
+// Largest total degree of the pair kernels' sums.  The cartesian kernels always
+// carry it (a smaller lmax only drops coefficients at conversion time); the
+// spin kernels come in the degrees of kDegrees, and a problem takes the
+// smallest that holds its lmax: a degree D has (D + 1)^2 sums a pair, so at
+// lmax = 4 a quarter of the work of degree 10.
 constexpr int kDeg = 10;
+constexpr int kDegrees[] = {4, 6, 8, 10};
+constexpr int kNumDegrees = 4;
+constexpr int kSpinCoef = kDeg / 2 + 1;  // most entries of a spin conversion row
 constexpr int kTermsCart = (kDeg + 1) * (kDeg + 2) * (kDeg + 3) / 6;  // 286
 constexpr int kTermsSpin = (kDeg + 1) * (kDeg + 1);                   // 121 real sums
 // Conversion tables: G3PCF_BASIS_CARTESIAN, G3PCF_BASIS_SPIN and
-// G3PCF_BASIS_SPIN_T (the spin terms with T_n(u_z) in place of u_z^n; only the
-// FP32 adjoint uses it, after a forward pass in either basis).
+// G3PCF_BASIS_SPIN_T (the spin terms with T_n(u_z) in place of u_z^n).
 constexpr int kConvTables = 3;
 // Internal "basis" of the pass that collects the degenerate (j = k) triangles:
-// per shell the sums w_j^2 P_n(u_z) of Legendre polynomials, n <= 2 kDeg.
+// per shell the sums w_j^2 T_n(u_z) of Chebyshev polynomials, n <= 2 kDeg; and
+// of the spin pass that collects them beside its own sums.
 constexpr int kBasisDeg = 3;
+constexpr int kBasisSpinDeg = 4;
 constexpr int kTermsDeg = 2 * kDeg + 1;                               // 21
 constexpr int kMaxBins = 32;
 constexpr int kWave = 64;
@@ -40,8 +47,15 @@ constexpr int kZetaRowsMin = 128;
 // the 8 XCDs round-robin), each counter on its own 64-byte line.
 constexpr int kQueues = 8;
 constexpr int kQueueStride = 16;
-// Persistent waves of the pair kernel.
-constexpr int kPairWaves = 4096;
+constexpr int kQueueAdjoint = 1;  // the adjoint's counter on the same line
+// Persistent waves of the pair kernel: as many as its occupancy lets run at
+// once on the 256 CUs' SIMDs, at most kPairWaves.
+constexpr int kSimds = 4 * 256;
+constexpr int kPairWaves = 4 * kSimds;
+// Pair-blocks of fewer primaries hand out single shells of a primary: whole
+// primaries leave the chip idle behind the last of them (kPairWaves waves run
+// at once).
+constexpr long long kSplitBelow = 4 * kPairWaves;
 // Spill-list entries per wave: a shell's secondaries kept for the later
 // accumulator chunks of a multi-chunk basis.
 constexpr int kSpillCap = 1 << 14;
@@ -57,22 +71,26 @@ struct ConvTable {
   int rowptr[kOutPerBin + 1];
   short term[4096];
   double coef[4096];
-  // the same entries grouped by monomial term (for the adjoint)
-  int trowptr[kTermsCart + 1];
-  short tout[4096];
-  double tcoef[4096];
 };
+
+// The spin-Chebyshev conversion a_lm = sum_n c_{lm,n} S_{m,n} of one degree D,
+// over the term order of its sums (the D + 1 real ones of m = 0, then pairs of
+// real and imaginary parts, n running to D - m); output o has l - m in n's
+// place.
+struct SpinTable {
+  // c[k][o]: coefficient of output o = (m, l - m = j) for n = j mod 2 + 2 k <= j
+  double c[kSpinCoef][128];
+  // ct[k][o]: coefficient of term o = (m, n) in the output l = m + n + 2 k <= D
+  double ct[kSpinCoef][128];
+  int meta[128];  // m | j << 4 | part << 8 | (term index of (m, 0, 0)) << 9
+};
+__host__ __device__ constexpr int spin_table_of(int deg) { return (deg - kDegrees[0]) / 2; }
+void build_spin_table(int deg, SpinTable* t);  // host
 
 // Host: build the conversion table for a basis (0 cartesian, 1 spin with
 // powers u_z^n, 2 spin with Chebyshev polynomials T_n(u_z)).
 void build_conv_table(int basis, ConvTable* t);
-// The table a problem basis accumulates and converts with: the spin basis
-// sums (u_x - i u_y)^m T_n(u_z), so it converts with the spin-Chebyshev table.
-__host__ __device__ constexpr int conv_table_of(int basis) {
-  return basis == G3PCF_BASIS_SPIN ? int(G3PCF_BASIS_SPIN_T) : basis;
-}
-
-// Degenerate-triangle table G[m][l][l'][n]: Pbar_lm Pbar_l'm = sum_n G P_n.
+// Degenerate-triangle table G[m][l][l'][n]: Pbar_lm Pbar_l'm = sum_n G T_n.
 constexpr int kDegTable = (kDeg + 1) * (kDeg + 1) * (kDeg + 1) * kTermsDeg;
 __host__ __device__ inline int deg_index(int m, int l, int lp, int n) {
   return ((m * (kDeg + 1) + l) * (kDeg + 1) + lp) * kTermsDeg + n;
@@ -118,12 +136,12 @@ struct PairArgs {
   int* spill;                // per-wave lists of a shell's secondaries
   int spill_cap;             // entries per wave (0: no spill lists: one search per shell and chunk)
   int* queue;                // kQueues counters (stride kQueueStride): next primary of each XCD's share
-  unsigned long long* pairs; // device scalar: accepted pairs
+  unsigned long long* pairs; // accepted pairs, a count per XCD (stride kQueueStride / 2); NULL: not counted
   long long p_begin;         // first primary of this pair-block
   long long p_count;         // primaries in this pair-block (upper bound)
   // geometry (double, used for the candidate search)
   int nc[3];
-  double s[3], inv_s[3], lo[3], L[3];
+  double s[3], inv_s[3], lo[3], L[3], inv_L[3];
   int periodic;
   int tight[3];
   double rmax, rmax_search;
@@ -137,9 +155,11 @@ struct PairArgs {
   // outputs
   double* A;                 // [p_count][W] a_lm rows (forward)
   RowLayout lay;
+  double* deg;               // [p_count][nbins (2 lmax + 1)] degenerate-triangle sums (kBasisSpinDeg)
+  const ConvTable* conv;     // cartesian conversion (device)
+  const SpinTable* spin;     // [kNumDegrees] spin conversions (device)
   // adjoint
-  const double* gcoef;       // [p_count][nbins][T] monomial-space adjoint coefficients (FP64 pairs)
-  const double* H;           // [p_count][W] H rows (FP32 pairs: converted per shell in the kernel)
+  const double* H;           // [p_count][W] H rows (converted per shell in the kernel)
   const int* perm;           // [n] slot -> original index
   double* grad_w;            // [n] cell order: FP64 pair path (secondary terms added atomically)
   float* grad_w32;           // [n] cell order: FP32 pair path (secondary terms added atomically)
@@ -178,12 +198,22 @@ hipError_t launch_fingerprint(const void* pos4, int fp64, const double* wsort, c
                               unsigned long long seed, unsigned long long* out, hipStream_t st);
 hipError_t launch_fill_int(int* p, int64_t count, int value, hipStream_t st);
 hipError_t launch_fill_double(double* p, int64_t count, double value, hipStream_t st);
-hipError_t launch_pair_forward(const PairArgs& a, int fp64, int basis, hipStream_t st);
-hipError_t launch_pair_adjoint(const PairArgs& a, int fp64, int basis, hipStream_t st);
-// Degenerate-triangle pass: per primary and shell the sums w_j^2 P_n(u_z),
-// n <= 2 lmax, into A[row][shell * (2 lmax + 1) + n] (FP64).
+// Forward pass (distinct: the spin kernels also collect the degenerate sums
+// into a.deg), adjoint pass (either basis), and the degenerate-triangle pass on
+// its own: per primary and shell the sums w_j^2 T_n(u_z), n <= 2 lmax, into
+// A[row][shell * (2 lmax + 1) + n] (FP64).
+hipError_t launch_pair_forward(const PairArgs& a, int fp64, int basis, bool distinct,
+                               hipStream_t st);
+hipError_t launch_pair_adjoint(const PairArgs& a, int fp64, hipStream_t st);
 hipError_t launch_pair_distinct(const PairArgs& a, int fp64, hipStream_t st);
-hipError_t upload_tables(int basis);
+// The spin kernels of one degree (forward, forward with degenerate sums,
+// adjoint), each compiled in its own file.
+enum { kSpinForward, kSpinForwardDeg, kSpinAdjoint };
+template <int DEG>
+hipError_t launch_pair_spin(const PairArgs& a, int fp64, int what, hipStream_t st);
+hipError_t upload_conv_table();
+hipError_t upload_spin_tables();
+hipError_t table_addresses(const ConvTable** conv, const SpinTable** spin);
 
 struct ZetaArgs {
   const double* A;           // [rows][W]
@@ -197,6 +227,7 @@ struct ZetaArgs {
   int parts;                 // blocks the partials have room for (>= K / kZetaBlock)
   double* zeta;
   int prec;
+  int* queue;                // the pair kernel's primary counters, cleared for its next launch
 };
 // Every block of a pair-block.
 hipError_t launch_zeta_pairblock(const ZetaArgs& z, hipStream_t st);
@@ -206,36 +237,24 @@ int zeta_parts(const RowLayout& L, long long PB);
 // Adjoint helpers
 struct AdjArgs {
   const double* A;           // [rows][W]
-  const double* gz;          // grad_zeta
-  const double* wsort;
-  const int* plist;
-  const int* perm;
   const long long* nprim;
   long long p_begin;
   long long p_count;
   RowLayout lay;
-  int basis;
-  const ConvTable* table;    // device copy of the conversion table
   const double* MHt;         // adjoint matrices M_H^m, transposed
   double* H;                 // [p_count][W] H rows
-  double* gcoef;             // [p_count][nbins][T]
-  double* grad_w;            // [n] cell order
+  int* queue;                // primary counters of both pair kernels, cleared for their next launch
 };
 size_t adj_matrix_doubles(const RowLayout& L);
 hipError_t launch_adj_matrix(const double* gz, const RowLayout& L, double* MHt, hipStream_t st);
-// H = X M_H^T (k_h_gemm) and, for the FP64 pair path, the primary terms and
-// the per-shell monomial coefficients (k_adj_finish); the FP32 adjoint pair
-// kernel forms both from H itself.
+// H = X M_H^T (k_h_gemm); the adjoint pair kernel forms the primary terms and the
+// per-shell coefficients from H itself.
 hipError_t launch_h_gemm(const AdjArgs& a, hipStream_t st);
-hipError_t launch_adj_finish(const AdjArgs& a, hipStream_t st);
 // grad[perm[s]] (=|+=) gs[s] (+ gs32[s] when gs32 is not null); NaN instead
 // when fp_saved is not null and *fp_saved != *fp_now
 hipError_t launch_unpermute(const double* gs, const float* gs32, const int* perm, int64_t n,
                             int accumulate, const unsigned long long* fp_saved,
                             const unsigned long long* fp_now, double* grad, hipStream_t st);
-// Device address of the uploaded conversion table of a basis.
-hipError_t conv_table_device(int basis, const ConvTable** out);
-
 size_t scan_tmp_bytes(int64_t count);
 hipError_t launch_scan(const int* in, int* out, int64_t count, void* tmp, size_t tmp_bytes,
                        hipStream_t st);
@@ -243,13 +262,15 @@ hipError_t launch_scan(const int* in, int* out, int64_t count, void* tmp, size_t
 int sum_wm2(const RowLayout& lay);
 
 // Degenerate triangles (distinct secondaries): table upload, the weighted sum
-// over a pair-block's rows X[r][b (2 lmax + 1) + n] into D (FP64, in order),
-// and the correction of zeta^m_{ll'}(b, b).
+// over a pair-block's rows X[r][b (2 lmax + 1) + n] into D (FP64, in order; it
+// clears the pair kernel's primary counters), and the correction of
+// zeta^m_{ll'}(b, b).
 hipError_t upload_deg_table();
 size_t deg_partial_doubles(long long PB, int nb, int lmax);
 hipError_t launch_deg_reduce(const double* X, int rowW, int nb, int lmax, const double* wsort,
                              const int* plist, const long long* nprim, long long p_begin,
-                             long long p_count, double* partial, double* D, hipStream_t st);
+                             long long p_count, double* partial, double* D, int* queue,
+                             hipStream_t st);
 hipError_t launch_deg_apply(const double* D, int lmax, int nb, double* zeta, hipStream_t st);
 // Isotropic multipoles from zeta (addition theorem).
 hipError_t launch_isotropic(const double* zeta, int lmax, int nb, double* iso, hipStream_t st);

@@ -1,7 +1,7 @@
 // Device helpers of the pair kernels: wave-uniform broadcasts, DPP wave sums
 // and the two monomial bases with their register-resident accumulators.
 //
-// Included by pairs.hip only (it opens an anonymous namespace).
+// Included by pair_kernel.h only (it opens an anonymous namespace).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -161,6 +161,48 @@ __device__ __forceinline__ double fold4(double a, double e, double b, double f) 
   return c + d2;
 }
 
+// Fold two values across neighbouring rows: rows 0 and 2 of the result hold a
+// summed over rows 0-1 and 2-3, rows 1 and 3 the same for b.
+__device__ __forceinline__ float fold2(float a, float b) {
+  unsigned ua = __float_as_uint(a);
+  const unsigned ub = pl16(ua, __float_as_uint(b));
+  return __uint_as_float(ua) + __uint_as_float(ub);
+}
+__device__ __forceinline__ double fold2(double a, double b) {
+  const double b2 = swap16_d(a, b);
+  return a + b2;
+}
+// Sums over each row of 16 lanes of four values at once: two values share a
+// register after each halving of the row, so that the last steps add all four
+// together (11 instructions instead of 16).
+__device__ __forceinline__ float dpp_ror8(float v) {
+  return __int_as_float(dpp_i<0x128, 0xF, 0xF>(__float_as_int(v)));
+}
+__device__ __forceinline__ double dpp_ror8(double v) { return dpp_d<0x128, 0xF, 0xF>(v); }
+__device__ __forceinline__ float dpp_half_mirror(float v) {
+  return __int_as_float(dpp_i<0x141, 0xF, 0xF>(__float_as_int(v)));
+}
+__device__ __forceinline__ double dpp_half_mirror(double v) { return dpp_d<0x141, 0xF, 0xF>(v); }
+__device__ __forceinline__ float quad_sum(float v) {
+  v += __int_as_float(dpp_i<0xB1, 0xF, 0xF>(__float_as_int(v)));
+  v += __int_as_float(dpp_i<0x4E, 0xF, 0xF>(__float_as_int(v)));
+  return v;
+}
+__device__ __forceinline__ double quad_sum(double v) {
+  v += dpp_d<0xB1, 0xF, 0xF>(v);
+  v += dpp_d<0x4E, 0xF, 0xF>(v);
+  return v;
+}
+// The lanes of quad 0 of a row return the row's sum of a, those of quad 1 of c,
+// of quad 2 of b and of quad 3 of d.
+template <typename Real>
+__device__ __forceinline__ Real row_sums4(Real a, Real b, Real c, Real d, int lane) {
+  const bool hi = (lane & 8) != 0, odd = (lane & 4) != 0;
+  const Real ab = (hi ? b : a) + dpp_ror8(hi ? a : b);
+  const Real cd = (hi ? d : c) + dpp_ror8(hi ? c : d);
+  return quad_sum((odd ? cd : ab) + dpp_half_mirror(odd ? ab : cd));
+}
+
 __device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_r(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -172,12 +214,6 @@ __host__ __device__ constexpr int cart_index_c(int k, int p, int q) {
   for (int pp = 0; pp < p; ++pp) t += kDeg - q - pp + 1;
   return t + k;
 }
-__host__ __device__ constexpr int spin_index_c(int m, int n, int part) {
-  int base = (m == 0) ? 0 : kDeg + 1;
-  for (int mm = 1; mm < m; ++mm) base += 2 * (kDeg + 1 - mm);
-  return (m == 0) ? n : base + 2 * n + part;
-}
-
 __host__ __device__ constexpr int cart_count(unsigned qmask) {
   int c = 0;
   for (int q = 0; q <= kDeg; ++q)
@@ -247,259 +283,277 @@ struct CartChunk {
       }
     });
   }
+};
 
-  // adjoint: sum over this chunk's monomials of g_t * monomial.  Powers of x
-  // and y are formed first so that every coefficient enters as a multiplicand
-  // (a scalar-register operand when the coefficients are uniform).
-  template <typename GetG>
-  static __device__ __forceinline__ Real poly(Real x, Real y, Real z, GetG&& g) {
-    Real xp[kDeg + 1], yp[kDeg + 1];
-    xp[0] = Real(1);
-    yp[0] = Real(1);
-#pragma unroll
-    for (int k = 1; k <= kDeg; ++k) {
-      xp[k] = xp[k - 1] * x;
-      yp[k] = yp[k - 1] * y;
-    }
-    Real total = Real(0);
-    Real zq = Real(1);
-    static_for<kDeg + 1>([&](auto qc) {
-      constexpr int q = decltype(qc)::value;
-      if constexpr (q > 0) zq = zq * z;
-      if constexpr (((QMASK >> q) & 1u) != 0) {
-        Real ysum = Real(0);
-        static_for<kDeg + 1 - q>([&](auto pc) {
-          constexpr int p = decltype(pc)::value;
-          constexpr int KM = kDeg - q - p;  // highest power of x
-          if constexpr (KM == 0) {
-            ysum = fma_r(g(cart_index_c(0, p, q)), yp[p], ysum);
-          } else {
-            // start from a product and add the constant term last, so that no
-            // coefficient has to be copied into a vector register first
-            Real hx = g(cart_index_c(1, p, q)) * xp[1];
-            static_for<KM - 1>([&](auto kc) {
-              constexpr int k = decltype(kc)::value + 2;
-              hx = fma_r(g(cart_index_c(k, p, q)), xp[k], hx);
-            });
-            hx = hx + g(cart_index_c(0, p, q));
-            ysum = fma_r(hx, yp[p], ysum);
-          }
-        });
-        total = fma_r(ysum, zq, total);
-      }
-    });
-    return total;
+// Term index of Re / Im S_{m,n} among the sums of degree at most D
+// ((D + 1)^2 of them): the D + 1 real ones of m = 0, then (Re, Im) pairs.
+template <int D>
+__host__ __device__ constexpr int spin_pair_c(int m, int n) {  // pair (m >= 1, n)
+  return (m - 1) * (D + 1) - (m - 1) * m / 2 + n;
+}
+template <int D>
+__host__ __device__ constexpr int spin_term_c(int m, int n, int part) {
+  return m == 0 ? n : D + 1 + 2 * spin_pair_c<D>(m, n) + part;
+}
+
+// Exchange of half waves: on return a holds the lower halves of both inputs
+// ([a.lo | b.lo]) and b the upper ones ([a.hi | b.hi]).
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  unsigned ua = __float_as_uint(a);
+  const unsigned ub = pl32(ua, __float_as_uint(b));
+  a = __uint_as_float(ua);
+  b = __uint_as_float(ub);
+}
+__device__ __forceinline__ void swap_halves(double& a, double& b) { b = swap32_d(a, b); }
+
+// Register pairs.  An FP32 multiply-add issues in about 2.5 cycles a SIMD where
+// its three source registers are not all even or all odd numbered, and in 4.4
+// where they are (measured; the register file has two banks).  Values held in
+// the halves of an aligned pair have a known parity: the empty statement makes
+// the compiler keep the two in one.  FP64 operands are pairs already.
+typedef float pair_f __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void keep_pair(float& even, float& odd) {
+  pair_f p = {even, odd};
+  asm("" : "+v"(p));
+  even = p.x;
+  odd = p.y;
+}
+__device__ __forceinline__ void keep_pair(double&, double&) {}
+
+// T_1..T_N of one lane, T_n in a register of n's parity; (D + 1)-entry arrays
+// with T_0 unused.
+template <int N, typename Real, int D>
+__device__ __forceinline__ void pair_up(Real (&t)[D]) {
+  static_for<N / 2>([&](auto kc) {
+    constexpr int n = 2 * (decltype(kc)::value + 1);
+    if constexpr (n + 1 <= N) keep_pair(t[n], t[n + 1]);
+  });
+}
+// Entries 1..N of a row, entry n in a register of the other parity than T_n.
+template <int N, typename Real>
+__device__ __forceinline__ void pair_down(Real* r) {
+  static_for<N / 2>([&](auto kc) {
+    constexpr int n = 2 * decltype(kc)::value + 1;
+    keep_pair(r[n], r[n + 1]);
+  });
+}
+
+// The half waves' operands.  For m >= 1 a register holds the real part of
+// something in the lower half of the wave and the imaginary part in the upper;
+// the 64 pairs are then taken 32 at a time, each by both halves, which need the
+// pair's z and powers (x - i y)^m: in LDS every lane leaves what they follow
+// from, and reads it for its half's part of a lower pair (lane mod 32) and of
+// an upper one.  (Exchanging registers by permlane32_swap costs 8.3 cycles each,
+// and 19 of them a wave of pairs, against none here.)  The real and the
+// imaginary parts c_m of w (x - i y)^m both follow
+//   c_{m+1} = 2 x c_m - (x^2 + y^2) c_{m-1}.
+template <typename Real>
+struct Half {
+  Real z, z2, x2, rho;  // z, 2 z, 2 x, x^2 + y^2
+  Real c0, c1;          // c_0, c_1: of the real part [w | 0], [w x | -w y]
+};
+// kWeighted: with w; else w = 1 (c_0 is then known, and takes no room).
+template <typename Real, bool kWeighted>
+struct Exchange {
+  static constexpr int kReals = (kWeighted ? 8 : 6) * kWave;  // per wave
+  typedef Real V4r __attribute__((ext_vector_type(4)));
+  typedef Real V2r __attribute__((ext_vector_type(2)));
+  static __device__ __forceinline__ void put(Real* s, int lane, Real x, Real y, Real z, Real w) {
+    reinterpret_cast<V4r*>(s)[lane] = V4r{z, z + z, x + x, fma_r(y, y, x * x)};
+    if constexpr (kWeighted)
+      reinterpret_cast<V4r*>(s)[kWave + lane] = V4r{w, w * x, Real(0), -(w * y)};
+    else
+      reinterpret_cast<V2r*>(s)[2 * kWave + lane] = V2r{x, -y};
   }
-
-  template <typename Store>
-  __device__ __forceinline__ void for_each_term(Store&& st) {
-    static_for<kDeg + 1>([&](auto qc) {
-      constexpr int q = decltype(qc)::value;
-      if constexpr (((QMASK >> q) & 1u) != 0) {
-        static_for<kDeg + 1 - q>([&](auto pc) {
-          constexpr int p = decltype(pc)::value;
-          static_for<kDeg + 1 - q - p>([&](auto kc) {
-            constexpr int k = decltype(kc)::value;
-            st(acc[cart_local(QMASK, k, p, q)], cart_index_c(k, p, q));
-          });
-        });
-      }
-    });
+  // upper: pairs 32..63 instead of 0..31
+  static __device__ __forceinline__ Half<Real> get(const Real* s, int lane, bool upper) {
+    const int p = (lane & 31) + (upper ? 32 : 0), half = lane >> 5;
+    const V4r a = reinterpret_cast<const V4r*>(s)[p];
+    if constexpr (kWeighted) {
+      const V2r c = reinterpret_cast<const V2r*>(s)[2 * (kWave + p) + half];
+      return Half<Real>{a.x, a.y, a.z, a.w, c.x, c.y};
+    } else {
+      const Real c = s[4 * kWave + 2 * p + half];
+      return Half<Real>{a.x, a.y, a.z, a.w, half ? Real(0) : Real(1), c};
+    }
+  }
+  static __device__ __forceinline__ void fence() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
   }
 };
 
-__host__ __device__ constexpr int spin_count(int m0, int m1) {
-  int c = 0;
-  for (int m = m0; m <= m1; ++m) c += (m == 0) ? (kDeg + 1) : 2 * (kDeg + 1 - m);
-  return c;
-}
-__host__ __device__ constexpr int spin_local(int m0, int m, int n, int part) {
-  int t = 0;
-  for (int mm = m0; mm < m; ++mm) t += (mm == 0) ? (kDeg + 1) : 2 * (kDeg + 1 - mm);
-  return (m == 0) ? t + n : t + 2 * n + part;
-}
-
-// Global term index of the i-th accumulator of a spin chunk (m0..m1).
-__host__ __device__ constexpr int spin_term_of(int m0, int m1, int i) {
-  int t = 0;
-  for (int m = m0; m <= m1; ++m)
-    for (int n = 0; m + n <= kDeg; ++n)
-      for (int part = 0; part < (m == 0 ? 1 : 2); ++part) {
-        if (t == i) return spin_index_c(m, n, part);
-        ++t;
-      }
-  return -1;
-}
-
-// Chebyshev polynomials T_0..T_NMAX of z by their three-term recurrence
+// T_1..T_N of z, given 2 z too, by their three-term recurrence
 // T_{n+1} = 2 z T_n - T_{n-1} (one FMA each).  In this basis the
 // coefficients of the spherical harmonics do not cancel: those of the powers
 // z^n do, by up to three orders of magnitude at l = 10 (for m = 0 they are
 // the power-basis coefficients of the Legendre polynomials), which costs
 // FP32 sums as many digits.
-template <int NMAX, typename Real>
-__device__ __forceinline__ void chebyshev(Real z, Real (&tn)[kDeg + 1]) {
-  tn[0] = Real(1);
+template <int N, typename Real, int D>
+__device__ __forceinline__ void chebyshev_z2(Real z, Real z2, Real (&tn)[D]) {
   tn[1] = z;
-  const Real z2 = z + z;
-  static_for<(NMAX > 1 ? NMAX - 1 : 0)>([&](auto nc) {
-    constexpr int n = decltype(nc)::value + 1;
+  if constexpr (N >= 2) tn[2] = fma_r(z2, z, Real(-1));
+  static_for<(N > 2 ? N - 2 : 0)>([&](auto nc) {
+    constexpr int n = decltype(nc)::value + 2;
     tn[n + 1] = fma_r(z2, tn[n], -tn[n - 1]);
   });
 }
 
-// Spin chunk: S_{m,n} = sum w (u_x - i u_y)^m T_n(u_z) for M0 <= m <= M1,
-// with T_n the Chebyshev polynomials (the conversion to a_lm uses the
-// spin-Chebyshev table).
-template <typename Real, int M0, int M1>
-struct SpinChunk {
-  static constexpr int NT = spin_count(M0, M1);
-  Real acc[NT];
-  static __host__ __device__ constexpr int term_of(int i) { return spin_term_of(M0, M1, i); }
+// Spin sums S_{m,n} = sum w (u_x - i u_y)^m T_n(u_z), m + n <= D, with T_n the
+// Chebyshev polynomials (the conversion to a_lm uses the spin-Chebyshev table).
+//
+// For m >= 1 the lower half of the wave holds the real part of S_{m,n} and the
+// upper half the imaginary part, in one register: 66 accumulators instead of
+// 121 at D = 10, four waves per SIMD instead of three, and the same number of
+// multiply-adds as with one pair per lane.
+template <typename Real, int D, bool DISTINCT>
+struct SpinSplit {
+  static constexpr int NP = D * (D + 1) / 2;  // (m >= 1, n) pairs
+  static constexpr int ND = DISTINCT ? 2 * D + 1 : 1;
+  Real acc0[D + 1];  // m = 0, one pair per lane
+  Real acc[NP];      // Re | Im
+  Real deg[ND];      // sum w^2 T_n(u_z), n <= 2 D (degenerate triangles)
 
   __device__ __forceinline__ void zero() {
 #pragma unroll
-    for (int i = 0; i < NT; ++i) acc[i] = Real(0);
+    for (int i = 0; i <= D; ++i) acc0[i] = Real(0);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) acc[i] = Real(0);
+#pragma unroll
+    for (int i = 0; i < ND; ++i) deg[i] = Real(0);
   }
 
-  __device__ __forceinline__ void add(Real x, Real y, Real z, Real w) {
-    constexpr int NMAX = kDeg - (M0 > 0 ? M0 : 0);
-    Real zn[kDeg + 1];
-    chebyshev<NMAX>(z, zn);
-    if constexpr (M0 == 0) {
-      acc[spin_local(M0, 0, 0, 0)] += w;
-      static_for<kDeg>([&](auto nc) {
+  // 32 pairs, both halves of the wave
+  __device__ __forceinline__ void add_half(const Half<Real>& h) {
+    Real t[D + 1];
+    chebyshev_z2<D - 1>(h.z, h.z2, t);
+    pair_up<D - 1>(t);
+    Real c0 = h.c0, c1 = h.c1;
+    static_for<D>([&](auto mc) {
+      constexpr int m = decltype(mc)::value + 1;
+      constexpr int q = spin_pair_c<D>(m, 0);
+      acc[q] += c1;
+      static_for<D - m>([&](auto nc) {
         constexpr int n = decltype(nc)::value + 1;
-        acc[spin_local(M0, 0, n, 0)] = fma_r(w, zn[n], acc[spin_local(M0, 0, n, 0)]);
+        acc[q + n] = fma_r(c1, t[n], acc[q + n]);
       });
-    }
-    if constexpr (M1 >= 1) {
-      Real cr = w * x, ci = -(w * y);  // w (x - i y)
-      static_for<M1>([&](auto mc) {
-        constexpr int m = decltype(mc)::value + 1;
-        if constexpr (m > 1) {
-          const Real nr = fma_r(cr, x, ci * y);
-          const Real ni = fma_r(ci, x, -(cr * y));
-          cr = nr;
-          ci = ni;
-        }
-        if constexpr (m >= M0) {
-          acc[spin_local(M0, m, 0, 0)] += cr;
-          acc[spin_local(M0, m, 0, 1)] += ci;
-          static_for<kDeg - m>([&](auto nc) {
-            constexpr int n = decltype(nc)::value + 1;
-            acc[spin_local(M0, m, n, 0)] = fma_r(cr, zn[n], acc[spin_local(M0, m, n, 0)]);
-            acc[spin_local(M0, m, n, 1)] = fma_r(ci, zn[n], acc[spin_local(M0, m, n, 1)]);
-          });
-        }
-      });
-    }
-  }
-
-  // adjoint: sum over this chunk of g_t * Re/Im parts of (x - i y)^m T_n(z),
-  // with the T_n formed first so that every coefficient enters as a
-  // multiplicand (a scalar-register operand when the coefficients are uniform).
-  template <typename GetG>
-  static __device__ __forceinline__ Real poly(Real x, Real y, Real z, GetG&& g) {
-    Real zn[kDeg + 1];
-    chebyshev<kDeg>(z, zn);
-    Real total = Real(0);
-    Real cr = Real(1), ci = Real(0);
-    static_for<M1 + 1>([&](auto mc) {
-      constexpr int m = decltype(mc)::value;
-      if constexpr (m > 0) {
-        const Real nr = fma_r(cr, x, ci * y);
-        const Real ni = fma_r(ci, x, -(cr * y));
-        cr = nr;
-        ci = ni;
-      }
-      if constexpr (m >= M0) {
-        constexpr int NM = kDeg - m;  // highest power of z
-        if constexpr (NM == 0) {
-          // m = kDeg: only the constant coefficients
-          if constexpr (m == 0)
-            total += g(spin_index_c(m, 0, 0));
-          else
-            total = fma_r(cr, g(spin_index_c(m, 0, 0)), fma_r(ci, g(spin_index_c(m, 0, 1)), total));
-        } else {
-          // start from a product and add the constant term last, so that no
-          // coefficient has to be copied into a vector register first
-          Real hr = g(spin_index_c(m, 1, 0)) * zn[1];
-          Real hi = Real(0);
-          if constexpr (m > 0) hi = g(spin_index_c(m, 1, 1)) * zn[1];
-          static_for<NM - 1>([&](auto nc) {
-            constexpr int n = decltype(nc)::value + 2;
-            hr = fma_r(g(spin_index_c(m, n, 0)), zn[n], hr);
-            if constexpr (m > 0) hi = fma_r(g(spin_index_c(m, n, 1)), zn[n], hi);
-          });
-          hr = hr + g(spin_index_c(m, 0, 0));
-          if constexpr (m > 0) hi = hi + g(spin_index_c(m, 0, 1));
-          if constexpr (m == 0)
-            total += hr;
-          else
-            total = fma_r(cr, hr, fma_r(ci, hi, total));
-        }
+      if constexpr (m < D) {
+        const Real c2 = fma_r(h.x2, c1, -(h.rho * c0));
+        c0 = c1;
+        c1 = c2;
       }
     });
-    return total;
   }
 
-  template <typename Store>
-  __device__ __forceinline__ void for_each_term(Store&& st) {
-    static_for<M1 - M0 + 1>([&](auto mc) {
-      constexpr int m = decltype(mc)::value + M0;
-      static_for<kDeg - m + 1>([&](auto nc) {
-        constexpr int n = decltype(nc)::value;
-        st(acc[spin_local(M0, m, n, 0)], spin_index_c(m, n, 0));
-        if constexpr (m > 0) st(acc[spin_local(M0, m, n, 1)], spin_index_c(m, n, 1));
-      });
+  __device__ __forceinline__ void add(Real x, Real y, Real z, Real w, Real* xch, int lane) {
+    Exchange<Real, true>::put(xch, lane, x, y, z, w);
+    static_for<D>([&](auto mc) {
+      constexpr int m = decltype(mc)::value + 1;
+      pair_down<D - m>(acc + spin_pair_c<D>(m, 0));
     });
+    pair_down<D>(acc0);
+    // m = 0 (and the degenerate sums) while the exchange is under way
+    Real t[D + 1];
+    chebyshev_z2<D>(z, z + z, t);
+    pair_up<D>(t);
+    acc0[0] += w;
+    static_for<D>([&](auto nc) {
+      constexpr int n = decltype(nc)::value + 1;
+      acc0[n] = fma_r(w, t[n], acc0[n]);
+    });
+    if constexpr (DISTINCT) {
+      const Real w2 = w * w, z2 = z + z;
+      deg[0] += w2;
+      static_for<D>([&](auto nc) {
+        constexpr int n = decltype(nc)::value + 1;
+        deg[n] = fma_r(w2, t[n], deg[n]);
+      });
+      Real p0 = t[D - 1], p1 = t[D];
+      static_for<D>([&](auto nc) {
+        constexpr int n = decltype(nc)::value + D + 1;
+        const Real p2 = fma_r(z2, p1, -p0);
+        deg[n] = fma_r(w2, p2, deg[n]);
+        p0 = p1;
+        p1 = p2;
+      });
+    }
+    Exchange<Real, true>::fence();
+    add_half(Exchange<Real, true>::get(xch, lane, false));
+    add_half(Exchange<Real, true>::get(xch, lane, true));
   }
 };
 
-// Adjoint polynomial of the FP32 path (either basis): the sum over (m, n) of the
+// Adjoint polynomial (either basis): the sum over (m, n), m + n <= D, of the
 // coefficients times the Re / Im parts of (x - i y)^m T_n(z), with Chebyshev
 // polynomials T_n in place of z^n.  In this basis the coefficients of the
 // spherical harmonics do not cancel (those of z^n do, by two to three orders
 // of magnitude at l = 10), so FP32 evaluation keeps close to FP32 accuracy.
-// The coefficients are the same for every lane (one set per primary and
-// shell) and are held in vector registers: an FMA with a scalar-register
-// operand issues more slowly than one with three vector registers.
-struct SpinTPoly {
-  float g[kTermsSpin];
+// The coefficients are the same for every pair (one set per primary and
+// shell) and are held in vector registers, for m >= 1 those of the real parts
+// in the lower half of the wave and those of the imaginary parts in the upper
+// (66 registers instead of 121 at D = 10, split as the sums of SpinSplit are):
+// each half evaluates its part of all 64 pairs, and one exchange at the end adds
+// the two.
+template <typename Real, int D>
+struct SplitPoly {
+  static constexpr int NP = D * (D + 1) / 2;
+  Real g0[D + 1];
+  Real g[NP];
 
+  // gc: the (D + 1)^2 coefficients in term order
   template <typename Ptr>
-  __device__ __forceinline__ void load(Ptr gc) {
+  __device__ __forceinline__ void load(Ptr gc, int lane) {
 #pragma unroll
-    for (int t = 0; t < kTermsSpin; ++t) g[t] = float(gc[t]);
+    for (int n = 0; n <= D; ++n) g0[n] = gc[n];
+    const int part = lane >> 5;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) g[q] = gc[D + 1 + 2 * q + part];
   }
 
-  __device__ __forceinline__ float eval(float x, float y, float z) const {
-    float tn[kDeg + 1];
-    chebyshev<kDeg>(z, tn);
-    float total = g[spin_index_c(0, 0, 0)];
-    static_for<kDeg>([&](auto nc) {
-      constexpr int n = decltype(nc)::value + 1;
-      total = fma_r(g[spin_index_c(0, n, 0)], tn[n], total);
-    });
-    float cr = x, ci = -y;  // (x - i y)^m, m = 1
-    static_for<kDeg>([&](auto mc) {
+  __device__ __forceinline__ Real eval_half(const Half<Real>& h) const {
+    Real t[D + 1];
+    chebyshev_z2<D - 1>(h.z, h.z2, t);
+    pair_up<D - 1>(t);
+    Real c0 = h.c0, c1 = h.c1, sum = Real(0);
+    static_for<D>([&](auto mc) {
       constexpr int m = decltype(mc)::value + 1;
-      if constexpr (m > 1) {
-        const float nr = fma_r(cr, x, ci * y);
-        const float ni = fma_r(ci, x, -(cr * y));
-        cr = nr;
-        ci = ni;
-      }
-      float hr = g[spin_index_c(m, 0, 0)], hi = g[spin_index_c(m, 0, 1)];
-      static_for<kDeg - m>([&](auto nc) {
+      constexpr int q = spin_pair_c<D>(m, 0);
+      Real v = g[q];
+      static_for<D - m>([&](auto nc) {
         constexpr int n = decltype(nc)::value + 1;
-        hr = fma_r(g[spin_index_c(m, n, 0)], tn[n], hr);
-        hi = fma_r(g[spin_index_c(m, n, 1)], tn[n], hi);
+        v = fma_r(g[q + n], t[n], v);
       });
-      total = fma_r(cr, hr, fma_r(ci, hi, total));
+      sum = m == 1 ? c1 * v : fma_r(c1, v, sum);
+      if constexpr (m < D) {
+        const Real c2 = fma_r(h.x2, c1, -(h.rho * c0));
+        c0 = c1;
+        c1 = c2;
+      }
     });
-    return total;
+    return sum;
+  }
+
+  // the polynomial of the lane's own pair
+  __device__ __forceinline__ Real eval(Real x, Real y, Real z, Real* xch, int lane) {
+    Exchange<Real, false>::put(xch, lane, x, y, z, Real(1));
+    static_for<D>([&](auto mc) {
+      constexpr int m = decltype(mc)::value + 1;
+      pair_down<D - m>(g + spin_pair_c<D>(m, 0));
+    });
+    pair_down<D>(g0);
+    Real t[D + 1];
+    chebyshev_z2<D>(z, z + z, t);
+    pair_up<D>(t);
+    Real total = g0[0];
+    static_for<D>([&](auto nc) {
+      constexpr int n = decltype(nc)::value + 1;
+      total = fma_r(g0[n], t[n], total);
+    });
+    Exchange<Real, false>::fence();
+    Real sa = eval_half(Exchange<Real, false>::get(xch, lane, false));
+    Real sb = eval_half(Exchange<Real, false>::get(xch, lane, true));
+    swap_halves(sa, sb);
+    return total + (sa + sb);
   }
 };
 
@@ -507,10 +561,10 @@ template <class... C>
 struct ChunkList {};
 
 // Chunking keeps each chunk's accumulators within the 256 architected VGPRs.
-template <typename Real, int BASIS>
+template <typename Real, int BASIS, int DEG>
 struct Chunks;
 template <>
-struct Chunks<float, G3PCF_BASIS_CARTESIAN> {
+struct Chunks<float, G3PCF_BASIS_CARTESIAN, kDeg> {
   // z powers {0, 5, 9, 10}, {1, 4, 7, 8}, {2, 3, 6}: 91, 99 and 96 sums, so
   // that each chunk fits three waves per SIMD (two chunks at two waves
   // measured 7% slower)
@@ -518,23 +572,14 @@ struct Chunks<float, G3PCF_BASIS_CARTESIAN> {
                          CartChunk<float, 0x04Cu>>;
 };
 template <>
-struct Chunks<double, G3PCF_BASIS_CARTESIAN> {
+struct Chunks<double, G3PCF_BASIS_CARTESIAN, kDeg> {
   using type = ChunkList<CartChunk<double, 0x601u>, CartChunk<double, 0x182u>,
                          CartChunk<double, 0x00Cu>, CartChunk<double, 0x070u>>;
 };
-template <>
-struct Chunks<float, G3PCF_BASIS_SPIN> {
-  using type = ChunkList<SpinChunk<float, 0, kDeg>>;
-};
-template <>
-struct Chunks<double, G3PCF_BASIS_SPIN> {
-  using type = ChunkList<SpinChunk<double, 0, 3>, SpinChunk<double, 4, kDeg>>;
-};
-
-// Degenerate-triangle sums: D_n = sum w^2 P_n(z), n <= 2 kDeg, with the
-// Legendre polynomials from their three-term recurrence (bounded by 1 on
-// [-1, 1], so FP32 is accurate).  conj(Y_lm) Y_l'm depends on z alone and is
-// a polynomial of degree l + l', i.e. a combination of these P_n.
+// Degenerate-triangle sums on their own (the cartesian basis): D_n = sum w^2
+// T_n(z), n <= 2 kDeg, with the Chebyshev polynomials (bounded by 1 on [-1, 1],
+// so FP32 is accurate).  conj(Y_lm) Y_l'm depends on z alone and is a polynomial
+// of degree l + l', i.e. a combination of these T_n.
 template <typename Real>
 struct DegChunk {
   static constexpr int NT = kTermsDeg;
@@ -549,12 +594,12 @@ struct DegChunk {
   __device__ __forceinline__ void add(Real, Real, Real z, Real w) {
     const Real w2 = w * w;
     Real p0 = Real(1), p1 = z;
+    const Real z2 = z + z;
     acc[0] += w2;
     acc[1] = fma_r(w2, p1, acc[1]);
     static_for<NT - 2>([&](auto nc) {
-      constexpr int n = decltype(nc)::value + 1;  // P_{n+1} from P_n and P_{n-1}
-      constexpr Real a = Real(2 * n + 1) / Real(n + 1), c = Real(n) / Real(n + 1);
-      const Real p2 = fma_r(a * z, p1, -(c * p0));
+      constexpr int n = decltype(nc)::value + 1;  // T_{n+1} from T_n and T_{n-1}
+      const Real p2 = fma_r(z2, p1, -p0);
       acc[n + 1] = fma_r(w2, p2, acc[n + 1]);
       p0 = p1;
       p1 = p2;
@@ -562,8 +607,16 @@ struct DegChunk {
   }
 };
 template <typename Real>
-struct Chunks<Real, kBasisDeg> {
+struct Chunks<Real, kBasisDeg, kDeg> {
   using type = ChunkList<DegChunk<Real>>;
+};
+template <typename Real, int DEG>
+struct Chunks<Real, G3PCF_BASIS_SPIN, DEG> {
+  using type = ChunkList<SpinSplit<Real, DEG, false>>;
+};
+template <typename Real, int DEG>
+struct Chunks<Real, kBasisSpinDeg, DEG> {
+  using type = ChunkList<SpinSplit<Real, DEG, true>>;
 };
 
 template <class... C, typename F>

@@ -99,19 +99,19 @@ void build_conv_table(int basis, ConvTable* t) {
             ++nnz;
           }
         } else if (basis == G3PCF_BASIS_SPIN_T) {
-          // u_z^n = 2^(1-n) sum_j binom(n, j) T_{n-2j}(u_z), the T_0 term halved
-          std::map<int, double> acc;
+          // u_z^n = 2^(1-n) sum_j binom(n, j) T_{n-2j}(u_z), the T_0 term halved.
+          // The terms cancel by up to three orders of magnitude, so they are
+          // added as integers (times 2^-10) in 64 bits and scaled once.
+          std::map<int, long double> acc;
           for (int k = 0; 2 * k <= l - m; ++k) {
             const int n = l - m - 2 * k;
-            const double c = scale * double(c_int(l, m, k));
-            for (int j = 0; 2 * j <= n; ++j) {
-              const double a = std::ldexp(double(binom(n, j)), (2 * j == n) ? -n : 1 - n);
-              acc[n - 2 * j] += c * a;
-            }
+            for (int j = 0; 2 * j <= n; ++j)
+              acc[n - 2 * j] += std::ldexp((long double)(c_int(l, m, k)) * binom(n, j),
+                                           (2 * j == n) ? -n : 1 - n);
           }
           for (auto& kv : acc) {
             t->term[nnz] = short(spin_index(m, kv.first, part));
-            t->coef[nnz] = kv.second;
+            t->coef[nnz] = double(scale * kv.second);
             ++nnz;
           }
         } else {
@@ -151,30 +151,41 @@ void build_conv_table(int basis, ConvTable* t) {
   t->rowptr[o] = nnz;
   t->nout = o;
   t->nnz = nnz;
-  // transpose: entries grouped by term
-  const int nterm = (basis == G3PCF_BASIS_CARTESIAN) ? kTermsCart : kTermsSpin;
-  std::vector<int> cnt(nterm + 1, 0);
-  for (int e = 0; e < nnz; ++e) cnt[t->term[e] + 1]++;
-  for (int k = 0; k < nterm; ++k) cnt[k + 1] += cnt[k];
-  for (int k = 0; k <= nterm; ++k) t->trowptr[k] = cnt[k];
-  for (int k = nterm + 1; k <= kTermsCart; ++k) t->trowptr[k] = cnt[nterm];
-  std::vector<int> fillp(cnt.begin(), cnt.end() - 1);
-  for (int oo = 0; oo < o; ++oo)
-    for (int e = t->rowptr[oo]; e < t->rowptr[oo + 1]; ++e) {
-      const int at = fillp[t->term[e]]++;
-      t->tout[at] = short(oo);
-      t->tcoef[at] = t->coef[e];
+}
+
+void build_spin_table(int deg, SpinTable* t) {
+  static ConvTable full;  // spin-Chebyshev, every degree
+  if (full.nout == 0) build_conv_table(G3PCF_BASIS_SPIN_T, &full);
+  std::memset(t, 0, sizeof(*t));
+  int o = 0;
+  for (int m = 0; m <= deg; ++m) {
+    const int base = o;
+    for (int j = 0; m + j <= deg; ++j)
+      for (int part = 0; part < (m == 0 ? 1 : 2); ++part, ++o)
+        t->meta[o] = m | j << 4 | part << 8 | base << 9;
+  }
+  for (int q = 0; q < full.nout; ++q) {
+    const int l = full.out_l[q], m = full.out_m[q], part = full.out_part[q], j = l - m;
+    if (l > deg) continue;
+    const int stride = m == 0 ? 1 : 2;
+    int base = 0;
+    for (int mm = 0; mm < m; ++mm) base += (mm == 0 ? 1 : 2) * (deg + 1 - mm);
+    for (int e = full.rowptr[q]; e < full.rowptr[q + 1]; ++e) {
+      const int n = (full.term[e] - spin_index(m, 0, part)) / stride;
+      t->c[(n - (j & 1)) / 2][base + stride * j + part] = full.coef[e];
+      t->ct[(j - n) / 2][base + stride * n + part] = full.coef[e];
     }
+  }
 }
 
 // Degenerate-triangle table.  For one secondary at unit separation u the j = k
 // term of zeta^m_{ll'} is w_i w_j^2 conj(Y_lm(u)) Y_l'm(u) = w_i w_j^2
 // Pbar_lm(u_z) Pbar_l'm(u_z) (the azimuthal factors cancel, Pbar_lm = N_lm P_l^m,
 // the Condon-Shortley signs square to one): a polynomial of degree l + l' in
-// u_z alone, expanded here in Legendre polynomials,
-//   Pbar_lm(z) Pbar_l'm(z) = sum_n G[m][l][l'][n] P_n(z),
-//   G = (2n + 1) / 2 int_{-1}^{1} Pbar_lm Pbar_l'm P_n dz,
-// by Gauss-Legendre quadrature with 32 nodes (exact to degree 63 >= 40).
+// u_z alone, expanded here in Chebyshev polynomials,
+//   Pbar_lm(z) Pbar_l'm(z) = sum_n G[m][l][l'][n] T_n(z),
+//   G = (2 - delta_n0) / K sum_q Pbar_lm Pbar_l'm T_n at the K = 32 Chebyshev
+// nodes (the discrete orthogonality of T_n, exact below degree 64 >= 40).
 namespace {
 
 // P_l^m(z) (Condon-Shortley phase) for m <= l <= kDeg: p[l] for fixed m.
@@ -189,54 +200,27 @@ void assoc_legendre(int m, double z, double* p) {
     p[l] = ((2.0 * l - 1.0) * z * p[l - 1] - (l + m - 1.0) * p[l - 2]) / double(l - m);
 }
 
-void legendre_all(double z, int nmax, double* p) {  // P_n(z), n <= nmax
-  p[0] = 1.0;
-  if (nmax >= 1) p[1] = z;
-  for (int n = 1; n < nmax; ++n) p[n + 1] = ((2.0 * n + 1.0) * z * p[n] - n * p[n - 1]) / (n + 1.0);
-}
-
-// Gauss-Legendre nodes and weights on [-1, 1]: Newton iteration on P_K from
-// the Chebyshev-like first guesses cos(pi (i + 3/4) / (K + 1/2)).
-void gauss_legendre(int K, double* x, double* w) {
-  std::vector<double> p(K + 1);
-  for (int i = 0; i < K; ++i) {
-    double z = std::cos(M_PI * (i + 0.75) / (K + 0.5));
-    double dp = 0.0;
-    for (int it = 0; it < 100; ++it) {
-      legendre_all(z, K, p.data());
-      dp = K * (z * p[K] - p[K - 1]) / (z * z - 1.0);  // P_K'(z)
-      const double dz = p[K] / dp;
-      z -= dz;
-      if (std::fabs(dz) < 1e-16) break;
-    }
-    legendre_all(z, K, p.data());
-    dp = K * (z * p[K] - p[K - 1]) / (z * z - 1.0);
-    x[i] = z;
-    w[i] = 2.0 / ((1.0 - z * z) * dp * dp);
-  }
-}
-
 }  // namespace
 
 void build_deg_table(double* G) {
   constexpr int K = 32;
-  double x[K], wq[K];
-  gauss_legendre(K, x, wq);
+  double x[K];
+  for (int q = 0; q < K; ++q) x[q] = std::cos(M_PI * (q + 0.5) / K);
   std::memset(G, 0, sizeof(double) * kDegTable);
   double pl[kDeg + 1], pn[kTermsDeg];
   for (int m = 0; m <= kDeg; ++m) {
     for (int q = 0; q < K; ++q) {
       assoc_legendre(m, x[q], pl);
-      legendre_all(x[q], kTermsDeg - 1, pn);
+      for (int n = 0; n < kTermsDeg; ++n) pn[n] = std::cos(n * M_PI * (q + 0.5) / K);
       for (int l = m; l <= kDeg; ++l) {
         const double nl =
             std::sqrt((2.0 * l + 1.0) / (4.0 * M_PI) * double(fact(l - m)) / double(fact(l + m)));
         for (int lp = m; lp <= kDeg; ++lp) {
           const double nlp = std::sqrt((2.0 * lp + 1.0) / (4.0 * M_PI) * double(fact(lp - m)) /
                                        double(fact(lp + m)));
-          const double f = wq[q] * nl * pl[l] * nlp * pl[lp];
+          const double f = nl * pl[l] * nlp * pl[lp] / K;
           for (int n = 0; n <= l + lp; ++n)
-            G[deg_index(m, l, lp, n)] += 0.5 * (2.0 * n + 1.0) * f * pn[n];
+            G[deg_index(m, l, lp, n)] += (n == 0 ? 1.0 : 2.0) * f * pn[n];
         }
       }
     }

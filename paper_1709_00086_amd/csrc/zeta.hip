@@ -388,6 +388,8 @@ __global__ __launch_bounds__(kAT * kAT) void k_zeta_accum_mt(ZetaArgs z, MDims d
                                                              double* __restrict__ zeta) {
   const RowLayout& L = z.lay;
   const int nb = L.nb, nm = L.lmax + 1;
+  // the pair kernel's next launch starts from cleared counters
+  if (blockIdx.x == 0 && threadIdx.x < kQueues) z.queue[threadIdx.x * kQueueStride] = 0;
   int t = blockIdx.x, m = 0;
   for (; m < nm; ++m) {
     const int nt = (L.d[m] + kAT - 1) / kAT;
@@ -497,7 +499,7 @@ hipError_t launch_zeta_pairblock(const ZetaArgs& z, hipStream_t st) {
 // The triangles j = k (the same secondary on both sides, so b1 = b2) are part
 // of the product a_lm conj(a_l'm) (Sec. 3.1).  Without them, zeta^m_{ll'}(b, b)
 // loses sum_i w_i sum_{j in b} w_j^2 conj(Y_lm(u_ij)) Y_l'm(u_ij), which is
-// sum_n G[m][l][l'][n] D(b, n) with D(b, n) = sum_i w_i sum_{j in b} w_j^2 P_n(u_z).
+// sum_n G[m][l][l'][n] D(b, n) with D(b, n) = sum_i w_i sum_{j in b} w_j^2 T_n(u_z).
 
 __device__ double g_deg[kDegTable];
 
@@ -525,7 +527,9 @@ __global__ __launch_bounds__(256) void k_deg_partial(const double* __restrict__ 
 
 // D[c] += sum over the workgroups, in order, of partial[blk][c]
 __global__ void k_deg_accum(const double* __restrict__ partial, int nblk, int ncols,
-                            double* __restrict__ D) {
+                            double* __restrict__ D, int* __restrict__ queue) {
+  // the pair kernel's next launch starts from cleared counters
+  if (blockIdx.x == 0 && threadIdx.x < kQueues) queue[threadIdx.x * kQueueStride] = 0;
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= ncols) return;
   double s = 0.0;
@@ -590,14 +594,15 @@ size_t deg_partial_doubles(long long PB, int nb, int lmax) {
 
 hipError_t launch_deg_reduce(const double* X, int rowW, int nb, int lmax, const double* wsort,
                              const int* plist, const long long* nprim, long long p_begin,
-                             long long p_count, double* partial, double* D, hipStream_t st) {
+                             long long p_count, double* partial, double* D, int* queue,
+                             hipStream_t st) {
   if (p_count <= 0) return hipSuccess;
   const int ncols = nb * (2 * lmax + 1);
   const unsigned nblk = unsigned((p_count + kDegRows - 1) / kDegRows);
   hipLaunchKernelGGL(k_deg_partial, dim3(nblk), dim3(256), 0, st, X, rowW, ncols, wsort, plist,
                      nprim, p_begin, p_count, partial);
   hipLaunchKernelGGL(k_deg_accum, dim3((ncols + 255) / 256), dim3(256), 0, st, partial,
-                     int(nblk), ncols, D);
+                     int(nblk), ncols, D, queue);
   return hipGetLastError();
 }
 

@@ -60,3 +60,33 @@ def test_gram_blocks_hold_any_number_of_primaries(dev, precision, count):
     e = np.abs(z - ref).max() / np.abs(ref).max()
     say(f"  max|dz|/max|z| = {e:.2e}")
     assert e <= TOL[precision]
+
+
+@pytest.mark.parametrize("los", ["z", "observer"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("lmax", [0, 3, 4, 5, 6, 7, 8, 9, 10])
+def test_every_degree_of_the_spin_kernels(dev, lmax, precision, los):
+    """zeta, the distinct zeta and the gradient at each l_max, on both sides of
+    the kernels' degrees 4, 6, 8 and 10.  Float32 positions and no pair within
+    1e-4 of a shell edge, so that FP32 puts every pair into the oracle's shell;
+    tolerances: FP64 1e-10, FP32 1e-5 of max|zeta| and 1e-4 of max|gradient|."""
+    say(f"case degree lmax={lmax} {precision} {los}")
+    cat = C.tiny(n=300, L=150.0, seed=75, rmax=45.0, nbins=5, lmax=lmax, periodic=(los == "z"),
+                 los=los, dtype=np.float32, observer=(-100.0, 20.0, -50.0))
+    pos, w = on(dev, cat)
+    cfg = cfg_of(cat, precision)
+    tol = TOL[precision]
+    for distinct in (False, True):
+        c = cfg_of(cat, precision, distinct=distinct)
+        z, pairs = api.zeta(pos, w, c, return_pairs=True)
+        ref, pairs_ref = oracle.zeta(cat, distinct=distinct, return_pairs=True)
+        e = np.abs(z.cpu().numpy() - ref).max() / np.abs(ref).max()
+        say(f"  distinct={distinct}: max|dz|/max|z| = {e:.2e}")
+        assert pairs == pairs_ref
+        assert e <= tol
+    gz = C.loss_weights(lmax, cat.nbins, seed=76)
+    g = api.zeta_backward(pos, w, cfg, torch.from_numpy(gz).to(dev)).cpu().numpy()
+    gref = oracle.grad(cat, gz)
+    e = np.abs(g - gref).max() / np.abs(gref).max()
+    say(f"  gradient: {e:.2e}")
+    assert e <= (1e-10 if precision == "fp64" else 1e-4)
