@@ -16,8 +16,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libg3pcf.so")
-SOURCES = ["pairs_d10.hip", "pairs_d8.hip", "pairs_d6.hip", "pairs_d4.hip", "pairs.hip",
-           "cells.hip", "zeta.hip", "adjoint.hip", "api.hip", "tables.cpp"]
+SOURCES = (["pairs_cart32.hip", "pairs_cart64.hip"]
+           + [f"pairs_d{d}_{k}.hip" for d in (10, 8, 6, 4) for k in ("deg", "adj", "fwd")]
+           + ["pairs_deg.hip", "pairs.hip", "cells.hip", "zeta.hip", "adjoint.hip", "api.hip", "tables.cpp"])
 ARCH = "gfx950"
 
 

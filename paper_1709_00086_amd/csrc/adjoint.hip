@@ -135,8 +135,8 @@ __global__ __launch_bounds__(256) void k_h_gemm(const double* __restrict__ A,
   const int tid = threadIdx.x;
   const int lane = tid % kWave, wv = tid / kWave;
   // the pair kernels on either side of this one start from cleared counters
-  if (blockIdx.x == 0 && blockIdx.y == 0 && tid < 2 * kQueues)
-    queue[(tid / 2) * kQueueStride + (tid & 1) * kQueueAdjoint] = 0;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid < kQueueKinds * kQueues)
+    queue[tid / kQueueKinds * kQueueStride + tid % kQueueKinds] = 0;
   const long long rows = min(p_count, (long long)(*nprim) - p_begin);
   const long long R0 = (long long)blockIdx.y * kHT;
   if (R0 >= rows) return;

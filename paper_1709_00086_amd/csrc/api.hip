@@ -204,10 +204,10 @@ T* at(void* ws, size_t off) {
 
 // Counts of one XCD's waves, on a 64-byte line of their own.
 struct XcdCounters {
-  int queue[2];                  // next primary: of the forward, of the adjoint
+  int queue[kQueueKinds];        // next item: of the forward, of the adjoint
   unsigned long long pairs;      // accepted pairs
   unsigned long long pairs_adj;
-  unsigned long long pad[5];
+  unsigned long long pad[3];
 };
 static_assert(sizeof(XcdCounters) == kQueueStride * 4, "one line each");
 
@@ -247,6 +247,49 @@ int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, hipStream_t s
   return G3PCF_OK;
 }
 
+// Neighbouring shells whose expected pairs (at the catalogue's mean density)
+// fit the list together make one group: a search costs a wave about 10 us of
+// waiting however little it finds (16 catalogues of 8192 with 274 pairs a
+// primary: 5.5 ms of pair kernels shell by shell, 2.6 ms in groups; FP64 step of
+// 4096 with 137 pairs: 422 and 250 us).  Not where every shell of every primary
+// can have a wave of its own.  A group of one shell is searched into the list
+// only for the cartesian basis, whose later chunks then read it again.  Depends
+// on the catalogue and the settings alone, so that every entry point sums a
+// shell's pairs in the same order.
+void shell_groups(const g3pcf_problem& p, PairArgs& a) {
+  const bool cart = p.basis == G3PCF_BASIS_CARTESIAN;
+  const double most = p.pair_prec == G3PCF_PREC_FP64 ? kListMean64 : kListMean32;
+  const double dr = p.rmax / p.nbins;
+  const double per = double(p.n) / (p.box[0] * p.box[1] * p.box[2]) * 4.0 / 3.0 * M_PI * dr * dr * dr;
+  auto expected = [&](int b0, int b1) {  // shells b0..b1
+    return per * (std::pow(b1 + 1.0, 3) - std::pow(double(b0), 3));
+  };
+  // nor on a tight axis (few cells, and the kernels would double)
+  const bool tight = a.tight[0] || a.tight[1] || a.tight[2];
+  bool single = p.n * p.nbins <= kPairWaves || tight;
+  if (!single) {
+    // the second launch costs each primary about as much as two searches
+    int searches = 0;
+    for (int b = 0, e; b < p.nbins; b = e + 1, ++searches)
+      for (e = b; e + 1 < p.nbins && expected(b, e + 1) <= most;) ++e;
+    single = p.nbins - searches < kListSaves && !cart;
+  }
+  a.ngroup = a.nsingle = 0;
+  for (int lists = 0; lists < 2; ++lists) {
+    for (int b = 0; b < p.nbins;) {
+      int e = b;  // last shell of the group
+      while (!single && e + 1 < p.nbins && expected(b, e + 1) <= most) ++e;
+      if (lists == int(e > b || (cart && !tight && expected(b, e) <= most))) {
+        a.group_lo[a.ngroup] = b;
+        a.group_hi[a.ngroup++] = e;
+      }
+      b = e + 1;
+    }
+    if (lists == 0) a.nsingle = a.ngroup;
+  }
+  a.primary_terms = 1;
+}
+
 int pair_args(const g3pcf_problem& p, const Ws& w, void* ws, PairArgs& a) {
   const hipError_t e = table_addresses(&a.conv, &a.spin);
   if (e != hipSuccess) return hip_fail(e, "table address");
@@ -256,6 +299,7 @@ int pair_args(const g3pcf_problem& p, const Ws& w, void* ws, PairArgs& a) {
   a.cell_start = at<int>(ws, w.cell_start);
   a.plist = at<int>(ws, w.plist);
   a.nprim = &c->nprim;
+  a.overflow = at<unsigned>(ws, w.flags);
   a.spill = at<int>(ws, w.spill);
   a.spill_cap = w.spill_cap;
   a.queue = c->xcd[0].queue;
@@ -280,6 +324,7 @@ int pair_args(const g3pcf_problem& p, const Ws& w, void* ws, PairArgs& a) {
     a.r2_lo[b] = (b == 0) ? 0.0f : std::nextafter(t0, 0.0f);
     a.r2_hi[b] = (b + 1 == p.nbins) ? float(p.rmax * p.rmax) : float(e1 * e1);
   }
+  shell_groups(p, a);
   a.nbins = p.nbins;
   a.lmax = p.lmax;
   a.los = p.los;

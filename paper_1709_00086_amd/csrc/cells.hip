@@ -209,7 +209,8 @@ __global__ void k_primary_flags(const uint8_t* __restrict__ mask,
   flags[s] = ((mask == nullptr || mask[i] != 0) && (region == nullptr || region[i] == r)) ? 1 : 0;
 }
 
-__global__ void k_primary_list(const int* __restrict__ flags, const int* __restrict__ pos,
+// (the flags are left zero)
+__global__ void k_primary_list(int* __restrict__ flags, const int* __restrict__ pos,
                                int64_t n, int* __restrict__ plist,
                                long long* __restrict__ nprim) {
   const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -219,6 +220,7 @@ __global__ void k_primary_list(const int* __restrict__ flags, const int* __restr
     return;
   }
   if (flags[s]) plist[pos[s]] = int(s);
+  flags[s] = 0;
 }
 
 __global__ void k_fill_int(int* p, int64_t count, int value) {

@@ -47,15 +47,22 @@ constexpr int kZetaRowsMin = 128;
 // the 8 XCDs round-robin), each counter on its own 64-byte line.
 constexpr int kQueues = 8;
 constexpr int kQueueStride = 16;
-constexpr int kQueueAdjoint = 1;  // the adjoint's counter on the same line
+// further counters on the same line: of either kernel's groups of shells searched
+// together, of such groups that overflowed, and all three of the adjoint
+constexpr int kQueueListed = 1, kQueueOverflow = 2, kQueueAdjoint = 3, kQueueKinds = 6;
 // Persistent waves of the pair kernel: as many as its occupancy lets run at
 // once on the 256 CUs' SIMDs, at most kPairWaves.
 constexpr int kSimds = 4 * 256;
 constexpr int kPairWaves = 4 * kSimds;
-// Pair-blocks of fewer primaries hand out single shells of a primary: whole
+// Pair-blocks of fewer primaries hand out single groups of shells: whole
 // primaries leave the chip idle behind the last of them (kPairWaves waves run
 // at once).
 constexpr long long kSplitBelow = 4 * kPairWaves;
+// Pairs expected in a group of shells searched together: the list holds 224
+// (FP32) or 128, i.e. six and four standard deviations more; a group that holds
+// still more (clustered galaxies) is searched again, shell by shell.
+constexpr double kListMean32 = 150.0, kListMean64 = 85.0;
+constexpr int kListSaves = 3;  // searches a primary that the groups have to save
 // Spill-list entries per wave: a shell's secondaries kept for the later
 // accumulator chunks of a multi-chunk basis.
 constexpr int kSpillCap = 1 << 14;
@@ -148,6 +155,12 @@ struct PairArgs {
   // FP32 shell test: shell b holds r^2 with r2_lo[b] < r^2 < r2_hi[b] (floats
   // next to the squared shell edges, so the shells partition the floats)
   float r2_lo[kMaxBins], r2_hi[kMaxBins];
+  // groups of neighbouring shells, group g being shells group_lo[g]..group_hi[g]:
+  // first the nsingle ones of a shell of its own, then those searched together
+  int ngroup, nsingle;
+  int group_lo[kMaxBins], group_hi[kMaxBins];
+  unsigned* overflow;        // [*nprim] per primary the groups (bits) that did not fit the list
+  int primary_terms;         // adjoint: this launch adds the primaries' own terms
   int nbins;
   int lmax;
   int los;                   // 0 z, 1 observer
@@ -186,7 +199,7 @@ size_t radix_hist_ints(int64_t n);
 hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b, int fp64,
                         hipStream_t st);
 // Primary list (cell order): galaxies in the mask (NULL: all) and, if region
-// is not NULL, with region[i] == r.
+// is not NULL, with region[i] == r.  Leaves flags zero (see PairArgs::overflow).
 hipError_t launch_primaries(const uint8_t* mask, const int32_t* region, int r, const int* perm,
                             int64_t n, int* flags, int* plist, long long* nprim,
                             void* scan_tmp, size_t scan_tmp_bytes, hipStream_t st);
@@ -206,11 +219,13 @@ hipError_t launch_pair_forward(const PairArgs& a, int fp64, int basis, bool dist
                                hipStream_t st);
 hipError_t launch_pair_adjoint(const PairArgs& a, int fp64, hipStream_t st);
 hipError_t launch_pair_distinct(const PairArgs& a, int fp64, hipStream_t st);
-// The spin kernels of one degree (forward, forward with degenerate sums,
-// adjoint), each compiled in its own file.
+hipError_t launch_pair_cart32(const PairArgs& a, hipStream_t st);
+hipError_t launch_pair_cart64(const PairArgs& a, hipStream_t st);
+// The spin kernels of one degree: forward, forward with degenerate sums, adjoint,
+// each compiled in its own file.
 enum { kSpinForward, kSpinForwardDeg, kSpinAdjoint };
-template <int DEG>
-hipError_t launch_pair_spin(const PairArgs& a, int fp64, int what, hipStream_t st);
+template <int DEG, int WHAT>
+hipError_t launch_pair_spin(const PairArgs& a, int fp64, hipStream_t st);
 hipError_t upload_conv_table();
 hipError_t upload_spin_tables();
 hipError_t table_addresses(const ConvTable** conv, const SpinTable** spin);

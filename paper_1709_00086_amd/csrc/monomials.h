@@ -329,14 +329,80 @@ __device__ __forceinline__ void pair_up(Real (&t)[D]) {
     if constexpr (n + 1 <= N) keep_pair(t[n], t[n + 1]);
   });
 }
-// Entries 1..N of a row, entry n in a register of the other parity than T_n.
+// Rows of sums (or coefficients) over n = 0..N, entries (1, 2), (3, 4), ... in
+// register pairs: entry n in a register of the other parity than T_n's.  The
+// pairs are kept as vectors, so that they stay in their registers around a loop.
 template <int N, typename Real>
-__device__ __forceinline__ void pair_down(Real* r) {
-  static_for<N / 2>([&](auto kc) {
-    constexpr int n = 2 * decltype(kc)::value + 1;
-    keep_pair(r[n], r[n + 1]);
-  });
-}
+struct Row;
+template <int N>
+struct Row<N, float> {
+  float first;                         // n = 0
+  pair_f pairs[N / 2 > 0 ? N / 2 : 1]; // (1, 2), (3, 4), ...
+  float last;                          // n = N if N is odd
+  template <int n>
+  __device__ __forceinline__ float get() const {
+    if constexpr (n == 0) return first;
+    else if constexpr (n == N && (N & 1)) return last;
+    else if constexpr (n & 1) return pairs[(n - 1) / 2].x;
+    else return pairs[(n - 1) / 2].y;
+  }
+  template <int n>
+  __device__ __forceinline__ void set(float v) {
+    if constexpr (n == 0) first = v;
+    else if constexpr (n == N && (N & 1)) last = v;
+    else if constexpr (n & 1) pairs[(n - 1) / 2].x = v;
+    else pairs[(n - 1) / 2].y = v;
+  }
+  __device__ __forceinline__ void keep() {
+    static_for<N / 2>([&](auto kc) { asm("" : "+v"(pairs[decltype(kc)::value])); });
+  }
+};
+template <int N>
+struct Row<N, double> {
+  double v[N + 1];
+  template <int n>
+  __device__ __forceinline__ double get() const {
+    return v[n];
+  }
+  template <int n>
+  __device__ __forceinline__ void set(double x) {
+    v[n] = x;
+  }
+  __device__ __forceinline__ void keep() {}
+};
+
+// The rows m = 1..D (n = 0..D - m).
+template <int M, int D, typename Real>
+struct Rows {
+  Row<D - M, Real> row;
+  Rows<M + 1, D, Real> rest;
+  template <int m>
+  __device__ __forceinline__ auto& at() {
+    if constexpr (m == M)
+      return row;
+    else
+      return rest.template at<m>();
+  }
+  template <int m>
+  __device__ __forceinline__ const auto& at() const {
+    if constexpr (m == M)
+      return row;
+    else
+      return rest.template at<m>();
+  }
+};
+template <int D, typename Real>
+struct Rows<D, D, Real> {
+  Row<0, Real> row;
+  template <int m>
+  __device__ __forceinline__ auto& at() {
+    return row;
+  }
+  template <int m>
+  __device__ __forceinline__ const auto& at() const {
+    return row;
+  }
+};
 
 // The half waves' operands.  For m >= 1 a register holds the real part of
 // something in the lower half of the wave and the imaginary part in the upper;
@@ -408,17 +474,18 @@ __device__ __forceinline__ void chebyshev_z2(Real z, Real z2, Real (&tn)[D]) {
 // multiply-adds as with one pair per lane.
 template <typename Real, int D, bool DISTINCT>
 struct SpinSplit {
-  static constexpr int NP = D * (D + 1) / 2;  // (m >= 1, n) pairs
   static constexpr int ND = DISTINCT ? 2 * D + 1 : 1;
-  Real acc0[D + 1];  // m = 0, one pair per lane
-  Real acc[NP];      // Re | Im
-  Real deg[ND];      // sum w^2 T_n(u_z), n <= 2 D (degenerate triangles)
+  Row<D, Real> acc0;        // m = 0, one pair per lane
+  Rows<1, D, Real> acc;     // Re | Im
+  Real deg[ND];             // sum w^2 T_n(u_z), n <= 2 D (degenerate triangles)
 
   __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int i = 0; i <= D; ++i) acc0[i] = Real(0);
-#pragma unroll
-    for (int i = 0; i < NP; ++i) acc[i] = Real(0);
+    static_for<D + 1>([&](auto nc) { acc0.template set<decltype(nc)::value>(Real(0)); });
+    static_for<D>([&](auto mc) {
+      constexpr int m = decltype(mc)::value + 1;
+      static_for<D - m + 1>(
+          [&](auto nc) { acc.template at<m>().template set<decltype(nc)::value>(Real(0)); });
+    });
 #pragma unroll
     for (int i = 0; i < ND; ++i) deg[i] = Real(0);
   }
@@ -431,11 +498,11 @@ struct SpinSplit {
     Real c0 = h.c0, c1 = h.c1;
     static_for<D>([&](auto mc) {
       constexpr int m = decltype(mc)::value + 1;
-      constexpr int q = spin_pair_c<D>(m, 0);
-      acc[q] += c1;
+      auto& r = acc.template at<m>();
+      r.template set<0>(r.template get<0>() + c1);
       static_for<D - m>([&](auto nc) {
         constexpr int n = decltype(nc)::value + 1;
-        acc[q + n] = fma_r(c1, t[n], acc[q + n]);
+        r.template set<n>(fma_r(c1, t[n], r.template get<n>()));
       });
       if constexpr (m < D) {
         const Real c2 = fma_r(h.x2, c1, -(h.rho * c0));
@@ -447,19 +514,16 @@ struct SpinSplit {
 
   __device__ __forceinline__ void add(Real x, Real y, Real z, Real w, Real* xch, int lane) {
     Exchange<Real, true>::put(xch, lane, x, y, z, w);
-    static_for<D>([&](auto mc) {
-      constexpr int m = decltype(mc)::value + 1;
-      pair_down<D - m>(acc + spin_pair_c<D>(m, 0));
-    });
-    pair_down<D>(acc0);
+    static_for<D>([&](auto mc) { acc.template at<decltype(mc)::value + 1>().keep(); });
+    acc0.keep();
     // m = 0 (and the degenerate sums) while the exchange is under way
     Real t[D + 1];
     chebyshev_z2<D>(z, z + z, t);
     pair_up<D>(t);
-    acc0[0] += w;
+    acc0.template set<0>(acc0.template get<0>() + w);
     static_for<D>([&](auto nc) {
       constexpr int n = decltype(nc)::value + 1;
-      acc0[n] = fma_r(w, t[n], acc0[n]);
+      acc0.template set<n>(fma_r(w, t[n], acc0.template get<n>()));
     });
     if constexpr (DISTINCT) {
       const Real w2 = w * w, z2 = z + z;
@@ -481,6 +545,22 @@ struct SpinSplit {
     add_half(Exchange<Real, true>::get(xch, lane, false));
     add_half(Exchange<Real, true>::get(xch, lane, true));
   }
+
+  // The sums as plain arrays: m = 0 by n, and the rest in pair order.
+  static constexpr int NP = D * (D + 1) / 2;  // (m >= 1, n) pairs
+  __device__ __forceinline__ void unpack(Real (&s0)[D + 1], Real (&s)[NP]) const {
+    static_for<D + 1>([&](auto nc) {
+      constexpr int n = decltype(nc)::value;
+      s0[n] = acc0.template get<n>();
+    });
+    static_for<D>([&](auto mc) {
+      constexpr int m = decltype(mc)::value + 1;
+      static_for<D - m + 1>([&](auto nc) {
+        constexpr int n = decltype(nc)::value;
+        s[spin_pair_c<D>(m, n)] = acc.template at<m>().template get<n>();
+      });
+    });
+  }
 };
 
 // Adjoint polynomial (either basis): the sum over (m, n), m + n <= D, of the
@@ -496,18 +576,24 @@ struct SpinSplit {
 // the two.
 template <typename Real, int D>
 struct SplitPoly {
-  static constexpr int NP = D * (D + 1) / 2;
-  Real g0[D + 1];
-  Real g[NP];
+  Row<D, Real> g0;
+  Rows<1, D, Real> g;
 
   // gc: the (D + 1)^2 coefficients in term order
   template <typename Ptr>
   __device__ __forceinline__ void load(Ptr gc, int lane) {
-#pragma unroll
-    for (int n = 0; n <= D; ++n) g0[n] = gc[n];
     const int part = lane >> 5;
-#pragma unroll
-    for (int q = 0; q < NP; ++q) g[q] = gc[D + 1 + 2 * q + part];
+    static_for<D + 1>([&](auto nc) {
+      constexpr int n = decltype(nc)::value;
+      g0.template set<n>(gc[n]);
+    });
+    static_for<D>([&](auto mc) {
+      constexpr int m = decltype(mc)::value + 1;
+      static_for<D - m + 1>([&](auto nc) {
+        constexpr int n = decltype(nc)::value;
+        g.template at<m>().template set<n>(gc[D + 1 + 2 * spin_pair_c<D>(m, n) + part]);
+      });
+    });
   }
 
   __device__ __forceinline__ Real eval_half(const Half<Real>& h) const {
@@ -517,11 +603,11 @@ struct SplitPoly {
     Real c0 = h.c0, c1 = h.c1, sum = Real(0);
     static_for<D>([&](auto mc) {
       constexpr int m = decltype(mc)::value + 1;
-      constexpr int q = spin_pair_c<D>(m, 0);
-      Real v = g[q];
+      const auto& r = g.template at<m>();
+      Real v = r.template get<0>();
       static_for<D - m>([&](auto nc) {
         constexpr int n = decltype(nc)::value + 1;
-        v = fma_r(g[q + n], t[n], v);
+        v = fma_r(r.template get<n>(), t[n], v);
       });
       sum = m == 1 ? c1 * v : fma_r(c1, v, sum);
       if constexpr (m < D) {
@@ -536,18 +622,15 @@ struct SplitPoly {
   // the polynomial of the lane's own pair
   __device__ __forceinline__ Real eval(Real x, Real y, Real z, Real* xch, int lane) {
     Exchange<Real, false>::put(xch, lane, x, y, z, Real(1));
-    static_for<D>([&](auto mc) {
-      constexpr int m = decltype(mc)::value + 1;
-      pair_down<D - m>(g + spin_pair_c<D>(m, 0));
-    });
-    pair_down<D>(g0);
+    static_for<D>([&](auto mc) { g.template at<decltype(mc)::value + 1>().keep(); });
+    g0.keep();
     Real t[D + 1];
     chebyshev_z2<D>(z, z + z, t);
     pair_up<D>(t);
-    Real total = g0[0];
+    Real total = g0.template get<0>();
     static_for<D>([&](auto nc) {
       constexpr int n = decltype(nc)::value + 1;
-      total = fma_r(g0[n], t[n], total);
+      total = fma_r(g0.template get<n>(), t[n], total);
     });
     Exchange<Real, false>::fence();
     Real sa = eval_half(Exchange<Real, false>::get(xch, lane, false));

@@ -26,6 +26,9 @@
 //      monomials, as in the paper's vectorisation section);
 //   4. reduces the per-lane partials once per (primary, shell) with DPP and
 //      converts the shell's monomial sums to a_lm in FP64.
+// Sparse neighbouring shells are searched together: a group of shells that is
+// expected to hold few pairs (PairArgs::group) is searched once, into a list in
+// LDS, and steps 2 and 3 then read the list for each of its shells.
 // No neighbour list ever leaves the compute unit.  A basis whose sums do not
 // fit in registers at once is accumulated in chunks: the first chunk's
 // search also writes the shell's secondary indices to the wave's spill list,
@@ -86,31 +89,56 @@ constexpr int kOutBuf = 4 * kWave;
 // the reduced sums have their own space (a later chunk may search again while
 // they wait); otherwise the sums of a shell take the ring's, which is empty by
 // then.
-template <typename Real, bool SPILL, bool SPINT, bool SPIN, bool ADJ>
+// The list: the accepted pairs of a group of sparse shells, found by one search
+// (see search_list).
+template <typename Real>
+constexpr int kList = sizeof(Real) == 4 ? 224 : 128;
+constexpr int kOutBufList = 3 * kWave;  // terms that may wait beside the list
+
+template <typename Real, bool SPILL, bool SPINT, bool SPIN, bool ADJ, bool LISTED>
 struct WaveLds {
   using V = typename V4<Real>::T;
-  static constexpr int kExchange = !SPIN ? 0 : Exchange<Real, !ADJ>::kReals;
-  static constexpr int kOut = SPINT ? kOutBuf : 0;
-  static constexpr int kSpilled = SPILL ? kRing : 0;
-  static constexpr int kSums = SPILL ? kTermsCart + 1 : 0;  // (+1 padding slot)
+  static constexpr int kExchange = SPIN ? int(Exchange<Real, !ADJ>::kReals * sizeof(Real)) : 0;
+  // FP32 spin kernels have 10 KB a wave (four waves per SIMD): with the list the
+  // exchange and the waiting terms go into the run table, which is not in use
+  // while the list is read
+  static constexpr bool kInRuns = LISTED && SPIN && sizeof(Real) == 4;
+  static constexpr int kOut = SPINT ? (LISTED ? kOutBufList : kOutBuf) : 0;  // waves of terms
+  static constexpr int kListBytes = LISTED ? kList<Real> * int(sizeof(V)) : 0;
+  static constexpr int kBins = LISTED && sizeof(Real) == 8 ? kList<Real> * 4 : 0;
+  static constexpr int kSums = SPILL ? (kTermsCart + 1) * int(sizeof(Real)) + 4 : 0;  // (+1 padding slot)
+  static constexpr int kSpilled = SPILL && !LISTED ? kRing * 4 : 0;
+  static constexpr int kMore = kListBytes + kBins + (kInRuns ? 0 : kExchange + kOut * 8) + kSums +
+                               kSpilled;
 
   V ring[kRing];               // (d_x, d_y, d_z, w) forward; (d_x, d_y, d_z, index) adjoint
   alignas(16) RunEntry<Real> run[kMaxRuns + 1];  // (+1: the FP32 search's sentinel run)
   // bit c of the span: a run starts at virtual candidate index mbase + c
   alignas(16) unsigned marks[kMarkWords];
-  // what the half waves take each other's pairs from (spin kernels), waiting
-  // terms (before the first, the shell's polynomial coefficients), the
-  // secondary indices of the ring's entries and the reduced sums
-  alignas(16) char more[kExchange * sizeof(Real) + kOut * 8 + kSpilled * 4 + kSums * sizeof(Real) + 16];
+  // the list and (FP64) its entries' shells; what the half waves take each
+  // other's pairs from (spin kernels); waiting terms (before the first, the
+  // shell's polynomial coefficients); the reduced sums and the secondary
+  // indices of the ring's entries (several chunks)
+  alignas(16) char more[kMore > 0 ? kMore : 16];
   int pre[kMaxRuns + 1];       // first virtual candidate index of each run
 
-  __device__ __forceinline__ Real* xch() { return reinterpret_cast<Real*>(more); }
-  __device__ __forceinline__ int2* out() {
-    return reinterpret_cast<int2*>(more + kExchange * sizeof(Real));
+  static_assert(!kInRuns || kExchange + kOut * 8 <= int(sizeof(run)), "the run table holds both");
+  __device__ __forceinline__ V* list() { return reinterpret_cast<V*>(more); }
+  __device__ __forceinline__ int* bins() { return reinterpret_cast<int*>(more + kListBytes); }
+  __device__ __forceinline__ Real* xch() {
+    if constexpr (kInRuns)
+      return reinterpret_cast<Real*>(run);
+    else
+      return reinterpret_cast<Real*>(more + kListBytes + kBins);
   }
-  __device__ __forceinline__ Real* sums() { return reinterpret_cast<Real*>(more); }
+  __device__ __forceinline__ int2* out() {
+    return reinterpret_cast<int2*>(reinterpret_cast<char*>(xch()) + kExchange);
+  }
+  __device__ __forceinline__ Real* sums() {
+    return reinterpret_cast<Real*>(more + kListBytes + kBins + kExchange + kOut * 8);
+  }
   __device__ __forceinline__ int* ring_j() {
-    return reinterpret_cast<int*>(more + kSums * sizeof(Real));
+    return reinterpret_cast<int*>(more + kListBytes + kBins + kExchange + kOut * 8 + kSums);
   }
 };
 
@@ -262,7 +290,7 @@ template <typename Real, int BASIS, bool ADJOINT, int DEG>
 struct Occ {
   static constexpr bool kF32 = std::is_same<Real, float>::value;
   static constexpr bool kSpinT = ADJOINT && kF32;
-  static constexpr int value = (BASIS == kBasisDeg)                ? 4
+  static constexpr int value = (BASIS == kBasisDeg)                ? (kF32 ? 4 : 2)
                                : (BASIS == G3PCF_BASIS_CARTESIAN) ? (kF32 ? 3 : 2)
                                : kF32 ? 4 : 2;
 };
@@ -278,8 +306,15 @@ constexpr int n_chunks(ChunkList<C...>) {
 // kMin: a periodic axis where the search window can wrap onto itself (FP32: the
 // minimum image per candidate).  All are fixed per launch, so each kernel holds
 // the code and the live values of one mode only.
-template <typename Real, int BASIS, bool ADJOINT, int DEG, bool kRot, bool kMin>
+// KIND: kKindSingle, every group of shells is one shell, whose pairs are
+// accumulated as its search finds them; kKindListed, the launch's groups are
+// searched into the list; kKindAfter, as the first, after a launch of the
+// second: also the groups that did not fit the list.  (A kernel that does more
+// than the first needs registers for it: 4 to 7% slower on a large catalogue.)
+enum { kKindSingle, kKindListed, kKindAfter };
+template <typename Real, int BASIS, bool ADJOINT, int DEG, bool kRot, bool kMin, int KIND>
 struct PairKernel {
+  static constexpr bool kListed = KIND == kKindListed;
   using V = typename V4<Real>::T;
   static constexpr bool kF32 = std::is_same<Real, float>::value;
   // FP32 adjoint: terms wait in LDS for their atomic additions
@@ -287,7 +322,7 @@ struct PairKernel {
   static constexpr bool kSpin = BASIS == G3PCF_BASIS_SPIN || BASIS == kBasisSpinDeg;
   using CL = typename Chunks<Real, BASIS, DEG>::type;
   static constexpr bool kMulti = !ADJOINT && n_chunks(CL{}) > 1;
-  using Lds = WaveLds<Real, kMulti, kSpinT, kSpin, ADJOINT>;
+  using Lds = WaveLds<Real, kMulti, kSpinT, kSpin, ADJOINT, kListed>;
   // the waves of the occupancy target fit a CU's LDS (the waves' first items are
   // dealt out in advance, so all of them have to run at once)
   static_assert(sizeof(Lds) * 4 * Occ<Real, BASIS, ADJOINT, DEG>::value <= 160 * 1024, "LDS");
@@ -580,17 +615,19 @@ struct PairKernel {
     }
   }
 
-  // One search of shell b over the annulus [r0, r1): every accepted pair is
+  // One search of the shells b..b_last over the annulus [r0, r1).
+  // kListed: the accepted pairs are written to the list (those past its end are
+  // only counted).  Else b = b_last, and every one is
   // appended to the LDS ring as (separation, weight or index), and every full
   // wave of pairs is handed to consume(entry, index, valid) (one pair per
   // lane; the index only with SPILL); the
   // remainder at the end.  The position loads of the next window are issued
   // before the current window is binned.
   template <bool MINIMG, bool SPILL, typename Consume>
-  static __device__ __forceinline__ unsigned search_shell(const PairArgs& a, Lds& W,
-                                                          const V* __restrict__ pos4,
-                                                          const Primary& P, int b, double r0,
-                                                          double r1, Consume&& consume) {
+  static __device__ __forceinline__ unsigned search(const PairArgs& a, Lds& W,
+                                                    const V* __restrict__ pos4, const Primary& P,
+                                                    int b, int b_last, double r0, double r1,
+                                                    Consume&& consume) {
     const int lane = threadIdx.x % kWave;
     const int* __restrict__ cs = a.cell_start;
     int c0[3] = {0, 0, 0}, c1[3] = {0, 0, 0};
@@ -619,7 +656,7 @@ struct PairKernel {
     float lo2 = 0.0f, hi2 = 0.0f;
     if constexpr (kF32) {
       lo2 = a.r2_lo[b];
-      hi2 = a.r2_hi[b];
+      hi2 = a.r2_hi[b_last];
     }
     int cnt = 0;
     unsigned accepted = 0;
@@ -641,6 +678,7 @@ struct PairKernel {
         Real d[3];
         bool acc;
         unsigned long long m;
+        int bin = 0;
         if constexpr (kF32) {
           const float* ref = MINIMG ? P.pref : rref;
           float dx = __fsub_rn(q.x, ref[0]), dy = __fsub_rn(q.y, ref[1]),
@@ -661,8 +699,8 @@ struct PairKernel {
           m = ballot(r2 > lo2) & ballot(r2 < hi2);
         } else {
           double r2;
-          const int bin = P.bin64.classify(q, P.p, d, r2);
-          acc = (v0 + lane < total) && bin == b;
+          bin = P.bin64.classify(q, P.p, d, r2);
+          acc = (v0 + lane < total) && bin >= b && bin <= b_last;
           m = ballot(acc);
         }
         if (acc) {
@@ -675,14 +713,21 @@ struct PairKernel {
           } else {
             ent.w = q.w;
           }
-          const int slot = cnt + lanes_below(m);  // below kRing: cnt < kWave here
-          W.ring[slot] = ent;
-          if constexpr (SPILL) W.ring_j()[slot] = j;
+          const int slot = cnt + lanes_below(m);  // ring: below kRing, as cnt < kWave here
+          if constexpr (kListed) {
+            if (slot < kList<Real>) {
+              W.list()[slot] = ent;
+              if constexpr (!kF32) W.bins()[slot] = bin;
+            }
+          } else {
+            W.ring[slot] = ent;
+            if constexpr (SPILL) W.ring_j()[slot] = j;
+          }
         }
         const int got = __popcll(m);
         cnt += got;
         accepted += unsigned(got);
-        if (cnt >= kWave) {
+        if (!kListed && cnt >= kWave) {
           // the first wave of pairs out, the rest (fewer than kWave) moved to
           // the front, so that slots need no wrap-around
           wave_lds_fence();
@@ -724,7 +769,7 @@ struct PairKernel {
       wave_lds_fence();
     }
     __builtin_amdgcn_s_setprio(0);
-    if (cnt > 0) {
+    if (!kListed && cnt > 0) {
       wave_lds_fence();
       V ent;
       int jj = 0;
@@ -741,6 +786,56 @@ struct PairKernel {
       wave_lds_fence();
     }
     return accepted;
+  }
+
+  // The pairs of shell b among the list's n entries, a wave at a time to
+  // consume, as search does (the same test on the same separations).
+  template <typename Consume>
+  static __device__ __forceinline__ void list_shell(const PairArgs& a, Lds& W, int b, int n,
+                                                    Consume&& consume) {
+    const int lane = threadIdx.x % kWave;
+    float lo2 = 0.0f, hi2 = 0.0f;
+    if constexpr (kF32) {
+      lo2 = a.r2_lo[b];
+      hi2 = a.r2_hi[b];
+    }
+    int cnt = 0;
+    wave_lds_fence();
+    for (int at = 0; at < n; at += kWave) {
+      const int i = at + lane;
+      const V e = W.list()[min(i, n - 1)];
+      bool acc = i < n;
+      if constexpr (kF32) {
+        const float r2 = fma_r(e.z, e.z, fma_r(e.y, e.y, __fmul_rn(e.x, e.x)));
+        acc = acc & (r2 > lo2) & (r2 < hi2);
+      } else {
+        acc = acc & (W.bins()[min(i, n - 1)] == b);
+      }
+      const unsigned long long m = ballot(acc);
+      if (acc) W.ring[cnt + lanes_below(m)] = e;
+      cnt += __popcll(m);
+      if (cnt >= kWave) {
+        wave_lds_fence();
+        const V ent = W.ring[lane];
+        W.ring[lane] = W.ring[kWave + lane];
+        consume(ent, 0, true);
+        cnt -= kWave;
+      }
+    }
+    if (cnt > 0) {
+      wave_lds_fence();
+      V ent;
+      if (lane < cnt) {
+        ent = W.ring[lane];
+      } else {
+        ent.x = Real(0);
+        ent.y = Real(0);
+        ent.z = Real(1);
+        ent.w = ADJOINT ? pack_index(0, Real(0)) : Real(0);
+      }
+      consume(ent, 0, lane < cnt);
+      wave_lds_fence();
+    }
   }
 
   // Separation of secondary j from the primary exactly as the search forms
@@ -824,14 +919,31 @@ struct PairKernel {
                             });
   }
 
-  // All chunks (forward) or the adjoint of shell b.  With several
-  // chunks, the first search also writes the shell's secondaries to the
-  // wave's spill list, and the later chunks replay it instead of searching
+  // The pairs of shell b to consume: by a search of its own, or (kListed) from
+  // the list, which holds the group's `found` pairs.
+  template <bool MINIMG, typename Consume>
+  static __device__ __forceinline__ unsigned pairs_of(const PairArgs& a, Lds& W,
+                                                      const V* __restrict__ pos4,
+                                                      const Primary& P, int b, double r0,
+                                                      double r1, int found, Consume&& consume) {
+    if constexpr (kListed) {
+      list_shell(a, W, b, found, consume);
+      return 0;
+    } else {
+      return search<MINIMG, false>(a, W, pos4, P, b, b, r0, r1, consume);
+    }
+  }
+
+  // All chunks (forward) or the adjoint of shell b; returns the pairs its search
+  // accepted (kListed: found pairs are counted by the caller).  With several
+  // chunks and no list, the first search also writes the shell's secondaries to
+  // the wave's spill list, and the later chunks replay it instead of searching
   // again (unless it overflowed).
   static __device__ __forceinline__ unsigned shell(const PairArgs& a, Lds& W,
                                                    const V* __restrict__ pos4, const Primary& P,
-                                                   int b, double r0, double r1, long long row,
-                                                   double w_prim, int* __restrict__ sp) {
+                                                   int b, double r0, double r1, int found,
+                                                   long long row, double w_prim,
+                                                   int* __restrict__ sp) {
     constexpr bool MINIMG = kF32 && kMin;
     const int lane = threadIdx.x % kWave;
     unsigned got = 0;
@@ -843,37 +955,34 @@ struct PairKernel {
         using Chunk = std::remove_pointer_t<decltype(tag)>;
         Chunk ch;
         ch.zero();
+        auto add_unit = [&](Real ux, Real uy, Real uz, Real w) {
+          if constexpr (kSpin)
+            ch.add(ux, uy, uz, w, W.xch(), lane);
+          else
+            ch.add(ux, uy, uz, w);
+        };
         auto add = [&](const V& e) {
           Real ux, uy, uz;
           unit(P, e, ux, uy, uz);
-          if constexpr (kSpin)
-            ch.add(ux, uy, uz, e.w, W.xch(), lane);
-          else
-            ch.add(ux, uy, uz, e.w);
+          add_unit(ux, uy, uz, e.w);
         };
-        if constexpr (kMulti) {
-          if (first && cap > 0) {
-            int nsp = 0;
-            got = search_shell<MINIMG, true>(a, W, pos4, P, b, r0, r1,
-                                             [&](const V& e, int j, bool valid) {
-                                               if (valid && nsp + lane < cap) sp[nsp + lane] = j;
-                                               nsp += __popcll(ballot(valid));
-                                               add(e);
-                                             });
-            replayable = got <= unsigned(cap);
-          } else if (!first && replayable) {
-            replay<MINIMG>(a, pos4, P, sp, int(got),
-                           [&](Real ux, Real uy, Real uz, Real w) { ch.add(ux, uy, uz, w); });
-          } else {
-            const unsigned g = search_shell<MINIMG, false>(
-                a, W, pos4, P, b, r0, r1, [&](const V& e, int, bool) { add(e); });
-            if (first) got = g;
-          }
-          first = false;
+        if (kMulti && !kListed && first && cap > 0) {
+          int nsp = 0;
+          got = search<MINIMG, kMulti && !kListed>(
+              a, W, pos4, P, b, b, r0, r1, [&](const V& e, int j, bool valid) {
+                if (valid && nsp + lane < cap) sp[nsp + lane] = j;
+                nsp += __popcll(ballot(valid));
+                add(e);
+              });
+          replayable = got <= unsigned(cap);
+        } else if (kMulti && !kListed && !first && replayable) {
+          replay<MINIMG>(a, pos4, P, sp, int(got), add_unit);
         } else {
-          got = search_shell<MINIMG, false>(a, W, pos4, P, b, r0, r1,
-                                            [&](const V& e, int, bool) { add(e); });
+          const unsigned g = pairs_of<MINIMG>(a, W, pos4, P, b, r0, r1, found,
+                                              [&](const V& e, int, bool) { add(e); });
+          if (first) got = g;
         }
+        first = false;
         if constexpr (kSpin) {
           reduce_split(W, ch);
         } else {
@@ -905,34 +1014,35 @@ struct PairKernel {
         // FP32 polynomial and FP32 atomics.
         const float wp = float(w_prim);
         // Each wave of terms goes to the LDS buffer and the buffer to the
-        // atomics every kOutBuf / kWave waves: a wait for the candidate loads
-        // then finds atomics outstanding (and has to wait for them, vmcnt
-        // counting both) once per flush instead of after every wave of pairs.
-        // A full buffer is flushed before the next wave's polynomial, which
-        // then runs while the atomics complete.
+        // atomics every few waves: a wait for the candidate loads then finds
+        // atomics outstanding (and has to wait for them, vmcnt counting both)
+        // once per flush instead of after every wave of pairs.  A full buffer
+        // is flushed before the next wave's polynomial, which then runs while
+        // the atomics complete.
         int nout = 0;
-        got = search_shell<MINIMG, false>(
-            a, W, pos4, P, b, r0, r1, [&](const V& e, int, bool valid) {
-              if (nout == kOutBuf) {
-                flush_terms(a, W, nout);
-                nout = 0;
-              }
-              Real ux, uy, uz;
-              unit(P, e, ux, uy, uz);
-              const float v = poly.eval(ux, uy, uz, W.xch(), lane_here());
-              W.out()[nout + lane_here()] =
-                  make_int2(valid ? unpack_index(e.w) : -1, __float_as_int(wp * v));
-              nout += kWave;
-            });
+        got = pairs_of<MINIMG>(a, W, pos4, P, b, r0, r1, found,
+                               [&](const V& e, int, bool valid) {
+                                 if (nout == Lds::kOut) {
+                                   flush_terms(a, W, nout);
+                                   nout = 0;
+                                 }
+                                 Real ux, uy, uz;
+                                 unit(P, e, ux, uy, uz);
+                                 const float v = poly.eval(ux, uy, uz, W.xch(), lane_here());
+                                 W.out()[nout + lane_here()] = make_int2(
+                                     valid ? unpack_index(e.w) : -1, __float_as_int(wp * v));
+                                 nout += kWave;
+                               });
         if (nout > 0) flush_terms(a, W, nout);
       } else {
-        got = search_shell<MINIMG, false>(
-            a, W, pos4, P, b, r0, r1, [&](const V& e, int, bool valid) {
-              Real ux, uy, uz;
-              unit(P, e, ux, uy, uz);
-              const double v = poly.eval(ux, uy, uz, W.xch(), lane_here());
-              if (valid) unsafeAtomicAdd(&a.grad_w[unpack_index(e.w)], w_prim * v);
-            });
+        got = pairs_of<MINIMG>(a, W, pos4, P, b, r0, r1, found,
+                               [&](const V& e, int, bool valid) {
+                                 Real ux, uy, uz;
+                                 unit(P, e, ux, uy, uz);
+                                 const double v = poly.eval(ux, uy, uz, W.xch(), lane_here());
+                                 if (valid)
+                                   unsafeAtomicAdd(&a.grad_w[unpack_index(e.w)], w_prim * v);
+                               });
       }
       wave_lds_fence();
     }
@@ -956,15 +1066,6 @@ struct PairKernel {
   static_assert(kMulti || sizeof(Lds::ring) >= (2 * kTermsSpin + 1) * sizeof(Real),
                 "the ring holds a shell's sums, or its H values and coefficients");
 
-  // The wave's next item of share x (first: items dealt out in advance).
-  static __device__ __forceinline__ int next_item(const PairArgs& a, int x, int first, int items,
-                                                  int lane) {
-    if (items <= first) return items;
-    int t = 0;
-    if (lane == 0) t = atomicAdd(a.queue + x * kQueueStride, 1);
-    return first + uniform_int(__shfl(t, 0));
-  }
-
   static __device__ __forceinline__ void run(const PairArgs& a) {
     extern __shared__ char smem_raw[];
     Lds* lds = reinterpret_cast<Lds*>(smem_raw);
@@ -984,13 +1085,26 @@ struct PairKernel {
     // contiguous shares, one per XCD: a wave takes primaries from its own XCD's
     // share first, so the candidates of the primaries an XCD works on at once
     // are neighbours in its L2, then helps the other shares.  Where there are
-    // few primaries a wave takes one shell of one primary at a time, the outer
-    // (larger) shells first.  A wave's first item is its own number in its
+    // few primaries a wave takes one group of shells of one primary at a time,
+    // the outer (larger) shells first.  A wave's first item is its own number in its
     // share (the launch holds no more waves than run at once), the further ones
     // come from the share's counter; a wave whose share is used up looks at all
     // counters in one load before it adds to another's (4096 waves that each
     // tried all eight counters in turn took 60 us to end).
-    const int per = NP < kSplitBelow ? nb : 1;  // items of a primary
+    // groups of this launch: the searched together, or the single shells; then,
+    // where some primary's list overflowed, also all groups again (the shells of
+    // those that did)
+    int mine = a.nsingle;
+    if constexpr (kListed) {
+      mine = a.ngroup - a.nsingle;
+    } else if constexpr (KIND == kKindAfter) {
+      bool any = false;
+      if (lane < kQueues) any = a.queue[lane * kQueueStride + (kListed ? kQueueOverflow - kQueueListed : kQueueOverflow)] != 0;
+      if (ballot(any) != 0) mine = a.ngroup;
+    }
+    if (mine == 0) return;
+    const int g_first = kListed ? a.nsingle : 0;
+    const int per = NP < kSplitBelow ? mine : 1;  // items of a primary
     const int grid = int(gridDim.x);
     const long long share = (NP + kQueues - 1) / kQueues;
     auto share_waves = [&](int x) { return (grid - x + kQueues - 1) / kQueues * kWavesPerBlock; };
@@ -1039,8 +1153,9 @@ struct PairKernel {
         if (tt < kAdjStripes * q) tt = (tt % kAdjStripes) * q + tt / kAdjStripes;
       }
       const long long qi = lo + tt;
-      // shells of this item, from the outermost in: all, or nb - 1 - item
-      const int b_hi = per > 1 ? nb - 1 - item : nb - 1, b_lo = per > 1 ? b_hi : 0;
+      // groups of shells of this item, from the outermost in: all, or one
+      const int g_hi = g_first + (per > 1 ? per - 1 - item : mine - 1);
+      const int g_lo = per > 1 ? g_hi : g_first;
       const int slot = uniform_int(a.plist[a.p_begin + qi]);
       const V pv = pos4[slot];
       Primary P;
@@ -1061,7 +1176,10 @@ struct PairKernel {
             }
           }
         }
-        t = next_item(a, x, share_waves(x), items, lane);
+        int next = items;
+        if (items > share_waves(x) && lane == 0)
+          next = share_waves(x) + atomicAdd(a.queue + x * kQueueStride, 1);
+        t = uniform_int(__shfl(next, 0));
         continue;
       }
       if constexpr (kRot) {
@@ -1096,18 +1214,49 @@ struct PairKernel {
       double w_prim = 0.0;
       if constexpr (ADJOINT) {
         w_prim = a.wsort[slot];
-        if (item == 0) primary_term(a, row, slot);
+        if (item == 0 && a.primary_terms) primary_term(a, row, slot);
       }
 
-      for (int bb = b_hi; bb >= b_lo; --bb) {
-        const int b = uniform_int(bb);  // in a scalar register throughout the shell
-        // annulus of shell b, widened by the search margin on both sides
-        const double r0 = uniform_double(fmax(0.0, b * a.rmax / nb - margin));
-        const double r1 =
-            uniform_double((b + 1 == nb) ? a.rmax_search : (b + 1) * a.rmax / nb + margin);
-        my_pairs += shell(a, W, pos4, P, b, r0, r1, row, w_prim, sp);
+      // annulus of a shell, widened by the search margin on both sides
+      auto inner = [&](int b) { return uniform_double(fmax(0.0, b * a.rmax / nb - margin)); };
+      auto outer = [&](int b) {
+        return uniform_double((b + 1 == nb) ? a.rmax_search : (b + 1) * a.rmax / nb + margin);
+      };
+      int next = items;
+      const int first = share_waves(x);
+      unsigned over = 0;
+      if constexpr (KIND == kKindAfter) {
+        if (mine > a.nsingle) over = unsigned(uniform_int(int(a.overflow[a.p_begin + qi])));
       }
-      t = next_item(a, x, share_waves(x), items, lane);
+      for (int g = g_hi; g >= g_lo; --g) {
+        // every shell is a group of its own where none are searched together
+        const int b0 = KIND == kKindSingle ? g : uniform_int(a.group_lo[g]);
+        const int b1 = KIND == kKindSingle ? g : uniform_int(a.group_hi[g]);
+        // the wave's next item is asked for before its last group
+        if (g == g_lo && items > first && lane == 0)
+          next = first + atomicAdd(a.queue + x * kQueueStride, 1);
+        int found = 0;
+        if constexpr (kListed) {
+          found = int(search<kF32 && kMin, false>(a, W, pos4, P, b0, b1, inner(b0), outer(b1),
+                                                  [](const V&, int, bool) {}));
+          if (found > kList<Real>) {
+            // left to the launch of the single shells
+            if (lane == 0) {
+              atomicOr(a.overflow + a.p_begin + qi, 1u << g);
+              atomicAdd(a.queue + x * kQueueStride + (kListed ? kQueueOverflow - kQueueListed : kQueueOverflow), 1);
+            }
+            continue;
+          }
+          my_pairs += unsigned(found);
+        } else if constexpr (KIND == kKindAfter) {
+          if (g >= a.nsingle && ((over >> g) & 1u) == 0) continue;
+        }
+        for (int bb = b1; bb >= b0; --bb) {
+          const int b = uniform_int(bb);  // in a scalar register throughout the shell
+          my_pairs += shell(a, W, pos4, P, b, inner(b), outer(b), found, row, w_prim, sp);
+        }
+      }
+      t = uniform_int(__shfl(next, 0));
     }
 
     // counted only where the caller asked for it, on its XCD's line (4096 waves
@@ -1194,6 +1343,8 @@ struct PairKernel {
                                                       SpinSplit<Real, DEG, BASIS == kBasisSpinDeg>& ch) {
     using Chunk = SpinSplit<Real, DEG, BASIS == kBasisSpinDeg>;
     constexpr int NP = Chunk::NP;
+    Real s0[DEG + 1], s[NP];
+    ch.unpack(s0, s);
     Real* M = sums(W);
     const int lane = lane_here();
     const int row = lane >> 4;
@@ -1207,7 +1358,7 @@ struct PairKernel {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int q = g + 2 * k;
-        c[k] = q < NP ? fold2(ch.acc[q < NP ? q : 0], q + 1 < NP ? ch.acc[q + 1 < NP ? q + 1 : 0] : Real(0))
+        c[k] = q < NP ? fold2(s[q < NP ? q : 0], q + 1 < NP ? s[q + 1 < NP ? q + 1 : 0] : Real(0))
                       : Real(0);
       }
       const Real tot = row_sums4(c[0], c[1], c[2], c[3], lane);
@@ -1215,7 +1366,7 @@ struct PairKernel {
       const int q = g + 2 * grp + (row & 1);
       if (leader && q < NP) M[DEG + 1 + 2 * q + (row >> 1)] = tot;
     }
-    fold_plain<DEG + 1>(M, ch.acc0, row, grp, leader, lane);
+    fold_plain<DEG + 1>(M, s0, row, grp, leader, lane);
     if constexpr (BASIS == kBasisSpinDeg)
       fold_plain<Chunk::ND>(M + kSpinTerms, ch.deg, row, grp, leader, lane);
   }
@@ -1377,27 +1528,48 @@ struct PairKernel {
   }
 };
 
-template <typename Real, int BASIS, bool ADJOINT, int DEG, bool ROT, bool MIN>
+template <typename Real, int BASIS, bool ADJOINT, int DEG, bool ROT, bool MIN, int KIND>
 __global__ __launch_bounds__(kWave* kWavesPerBlock)
     __attribute__((amdgpu_waves_per_eu(Occ<Real, BASIS, ADJOINT, DEG>::value))) void k_pairs(
         PairArgs a) {
-  PairKernel<Real, BASIS, ADJOINT, DEG, ROT, MIN>::run(a);
+  PairKernel<Real, BASIS, ADJOINT, DEG, ROT, MIN, KIND>::run(a);
 }
 
-template <typename Real, int BASIS, bool ADJOINT, int DEG, bool ROT, bool MIN>
-hipError_t launch_mode(const PairArgs& a, hipStream_t st) {
-  // a wave per primary, or per primary and shell where they may be handed out so;
+template <typename Real, int BASIS, bool ADJOINT, int DEG, bool ROT, bool MIN, int KIND>
+hipError_t launch_groups(const PairArgs& a, hipStream_t st) {
+  // a wave per primary, or per primary and group where they may be handed out so;
   // no more than run at once (the waves' first items are dealt out in advance)
-  const long long items = a.p_count < kSplitBelow ? a.p_count * a.nbins : a.p_count;
+  const long long items = a.p_count < kSplitBelow ? a.p_count * a.ngroup : a.p_count;
   const long long want = (items + kWavesPerBlock - 1) / kWavesPerBlock;
   constexpr int kWaves = Occ<Real, BASIS, ADJOINT, DEG>::value * kSimds;
   static_assert(kWaves <= kPairWaves, "spill lists of every wave");
   const unsigned blocks = unsigned(std::min<long long>(want, kWaves / kWavesPerBlock));
   const size_t lds =
-      sizeof(typename PairKernel<Real, BASIS, ADJOINT, DEG, ROT, MIN>::Lds) * kWavesPerBlock;
-  hipLaunchKernelGGL((k_pairs<Real, BASIS, ADJOINT, DEG, ROT, MIN>), dim3(blocks > 0 ? blocks : 1),
-                     dim3(kWave * kWavesPerBlock), lds, st, a);
+      sizeof(typename PairKernel<Real, BASIS, ADJOINT, DEG, ROT, MIN, KIND>::Lds) *
+      kWavesPerBlock;
+  static_assert(sizeof(typename PairKernel<Real, BASIS, ADJOINT, DEG, ROT, MIN, KIND>::Lds) *
+                        kWavesPerBlock <= 64 * 1024, "LDS of a workgroup");
+  hipLaunchKernelGGL((k_pairs<Real, BASIS, ADJOINT, DEG, ROT, MIN, KIND>),
+                     dim3(blocks > 0 ? blocks : 1), dim3(kWave * kWavesPerBlock), lds, st, a);
   return hipGetLastError();
+}
+
+// The groups of sparse shells, then the single shells (a tight box has no groups:
+// see shell_groups in api.hip).
+template <typename Real, int BASIS, bool ADJOINT, int DEG, bool ROT, bool MIN>
+hipError_t launch_mode(const PairArgs& a, hipStream_t st) {
+  if constexpr (!MIN) {
+    if (a.nsingle < a.ngroup) {
+      PairArgs after = a, listed = a;
+      listed.queue += kQueueListed;
+      after.primary_terms = 0;
+      const hipError_t e =
+          launch_groups<Real, BASIS, ADJOINT, DEG, ROT, MIN, kKindListed>(listed, st);
+      if (e != hipSuccess) return e;
+      return launch_groups<Real, BASIS, ADJOINT, DEG, ROT, MIN, kKindAfter>(after, st);
+    }
+  }
+  return launch_groups<Real, BASIS, ADJOINT, DEG, ROT, MIN, kKindSingle>(a, st);
 }
 
 // The kernel of the problem's mode: rotation (observer line of sight) and tight

@@ -1,7 +1,6 @@
-// The pair kernels' conversion tables on the device, the choice of kernel for a
-// problem, and the cartesian kernels (the spin kernels are compiled by degree
-// in pairs_d*.hip).
-#include "pair_kernel.h"
+// The pair kernels' conversion tables on the device and the choice of kernel for a
+// problem (the kernels themselves are compiled in the other pairs_*.hip).
+#include "internal.h"
 
 namespace g3 {
 
@@ -41,11 +40,12 @@ hipError_t table_addresses(const ConvTable** conv, const SpinTable** spin) {
 namespace {
 
 // The smallest degree that holds l_max.
-hipError_t launch_spin(const PairArgs& a, int fp64, int what, hipStream_t st) {
-  if (a.lmax <= 4) return launch_pair_spin<4>(a, fp64, what, st);
-  if (a.lmax <= 6) return launch_pair_spin<6>(a, fp64, what, st);
-  if (a.lmax <= 8) return launch_pair_spin<8>(a, fp64, what, st);
-  return launch_pair_spin<10>(a, fp64, what, st);
+template <int WHAT>
+hipError_t launch_spin(const PairArgs& a, int fp64, hipStream_t st) {
+  if (a.lmax <= 4) return launch_pair_spin<4, WHAT>(a, fp64, st);
+  if (a.lmax <= 6) return launch_pair_spin<6, WHAT>(a, fp64, st);
+  if (a.lmax <= 8) return launch_pair_spin<8, WHAT>(a, fp64, st);
+  return launch_pair_spin<10, WHAT>(a, fp64, st);
 }
 
 }  // namespace
@@ -53,21 +53,16 @@ hipError_t launch_spin(const PairArgs& a, int fp64, int what, hipStream_t st) {
 hipError_t launch_pair_forward(const PairArgs& a, int fp64, int basis, bool distinct,
                                hipStream_t st) {
   if (basis == G3PCF_BASIS_SPIN)
-    return launch_spin(a, fp64, distinct ? kSpinForwardDeg : kSpinForward, st);
-  return fp64 ? launch_one<double, G3PCF_BASIS_CARTESIAN, false, kDeg>(a, st)
-              : launch_one<float, G3PCF_BASIS_CARTESIAN, false, kDeg>(a, st);
-}
-
-hipError_t launch_pair_distinct(const PairArgs& a, int fp64, hipStream_t st) {
-  return fp64 ? launch_one<double, kBasisDeg, false, kDeg>(a, st)
-              : launch_one<float, kBasisDeg, false, kDeg>(a, st);
+    return distinct ? launch_spin<kSpinForwardDeg>(a, fp64, st)
+                    : launch_spin<kSpinForward>(a, fp64, st);
+  return fp64 ? launch_pair_cart64(a, st) : launch_pair_cart32(a, st);
 }
 
 // The per-pair polynomial represents sum_lm H_lm conj(Y_lm(u)) whatever
 // monomial basis the forward pass accumulated in: the adjoint always evaluates
 // it in the spin-Chebyshev basis.
 hipError_t launch_pair_adjoint(const PairArgs& a, int fp64, hipStream_t st) {
-  return launch_spin(a, fp64, kSpinAdjoint, st);
+  return launch_spin<kSpinAdjoint>(a, fp64, st);
 }
 
 }  // namespace g3

@@ -389,7 +389,8 @@ __global__ __launch_bounds__(kAT * kAT) void k_zeta_accum_mt(ZetaArgs z, MDims d
   const RowLayout& L = z.lay;
   const int nb = L.nb, nm = L.lmax + 1;
   // the pair kernel's next launch starts from cleared counters
-  if (blockIdx.x == 0 && threadIdx.x < kQueues) z.queue[threadIdx.x * kQueueStride] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < kQueueAdjoint * kQueues)
+    z.queue[threadIdx.x / kQueueAdjoint * kQueueStride + threadIdx.x % kQueueAdjoint] = 0;
   int t = blockIdx.x, m = 0;
   for (; m < nm; ++m) {
     const int nt = (L.d[m] + kAT - 1) / kAT;
@@ -529,7 +530,8 @@ __global__ __launch_bounds__(256) void k_deg_partial(const double* __restrict__ 
 __global__ void k_deg_accum(const double* __restrict__ partial, int nblk, int ncols,
                             double* __restrict__ D, int* __restrict__ queue) {
   // the pair kernel's next launch starts from cleared counters
-  if (blockIdx.x == 0 && threadIdx.x < kQueues) queue[threadIdx.x * kQueueStride] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < kQueueAdjoint * kQueues)
+    queue[threadIdx.x / kQueueAdjoint * kQueueStride + threadIdx.x % kQueueAdjoint] = 0;
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= ncols) return;
   double s = 0.0;

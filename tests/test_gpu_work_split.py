@@ -90,3 +90,40 @@ def test_every_degree_of_the_spin_kernels(dev, lmax, precision, los):
     e = np.abs(g - gref).max() / np.abs(gref).max()
     say(f"  gradient: {e:.2e}")
     assert e <= (1e-10 if precision == "fp64" else 1e-4)
+
+
+def clump(seed, n=3000, L=300.0, k=400):
+    """k galaxies within 2 Mpc/h of each other in a sparse periodic box."""
+    rng = np.random.default_rng(seed)
+    pos = rng.uniform(0.0, L, size=(n, 3))
+    pos[:k] = np.array([150.0, 140.0, 160.0]) + rng.uniform(-1.0, 1.0, size=(k, 3))
+    return C.Catalogue("clump", pos.astype(np.float32), rng.uniform(0.5, 1.5, size=n), (L,) * 3,
+                       (0.0,) * 3, True, 60.0, 6, 10, "z")
+
+
+@pytest.mark.parametrize("basis", ["spin", "cartesian"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_shells_searched_together_and_their_overflow(dev, precision, basis):
+    """A sparse catalogue, whose shells are searched together into a list of 224
+    (FP32) or 128 pairs, with a clump whose primaries have 399 pairs in the first
+    shell: pair counts, zeta, the distinct zeta and the gradient.  Float32
+    positions and no pair within 1e-5 of a shell edge; tolerances: FP64 1e-10,
+    FP32 1e-5 of max|zeta| and 1e-4 of max|gradient|."""
+    say(f"case clump {precision} {basis}")
+    cat = clump(81)
+    pos, w = on(dev, cat)
+    for distinct in (False, True):
+        z, pairs = api.zeta(pos, w, cfg_of(cat, precision, basis, distinct=distinct),
+                            return_pairs=True)
+        ref, pairs_ref = oracle.zeta(cat, distinct=distinct, return_pairs=True)
+        e = np.abs(z.cpu().numpy() - ref).max() / np.abs(ref).max()
+        say(f"  distinct={distinct}: pairs {pairs} ({pairs_ref}), max|dz|/max|z| = {e:.2e}")
+        assert pairs == pairs_ref
+        assert e <= TOL[precision]
+    gz = C.loss_weights(cat.lmax, cat.nbins, seed=78)
+    g = api.zeta_backward(pos, w, cfg_of(cat, precision, basis),
+                          torch.from_numpy(gz).to(dev)).cpu().numpy()
+    gref = oracle.grad(cat, gz)
+    e = np.abs(g - gref).max() / np.abs(gref).max()
+    say(f"  gradient: {e:.2e}")
+    assert e <= (1e-10 if precision == "fp64" else 1e-4)
