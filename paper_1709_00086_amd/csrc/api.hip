@@ -191,7 +191,7 @@ int ensure_tables(int basis) {
   if (g_tab_done.count({dev, basis})) return G3PCF_OK;
   e = (basis == kBasisDeg)          ? upload_deg_table()
       : (basis == G3PCF_BASIS_SPIN) ? upload_spin_tables()
-                                    : upload_conv_table();
+                                    : upload_cart_tables();
   if (e != hipSuccess) return hip_fail(e, "table upload");
   g_tab_done.insert({dev, basis});
   return G3PCF_OK;
@@ -258,7 +258,8 @@ int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, hipStream_t s
 // shell's pairs in the same order.
 void shell_groups(const g3pcf_problem& p, PairArgs& a) {
   const bool cart = p.basis == G3PCF_BASIS_CARTESIAN;
-  const double most = p.pair_prec == G3PCF_PREC_FP64 ? kListMean64 : kListMean32;
+  const bool fp64 = p.pair_prec == G3PCF_PREC_FP64;
+  const double most = fp64 ? kListMean64 : kListMean32;
   const double dr = p.rmax / p.nbins;
   const double per = double(p.n) / (p.box[0] * p.box[1] * p.box[2]) * 4.0 / 3.0 * M_PI * dr * dr * dr;
   auto expected = [&](int b0, int b1) {  // shells b0..b1
@@ -291,7 +292,8 @@ void shell_groups(const g3pcf_problem& p, PairArgs& a) {
 }
 
 int pair_args(const g3pcf_problem& p, const Ws& w, void* ws, PairArgs& a) {
-  const hipError_t e = table_addresses(&a.conv, &a.spin);
+  const hipError_t e =
+      table_addresses(p.pair_prec == G3PCF_PREC_FP64, &a.cart, &a.spin);
   if (e != hipSuccess) return hip_fail(e, "table address");
   Counters* c = at<Counters>(ws, w.counters);
   a.pos4 = at<void>(ws, w.pos4);

@@ -58,9 +58,15 @@ constexpr int kPairWaves = 4 * kSimds;
 // primaries leave the chip idle behind the last of them (kPairWaves waves run
 // at once).
 constexpr long long kSplitBelow = 4 * kPairWaves;
-// Pairs expected in a group of shells searched together: the list holds 224
-// (FP32) or 128, i.e. six and four standard deviations more; a group that holds
-// still more (clustered galaxies) is searched again, shell by shell.
+// Pairs the list of a group of shells searched together holds (LDS decides, see
+// WaveLds), and pairs expected in a group: about five standard deviations fewer;
+// a group that holds still more (clustered galaxies) is searched again, shell by
+// shell.  (16 catalogues of 8192, FP32: 6.03 ms a call at a mean of 70, 5.22 at
+// 130, 5.05 at 150, 4.99 at 180; FP64 step of 4096: 0.68 ms at 70, 0.63 at 100,
+// 0.79 at 130, where lists overflow.  Longer lists for the cartesian kernels,
+// 368 pairs at a mean of 275, were no gain: 3.24 against 2.85 ms for 40,000
+// galaxies.)
+constexpr int kListMost32 = 224, kListMost64 = 128;
 constexpr double kListMean32 = 150.0, kListMean64 = 85.0;
 constexpr int kListSaves = 3;  // searches a primary that the groups have to save
 // Spill-list entries per wave: a shell's secondaries kept for the later
@@ -69,7 +75,7 @@ constexpr int kSpillCap = 1 << 14;
 // Maximum pair-block (primaries whose a_lm rows are held at once).
 constexpr int kPairBlockMax = 524288;
 
-// Sparse monomial -> a_lm conversion table, one row per real output of a
+// Sparse monomial -> a_lm conversion table (host), one row per real output of a
 // shell.  Output o = (m, part, l) with part 0 = Re, 1 = Im (m >= 1 only).
 struct ConvTable {
   int nout;            // 121
@@ -79,6 +85,25 @@ struct ConvTable {
   short term[4096];
   double coef[4096];
 };
+
+// The cartesian conversion on the device: lane i of a wave forms output i of
+// each round, entry by entry, so that a wave's loads are contiguous (an entry of
+// every row at a time; with a row per lane each load touched 64 lines).  Rows in
+// the order of their length, the longest 64 in the first round.  Terms count in
+// the order in which the kernel's chunks hold their sums (one table for each
+// precision).
+constexpr int kCartLen = 24;  // room for a row (the longest has 21 entries)
+struct CartTable {
+  int meta[2][64];            // l | m << 4 | part << 8 | entries << 9 of the output
+  int most[2];                // entries of the round's longest row
+  double coef[2][kCartLen][64];
+  short term[2][kCartLen][64];
+};
+// order: [kTermsCart] place of each canonical term among the chunks' sums.
+// False if a row is too long.
+bool build_cart_table(const short* order, CartTable* t);  // host
+const short* cart_order32();
+const short* cart_order64();
 
 // The spin-Chebyshev conversion a_lm = sum_n c_{lm,n} S_{m,n} of one degree D,
 // over the term order of its sums (the D + 1 real ones of m = 0, then pairs of
@@ -169,7 +194,7 @@ struct PairArgs {
   double* A;                 // [p_count][W] a_lm rows (forward)
   RowLayout lay;
   double* deg;               // [p_count][nbins (2 lmax + 1)] degenerate-triangle sums (kBasisSpinDeg)
-  const ConvTable* conv;     // cartesian conversion (device)
+  const CartTable* cart;     // cartesian conversion of the kernel's precision (device)
   const SpinTable* spin;     // [kNumDegrees] spin conversions (device)
   // adjoint
   const double* H;           // [p_count][W] H rows (converted per shell in the kernel)
@@ -226,9 +251,9 @@ hipError_t launch_pair_cart64(const PairArgs& a, hipStream_t st);
 enum { kSpinForward, kSpinForwardDeg, kSpinAdjoint };
 template <int DEG, int WHAT>
 hipError_t launch_pair_spin(const PairArgs& a, int fp64, hipStream_t st);
-hipError_t upload_conv_table();
+hipError_t upload_cart_tables();
 hipError_t upload_spin_tables();
-hipError_t table_addresses(const ConvTable** conv, const SpinTable** spin);
+hipError_t table_addresses(int fp64, const CartTable** cart, const SpinTable** spin);
 
 struct ZetaArgs {
   const double* A;           // [rows][W]

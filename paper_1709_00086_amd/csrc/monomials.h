@@ -703,7 +703,7 @@ struct Chunks<Real, kBasisSpinDeg, DEG> {
 };
 
 template <class... C, typename F>
-__device__ __forceinline__ void for_each_chunk(ChunkList<C...>, F&& f) {
+__host__ __device__ __forceinline__ void for_each_chunk(ChunkList<C...>, F&& f) {
   (f(static_cast<C*>(nullptr)), ...);
 }
 

@@ -90,9 +90,10 @@ constexpr int kOutBuf = 4 * kWave;
 // they wait); otherwise the sums of a shell take the ring's, which is empty by
 // then.
 // The list: the accepted pairs of a group of sparse shells, found by one search
-// (see search_list).
+// (see search).  As many as the LDS of the occupancy target has room for (FP64:
+// of a workgroup's 64 KB).
 template <typename Real>
-constexpr int kList = sizeof(Real) == 4 ? 224 : 128;
+constexpr int kList = sizeof(Real) == 4 ? kListMost32 : kListMost64;
 constexpr int kOutBufList = 3 * kWave;  // terms that may wait beside the list
 
 template <typename Real, bool SPILL, bool SPINT, bool SPIN, bool ADJ, bool LISTED>
@@ -104,8 +105,9 @@ struct WaveLds {
   // while the list is read
   static constexpr bool kInRuns = LISTED && SPIN && sizeof(Real) == 4;
   static constexpr int kOut = SPINT ? (LISTED ? kOutBufList : kOutBuf) : 0;  // waves of terms
-  static constexpr int kListBytes = LISTED ? kList<Real> * int(sizeof(V)) : 0;
-  static constexpr int kBins = LISTED && sizeof(Real) == 8 ? kList<Real> * 4 : 0;
+  static constexpr int kEntries = kList<Real>;
+  static constexpr int kListBytes = LISTED ? kEntries * int(sizeof(V)) : 0;
+  static constexpr int kBins = LISTED && sizeof(Real) == 8 ? kEntries * 4 : 0;
   static constexpr int kSums = SPILL ? (kTermsCart + 1) * int(sizeof(Real)) + 4 : 0;  // (+1 padding slot)
   static constexpr int kSpilled = SPILL && !LISTED ? kRing * 4 : 0;
   static constexpr int kMore = kListBytes + kBins + (kInRuns ? 0 : kExchange + kOut * 8) + kSums +
@@ -715,7 +717,7 @@ struct PairKernel {
           }
           const int slot = cnt + lanes_below(m);  // ring: below kRing, as cnt < kWave here
           if constexpr (kListed) {
-            if (slot < kList<Real>) {
+            if (slot < Lds::kEntries) {
               W.list()[slot] = ent;
               if constexpr (!kF32) W.bins()[slot] = bin;
             }
@@ -951,6 +953,7 @@ struct PairKernel {
       const int cap = a.spill_cap;
       bool first = true;
       bool replayable = false;
+      int base = 0;
       for_each_chunk(CL{}, [&](auto* tag) {
         using Chunk = std::remove_pointer_t<decltype(tag)>;
         Chunk ch;
@@ -986,7 +989,11 @@ struct PairKernel {
         if constexpr (kSpin) {
           reduce_split(W, ch);
         } else {
-          reduce_store(W, ch);
+          // a cartesian chunk's sums (or the degenerate ones) after the last's
+          const int wl = lane_here();
+          fold_plain<Chunk::NT>(sums(W) + base, ch.acc, wl >> 4,
+                                ((wl >> 3) & 1) | ((wl >> 1) & 2), (wl & 3) == 0, wl);
+          base += Chunk::NT;
         }
       });
       wave_lds_fence();
@@ -1239,7 +1246,7 @@ struct PairKernel {
         if constexpr (kListed) {
           found = int(search<kF32 && kMin, false>(a, W, pos4, P, b0, b1, inner(b0), outer(b1),
                                                   [](const V&, int, bool) {}));
-          if (found > kList<Real>) {
+          if (found > Lds::kEntries) {
             // left to the launch of the single shells
             if (lane == 0) {
               atomicOr(a.overflow + a.p_begin + qi, 1u << g);
@@ -1294,44 +1301,6 @@ struct PairKernel {
     P.Rm[6] = Real(-vy);
     P.Rm[7] = Real(vx);
     P.Rm[8] = Real(1.0 - vv * f);
-  }
-
-  // Wave sums of a cartesian chunk's accumulators (or the degenerate sums'),
-  // four at a time: one fold across rows first (each lane of row r then holds
-  // four lanes' worth of value r), then row sums by DPP leave the four totals
-  // in rows 0..3, and one lane of each row stores its row's.
-  template <class Chunk>
-  static __device__ __forceinline__ void reduce_store(Lds& W, Chunk& ch) {
-    constexpr int NT = Chunk::NT;
-    constexpr int kJunk = kTermsCart;  // slot that absorbs padding in the last group
-    Real* M = sums(W);
-    const int lane = lane_here();
-    const int row = lane >> 4;
-    const bool ge1 = row >= 1, ge2 = row >= 2, ge3 = row >= 3;
-    const bool leader = (lane & 15) == 0;  // one store per row
-    static_for<(NT + 3) / 4>([&](auto gc) {
-      constexpr int g = decltype(gc)::value;
-      constexpr int i0 = 4 * g, i1 = 4 * g + 1, i2 = 4 * g + 2, i3 = 4 * g + 3;
-      Real e = Real(0), b = Real(0), f = Real(0);
-      if constexpr (i1 < NT) e = ch.acc[i1];
-      if constexpr (i2 < NT) b = ch.acc[i2];
-      if constexpr (i3 < NT) f = ch.acc[i3];
-      const Real tot = row_sum(fold4(ch.acc[i0], e, b, f));
-      constexpr int ta = Chunk::term_of(i0);
-      constexpr int te = (i1 < NT) ? Chunk::term_of(i1) : kJunk;
-      constexpr int tb = (i2 < NT) ? Chunk::term_of(i2) : kJunk;
-      constexpr int tf = (i3 < NT) ? Chunk::term_of(i3) : kJunk;
-      int t;
-      if constexpr (te == ta + 1 && tb == ta + 2 && tf == ta + 3) {
-        t = ta + row;
-      } else {
-        t = ta;
-        t = ge1 ? te : t;
-        t = ge2 ? tb : t;
-        t = ge3 ? tf : t;
-      }
-      if (leader) M[t] = tot;
-    });
   }
 
   // Wave sums of the spin sums into sums(W), in term order (the degenerate
@@ -1390,33 +1359,31 @@ struct PairKernel {
     }
   }
 
-  // Convert the shell's monomial sums to a_lm (FP64) and write them.  Eight
-  // entries of an output at a time, so that their loads overlap.
+  // Convert the shell's cartesian sums to a_lm (FP64) and write them, four
+  // entries of the 64 rows of a round at a time.
   static __device__ __forceinline__ void convert(const PairArgs& a, const Real* M, int b,
                                                  long long row) {
     const int lane = threadIdx.x % kWave;
-    const ConvTable& t = *a.conv;
+    const CartTable& t = *a.cart;
     const RowLayout& L = a.lay;
     double* out = a.A + row * L.W;
-    for (int o = lane; o < kOutPerBin; o += kWave) {
-      const int l = t.out_l[o];
-      if (l > L.lmax) continue;
-      const int m = t.out_m[o], part = t.out_part[o];
-      const int e1 = t.rowptr[o + 1];
+    for (int r = 0; r < 2; ++r) {
+      const int meta = t.meta[r][lane], most = t.most[r];
+      const int l = meta & 15, m = (meta >> 4) & 15, part = (meta >> 8) & 1, n = meta >> 9;
       double s = 0.0;
-      for (int e = t.rowptr[o]; e < e1; e += 8) {
-        double c[8];
-        int k[8];
+      for (int k0 = 0; k0 < most; k0 += 4) {
+        double c[4];
+        int k[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          c[i] = t.coef[min(e + i, e1 - 1)];
-          k[i] = t.term[min(e + i, e1 - 1)];
+        for (int i = 0; i < 4; ++i) {
+          c[i] = t.coef[r][k0 + i][lane];
+          k[i] = t.term[r][k0 + i][lane];
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (e + i < e1) s = __builtin_fma(c[i], double(M[k[i]]), s);
+        for (int i = 0; i < 4; ++i)
+          if (k0 + i < n) s = __builtin_fma(c[i], double(M[k[i]]), s);
       }
-      out[L.off[m] + part * L.d[m] + L.pos(m, l, b)] = s;
+      if (l <= L.lmax) out[L.off[m] + part * L.d[m] + L.pos(m, l, b)] = s;
     }
   }
 

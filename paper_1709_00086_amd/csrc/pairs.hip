@@ -4,17 +4,18 @@
 
 namespace g3 {
 
-__device__ ConvTable g_conv;
+__device__ CartTable g_cart[2];  // FP32, FP64
 __device__ SpinTable g_spin[kNumDegrees];
 
-hipError_t upload_conv_table() {
-  static ConvTable host;
+hipError_t upload_cart_tables() {
+  static CartTable host[2];
   static bool built = false;
   if (!built) {
-    build_conv_table(G3PCF_BASIS_CARTESIAN, &host);
+    if (!build_cart_table(cart_order32(), &host[0]) || !build_cart_table(cart_order64(), &host[1]))
+      return hipErrorInvalidValue;
     built = true;
   }
-  return hipMemcpyToSymbol(HIP_SYMBOL(g_conv), &host, sizeof(host), 0, hipMemcpyHostToDevice);
+  return hipMemcpyToSymbol(HIP_SYMBOL(g_cart), host, sizeof(host), 0, hipMemcpyHostToDevice);
 }
 
 hipError_t upload_spin_tables() {
@@ -27,11 +28,11 @@ hipError_t upload_spin_tables() {
   return hipMemcpyToSymbol(HIP_SYMBOL(g_spin), host, sizeof(host), 0, hipMemcpyHostToDevice);
 }
 
-hipError_t table_addresses(const ConvTable** conv, const SpinTable** spin) {
+hipError_t table_addresses(int fp64, const CartTable** cart, const SpinTable** spin) {
   void* p = nullptr;
-  hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(g_conv));
+  hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(g_cart));
   if (e != hipSuccess) return e;
-  *conv = static_cast<const ConvTable*>(p);
+  *cart = static_cast<const CartTable*>(p) + (fp64 ? 1 : 0);
   if ((e = hipGetSymbolAddress(&p, HIP_SYMBOL(g_spin))) != hipSuccess) return e;
   *spin = static_cast<const SpinTable*>(p);
   return hipSuccess;

@@ -19,6 +19,7 @@
 // u_x^K u_y^P u_z^Q (K + P + Q = l) appear.
 //
 // Integer parts are accumulated exactly in int64, then scaled in double.
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -151,6 +152,32 @@ void build_conv_table(int basis, ConvTable* t) {
   t->rowptr[o] = nnz;
   t->nout = o;
   t->nnz = nnz;
+}
+
+bool build_cart_table(const short* order, CartTable* t) {
+  static ConvTable full;
+  if (full.nout == 0) build_conv_table(G3PCF_BASIS_CARTESIAN, &full);
+  std::memset(t, 0, sizeof(*t));
+  std::vector<int> rows(full.nout);
+  for (int o = 0; o < full.nout; ++o) rows[o] = o;
+  auto len = [&](int o) { return full.rowptr[o + 1] - full.rowptr[o]; };
+  std::stable_sort(rows.begin(), rows.end(), [&](int a, int b) { return len(a) > len(b); });
+  for (int i = 0; i < 128; ++i) {
+    const int r = i / 64, lane = i % 64;
+    if (i >= full.nout) {
+      t->meta[r][lane] = kDeg + 1;  // no output: l above every l_max
+      continue;
+    }
+    const int o = rows[i], n = len(o);
+    if (n > kCartLen) return false;
+    t->meta[r][lane] = full.out_l[o] | full.out_m[o] << 4 | full.out_part[o] << 8 | n << 9;
+    if (n > t->most[r]) t->most[r] = n;
+    for (int k = 0; k < n; ++k) {
+      t->coef[r][k][lane] = full.coef[full.rowptr[o] + k];
+      t->term[r][k][lane] = order[full.term[full.rowptr[o] + k]];
+    }
+  }
+  return true;
 }
 
 void build_spin_table(int deg, SpinTable* t) {
