@@ -219,8 +219,10 @@ struct Counters {
 };
 static_assert(sizeof(Counters) <= kCountersBytes, "counters block");
 
-// Stages shared by forward and backward: cell list and primary list.
-int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, hipStream_t st) {
+// Stages shared by forward and backward: cell list and primary list, and the
+// pass's clears z (n > 0).  primaries = false: the list is left to the caller.
+int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, const Clears& z,
+                    hipStream_t st, bool primaries = true) {
   const int fp64 = (p.pair_prec == G3PCF_PREC_FP64);
   CellBufs b{};
   b.pos4 = at<void>(ws, w.pos4);
@@ -235,15 +237,11 @@ int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, hipStream_t s
   b.wsort = at<double>(ws, w.wsort);
   b.scan_tmp = at<void>(ws, w.scan);
   b.scan_bytes = w.scan_bytes;
-  hipError_t e = launch_cells(p, w.grid, b, fp64, st);
-  if (e != hipSuccess) return hip_fail(e, "cell list");
   Counters* c = at<Counters>(ws, w.counters);
-  e = launch_fill_int(reinterpret_cast<int*>(c), sizeof(Counters) / 4, 0, st);
-  if (e != hipSuccess) return hip_fail(e, "counters");
-  e = launch_primaries(p.primary_mask, nullptr, 0, at<int>(ws, w.perm), p.n,
-                       at<int>(ws, w.flags), at<int>(ws, w.plist), &c->nprim, at<void>(ws, w.scan),
-                       w.scan_bytes, st);
-  if (e != hipSuccess) return hip_fail(e, "primary list");
+  Primaries pr{p.primary_mask, primaries ? at<int>(ws, w.flags) : nullptr, at<int>(ws, w.plist),
+               &c->nprim, reinterpret_cast<int*>(c), int(sizeof(Counters) / 4)};
+  const hipError_t e = launch_cells(p, w.grid, b, pr, z, fp64, st);
+  if (e != hipSuccess) return hip_fail(e, "cell list");
   return G3PCF_OK;
 }
 
@@ -509,9 +507,10 @@ int forward_run(const g3pcf_problem& p, const Ws& w, double* zeta, void* ws, hip
   if ((rc = forward_tables(p))) return rc;
   const size_t zlen = g3pcf_zeta_len(p.lmax, p.nbins);
   hipError_t e;
-  if (!p.accumulate && (e = launch_fill_double(zeta, int64_t(zlen), 0.0, st)) != hipSuccess)
-    return hip_fail(e, "zeta clear");
+  Clears z;
+  if (!p.accumulate) z.add(zeta, int64_t(zlen) * 2);
   if (p.n == 0) {
+    if ((e = launch_clears(z, st)) != hipSuccess) return hip_fail(e, "zeta clear");
     if (p.alm && (e = launch_fill_int(static_cast<int*>(p.alm), 2, 0, st)) != hipSuccess)
       return hip_fail(e, "alm store header");
     if (p.pairs_out) *p.pairs_out = 0;
@@ -519,7 +518,7 @@ int forward_run(const g3pcf_problem& p, const Ws& w, double* zeta, void* ws, hip
   }
   {
     StageScope sc(p.trace, G3PCF_STAGE_CELLS, st);
-    if ((rc = stage_catalogue(p, w, ws, st))) return rc;
+    if ((rc = stage_catalogue(p, w, ws, z, st))) return rc;
     if (p.alm && (e = fingerprint(p, w, ws, static_cast<unsigned long long*>(p.alm), st)) !=
                      hipSuccess)
       return hip_fail(e, "alm store fingerprint");
@@ -694,7 +693,7 @@ int g3pcf_forward_regions(const g3pcf_problem* prob, const int32_t* region, int 
   }
   {
     StageScope sc(p.trace, G3PCF_STAGE_CELLS, st);
-    if ((rc = stage_catalogue(p, w, ws, st))) return rc;
+    if ((rc = stage_catalogue(p, w, ws, Clears(), st, false))) return rc;
   }
   // one cell list; per region its own primary list and pair-blocks, sized by
   // the region's primary count (read back: one wait per region)
@@ -755,7 +754,7 @@ int g3pcf_forward_batch(const g3pcf_problem* prob, int ncat, const int64_t* offs
     if ((rc = check_workspace(w, ws, ws_bytes))) return rc;
     {
       StageScope sc(p.trace, G3PCF_STAGE_CELLS, st);
-      if ((rc = stage_catalogue(q, w, ws, st))) return rc;
+      if ((rc = stage_catalogue(q, w, ws, Clears(), st))) return rc;
     }
     if ((rc = forward_pairs(q, w, ws, zeta + zlen * size_t(c), q.n, nullptr, st))) return rc;
     if ((rc = finish_pairs(q, w, ws, st))) return rc;
@@ -787,19 +786,18 @@ int g3pcf_backward(const g3pcf_problem* prob, const double* grad_zeta, double* g
   }
   hipError_t e;
   Counters* c = at<Counters>(ws, w.counters);
+  double* gsort = at<double>(ws, w.gsort);
+  // FP32 pair path: the secondary terms are summed in FP32 on their own array
+  float* gsort32 = (p.pair_prec == G3PCF_PREC_FP64) ? nullptr : at<float>(ws, w.gsort32);
   {
     StageScope sc(p.trace, G3PCF_STAGE_CELLS, st);
-    if ((rc = stage_catalogue(p, w, ws, st))) return rc;
+    Clears z;
+    z.add(gsort, 2 * p.n);
+    if (gsort32) z.add(gsort32, p.n);
+    if ((rc = stage_catalogue(p, w, ws, z, st))) return rc;
     if (p.alm && (e = fingerprint(p, w, ws, &c->inputs_hash, st)) != hipSuccess)
       return hip_fail(e, "input fingerprint");
   }
-  double* gsort = at<double>(ws, w.gsort);
-  if ((e = launch_fill_double(gsort, p.n, 0.0, st)) != hipSuccess)
-    return hip_fail(e, "gradient clear");
-  // FP32 pair path: the secondary terms are summed in FP32 on their own array
-  float* gsort32 = (p.pair_prec == G3PCF_PREC_FP64) ? nullptr : at<float>(ws, w.gsort32);
-  if (gsort32 && (e = launch_fill_int(reinterpret_cast<int*>(gsort32), p.n, 0, st)) != hipSuccess)
-    return hip_fail(e, "gradient clear");
   {
     StageScope sc(p.trace, G3PCF_STAGE_ADJ_COEF, st);
     if ((e = launch_adj_matrix(grad_zeta, w.lay, at<double>(ws, w.mht), st)) != hipSuccess)

@@ -22,7 +22,9 @@ constexpr int kScanItems = 4;  // per thread
 constexpr int kScanTile = kScanBlock * kScanItems;
 
 __device__ inline double wrap_coord(double x, double lo, double L) {
-  double t = fmod(x - lo, L);
+  double t = x - lo;
+  if (t >= 0.0 && t < L) return lo + t;  // fmod is exact: t itself
+  t = fmod(t, L);
   if (t < 0.0) t += L;
   if (t >= L) t = 0.0;
   return lo + t;
@@ -54,13 +56,12 @@ __device__ inline int cell_axis(double x, double lo, double inv_s, int nc) {
   return f >= double(nc) ? nc - 1 : int(f);
 }
 
-// Wrap (periodic), convert to the compute precision and assign a cell.
+// Wrap (periodic), convert to the compute precision and assign a cell: the
+// staged value of galaxy i and its cell.
 template <typename Real, typename In>
-__global__ void k_assign(const In* __restrict__ pos, const double* __restrict__ w, int64_t n,
-                         GridDev g, typename Vec4<Real>::T* __restrict__ out4,
-                         int* __restrict__ cid, int* __restrict__ count) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+__device__ __forceinline__ typename Vec4<Real>::T staged(const In* __restrict__ pos,
+                                                         const double* __restrict__ w, int64_t i,
+                                                         const GridDev& g, int& cell) {
   double x[3];
   for (int a = 0; a < 3; ++a) {
     double v = double(pos[3 * i + a]);
@@ -78,15 +79,33 @@ __global__ void k_assign(const In* __restrict__ pos, const double* __restrict__ 
   const int cx = cell_axis(x[0], g.lo[0], g.inv_s[0], g.nc[0]);
   const int cy = cell_axis(x[1], g.lo[1], g.inv_s[1], g.nc[1]);
   const int cz = cell_axis(x[2], g.lo[2], g.inv_s[2], g.nc[2]);
-  const int c = (cz * g.nc[1] + cy) * g.nc[0] + cx;
+  cell = (cz * g.nc[1] + cy) * g.nc[0] + cx;
   typename Vec4<Real>::T v4;
   v4.x = Real(x[0]);
   v4.y = Real(x[1]);
   v4.z = Real(x[2]);
   v4.w = Real(w[i]);
-  out4[i] = v4;
+  return v4;
+}
+
+template <typename Real, typename In>
+__global__ void k_assign(const In* __restrict__ pos, const double* __restrict__ w, int64_t n,
+                         GridDev g, typename Vec4<Real>::T* __restrict__ out4,
+                         int* __restrict__ cid, int* __restrict__ count) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  int c;
+  out4[i] = staged<Real, In>(pos, w, i, g, c);
   cid[i] = c;
   atomicAdd(&count[c], 1);
+}
+
+// Every clear of a pass in one launch.
+__global__ __launch_bounds__(256) void k_clear(Clears z) {
+  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t step = int64_t(gridDim.x) * blockDim.x;
+  for (int k = 0; k < z.count; ++k)
+    for (int64_t i = t; i < z.words[k]; i += step) z.at[k][i] = 0;
 }
 
 // ---- stable LSD radix sort of the cell ids (values: original indices) ----
@@ -209,6 +228,16 @@ __global__ void k_primary_flags(const uint8_t* __restrict__ mask,
   flags[s] = ((mask == nullptr || mask[i] != 0) && (region == nullptr || region[i] == r)) ? 1 : 0;
 }
 
+// every galaxy a primary
+__global__ void k_primary_all(int* __restrict__ flags, int64_t n, int* __restrict__ plist,
+                              long long* __restrict__ nprim) {
+  const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (s > n) return;
+  flags[s] = 0;
+  if (s == n) *nprim = n;
+  else plist[s] = int(s);
+}
+
 // (the flags are left zero)
 __global__ void k_primary_list(int* __restrict__ flags, const int* __restrict__ pos,
                                int64_t n, int* __restrict__ plist,
@@ -221,6 +250,184 @@ __global__ void k_primary_list(int* __restrict__ flags, const int* __restrict__ 
   }
   if (flags[s]) plist[pos[s]] = int(s);
   flags[s] = 0;
+}
+
+// ---- the whole cell stage of a small catalogue in one workgroup ----
+// Up to kSmallN galaxies: the launches of the general path (17 with a mask, each
+// 2 to 5 us and as much again between them) cost more than one workgroup's time.
+// Bound by the workgroup's instruction issue over two sort passes of two rounds of
+// ballots.  The cell ids stay in LDS (below 2^16: the grid has at most 4 n cells) and the
+// same stable LSD radix sort by 8-bit digits runs over contiguous chunks, one a
+// wave, so the order is that of the general path.  The other workgroups of the
+// launch do the pass's clears.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / kWave;
+
+struct SmallOut {
+  int* perm;
+  double* wsort;
+  int* cell_start;
+  int ncell;
+  int* flags;                // [n + 1] zeroed, or NULL: no primary list
+  int* plist;
+  long long* nprim;
+  int* counters;             // zeroed
+  int counter_words;
+};
+
+template <typename Real, typename In>
+__global__ __launch_bounds__(kSmallThreads) void k_cells_small(
+    const In* __restrict__ pos, const double* __restrict__ w, int n, GridDev g,
+    const uint8_t* __restrict__ mask, typename Vec4<Real>::T* stage4,
+    typename Vec4<Real>::T* __restrict__ pos4, SmallOut o, Clears z) {
+  using V4 = typename Vec4<Real>::T;
+  __shared__ unsigned short key[kSmallN];
+  __shared__ unsigned short val[2][kSmallN];
+  __shared__ unsigned short hist[kSmallWaves][kRadixDigits];  // then running offsets
+  __shared__ int wtot[kSmallWaves];
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  if (blockIdx.x > 0) {
+    const int64_t t = int64_t(blockIdx.x - 1) * kSmallThreads + tid;
+    const int64_t step = int64_t(gridDim.x - 1) * kSmallThreads;
+    for (int k = 0; k < z.count; ++k)
+      for (int64_t i = t; i < z.words[k]; i += step) z.at[k][i] = 0;
+    return;
+  }
+  for (int i = tid; i < o.counter_words; i += kSmallThreads) o.counters[i] = 0;
+  for (int i = tid; i < n; i += kSmallThreads) {
+    int c;
+    stage4[i] = staged<Real, In>(pos, w, i, g, c);
+    key[i] = (unsigned short)c;
+    val[0][i] = (unsigned short)i;
+  }
+  const int chunk = (n + kSmallThreads - 1) / kSmallThreads * kWave;  // per wave
+  const int c0 = wave * chunk, c1 = min(n, c0 + chunk);
+  const int passes = o.ncell > kRadixDigits ? 2 : 1;
+  for (int pass = 0; pass < passes; ++pass) {
+    const unsigned short* in = val[pass];
+    unsigned short* out = val[pass ^ 1];
+    const int shift = pass * kRadixBits;
+    for (int d = lane; d < kRadixDigits; d += kWave) hist[wave][d] = 0;
+    __syncthreads();
+    // the lane's digit, its rank among the wave's equal digits and their number
+    auto match = [&](int e, int& d, int& v, int& rank, int& same) {
+      const bool valid = e < c1;
+      v = valid ? in[e] : 0;
+      d = valid ? (key[v] >> shift) & (kRadixDigits - 1) : 0;
+      unsigned long long peers = __builtin_amdgcn_ballot_w64(valid);
+      for (int bit = 0; bit < kRadixBits; ++bit) {
+        const bool on = (d >> bit) & 1;
+        const unsigned long long b = __builtin_amdgcn_ballot_w64(on);
+        peers &= on ? b : ~b;
+      }
+      rank = __builtin_amdgcn_mbcnt_hi(unsigned(peers >> 32),
+                                       __builtin_amdgcn_mbcnt_lo(unsigned(peers), 0));
+      same = __popcll(peers);
+      return valid;
+    };
+    for (int e = c0 + lane; e - lane < c1; e += kWave) {
+      int d, v, rank, same;
+      if (match(e, d, v, rank, same) && rank == 0)
+        hist[wave][d] = (unsigned short)(hist[wave][d] + same);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    // offsets, digit-major across waves: a thread for four waves of a digit
+    {
+      static_assert(kSmallThreads * 4 == kRadixDigits * kSmallWaves, "four counts a thread");
+      const int d = tid / 4, u0 = 4 * (tid % 4);
+      int c[4], sum = 0;
+      for (int k = 0; k < 4; ++k) {
+        c[k] = hist[u0 + k][d];
+        sum += c[k];
+      }
+      int incl = sum;
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int up = __shfl_up(incl, off);
+        if (lane >= off) incl += up;
+      }
+      if (lane == kWave - 1) wtot[wave] = incl;
+      __syncthreads();
+      int at = incl - sum;
+      for (int u = 0; u < kSmallWaves; ++u) at += u < wave ? wtot[u] : 0;
+      for (int k = 0; k < 4; ++k) {
+        hist[u0 + k][d] = (unsigned short)at;
+        at += c[k];
+      }
+    }
+    __syncthreads();
+    for (int e = c0 + lane; e - lane < c1; e += kWave) {
+      int d, v, rank, same;
+      const bool valid = match(e, d, v, rank, same);
+      const int at = valid ? hist[wave][d] : 0;
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      if (valid) out[at + rank] = (unsigned short)v;
+      if (valid && rank == 0) hist[wave][d] = (unsigned short)(at + same);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+  }
+  const unsigned short* order = val[passes & 1];
+  for (int s = tid; s < n + kSentinel; s += kSmallThreads) {
+    if (s < n) {
+      const int i = order[s];
+      o.perm[s] = i;
+      pos4[s] = stage4[i];
+      o.wsort[s] = w[i];
+    } else {
+      const Real nan = Real(__builtin_nan(""));
+      pos4[s] = V4{nan, nan, nan, nan};
+    }
+  }
+  // cell_start[c] = galaxies in cells below c; a run of cells per thread, the
+  // next start found by doubling steps
+  const int per = (o.ncell + 1 + kSmallThreads - 1) / kSmallThreads;
+  auto cell_at = [&](int s) { return int(key[order[s]]); };
+  int s = 0;
+  for (int c = tid * per; c < min((tid + 1) * per, o.ncell + 1); ++c) {
+    int step = c == tid * per ? n : 1;  // the thread's first cell: a plain bisection
+    int hi = s;
+    while (hi < n && cell_at(hi) < c) {
+      s = hi + 1;
+      hi = min(hi + step, n);
+      step *= 2;
+    }
+    while (s < hi) {  // first slot whose cell is not below c
+      const int mid = (s + hi) / 2;
+      if (cell_at(mid) < c) s = mid + 1;
+      else hi = mid;
+    }
+    o.cell_start[c] = s;
+  }
+  if (!o.flags) return;
+  // primaries in cell order
+  for (int i = tid; i <= n; i += kSmallThreads) o.flags[i] = 0;
+  if (!mask) {
+    for (int i = tid; i < n; i += kSmallThreads) o.plist[i] = i;
+    if (tid == 0) *o.nprim = n;
+    return;
+  }
+  int base = 0;
+  for (int s0 = 0; s0 < n; s0 += kSmallThreads) {
+    const int q = s0 + tid;
+    const bool on = q < n && mask[order[q]] != 0;
+    const unsigned long long b = __builtin_amdgcn_ballot_w64(on);
+    if (lane == 0) wtot[wave] = __popcll(b);
+    __syncthreads();
+    int before = base;
+    for (int u = 0; u < kSmallWaves; ++u) {
+      if (u < wave) before += wtot[u];
+      base += wtot[u];
+    }
+    if (on)
+      o.plist[before + __builtin_amdgcn_mbcnt_hi(unsigned(b >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo(unsigned(b), 0))] = q;
+    __syncthreads();
+  }
+  if (tid == 0) *o.nprim = base;
 }
 
 __global__ void k_fill_int(int* p, int64_t count, int value) {
@@ -357,6 +564,14 @@ hipError_t launch_scan(const int* in, int* out, int64_t count, void* tmp, size_t
   return hipGetLastError();
 }
 
+hipError_t launch_clears(const Clears& z, hipStream_t st) {
+  int64_t most = 0;
+  for (int k = 0; k < z.count; ++k) most = std::max(most, z.words[k]);
+  if (most == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_clear, dim3(std::min(2048u, blocks_for(most, 256))), dim3(256), 0, st, z);
+  return hipGetLastError();
+}
+
 hipError_t launch_fill_int(int* p, int64_t count, int value, hipStream_t st) {
   if (count <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_fill_int, dim3(blocks_for(count, 256)), dim3(256), 0, st, p, count,
@@ -411,8 +626,8 @@ size_t radix_hist_ints(int64_t n) {
   return size_t(ntiles) * kRadixDigits;
 }
 
-hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b, int fp64,
-                        hipStream_t st) {
+hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b,
+                        const Primaries& pr, Clears z, int fp64, hipStream_t st) {
   const int64_t n = p.n;
   GridDev gd;
   for (int a = 0; a < 3; ++a) {
@@ -422,9 +637,34 @@ hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b
     gd.L[a] = g.L[a];
   }
   gd.periodic = g.periodic;
-  hipError_t e = launch_fill_int(b.cell_count, g.ncell + 1, 0, st);
+  // n <= kSmallN galaxies: one launch (the grid has at most 4 n cells)
+  if (n > 0 && n <= kSmallN && g.ncell <= 4 * kSmallN) {
+    SmallOut o{b.perm, b.wsort, b.cell_start, int(g.ncell), pr.flags, pr.plist, pr.nprim,
+               pr.counters, pr.counter_words};
+    int64_t words = 0;
+    for (int k = 0; k < z.count; ++k) words += z.words[k];
+    const unsigned grid = 1u + unsigned(std::min<int64_t>(255, blocks_for(words, kSmallThreads * 4)));
+    auto go = [&](auto real, auto in) {
+      using Real = decltype(real);
+      using In = decltype(in);
+      using V = typename Vec4<Real>::T;
+      hipLaunchKernelGGL((k_cells_small<Real, In>), dim3(grid), dim3(kSmallThreads), 0, st,
+                         static_cast<const In*>(p.pos), p.w, int(n), gd, pr.mask,
+                         static_cast<V*>(b.stage4), static_cast<V*>(b.pos4), o, z);
+    };
+    if (fp64) {
+      if (p.pos_dtype == G3PCF_F64) go(double(), double());
+      else go(double(), float());
+    } else {
+      if (p.pos_dtype == G3PCF_F64) go(float(), double());
+      else go(float(), float());
+    }
+    return hipGetLastError();
+  }
+  z.add(pr.counters, pr.counter_words);
+  z.add(b.cell_count, g.ncell + 1);
+  hipError_t e = launch_clears(z, st);
   if (e != hipSuccess) return e;
-  if (n == 0) return launch_fill_int(b.cell_start, g.ncell + 1, 0, st);
   const unsigned nb = blocks_for(n, 256);
   // staged values (input order) into stage4, the cell id of every galaxy
   // into key_a, and the cell counts
@@ -488,13 +728,19 @@ hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b
     hipLaunchKernelGGL((k_gather_sorted<float4>), dim3(ng), dim3(256), 0, st,
                        static_cast<const float4*>(b.stage4), b.perm, n, p.w,
                        static_cast<float4*>(b.pos4), b.wsort);
-  return hipGetLastError();
+  if ((e = hipGetLastError()) != hipSuccess || !pr.flags) return e;
+  return launch_primaries(pr.mask, nullptr, 0, b.perm, n, pr.flags, pr.plist, pr.nprim,
+                          b.scan_tmp, b.scan_bytes, st);
 }
 
 hipError_t launch_primaries(const uint8_t* mask, const int32_t* region, int r, const int* perm,
                             int64_t n, int* flags, int* plist, long long* nprim,
                             void* scan_tmp, size_t scan_tmp_bytes_, hipStream_t st) {
   const unsigned nb = blocks_for(n + 1, 256);
+  if (!mask && !region) {
+    hipLaunchKernelGGL(k_primary_all, dim3(nb), dim3(256), 0, st, flags, n, plist, nprim);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_primary_flags, dim3(nb), dim3(256), 0, st, mask, region, r, perm, n,
                      flags);
   hipError_t e = hipGetLastError();

@@ -221,8 +221,33 @@ struct CellBufs {
   size_t scan_bytes;
 };
 size_t radix_hist_ints(int64_t n);
-hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b, int fp64,
-                        hipStream_t st);
+// Buffers a pass starts from zero, cleared in one launch (32-bit words).
+struct Clears {
+  int count = 0;
+  int* at[5];
+  int64_t words[5];
+  void add(void* p, int64_t n) {
+    at[count] = static_cast<int*>(p);
+    words[count++] = n;
+  }
+};
+hipError_t launch_clears(const Clears& z, hipStream_t st);
+// The primary list of the cell stage (flags NULL: none) and its counters.
+struct Primaries {
+  const uint8_t* mask;       // [n] or NULL: every galaxy
+  int* flags;                // [2 (n + 1)] scratch; left zero in its first half
+  int* plist;                // [n] out
+  long long* nprim;          // out
+  int* counters;             // cleared
+  int counter_words;
+};
+// Galaxies up to which the cell stage runs in one workgroup: 11 us at 300, 13 at
+// 700, 40 at 4096, 52 at 6000 and 66 at 8192 galaxies, against 56 us for the
+// general path's launches at any of these sizes.
+constexpr int kSmallN = 6144;
+// The cell list, the primary list and the pass's clears.
+hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b,
+                        const Primaries& pr, Clears z, int fp64, hipStream_t st);
 // Primary list (cell order): galaxies in the mask (NULL: all) and, if region
 // is not NULL, with region[i] == r.  Leaves flags zero (see PairArgs::overflow).
 hipError_t launch_primaries(const uint8_t* mask, const int32_t* region, int r, const int* perm,

@@ -127,3 +127,26 @@ def test_shells_searched_together_and_their_overflow(dev, precision, basis):
     e = np.abs(g - gref).max() / np.abs(gref).max()
     say(f"  gradient: {e:.2e}")
     assert e <= (1e-10 if precision == "fp64" else 1e-4)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1025, 6143, 6144, 6145])
+@pytest.mark.parametrize("masked", [False, True])
+def test_cell_stage_of_small_catalogues(dev, n, masked):
+    """The cell stage of one workgroup (up to 6144 galaxies) and the general one:
+    pair counts and zeta against the oracle (FP64, 1e-10), a third of the galaxies
+    in one clump so that cells are empty and crowded."""
+    say(f"case cell stage n={n} masked={masked}")
+    rng = np.random.default_rng(83)
+    pos = rng.uniform(0.0, 200.0, size=(n, 3))
+    pos[: n // 3] = 90.0 + rng.normal(0.0, 2.0, size=(n // 3, 3))
+    cat = C.Catalogue("cells", pos, rng.uniform(0.5, 1.5, size=n), (200.0,) * 3, (0.0,) * 3, True,
+                      20.0, 3, 4, "z")
+    mask = (rng.uniform(size=n) < 0.4).astype(np.uint8) if masked else None
+    p, w = on(dev, cat)
+    z, pairs = api.zeta(p, w, cfg_of(cat, "fp64"), return_pairs=True,
+                        primary_mask=None if mask is None else torch.from_numpy(mask).to(dev))
+    ref, pairs_ref = oracle.zeta(cat, primary_mask=mask, return_pairs=True)
+    e = np.abs(z.cpu().numpy() - ref).max()
+    say(f"  pairs {pairs}, max|dz| = {e:.2e} of {np.abs(ref).max():.2e}")
+    assert pairs == pairs_ref
+    assert e <= 1e-10 * np.abs(ref).max()
