@@ -235,10 +235,9 @@ int g3pcf_forward_noalloc(const g3pcf_problem* prob, double* zeta, void* stream)
  * region[i] when 0 <= region[i] < nregions (and, if primary_mask is set,
  * primary_mask[i] != 0); every galaxy is a secondary of every region.
  * zeta: device [nregions][g3pcf_zeta_len] doubles, region-major, overwritten
- * (or added into with accumulate = 1).  The cell list is built once; each
- * region runs its own primary list through the pair stage, so the pair work
- * is that of one forward pass over all assigned primaries; the call waits for
- * the stream once per region to read the region's primary count.  ws: at least
+ * (or added into with accumulate = 1).  The cell list is built once and all
+ * assigned primaries, region after region, go through the pair stage in one
+ * pass; each region's rows are then reduced on their own.  ws: at least
  * g3pcf_workspace_bytes(prob, 0) bytes.  pairs_out (if set): accepted pairs
  * summed over the regions.  Errors as g3pcf_forward, and G3PCF_EINVAL for
  * nregions outside 1..2^20 or a NULL region with n > 0. */

@@ -219,11 +219,7 @@ struct Counters {
 };
 static_assert(sizeof(Counters) <= kCountersBytes, "counters block");
 
-// Stages shared by forward and backward: cell list and primary list, and the
-// pass's clears z (n > 0).  primaries = false: the list is left to the caller.
-int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, const Clears& z,
-                    hipStream_t st, bool primaries = true) {
-  const int fp64 = (p.pair_prec == G3PCF_PREC_FP64);
+CellBufs cell_bufs(const Ws& w, void* ws) {
   CellBufs b{};
   b.pos4 = at<void>(ws, w.pos4);
   b.stage4 = at<void>(ws, w.tmp4);
@@ -237,6 +233,15 @@ int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, const Clears&
   b.wsort = at<double>(ws, w.wsort);
   b.scan_tmp = at<void>(ws, w.scan);
   b.scan_bytes = w.scan_bytes;
+  return b;
+}
+
+// Stages shared by forward and backward: cell list and primary list, and the
+// pass's clears z (n > 0).  primaries = false: the list is left to the caller.
+int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, const Clears& z,
+                    hipStream_t st, bool primaries = true) {
+  const int fp64 = (p.pair_prec == G3PCF_PREC_FP64);
+  const CellBufs b = cell_bufs(w, ws);
   Counters* c = at<Counters>(ws, w.counters);
   Primaries pr{p.primary_mask, primaries ? at<int>(ws, w.flags) : nullptr, at<int>(ws, w.plist),
                &c->nprim, reinterpret_cast<int*>(c), int(sizeof(Counters) / 4)};
@@ -420,18 +425,18 @@ int forward_tables(const g3pcf_problem& p) {
 // The pair-blocks of the current primary list (at most `cover` primaries):
 // pair kernel, Gram products into zeta, and (distinct) the degenerate-triangle
 // pass and its correction.  rows: where the a_lm rows go (NULL: the
-// workspace's pair-block rows; else rows of every primary, kept).
+// workspace's pair-block rows; else rows of every primary, kept).  starts: NULL,
+// or the parts of the list (device, nparts + 1 of them, see
+// launch_region_primaries), each reduced into a zeta of its own.
 int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, int64_t cover,
-                  double* rows, hipStream_t st) {
+                  double* rows, const int* starts, int nparts, hipStream_t st) {
   hipError_t e;
   PairArgs a{};
   if (int rc = pair_args(p, w, ws, a)) return rc;
   const int fp64 = (p.pair_prec == G3PCF_PREC_FP64);
   Counters* c = at<Counters>(ws, w.counters);
   double* degD = at<double>(ws, w.degD);
-  if (p.distinct &&
-      (e = launch_fill_double(degD, int64_t(p.nbins) * (2 * p.lmax + 1), 0.0, st)) != hipSuccess)
-    return hip_fail(e, "degenerate sums clear");
+  const size_t zlen = g3pcf_zeta_len(p.lmax, p.nbins);
   for (int64_t b0 = 0; b0 < cover; b0 += w.PB) {
     a.p_begin = b0;
     a.p_count = std::min<int64_t>(w.PB, cover - b0);
@@ -454,10 +459,13 @@ int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, i
       z.lay = w.lay;
       z.C64 = at<double>(ws, w.C);
       z.parts = w.parts;
-      z.zeta = zeta;
       z.prec = p.zeta_prec;
       z.queue = a.queue;
-      if ((e = launch_zeta_pairblock(z, st)) != hipSuccess) return hip_fail(e, "zeta");
+      for (int r = 0; r < nparts; ++r) {
+        z.range = starts ? starts + r : nullptr;
+        z.zeta = zeta + zlen * size_t(r);
+        if ((e = launch_zeta_pairblock(z, st)) != hipSuccess) return hip_fail(e, "zeta");
+      }
     }
     if (p.distinct) {
       // the sums w_j^2 T_n(u_z) of each primary, summed with w_i; without rows
@@ -469,16 +477,19 @@ int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, i
         return hip_fail(e, "degenerate-triangle pass");
       const double* X = w.deg_fused ? a.deg : a.A;
       const int rowW = w.deg_fused ? p.nbins * (2 * p.lmax + 1) : w.lay.W;
-      if ((e = launch_deg_reduce(X, rowW, p.nbins, p.lmax, a.wsort, a.plist, &c->nprim, b0,
-                                 a.p_count, at<double>(ws, w.degP), degD, a.queue, st)) !=
-          hipSuccess)
-        return hip_fail(e, "degenerate-triangle sums");
+      for (int r = 0; r < nparts; ++r) {
+        if ((e = launch_fill_double(degD, int64_t(p.nbins) * (2 * p.lmax + 1), 0.0, st)) !=
+            hipSuccess)
+          return hip_fail(e, "degenerate sums clear");
+        if ((e = launch_deg_reduce(X, rowW, p.nbins, p.lmax, a.wsort, a.plist, &c->nprim,
+                                   starts ? starts + r : nullptr, b0, a.p_count,
+                                   at<double>(ws, w.degP), degD, a.queue, st)) != hipSuccess)
+          return hip_fail(e, "degenerate-triangle sums");
+        if ((e = launch_deg_apply(degD, p.lmax, p.nbins, zeta + zlen * size_t(r), st)) !=
+            hipSuccess)
+          return hip_fail(e, "degenerate-triangle correction");
+      }
     }
-  }
-  if (p.distinct) {
-    StageScope scd(p.trace, G3PCF_STAGE_DISTINCT, st);
-    if ((e = launch_deg_apply(degD, p.lmax, p.nbins, zeta, st)) != hipSuccess)
-      return hip_fail(e, "degenerate-triangle correction");
   }
   return G3PCF_OK;
 }
@@ -523,7 +534,8 @@ int forward_run(const g3pcf_problem& p, const Ws& w, double* zeta, void* ws, hip
                      hipSuccess)
       return hip_fail(e, "alm store fingerprint");
   }
-  if ((rc = forward_pairs(p, w, ws, zeta, p.n, p.alm ? alm_rows(p) : nullptr, st))) return rc;
+  if ((rc = forward_pairs(p, w, ws, zeta, p.n, p.alm ? alm_rows(p) : nullptr, nullptr, 1, st)))
+    return rc;
   return finish_pairs(p, w, ws, st);
 }
 
@@ -684,35 +696,36 @@ int g3pcf_forward_regions(const g3pcf_problem* prob, const int32_t* region, int 
   if ((rc = forward_tables(p))) return rc;
   const size_t zlen = g3pcf_zeta_len(p.lmax, p.nbins);
   hipError_t e;
-  if (!p.accumulate &&
-      (e = launch_fill_double(zeta, int64_t(zlen) * nregions, 0.0, st)) != hipSuccess)
-    return hip_fail(e, "zeta clear");
+  Clears z;
+  if (!p.accumulate) z.add(zeta, int64_t(zlen) * nregions * 2);
   if (p.n == 0) {
+    if ((e = launch_clears(z, st)) != hipSuccess) return hip_fail(e, "zeta clear");
     if (p.pairs_out) *p.pairs_out = 0;
     return G3PCF_OK;
   }
   {
     StageScope sc(p.trace, G3PCF_STAGE_CELLS, st);
-    if ((rc = stage_catalogue(p, w, ws, Clears(), st, false))) return rc;
+    if ((rc = stage_catalogue(p, w, ws, z, st, false))) return rc;
   }
-  // one cell list; per region its own primary list and pair-blocks, sized by
-  // the region's primary count (read back: one wait per region)
+  // One cell list and, region after region in one primary list, one pass of the
+  // pair kernel; then a Gram product per region over its part of the rows.  (As
+  // many regions at a time as there are galaxies: their starts share the scan's
+  // space.)  27 regions of 3700 primaries as passes of their own took 8.0 ms, of
+  // which 4.9 in pair kernels and 1.4 in waits for each region's count.
   Counters* c = at<Counters>(ws, w.counters);
-  for (int r = 0; r < nregions; ++r) {
-    long long count = 0;
+  int* flags = at<int>(ws, w.flags);
+  int* starts = flags + (p.n + 1);
+  for (int r0 = 0; r0 < nregions;) {
+    const int m = int(std::min<int64_t>(nregions - r0, p.n));
     {
       StageScope sc(p.trace, G3PCF_STAGE_CELLS, st);
-      if ((e = launch_primaries(p.primary_mask, region, r, at<int>(ws, w.perm), p.n,
-                                at<int>(ws, w.flags), at<int>(ws, w.plist), &c->nprim,
-                                at<void>(ws, w.scan), w.scan_bytes, st)) != hipSuccess)
+      if ((e = launch_region_primaries(p.primary_mask, region, r0, m, cell_bufs(w, ws), p.n, flags,
+                                       starts, at<int>(ws, w.plist), &c->nprim, st)) != hipSuccess)
         return hip_fail(e, "region primary list");
     }
-    if ((e = hipMemcpyAsync(&count, &c->nprim, sizeof(count), hipMemcpyDeviceToHost, st)) !=
-            hipSuccess ||
-        (e = hipStreamSynchronize(st)) != hipSuccess)
-      return hip_fail(e, "region primary count");
-    if (count > 0 && (rc = forward_pairs(p, w, ws, zeta + zlen * size_t(r), count, nullptr, st)))
+    if ((rc = forward_pairs(p, w, ws, zeta + zlen * size_t(r0), p.n, nullptr, starts, m, st)))
       return rc;
+    r0 += m;
   }
   return finish_pairs(p, w, ws, st);
 }
@@ -756,7 +769,8 @@ int g3pcf_forward_batch(const g3pcf_problem* prob, int ncat, const int64_t* offs
       StageScope sc(p.trace, G3PCF_STAGE_CELLS, st);
       if ((rc = stage_catalogue(q, w, ws, Clears(), st))) return rc;
     }
-    if ((rc = forward_pairs(q, w, ws, zeta + zlen * size_t(c), q.n, nullptr, st))) return rc;
+    if ((rc = forward_pairs(q, w, ws, zeta + zlen * size_t(c), q.n, nullptr, nullptr, 1, st)))
+      return rc;
     if ((rc = finish_pairs(q, w, ws, st))) return rc;
     total += pairs_c;
   }

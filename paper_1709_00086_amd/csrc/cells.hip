@@ -212,20 +212,41 @@ __global__ void k_gather_sorted(const V4* __restrict__ in4, const int* __restric
   wsort[s] = w[i];
 }
 
-// primary flag of the galaxy in cell-order slot s: in the mask (if any) and,
-// when region ids are given, in region r
-__global__ void k_primary_flags(const uint8_t* __restrict__ mask,
-                                const int32_t* __restrict__ region, int r,
-                                const int* __restrict__ perm, int64_t n,
-                                int* __restrict__ flags) {
+// primary flag of the galaxy in cell-order slot s
+__global__ void k_primary_flags(const uint8_t* __restrict__ mask, const int* __restrict__ perm,
+                                int64_t n, int* __restrict__ flags) {
   const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (s > n) return;
-  if (s == n) {
-    flags[s] = 0;
-    return;
-  }
+  flags[s] = s < n && mask[perm[s]] != 0 ? 1 : 0;
+}
+
+// region (from region0) of the galaxy in slot s; nregions: none of them
+__global__ void k_region_keys(const uint8_t* __restrict__ mask,
+                              const int32_t* __restrict__ region, int region0, int nregions,
+                              const int* __restrict__ perm, int64_t n, int* __restrict__ keys,
+                              int* __restrict__ flags) {
+  const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (s > n) return;
+  flags[s] = 0;
+  if (s == n) return;
   const int i = perm[s];
-  flags[s] = ((mask == nullptr || mask[i] != 0) && (region == nullptr || region[i] == r)) ? 1 : 0;
+  const int64_t r = int64_t(region[i]) - region0;
+  keys[s] = r >= 0 && r < nregions && (mask == nullptr || mask[i] != 0) ? int(r) : nregions;
+}
+
+// starts[r] = slots sorted below region r
+__global__ void k_region_starts(const int* __restrict__ keys, int64_t n, int nregions,
+                                int* __restrict__ starts, long long* __restrict__ nprim) {
+  const int r = int(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (r > nregions) return;
+  int64_t lo = 0, hi = n;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (keys[mid] < r) lo = mid + 1;
+    else hi = mid;
+  }
+  starts[r] = int(lo);
+  if (r == nregions) *nprim = lo;
 }
 
 // every galaxy a primary
@@ -626,6 +647,40 @@ size_t radix_hist_ints(int64_t n) {
   return size_t(ntiles) * kRadixDigits;
 }
 
+// Indices 0..n-1 sorted stably by the keys in b.key_a (below `bound`) into `out`;
+// the sorted keys into *keys, if it is not NULL.
+static hipError_t radix_sort(const CellBufs& b, int64_t n, int64_t bound, int* out, int** keys,
+                             hipStream_t st) {
+  int bits = 0;
+  while ((int64_t(1) << bits) < bound) ++bits;
+  const int passes = std::max(1, (bits + kRadixBits - 1) / kRadixBits);
+  const int ntiles = int((n + kRadixTile - 1) / kRadixTile);
+  const int64_t nh = int64_t(ntiles) * kRadixDigits;
+  int* hist = b.hist;
+  int* offs = b.hist + nh;
+  const int* kin = b.key_a;
+  const int* vin = nullptr;
+  hipError_t e;
+  for (int pass = 0; pass < passes; ++pass) {
+    const int shift = pass * kRadixBits;
+    const bool last = pass + 1 == passes;
+    int* kout = last && !keys ? nullptr : (kin == b.key_a ? b.key_b : b.key_a);
+    // the last pass writes out; the ones before alternate so that it does
+    int* vout = ((passes - 1 - pass) % 2 == 0) ? out : b.val_a;
+    hipLaunchKernelGGL(k_radix_hist, dim3(ntiles), dim3(kRadixThreads), 0, st, kin, n, shift,
+                       ntiles, hist);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_scan(hist, offs, nh, b.scan_tmp, b.scan_bytes, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_radix_scatter, dim3(ntiles), dim3(kRadixThreads), 0, st, kin, vin, n,
+                       shift, ntiles, offs, kout, vout);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    kin = kout;
+    vin = vout;
+  }
+  if (keys) *keys = const_cast<int*>(kin);
+  return hipSuccess;
+}
+
 hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b,
                         const Primaries& pr, Clears z, int fp64, hipStream_t st) {
   const int64_t n = p.n;
@@ -693,31 +748,7 @@ hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b
       hipSuccess)
     return e;
   // perm = input indices sorted stably by cell id
-  int bits = 0;
-  while ((int64_t(1) << bits) < g.ncell) ++bits;
-  const int passes = std::max(1, (bits + kRadixBits - 1) / kRadixBits);
-  const int ntiles = int((n + kRadixTile - 1) / kRadixTile);
-  const int64_t nh = int64_t(ntiles) * kRadixDigits;
-  int* hist = b.hist;
-  int* offs = b.hist + nh;
-  const int* kin = b.key_a;
-  const int* vin = nullptr;
-  for (int pass = 0; pass < passes; ++pass) {
-    const int shift = pass * kRadixBits;
-    const bool last = pass + 1 == passes;
-    int* kout = last ? nullptr : (kin == b.key_a ? b.key_b : b.key_a);
-    // the last pass writes perm; the ones before alternate so that it does
-    int* vout = ((passes - 1 - pass) % 2 == 0) ? b.perm : b.val_a;
-    hipLaunchKernelGGL(k_radix_hist, dim3(ntiles), dim3(kRadixThreads), 0, st, kin, n, shift,
-                       ntiles, hist);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = launch_scan(hist, offs, nh, b.scan_tmp, b.scan_bytes, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_radix_scatter, dim3(ntiles), dim3(kRadixThreads), 0, st, kin, vin, n,
-                       shift, ntiles, offs, kout, vout);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    kin = kout;
-    vin = vout;
-  }
+  if ((e = radix_sort(b, n, g.ncell, b.perm, nullptr, st)) != hipSuccess) return e;
   // the gather also writes the kSentinel NaN entries after the catalogue
   const unsigned ng = blocks_for(n + kSentinel, 256);
   if (fp64)
@@ -729,20 +760,33 @@ hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b
                        static_cast<const float4*>(b.stage4), b.perm, n, p.w,
                        static_cast<float4*>(b.pos4), b.wsort);
   if ((e = hipGetLastError()) != hipSuccess || !pr.flags) return e;
-  return launch_primaries(pr.mask, nullptr, 0, b.perm, n, pr.flags, pr.plist, pr.nprim,
-                          b.scan_tmp, b.scan_bytes, st);
+  return launch_primaries(pr.mask, b.perm, n, pr.flags, pr.plist, pr.nprim, b.scan_tmp,
+                          b.scan_bytes, st);
 }
 
-hipError_t launch_primaries(const uint8_t* mask, const int32_t* region, int r, const int* perm,
-                            int64_t n, int* flags, int* plist, long long* nprim,
-                            void* scan_tmp, size_t scan_tmp_bytes_, hipStream_t st) {
+hipError_t launch_region_primaries(const uint8_t* mask, const int32_t* region, int region0,
+                                   int nregions, const CellBufs& b, int64_t n, int* flags,
+                                   int* starts, int* plist, long long* nprim, hipStream_t st) {
+  hipLaunchKernelGGL(k_region_keys, dim3(blocks_for(n + 1, 256)), dim3(256), 0, st, mask, region,
+                     region0, nregions, b.perm, n, b.key_a, flags);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  int* keys = nullptr;
+  if ((e = radix_sort(b, n, int64_t(nregions) + 1, plist, &keys, st)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_region_starts, dim3(blocks_for(int64_t(nregions) + 1, 256)), dim3(256), 0,
+                     st, keys, n, nregions, starts, nprim);
+  return hipGetLastError();
+}
+
+hipError_t launch_primaries(const uint8_t* mask, const int* perm, int64_t n, int* flags,
+                            int* plist, long long* nprim, void* scan_tmp, size_t scan_tmp_bytes_,
+                            hipStream_t st) {
   const unsigned nb = blocks_for(n + 1, 256);
-  if (!mask && !region) {
+  if (!mask) {
     hipLaunchKernelGGL(k_primary_all, dim3(nb), dim3(256), 0, st, flags, n, plist, nprim);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_primary_flags, dim3(nb), dim3(256), 0, st, mask, region, r, perm, n,
-                     flags);
+  hipLaunchKernelGGL(k_primary_flags, dim3(nb), dim3(256), 0, st, mask, perm, n, flags);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // positions: exclusive scan into flags + (n + 1)

@@ -248,11 +248,18 @@ constexpr int kSmallN = 6144;
 // The cell list, the primary list and the pass's clears.
 hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b,
                         const Primaries& pr, Clears z, int fp64, hipStream_t st);
-// Primary list (cell order): galaxies in the mask (NULL: all) and, if region
-// is not NULL, with region[i] == r.  Leaves flags zero (see PairArgs::overflow).
-hipError_t launch_primaries(const uint8_t* mask, const int32_t* region, int r, const int* perm,
-                            int64_t n, int* flags, int* plist, long long* nprim,
-                            void* scan_tmp, size_t scan_tmp_bytes, hipStream_t st);
+// Primary list (cell order): galaxies in the mask (NULL: all).  Leaves flags zero
+// (see PairArgs::overflow).
+hipError_t launch_primaries(const uint8_t* mask, const int* perm, int64_t n, int* flags,
+                            int* plist, long long* nprim, void* scan_tmp, size_t scan_tmp_bytes,
+                            hipStream_t st);
+// The same for the galaxies with region0 <= region[i] < region0 + nregions, by
+// region and within one in cell order: region r's are plist[starts[r - region0]] to
+// plist[starts[r - region0 + 1] - 1].  nregions <= n; starts shares flags' second
+// half.
+hipError_t launch_region_primaries(const uint8_t* mask, const int32_t* region, int region0,
+                                   int nregions, const CellBufs& b, int64_t n, int* flags,
+                                   int* starts, int* plist, long long* nprim, hipStream_t st);
 // *out += order-independent hash of the cell-order catalogue (slot -> index,
 // stored position words, weight) and the primary list, keyed by `seed` (a hash
 // of the settings); *out must be cleared first.
@@ -285,6 +292,7 @@ struct ZetaArgs {
   const double* wsort;       // weights in cell order
   const int* plist;
   const long long* nprim;
+  const int* range;          // part of the list that is summed (device, first and past the last), or NULL
   long long row_begin;       // global primary index of A row 0
   long long K;               // rows of the pair-block (upper bound)
   RowLayout lay;
@@ -333,9 +341,9 @@ int sum_wm2(const RowLayout& lay);
 hipError_t upload_deg_table();
 size_t deg_partial_doubles(long long PB, int nb, int lmax);
 hipError_t launch_deg_reduce(const double* X, int rowW, int nb, int lmax, const double* wsort,
-                             const int* plist, const long long* nprim, long long p_begin,
-                             long long p_count, double* partial, double* D, int* queue,
-                             hipStream_t st);
+                             const int* plist, const long long* nprim, const int* range,
+                             long long p_begin, long long p_count, double* partial, double* D,
+                             int* queue, hipStream_t st);
 hipError_t launch_deg_apply(const double* D, int lmax, int nb, double* zeta, hipStream_t st);
 // Isotropic multipoles from zeta (addition theorem).
 hipError_t launch_isotropic(const double* zeta, int lmax, int nb, double* iso, hipStream_t st);

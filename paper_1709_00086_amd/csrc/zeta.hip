@@ -24,11 +24,18 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef double double4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
-__device__ __forceinline__ long long valid_rows(const ZetaArgs& z) {
-  // primaries in the pair-block
-  long long kv = (long long)(*z.nprim) - z.row_begin;
-  if (kv > z.K) kv = z.K;
-  return kv < 0 ? 0 : kv;
+// Rows of the pair-block [begin, begin + count) that are summed: its primaries,
+// or those of the list's part range[0]..range[1] - 1; the first of them in `first`.
+__device__ __forceinline__ long long valid_rows(const long long* nprim, const int* range,
+                                                long long begin, long long count,
+                                                long long& first) {
+  const long long lo = range ? max((long long)range[0], begin) : begin;
+  const long long hi = min(range ? (long long)range[1] : (long long)*nprim, begin + count);
+  first = lo - begin;
+  return max(hi - lo, 0ll);
+}
+__device__ __forceinline__ long long valid_rows(const ZetaArgs& z, long long& first) {
+  return valid_rows(z.nprim, z.range, z.row_begin, z.K, first);
 }
 
 // Rows per Gram block: the valid rows spread over the workspace's partials, a
@@ -131,12 +138,13 @@ __global__ __launch_bounds__(256) void k_gram_mt(ZetaArgs z, MDims d, double* __
   macro_tile_of(d, blockIdx.x, m, ti, tj);
   const int W = d.W[m];
   const bool diag = (ti == tj);
-  const long long Kv = valid_rows(z), rows = block_rows(Kv, z.parts);
+  long long first;
+  const long long Kv = valid_rows(z, first), rows = block_rows(Kv, z.parts);
   const long long r0 = s * rows;
   const long long r1 = min(Kv, r0 + rows);
   if (r0 >= r1) return;
-  const double* A = z.A + d.off[m];
-  const int* plist = z.plist + z.row_begin;
+  const double* A = z.A + first * z.lay.W + d.off[m];
+  const int* plist = z.plist + z.row_begin + first;
 
   // staging: thread -> (row srow, 8 columns from scol) of both column ranges
   const int srow = tid / 8, scol = (tid % 8) * 8;
@@ -252,12 +260,13 @@ __global__ __launch_bounds__(256) void k_gram_bf16x3_mt(ZetaArgs z, MDims d,
   macro_tile_of(d, blockIdx.x, m, ti, tj);
   const int W = d.W[m];
   const bool diag = (ti == tj);
-  const long long Kv = valid_rows(z), rows = block_rows(Kv, z.parts);
+  long long first;
+  const long long Kv = valid_rows(z, first), rows = block_rows(Kv, z.parts);
   const long long r0 = s * rows;
   const long long r1 = min(Kv, r0 + rows);
   if (r0 >= r1) return;
-  const double* A = z.A + d.off[m];
-  const int* plist = z.plist + z.row_begin;
+  const double* A = z.A + first * z.lay.W + d.off[m];
+  const int* plist = z.plist + z.row_begin + first;
   const int ci = ti * kMT + lane, cj = tj * kMT + lane;
 
   double xr[8], yr[8], wgt[8];
@@ -399,7 +408,8 @@ __global__ __launch_bounds__(kAT * kAT) void k_zeta_accum_mt(ZetaArgs z, MDims d
   }
   const int dm = L.d[m], nt = (dm + kAT - 1) / kAT, nl = nm - m;
   const int P = (t / nt) * kAT + int(threadIdx.x) / kAT, Pp = (t % nt) * kAT + int(threadIdx.x) % kAT;
-  const long long Kv = valid_rows(z);
+  long long first;
+  const long long Kv = valid_rows(z, first);
   if (P >= dm || Pp >= dm || Kv == 0) return;
   const long long rows = block_rows(Kv, z.parts);
   const int nsub = int((Kv + rows - 1) / rows);
@@ -514,11 +524,16 @@ __global__ __launch_bounds__(256) void k_deg_partial(const double* __restrict__ 
                                                      int ncols, const double* __restrict__ wsort,
                                                      const int* __restrict__ plist,
                                                      const long long* __restrict__ nprim,
+                                                     const int* __restrict__ range,
                                                      long long p_begin, long long p_count,
                                                      double* __restrict__ partial) {
-  const long long valid = min(p_count, (long long)(*nprim) - p_begin);
+  long long first;
+  const long long valid = valid_rows(nprim, range, p_begin, p_count, first);
   const long long r0 = (long long)blockIdx.x * kDegRows;
   const long long r1 = min(r0 + kDegRows, valid);
+  if (r0 >= r1) return;
+  X += first * rowW;
+  plist += first;
   for (int c = threadIdx.x; c < ncols; c += blockDim.x) {
     double s = 0.0;
     for (long long r = r0; r < r1; ++r) s += wsort[plist[p_begin + r]] * X[r * rowW + c];
@@ -527,14 +542,19 @@ __global__ __launch_bounds__(256) void k_deg_partial(const double* __restrict__ 
 }
 
 // D[c] += sum over the workgroups, in order, of partial[blk][c]
-__global__ void k_deg_accum(const double* __restrict__ partial, int nblk, int ncols,
+__global__ void k_deg_accum(const double* __restrict__ partial,
+                            const long long* __restrict__ nprim, const int* __restrict__ range,
+                            long long p_begin, long long p_count, int ncols,
                             double* __restrict__ D, int* __restrict__ queue) {
   // the pair kernel's next launch starts from cleared counters
   if (blockIdx.x == 0 && threadIdx.x < kQueueAdjoint * kQueues)
     queue[threadIdx.x / kQueueAdjoint * kQueueStride + threadIdx.x % kQueueAdjoint] = 0;
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= ncols) return;
+  long long first;
+  const int nblk = int((valid_rows(nprim, range, p_begin, p_count, first) + kDegRows - 1) / kDegRows);
   double s = 0.0;
+#pragma unroll 4
   for (int b = 0; b < nblk; ++b) s += partial[(long long)b * ncols + c];
   D[c] += s;
 }
@@ -595,16 +615,16 @@ size_t deg_partial_doubles(long long PB, int nb, int lmax) {
 }
 
 hipError_t launch_deg_reduce(const double* X, int rowW, int nb, int lmax, const double* wsort,
-                             const int* plist, const long long* nprim, long long p_begin,
-                             long long p_count, double* partial, double* D, int* queue,
-                             hipStream_t st) {
+                             const int* plist, const long long* nprim, const int* range,
+                             long long p_begin, long long p_count, double* partial, double* D,
+                             int* queue, hipStream_t st) {
   if (p_count <= 0) return hipSuccess;
   const int ncols = nb * (2 * lmax + 1);
   const unsigned nblk = unsigned((p_count + kDegRows - 1) / kDegRows);
   hipLaunchKernelGGL(k_deg_partial, dim3(nblk), dim3(256), 0, st, X, rowW, ncols, wsort, plist,
-                     nprim, p_begin, p_count, partial);
+                     nprim, range, p_begin, p_count, partial);
   hipLaunchKernelGGL(k_deg_accum, dim3((ncols + 255) / 256), dim3(256), 0, st, partial,
-                     int(nblk), ncols, D, queue);
+                     nprim, range, p_begin, p_count, ncols, D, queue);
   return hipGetLastError();
 }
 

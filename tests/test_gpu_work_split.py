@@ -150,3 +150,31 @@ def test_cell_stage_of_small_catalogues(dev, n, masked):
     say(f"  pairs {pairs}, max|dz| = {e:.2e} of {np.abs(ref).max():.2e}")
     assert pairs == pairs_ref
     assert e <= 1e-10 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("n,nregions,distinct", [(7, 12, False), (1500, 1, True),
+                                                 (1500, 300, False), (1500, 1499, True)])
+def test_regions_in_one_pass(dev, n, nregions, distinct):
+    """Region ids outside the range and a mask; more regions than galaxies, and
+    more than one digit of the sort.  Each region's zeta against the oracle with
+    the region as the mask (FP64, 1e-10 of max|zeta| over all of them)."""
+    say(f"case regions n={n} R={nregions} distinct={distinct}")
+    cat = C.tiny(n=n, L=150.0, seed=87, rmax=40.0, nbins=3, lmax=3)
+    rng = np.random.default_rng(88)
+    region = rng.integers(-2, nregions + 2, size=n).astype(np.int32)
+    mask = (rng.uniform(size=n) < 0.7).astype(np.uint8)
+    pos, w = on(dev, cat)
+    z = api.zeta_regions(pos, w, cfg_of(cat, "fp64", distinct=distinct),
+                         torch.from_numpy(region).to(dev), nregions,
+                         primary_mask=torch.from_numpy(mask).to(dev)).cpu().numpy()
+    refs = {r: oracle.zeta(cat, primary_mask=((region == r) & (mask != 0)).astype(np.uint8),
+                           distinct=distinct)
+            for r in sorted({0, nregions // 2, nregions - 1, min(6, nregions - 1)})}
+    scale = max(np.abs(v).max() for v in refs.values())
+    for r, ref in refs.items():
+        assert np.abs(z[r] - ref).max() <= 1e-10 * scale, r
+    every = oracle.zeta(cat, primary_mask=((region >= 0) & (region < nregions) &
+                                           (mask != 0)).astype(np.uint8), distinct=distinct)
+    e = np.abs(z.sum(0) - every).max() / max(np.abs(every).max(), 1e-300)
+    say(f"  sum over regions: {e:.2e}")
+    assert e <= 1e-10
