@@ -39,10 +39,12 @@ constexpr int kWave = 64;
 constexpr int kSentinel = kWave;
 constexpr int kOutPerBin = (kDeg + 1) * (kDeg + 1);  // real a_lm outputs per shell (121)
 
-// Rows of A (primaries) reduced per Gram product on MFMA: at most, and (where
-// few rows would leave CUs idle) at least.
+// Rows of A (primaries) reduced per Gram block: at most (one list part), and
+// (where few rows would leave CUs idle) at least.
 constexpr int kZetaBlock = 4096;
 constexpr int kZetaRowsMin = 128;
+// Parts of the primary list that one launch of the Gram products takes at most.
+constexpr int kZetaLists = 32;
 // Primary queues of the pair kernel: one per XCD (workgroups are dispatched to
 // the 8 XCDs round-robin), each counter on its own 64-byte line.
 constexpr int kQueues = 8;
@@ -292,13 +294,14 @@ struct ZetaArgs {
   const double* wsort;       // weights in cell order
   const int* plist;
   const long long* nprim;
-  const int* range;          // part of the list that is summed (device, first and past the last), or NULL
+  const int* range;          // parts of the list that are summed (device, `lists` + 1 of them), or NULL
+  int lists;                 // parts of the list (1 without `range`), at most kZetaLists
   long long row_begin;       // global primary index of A row 0
   long long K;               // rows of the pair-block (upper bound)
   RowLayout lay;
   double* C64;               // [parts][sum W_m^2] per-block Gram products (FP64)
-  int parts;                 // blocks the partials have room for (>= K / kZetaBlock)
-  double* zeta;
+  int parts;                 // blocks the partials have room for (>= K / kZetaBlock and `lists`)
+  double* zeta;              // one a list part
   int prec;
   int* queue;                // the pair kernel's primary counters, cleared for its next launch
 };

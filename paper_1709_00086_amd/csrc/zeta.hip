@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -34,29 +35,73 @@ __device__ __forceinline__ long long valid_rows(const long long* nprim, const in
   first = lo - begin;
   return max(hi - lo, 0ll);
 }
-__device__ __forceinline__ long long valid_rows(const ZetaArgs& z, long long& first) {
-  return valid_rows(z.nprim, z.range, z.row_begin, z.K, first);
+// The Gram blocks of a launch: the valid rows of its list parts spread over the
+// workspace's partials, every block within one part, `rows` of them (a multiple
+// of kZetaRowsMin).  Only the device knows how many primaries there are (a mask
+// may leave few of the rows the launch covers, a region's part may hold any number
+// of them), so the blocks are dealt out here, one list part a lane; the workgroups
+// past the last block leave at once.
+struct GramBlocks {
+  int first, count;  // rows of the lane's list part
+  int rows;          // rows of a block of the lane's list part
+  int begin, end;    // blocks of the lane's list part
+};
+static_assert(kZetaLists <= kWave, "a lane per list part");
+
+__device__ __forceinline__ GramBlocks gram_blocks(const ZetaArgs& z) {
+  const int lane = threadIdx.x % kWave;
+  GramBlocks g{};
+  if (lane < z.lists) {
+    long long first;
+    g.count = int(valid_rows(z.nprim, z.range ? z.range + lane : nullptr, z.row_begin, z.K, first));
+    g.first = int(first);
+  }
+  int all = g.count;
+#pragma unroll
+  for (int o = 1; o < kWave; o *= 2) all += __shfl_xor(all, o);
+  // sum of ceil(count / rows) <= ceil(all / rows) + lists - 1 <= parts
+  const int share = z.parts - z.lists + 1;
+  auto whole = [](int r) {
+    return max(r + kZetaRowsMin - 1, kZetaRowsMin) / kZetaRowsMin * kZetaRowsMin;
+  };
+  const int most = whole((all + share - 1) / share);
+  int n = (g.count + most - 1) / most;
+  g.rows = whole(n ? (g.count + n - 1) / n : 0);
+  n = (g.count + g.rows - 1) / g.rows;
+  g.end = n;
+#pragma unroll
+  for (int o = 1; o < kWave; o *= 2) {
+    const int v = __shfl_up(g.end, o);
+    if (lane >= o) g.end += v;
+  }
+  g.begin = g.end - n;
+  return g;
 }
 
-// Rows per Gram block: the valid rows spread over the workspace's partials, a
-// multiple of kZetaRowsMin.  Only the device knows how
-// many primaries there are (a mask or a region may leave few of the rows the
-// launch covers), so the blocks choose it; the ones past the rows leave at once.
-__device__ __forceinline__ long long block_rows(long long kv, int parts) {
-  const long long r = (kv + parts - 1) / parts;
-  return max(r + kZetaRowsMin - 1, (long long)kZetaRowsMin) / kZetaRowsMin * kZetaRowsMin;
-}
-
-// ---- FP32 / FP64: one workgroup per (m, 64 x 64 macro tile of C_m on or
-// above the diagonal, block of at most 4096 primaries).  Each step stages 32 rows of
-// the two column ranges in LDS (weights applied to the left operand, FP64 rows
-// converted to the working precision on the way), and each wave accumulates a
-// 32 x 32 quadrant as 2 x 2 MFMA tiles over the block's rows.  The next step's
-// rows are loaded into registers while the current step is multiplied.  In
-// FP32 the MFMA accumulators are added into FP64 ones every kFlush rows, so the
-// block's partial is FP64 like the sum across blocks.
-constexpr int kMT = 64;     // macro tile
-constexpr int kKS = 32;     // rows per step
+// ---- One workgroup per (m, 128 x 128 macro tile of C_m on or above the diagonal,
+// Gram block of rows).  Each step puts kStep rows of the macro tile's two column
+// panels in LDS (weights applied to the left operand, FP64 rows converted to the
+// working precision on the way), and the eight waves share out its units: two
+// 16 x 16 tiles below each other, so that a right operand is read from LDS once for
+// two tiles.  In FP32 and BF16x3 the MFMA accumulators are added into FP64 ones
+// every kFlush rows, so the block's partial is FP64 like the sum across blocks.
+//
+// What bounds it: the staging, that is the reads of the FP64 rows and the vector
+// instructions that convert and split them (BF16x3, 2^19 rows of 1210: 7.9 GB staged
+// in 2.6 ms, 3.0 TB/s; the MFMAs alone 0.55 ms).  With 64 x 64 macro tiles every
+// column was staged in up to five workgroups; 128-wide panels stage it in at most
+// three, and tiles below the diagonal or past the last column are left out (395 of
+// 16 x 16 a block at lmax 10 and 10 shells instead of 688).  The rows of a step are
+// read two steps ahead and its row numbers three, without a branch around a load:
+// with a wait for the weights (row number, then weight, then lane reads) in every
+// step one took 3.2 us, now 2.2.  50001 primaries BF16x3 555 -> 290 us, 40000 FP32
+// 375 -> 253, 50021 FP64 577 -> 415.
+constexpr int kPanel = 128;        // columns of a panel
+constexpr int kTile = 16;
+constexpr int kPT = kPanel / kTile;  // tiles of a panel
+constexpr int kGramThreads = 512;
+constexpr int kGramWaves = kGramThreads / kWave;
+constexpr int kUnits = kPT / 2 * kPT / kGramWaves;  // units a wave holds at most
 // Rows per FP32 accumulation before the FP64 sum: blocks hold whole ones, so
 // the FP32 sums do not depend on how many blocks the rows are cut into.
 constexpr int kFlush = kZetaRowsMin;
@@ -66,7 +111,8 @@ struct MDims {
   int W[kDeg + 1];
   int off[kDeg + 1];
   int cw[kDeg + 2];       // offsets of each C_m in a partial
-  int mt[kDeg + 2];       // cumulative macro tiles on or above the diagonal
+  int order[kDeg + 1];    // the m's, widest first
+  int mt[kDeg + 2];       // cumulative macro tiles of order[]
   int csize;
 };
 
@@ -78,9 +124,13 @@ MDims make_mdims(const RowLayout& L) {
     d.W[m] = L.wm[m];
     d.off[m] = L.off[m];
     d.cw[m] = cw;
-    d.mt[m] = mt;
     cw += L.wm[m] * L.wm[m];
-    const int t = (L.wm[m] + kMT - 1) / kMT;
+    d.order[m] = m;
+  }
+  std::stable_sort(d.order, d.order + d.nm, [&](int a, int b) { return L.wm[a] > L.wm[b]; });
+  for (int k = 0; k < d.nm; ++k) {
+    d.mt[k] = mt;
+    const int t = (L.wm[d.order[k]] + kPanel - 1) / kPanel;
     mt += t * (t + 1) / 2;
   }
   d.cw[d.nm] = cw;
@@ -90,10 +140,11 @@ MDims make_mdims(const RowLayout& L) {
 }
 
 __device__ __forceinline__ void macro_tile_of(const MDims& d, int t, int& m, int& ti, int& tj) {
-  m = 0;
-  while (m + 1 < d.nm && t >= d.mt[m + 1]) ++m;
-  int r = t - d.mt[m];
-  const int nt = (d.W[m] + kMT - 1) / kMT;
+  int k = 0;
+  while (k + 1 < d.nm && t >= d.mt[k + 1]) ++k;
+  m = d.order[k];
+  int r = t - d.mt[k];
+  const int nt = (d.W[m] + kPanel - 1) / kPanel;
   ti = 0;
   while (r >= nt - ti) {
     r -= nt - ti;
@@ -102,294 +153,310 @@ __device__ __forceinline__ void macro_tile_of(const MDims& d, int t, int& m, int
   tj = ti + r;
 }
 
-template <typename Real>
-struct MfmaAcc;
-template <>
-struct MfmaAcc<float> {
-  using T = float4_t;
-  static __device__ __forceinline__ T mma(float a, float b, T c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+// The operands of a precision: how a step's rows lie in LDS and how a unit's two
+// tiles take them.
+template <int PREC>
+struct Operands;
+
+// FP32 / FP64: [row][column]
+template <typename Real, int STEP>
+struct PlainOperands {
+  using Acc = std::conditional_t<sizeof(Real) == 4, float4_t, double4_t>;
+  static constexpr int kStep = STEP;
+  static constexpr int kStride = kPanel + (sizeof(Real) == 4 ? 16 : 8);
+  Real v[2][kStep][kStride];  // left (weighted), right
+  // eight rows from r0 of one column
+  static constexpr int kRows = STEP / 4;
+  __device__ __forceinline__ void put(int side, int col, int rg, const double* x,
+                                      const double* wgt) {
+#pragma unroll
+    for (int q = 0; q < kRows; ++q)
+      v[side][rg * kRows + q][col] = Real(side == 0 ? wgt[q] * x[q] : x[q]);
   }
-  // row of register r of lane group g in the 16 x 16 result
-  static __device__ __forceinline__ int row(int g, int r) { return 4 * g + r; }
+  __device__ __forceinline__ static Acc mma(Real a, Real b, Acc c) {
+    if constexpr (sizeof(Real) == 4)
+      return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    else
+      return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  // row of register r of lane group g in the result (the FP64 one interleaves
+  // rows: measured on gfx950)
+  __device__ __forceinline__ static int row(int g, int r) {
+    return sizeof(Real) == 4 ? 4 * g + r : g + 4 * r;
+  }
+  struct Left {
+    Real a[2][kStep / 4];
+  };
+  __device__ __forceinline__ void left(Left& l, int i, int lane) const {
+    const int li = lane % 16, g = lane / 16;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int k = 0; k < kStep / 4; ++k) l.a[t][k] = v[0][4 * k + g][i + t * kTile + li];
+  }
+  __device__ __forceinline__ void unit(const Left& l, int j, int lane, Acc (&acc)[2]) const {
+    const int li = lane % 16, g = lane / 16;
+#pragma unroll
+    for (int k = 0; k < kStep / 4; ++k) {
+      const Real b = v[1][4 * k + g][j + li];
+      acc[0] = mma(l.a[0][k], b, acc[0]);
+      acc[1] = mma(l.a[1][k], b, acc[1]);
+    }
+  }
 };
 template <>
-struct MfmaAcc<double> {
-  using T = double4_t;
-  static __device__ __forceinline__ T mma(double a, double b, T c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  // the FP64 16x16x4 result interleaves rows (measured on gfx950)
-  static __device__ __forceinline__ int row(int g, int r) { return g + 4 * r; }
-};
+struct Operands<G3PCF_PREC_FP32> : PlainOperands<float, 32> {};
+template <>
+struct Operands<G3PCF_PREC_FP64> : PlainOperands<double, 16> {};
 
-template <typename Real>
-__global__ __launch_bounds__(256) void k_gram_mt(ZetaArgs z, MDims d, double* __restrict__ Cpart) {
-  constexpr int kPad = (sizeof(Real) == 4) ? 16 : 8;  // row stride off the bank period
-  __shared__ Real Xs[2][kKS][kMT + kPad];
-  __shared__ Real Ys[2][kKS][kMT + kPad];
-  using Acc = MfmaAcc<Real>;
-  using AT = typename Acc::T;
-
-  const int tid = threadIdx.x;
-  const int lane = tid % kWave, wv = tid / kWave;
-  const int s = blockIdx.y;
-  int m, ti, tj;
-  macro_tile_of(d, blockIdx.x, m, ti, tj);
-  const int W = d.W[m];
-  const bool diag = (ti == tj);
-  long long first;
-  const long long Kv = valid_rows(z, first), rows = block_rows(Kv, z.parts);
-  const long long r0 = s * rows;
-  const long long r1 = min(Kv, r0 + rows);
-  if (r0 >= r1) return;
-  const double* A = z.A + first * z.lay.W + d.off[m];
-  const int* plist = z.plist + z.row_begin + first;
-
-  // staging: thread -> (row srow, 8 columns from scol) of both column ranges
-  const int srow = tid / 8, scol = (tid % 8) * 8;
-  const int ci0 = ti * kMT + scol, cj0 = tj * kMT + scol;
-  double xr[8], yr[8], wr = 0.0;
-  auto load = [&](long long kb) {
-    const long long r = kb + srow;
-    const bool ok = r < r1;
-    wr = ok ? z.wsort[plist[r]] : 0.0;
-    const double* row = A + (ok ? r : r0) * (long long)z.lay.W;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      xr[c] = (ok && ci0 + c < W) ? row[ci0 + c] : 0.0;
-      if (!diag) yr[c] = (ok && cj0 + c < W) ? row[cj0 + c] : 0.0;
-    }
-  };
-  auto store = [&](int buf) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      Xs[buf][srow][scol + c] = Real(wr * xr[c]);
-      Ys[buf][srow][scol + c] = Real(diag ? xr[c] : yr[c]);
-    }
-  };
-
-  AT acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = AT{0, 0, 0, 0};
-  const int qi = (wv >> 1) * 32, qj = (wv & 1) * 32;
-  const int li = lane % 16, g = lane / 16;
-
-  // FP32 accumulation runs over kFlush rows at a time and is then added into
-  // FP64 accumulators (the FP64 form accumulates in FP64 throughout)
-  double4_t tot[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) tot[a][b] = double4_t{0.0, 0.0, 0.0, 0.0};
-  auto flush = [&]() {
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          tot[a][b][r] += double(acc[a][b][r]);
-          acc[a][b][r] = Real(0);
-        }
-  };
-
-  int buf = 0;
-  load(r0);
-  store(0);
-  __syncthreads();
-  for (long long kb = r0; kb < r1; kb += kKS) {
-    const bool more = kb + kKS < r1;
-    if constexpr (sizeof(Real) == 4) {
-      if (kb > r0 && (kb - r0) % kFlush == 0) flush();
-    }
-    if (more) load(kb + kKS);
-#pragma unroll
-    for (int k = 0; k < kKS; k += 4) {
-      const int kk = k + g;
-      Real xa[2], yb[2];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) xa[a] = Xs[buf][kk][qi + a * 16 + li];
-#pragma unroll
-      for (int b = 0; b < 2; ++b) yb[b] = Ys[buf][kk][qj + b * 16 + li];
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = Acc::mma(xa[a], yb[b], acc[a][b]);
-    }
-    if (more) store(buf ^ 1);
-    __syncthreads();
-    buf ^= 1;
-  }
-
-  flush();
-  double* C = Cpart + (long long)s * d.csize + d.cw[m];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = ti * kMT + qi + a * 16 + Acc::row(g, r);
-        const int j = tj * kMT + qj + b * 16 + li;
-        if (i < W && j < W) C[i * W + j] = tot[a][b][r];
-      }
-}
-
-// ---- BF16x3: the same macro tiles and blocks as k_gram_mt, with every FP32
-// operand x split as x0 + x1 + x2, each xk the round-to-nearest-even bfloat16
-// of what is left, and the six products with i + j <= 2 on the bfloat16
-// matrix cores (FP32 accumulation over kFlush rows, then FP64).  Wave w stages
-// rows 8w..8w+7 of each 32-row step, one column per lane: the eight values of
-// a column are split and written to LDS as one 16-byte vector per part, laid
-// out [column][row] so that an MFMA lane reads its eight rows of a column with
-// one load.  The rows' weights come from lanes 0..31 of each wave by readlane.
-constexpr int kBPad = 8;  // bf16 padding of a column's 32 rows (bank spread)
-
-__global__ __launch_bounds__(256) void k_gram_bf16x3_mt(ZetaArgs z, MDims d,
-                                                        double* __restrict__ Cpart) {
-  __shared__ bf16x8_t Xs[2][3][kMT][(kKS + kBPad) / 8];
-  __shared__ bf16x8_t Ys[2][3][kMT][(kKS + kBPad) / 8];
-  const int tid = threadIdx.x;
-  const int lane = tid % kWave;
-  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int s = blockIdx.y;
-  int m, ti, tj;
-  macro_tile_of(d, blockIdx.x, m, ti, tj);
-  const int W = d.W[m];
-  const bool diag = (ti == tj);
-  long long first;
-  const long long Kv = valid_rows(z, first), rows = block_rows(Kv, z.parts);
-  const long long r0 = s * rows;
-  const long long r1 = min(Kv, r0 + rows);
-  if (r0 >= r1) return;
-  const double* A = z.A + first * z.lay.W + d.off[m];
-  const int* plist = z.plist + z.row_begin + first;
-  const int ci = ti * kMT + lane, cj = tj * kMT + lane;
-
-  double xr[8], yr[8], wgt[8];
-  auto load = [&](long long kb) {
-    // lanes 0..31 fetch the step's weights; every lane takes its wave's 8
-    const long long rw = kb + lane;
-    const double wl = (lane < kKS && rw < r1) ? z.wsort[plist[rw]] : 0.0;
-    const long long wb = __double_as_longlong(wl);
-    const int wlo = int(wb & 0xffffffffll), whi = int(wb >> 32);
+// BF16x3: every FP32 operand x split as x0 + x1 + x2, each xk the
+// round-to-nearest-even bfloat16 of what is left, and the six products with
+// i + j <= 2 on the bfloat16 matrix cores.  [part][column][row], so that an MFMA
+// lane reads its eight rows of a column with one load.
+template <>
+struct Operands<G3PCF_PREC_BF16X3> {
+  using Acc = float4_t;
+  static constexpr int kStep = 32;
+  static constexpr int kRows = 8;
+  static constexpr int kPad = 8;  // bf16 padding of a column's 32 rows (bank spread)
+  bf16x8_t v[2][3][kPanel][(kStep + kPad) / 8];
+  __device__ __forceinline__ void put(int side, int col, int rg, const double* x,
+                                      const double* wgt) {
+    bf16x8_t p[3];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const int lo = __builtin_amdgcn_readlane(wlo, 8 * wv + q);
-      const int hi = __builtin_amdgcn_readlane(whi, 8 * wv + q);
-      wgt[q] = __longlong_as_double((static_cast<long long>(hi) << 32) |
-                                    static_cast<unsigned int>(lo));
-      const long long r = kb + 8 * wv + q;
-      const bool ok = r < r1;
-      const double* row = A + (ok ? r : r0) * (long long)z.lay.W;
-      xr[q] = (ok && ci < W) ? row[ci] : 0.0;
-      if (!diag) yr[q] = (ok && cj < W) ? row[cj] : 0.0;
-    }
-  };
-  auto split8 = [](const float v[8], bf16x8_t parts[3]) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      float rem = v[q];
+      float rem = float(side == 0 ? wgt[q] * x[q] : x[q]);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         const __bf16 h = static_cast<__bf16>(rem);
-        parts[k][q] = h;
+        p[k][q] = h;
         rem -= float(h);
       }
     }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[side][k][col][rg] = p[k];
+  }
+  __device__ __forceinline__ static int row(int g, int r) { return 4 * g + r; }
+  struct Left {
+    bf16x8_t a[2][3];
   };
-  auto store = [&](int buf) {
-    float xv[8], yv[8];
+  __device__ __forceinline__ void left(Left& l, int i, int lane) const {
+    const int li = lane % 16, g = lane / 16;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      xv[q] = float(wgt[q] * xr[q]);
-      yv[q] = float(diag ? xr[q] : yr[q]);
-    }
-    bf16x8_t xp[3], yp[3];
-    split8(xv, xp);
-    split8(yv, yp);
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      Xs[buf][k][lane][wv] = xp[k];
-      Ys[buf][k][lane][wv] = yp[k];
+      for (int k = 0; k < 3; ++k) l.a[t][k] = v[0][k][i + t * kTile + li][g];
+  }
+  __device__ __forceinline__ void unit(const Left& l, int j, int lane, Acc (&acc)[2]) const {
+    const int li = lane % 16, g = lane / 16;
+    const bf16x8_t y0 = v[1][0][j + li][g], y1 = v[1][1][j + li][g], y2 = v[1][2][j + li][g];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      float4_t c = acc[t];
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l.a[t][2], y0, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l.a[t][1], y1, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l.a[t][0], y2, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l.a[t][1], y0, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l.a[t][0], y1, c, 0, 0, 0);
+      acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l.a[t][0], y0, c, 0, 0, 0);
     }
+  }
+};
+
+template <int PREC, bool DIAG>
+__device__ __forceinline__ void gram_tile(const ZetaArgs& z, const MDims& d, Operands<PREC>* lds,
+                                          int m, int ti, int tj, int first, int r0, int r1,
+                                          double* __restrict__ C) {
+  using Op = Operands<PREC>;
+  using Acc = typename Op::Acc;
+  constexpr int kStep = Op::kStep, kRows = Op::kRows;
+  const int tid = threadIdx.x;
+  const int lane = tid % kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int W = d.W[m];
+  const double* A = z.A + (long long)first * z.lay.W + d.off[m];
+  const int* plist = z.plist + z.row_begin + first;
+
+  // staging: thread -> column tid % 128 of both panels, a quarter of the step's
+  // rows (the same for a whole wave, so the rows' weights come by readlane)
+  const int col = tid % kPanel, rg = __builtin_amdgcn_readfirstlane(tid / kPanel);
+  const int ci = min(ti * kPanel + col, W - 1), cj = min(tj * kPanel + col, W - 1);
+  // A step on its way: the thread's rows of both panels, and in lane r the weight
+  // of the step's row r.  Rows and columns past the end are read from the last one,
+  // so that no load hangs on a branch.
+  struct Stage {
+    double x[kRows], y[kRows], w;
+  };
+  auto index = [&](int kb) { return plist[min(kb + min(lane, kStep - 1), r1 - 1)]; };
+  auto load = [&](Stage& g, int kb, int idx) {
+    g.w = z.wsort[idx];
+#pragma unroll
+    for (int q = 0; q < kRows; ++q) {
+      const double* row = A + min(kb + kRows * rg + q, r1 - 1) * (long long)z.lay.W;
+      g.x[q] = row[ci];
+      if constexpr (!DIAG) g.y[q] = row[cj];
+    }
+  };
+  auto store = [&](Stage& g, int kb, int buf) {
+    const long long wb = __double_as_longlong(g.w);
+    const int wlo = int(wb & 0xffffffffll), whi = int(wb >> 32);
+    double wgt[kRows];
+#pragma unroll
+    for (int q = 0; q < kRows; ++q) {
+      const int lo = __builtin_amdgcn_readlane(wlo, kRows * rg + q);
+      const int hi = __builtin_amdgcn_readlane(whi, kRows * rg + q);
+      wgt[q] = __longlong_as_double((static_cast<long long>(hi) << 32) |
+                                    static_cast<unsigned int>(lo));
+    }
+    if (kb + kStep > r1) {
+#pragma unroll
+      for (int q = 0; q < kRows; ++q)
+        if (kb + kRows * rg + q >= r1) {
+          g.x[q] = wgt[q] = 0.0;
+          if constexpr (!DIAG) g.y[q] = 0.0;
+        }
+    }
+    lds[buf].put(0, col, rg, g.x, wgt);
+    if constexpr (DIAG)
+      lds[buf].put(1, col, rg, g.x, wgt);
+    else
+      lds[buf].put(1, col, rg, g.y, wgt);
   };
 
-  float4_t acc[2][2];
-  double4_t tot[2][2];
+  // this wave's units: pairs of tile rows (strips), the tiles of a strip from the
+  // diagonal on (diagonal macro tiles) or all
+  const int nti = (min(W - ti * kPanel, kPanel) + kTile - 1) / kTile;
+  const int ntj = (min(W - tj * kPanel, kPanel) + kTile - 1) / kTile;
+  int total = 0;
+  for (int i = 0; i < nti; i += 2) total += DIAG ? ntj - i : ntj;
+  const int per = (total + kGramWaves - 1) / kGramWaves;  // <= kUnits
+  int ui[kUnits], uj[kUnits];
+  {
+    int i = 0, j = wv * per;  // j: units to skip, then the column within strip i
+    while (i < nti && j >= (DIAG ? ntj - i : ntj)) {
+      j -= DIAG ? ntj - i : ntj;
+      i += 2;
+    }
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int u = 0; u < kUnits; ++u) {
+      const bool on = u < per && wv * per + u < total;
+      ui[u] = on ? i : -1;
+      uj[u] = on ? j + (DIAG ? i : 0) : 0;
+      if (on && ++j >= (DIAG ? ntj - i : ntj)) {
+        j = 0;
+        i += 2;
+      }
+    }
+  }
+
+  Acc acc[kUnits][2];
+  double4_t tot[kUnits][2];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      acc[a][b] = float4_t{0.f, 0.f, 0.f, 0.f};
-      tot[a][b] = double4_t{0.0, 0.0, 0.0, 0.0};
+  for (int u = 0; u < kUnits; ++u)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      acc[u][t] = Acc{0, 0, 0, 0};
+      tot[u][t] = double4_t{0.0, 0.0, 0.0, 0.0};
     }
   auto flush = [&]() {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int u = 0; u < kUnits; ++u)
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          tot[a][b][r] += double(acc[a][b][r]);
-          acc[a][b][r] = 0.f;
+          tot[u][t][r] += double(acc[u][t][r]);
+          acc[u][t][r] = 0;
         }
   };
-  const int qi = (wv >> 1) * 32, qj = (wv & 1) * 32;
-  const int li = lane % 16, g = lane / 16;
 
-  int buf = 0;
-  load(r0);
-  store(0);
+  auto products = [&](int kb, int buf) {
+    if constexpr (PREC != G3PCF_PREC_FP64) {
+      if (kb > r0 && (kb - r0) % kFlush == 0) flush();
+    }
+    typename Op::Left l;
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+      if (ui[u] < 0) continue;
+      if (u == 0 || ui[u] != ui[u > 0 ? u - 1 : 0]) lds[buf].left(l, ui[u] * kTile, lane);
+      lds[buf].unit(l, uj[u] * kTile, lane, acc[u]);
+    }
+  };
+
+  // Two steps in flight besides the one in LDS: `even` and `odd` hold those of
+  // their parity, and a step's row numbers are read a step before its rows.
+  Stage even, odd;
+  const int idx0 = index(r0), idx1 = index(r0 + kStep);
+  int idx = index(r0 + 2 * kStep);
+  load(even, r0, idx0);
+  load(odd, r0 + kStep, idx1);
+  store(even, r0, 0);
   __syncthreads();
-  for (long long kb = r0; kb < r1; kb += kKS) {
-    const bool more = kb + kKS < r1;
-    if (kb > r0 && (kb - r0) % kFlush == 0) flush();
-    if (more) load(kb + kKS);
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const bf16x8_t x0 = Xs[buf][0][qi + a * 16 + li][g], x1 = Xs[buf][1][qi + a * 16 + li][g],
-                       x2 = Xs[buf][2][qi + a * 16 + li][g];
-        const bf16x8_t y0 = Ys[buf][0][qj + b * 16 + li][g], y1 = Ys[buf][1][qj + b * 16 + li][g],
-                       y2 = Ys[buf][2][qj + b * 16 + li][g];
-        float4_t c = acc[a][b];
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x2, y0, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, y1, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, y2, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, y0, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, y1, c, 0, 0, 0);
-        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, y0, c, 0, 0, 0);
-      }
-    if (more) store(buf ^ 1);
+  for (int kb = r0;; kb += 2 * kStep) {
+    const int next = index(kb + 3 * kStep);
+    load(even, kb + 2 * kStep, idx);
+    products(kb, 0);
+    if (kb + kStep >= r1) break;
+    store(odd, kb + kStep, 1);
     __syncthreads();
-    buf ^= 1;
+    idx = index(kb + 4 * kStep);
+    load(odd, kb + 3 * kStep, next);
+    products(kb + kStep, 1);
+    if (kb + 2 * kStep >= r1) break;
+    store(even, kb + 2 * kStep, 0);
+    __syncthreads();
   }
-
   flush();
-  double* C = Cpart + (long long)s * d.csize + d.cw[m];
+  const int li = lane % 16, g = lane / 16;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int u = 0; u < kUnits; ++u) {
+    if (ui[u] < 0) continue;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = ti * kMT + qi + a * 16 + 4 * g + r;
-        const int j = tj * kMT + qj + b * 16 + li;
-        if (i < W && j < W) C[i * W + j] = tot[a][b][r];
+        const int i = ti * kPanel + (ui[u] + t) * kTile + Op::row(g, r);
+        const int j = tj * kPanel + uj[u] * kTile + li;
+        if (i < W && j < W) C[i * W + j] = tot[u][t][r];
       }
+  }
+}
+
+// Workgroups are numbered macro tile by macro tile, widest first, within chunks of
+// at most kChunkMost blocks: the last workgroups of a launch are small ones, and the
+// macro tiles of one m, which share panels, run close together.
+constexpr int kChunkMost = 64;
+
+template <int PREC>
+__global__ __launch_bounds__(kGramThreads) void k_gram(ZetaArgs z, MDims d,
+                                                       double* __restrict__ Cpart, int chunk) {
+  __shared__ Operands<PREC> lds[2];
+  const int tiles = d.mt[d.nm];
+  const int t = int(blockIdx.x) / chunk;
+  const int blk = t / tiles * chunk + int(blockIdx.x) % chunk;
+  const GramBlocks g = gram_blocks(z);
+  const unsigned long long past = __ballot(g.end > blk);
+  if (!past) return;
+  const int r = __builtin_ctzll(past);  // the block's list part
+  const int rows = __builtin_amdgcn_readlane(g.rows, r);
+  const int r0 = (blk - __builtin_amdgcn_readlane(g.begin, r)) * rows;
+  const int r1 = min(__builtin_amdgcn_readlane(g.count, r), r0 + rows);
+  const int first = __builtin_amdgcn_readlane(g.first, r);
+  int m, ti, tj;
+  macro_tile_of(d, t % tiles, m, ti, tj);
+  double* C = Cpart + (long long)blk * d.csize + d.cw[m];
+  if (ti == tj)
+    gram_tile<PREC, true>(z, d, lds, m, ti, tj, first, r0, r1, C);
+  else
+    gram_tile<PREC, false>(z, d, lds, m, ti, tj, first, r0, r1, C);
 }
 
 // zeta[m][l][l'][b1][b2] += sum over the pair-block's blocks (in order, FP64)
-// of the block Gram products.  Only macro tiles on or above the diagonal are
-// stored; C_m is symmetric.  One workgroup per 16 x 16 tile of one m's (l, b1)
+// of the block Gram products.  Only tiles on or above the diagonal are read;
+// C_m is symmetric.  One workgroup per 16 x 16 tile of one m's (l, b1)
 // x (l', b2) entries, so that the partials are read in 128-byte pieces whether
-// an entry is stored as it is or transposed; only the blocks that hold primaries
-// are read.  Reading the partials bounds it: 166,100 doubles per block (lmax 10,
+// an entry is stored as it is or transposed, and list part; only the part's
+// blocks are read.  Reading the partials bounds it: 166,100 doubles per block (lmax 10,
 // 10 shells).
 constexpr int kAT = 16;
 
@@ -398,7 +465,7 @@ __global__ __launch_bounds__(kAT * kAT) void k_zeta_accum_mt(ZetaArgs z, MDims d
   const RowLayout& L = z.lay;
   const int nb = L.nb, nm = L.lmax + 1;
   // the pair kernel's next launch starts from cleared counters
-  if (blockIdx.x == 0 && threadIdx.x < kQueueAdjoint * kQueues)
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kQueueAdjoint * kQueues)
     z.queue[threadIdx.x / kQueueAdjoint * kQueueStride + threadIdx.x % kQueueAdjoint] = 0;
   int t = blockIdx.x, m = 0;
   for (; m < nm; ++m) {
@@ -408,14 +475,13 @@ __global__ __launch_bounds__(kAT * kAT) void k_zeta_accum_mt(ZetaArgs z, MDims d
   }
   const int dm = L.d[m], nt = (dm + kAT - 1) / kAT, nl = nm - m;
   const int P = (t / nt) * kAT + int(threadIdx.x) / kAT, Pp = (t % nt) * kAT + int(threadIdx.x) % kAT;
-  long long first;
-  const long long Kv = valid_rows(z, first);
-  if (P >= dm || Pp >= dm || Kv == 0) return;
-  const long long rows = block_rows(Kv, z.parts);
-  const int nsub = int((Kv + rows - 1) / rows);
+  const GramBlocks g = gram_blocks(z);
+  const int begin = __builtin_amdgcn_readlane(g.begin, blockIdx.y);
+  const int nsub = __builtin_amdgcn_readlane(g.end, blockIdx.y) - begin;
+  if (P >= dm || Pp >= dm || nsub == 0) return;
   const int W = d.W[m];
   auto at = [&](int i, int j) {
-    if (i / kMT > j / kMT) {
+    if (i / kTile > j / kTile) {
       const int x = i;
       i = j;
       j = x;
@@ -427,7 +493,7 @@ __global__ __launch_bounds__(kAT * kAT) void k_zeta_accum_mt(ZetaArgs z, MDims d
   const int iQQ = (m > 0) ? at(Q, Qp) : 0, iQP = (m > 0) ? at(Q, Pp) : 0,
             iPQ = (m > 0) ? at(P, Qp) : 0;
   double re = 0.0, im = 0.0;
-  const double* c = z.C64;
+  const double* c = z.C64 + (long long)begin * d.csize;
   if (m == 0) {
 #pragma unroll 4
     for (int s = 0; s < nsub; ++s, c += d.csize) re += c[iPP];
@@ -439,6 +505,7 @@ __global__ __launch_bounds__(kAT * kAT) void k_zeta_accum_mt(ZetaArgs z, MDims d
     }
   }
   const int l = m + P % nl, b1 = P / nl, lp = m + Pp % nl, b2 = Pp / nl;
+  zeta += 2LL * nm * nm * nm * nb * nb * blockIdx.y;
   double* o = zeta + ((((long long)m * nm + l) * nm + lp) * nb + b1) * (2LL * nb) + 2 * b2;
   o[0] += re;
   o[1] += im;
@@ -470,13 +537,14 @@ RowLayout make_layout(int lmax, int nb) {
 
 // Partials of a pair-block of at most PB primaries.  4096 rows a block keep the
 // partials few where there are many rows; a small pair-block is cut into more,
-// until the macro tiles times the blocks give every CU about five workgroups
-// (a tile's 4096 rows are one serial chain of 128 steps: the Gram products of 16
-// catalogues of 8192 took 4.55 ms in blocks of 4096 rows and take 1.20 ms in 32
-// blocks; 27 regions of 3700 primaries 6.97 and 1.02 ms).
+// until the macro tiles times the blocks give every CU, which holds one workgroup
+// at a time, about two (a tile's 4096 rows are one serial chain of 128 steps: the
+// Gram products of 16 catalogues of 8192 took 4.55 ms in blocks of 4096 rows and take
+// 0.91 ms in 27; three or six workgroups a CU 3 to 8% more of the whole call, and
+// the sum over the blocks grows with them).
 int zeta_parts(const RowLayout& L, long long PB) {
   const long long tiles = make_mdims(L).mt[L.lmax + 1];
-  const long long fill = (5 * 256 + tiles - 1) / tiles;
+  const long long fill = (2 * 256 + tiles - 1) / tiles;
   const long long least = (PB + kZetaBlock - 1) / kZetaBlock;
   return int(std::max(least, std::min(fill, (PB + kZetaRowsMin - 1) / kZetaRowsMin)));
 }
@@ -485,16 +553,19 @@ int zeta_parts(const RowLayout& L, long long PB) {
 hipError_t launch_zeta_pairblock(const ZetaArgs& z, hipStream_t st) {
   const MDims d = make_mdims(z.lay);
   if (z.K <= 0) return hipSuccess;
-  // at most `parts` blocks, each of at least kZetaRowsMin rows
-  const long long nsub =
-      std::min<long long>(z.parts, (z.K + kZetaRowsMin - 1) / kZetaRowsMin);
-  const dim3 grid(unsigned(d.mt[d.nm]), unsigned(nsub));
+  // at most `parts` blocks, each of at least kZetaRowsMin rows but a list part's last
+  const long long blocks = std::min<long long>(
+      z.parts, (z.K + kZetaRowsMin - 1) / kZetaRowsMin + z.lists - 1);
+  const long long chunks = (blocks + kChunkMost - 1) / kChunkMost;
+  const int chunk = int((blocks + chunks - 1) / chunks);
+  const dim3 grid(unsigned(chunks * chunk * d.mt[d.nm]));
+  const dim3 block(kGramThreads);
   if (z.prec == G3PCF_PREC_FP32)
-    hipLaunchKernelGGL((k_gram_mt<float>), grid, dim3(256), 0, st, z, d, z.C64);
+    hipLaunchKernelGGL(k_gram<G3PCF_PREC_FP32>, grid, block, 0, st, z, d, z.C64, chunk);
   else if (z.prec == G3PCF_PREC_BF16X3)
-    hipLaunchKernelGGL(k_gram_bf16x3_mt, grid, dim3(256), 0, st, z, d, z.C64);
+    hipLaunchKernelGGL(k_gram<G3PCF_PREC_BF16X3>, grid, block, 0, st, z, d, z.C64, chunk);
   else
-    hipLaunchKernelGGL((k_gram_mt<double>), grid, dim3(256), 0, st, z, d, z.C64);
+    hipLaunchKernelGGL(k_gram<G3PCF_PREC_FP64>, grid, block, 0, st, z, d, z.C64, chunk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   unsigned ab = 0;
@@ -502,7 +573,7 @@ hipError_t launch_zeta_pairblock(const ZetaArgs& z, hipStream_t st) {
     const unsigned nt = unsigned((z.lay.d[m] + kAT - 1) / kAT);
     ab += nt * nt;
   }
-  hipLaunchKernelGGL(k_zeta_accum_mt, dim3(ab), dim3(kAT * kAT), 0, st, z, d, z.zeta);
+  hipLaunchKernelGGL(k_zeta_accum_mt, dim3(ab, unsigned(z.lists)), dim3(kAT * kAT), 0, st, z, d, z.zeta);
   return hipGetLastError();
 }
 

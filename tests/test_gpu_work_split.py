@@ -1,4 +1,4 @@
-"""How the work is cut up must not change the results: Gram blocks of few rows.
+"""How the work is cut up must not change the results.
 FP64 against the oracle (1e-10 of max|zeta|); the FP32 and BF16x3 zeta stages
 against the FP64 zeta stage on the same FP32 pairs (1e-5)."""
 import sys
@@ -178,3 +178,47 @@ def test_regions_in_one_pass(dev, n, nregions, distinct):
     e = np.abs(z.sum(0) - every).max() / max(np.abs(every).max(), 1e-300)
     say(f"  sum over regions: {e:.2e}")
     assert e <= 1e-10
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("lmax,nbins", [(0, 1), (0, 16), (0, 17), (0, 32), (1, 8), (3, 32),
+                                        (9, 13), (10, 6), (10, 32)])
+def test_gram_macro_tiles_of_any_width(dev, precision, lmax, nbins):
+    """Blocks C_m of 1 to 640 columns: one tile, one past a tile, an odd number of
+    tiles, exactly one panel of 128, one past it, several."""
+    say(f"case gram widths lmax={lmax} nbins={nbins} {precision}")
+    cat = C.uniform(300, 100.0, seed=73, dtype=np.float64, weights="uniform", rmax=45.0,
+                    nbins=nbins, lmax=lmax)
+    pos, w = on(dev, cat)
+    z = api.zeta(pos, w, cfg_of(cat, precision)).cpu().numpy()
+    if precision == "fp64":
+        ref = oracle.zeta(cat)
+    else:
+        ref = api.zeta(pos, w, cfg_of(cat, precision, zeta_precision="fp64")).cpu().numpy()
+    e = np.abs(z - ref).max() / np.abs(ref).max()
+    say(f"  max|dz|/max|z| = {e:.2e}")
+    assert e <= TOL[precision]
+
+
+@pytest.mark.parametrize("nregions", [2, 40, 70])
+def test_regions_of_very_different_sizes(dev, nregions):
+    """One region holds nearly all galaxies (many Gram blocks), others a few or
+    none; more regions than one launch of the Gram products takes.  FP64, 1e-10 of
+    the largest zeta."""
+    say(f"case uneven regions {nregions}")
+    n = 4000
+    cat = C.uniform(n, 250.0, seed=75, dtype=np.float64, weights="uniform", rmax=30.0, nbins=4,
+                    lmax=4)
+    rng = np.random.default_rng(76)
+    region = np.full(n, nregions // 2, dtype=np.int32)
+    few = rng.choice(n, size=600, replace=False)
+    region[few] = rng.integers(0, nregions, size=600)
+    region[region == nregions - 1] = 0  # the last one holds none
+    pos, w = on(dev, cat)
+    z = api.zeta_regions(pos, w, cfg_of(cat, "fp64"), torch.from_numpy(region).to(dev),
+                         nregions).cpu().numpy()
+    scale = np.abs(z).max()
+    for r in sorted({0, nregions // 2, nregions - 2, nregions - 1}):
+        ref = oracle.zeta(cat, primary_mask=(region == r).astype(np.uint8))
+        assert np.abs(z[r] - ref).max() <= 1e-10 * scale, r
+    assert not z[nregions - 1].any()
