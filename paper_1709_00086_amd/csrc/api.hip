@@ -214,9 +214,12 @@ static_assert(sizeof(XcdCounters) == kQueueStride * 4, "one line each");
 struct Counters {
   long long nprim;
   unsigned long long inputs_hash;  // backward: fingerprint of its inputs (a_lm store check)
-  long long pad[6];
+  long long first;                 // first row among its group's (catalogues of a batch)
+  long long pad[5];
   XcdCounters xcd[kQueues];
 };
+static_assert(sizeof(Counters) == kCatStride * 8 && offsetof(Counters, first) == kCatFirst * 8,
+              "head of a catalogue of a group");
 static_assert(sizeof(Counters) <= kCountersBytes, "counters block");
 
 CellBufs cell_bufs(const Ws& w, void* ws) {
@@ -422,6 +425,15 @@ int forward_tables(const g3pcf_problem& p) {
   return rc;
 }
 
+// List parts of `n` that one launch of the Gram products takes: so many that each
+// has four blocks of partials on average (16 catalogues of 8192: 4.08 ms of the
+// whole call with two, 3.67 with three or four, 3.70 with eight).
+int lists_at_once(const Ws& w, int n) {
+  const int most = std::max(1, std::min(kZetaLists, w.parts / 4));
+  const int launches = (n + most - 1) / most;
+  return (n + launches - 1) / launches;
+}
+
 // The pair-blocks of the current primary list (at most `cover` primaries):
 // pair kernel, Gram products into zeta, and (distinct) the degenerate-triangle
 // pass and its correction.  rows: where the a_lm rows go (NULL: the
@@ -461,10 +473,7 @@ int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, i
       z.parts = w.parts;
       z.prec = p.zeta_prec;
       z.queue = a.queue;
-      // as many list parts at a time as leave each two blocks of partials on average
-      const int most = std::max(1, std::min(kZetaLists, w.parts / 2));
-      const int launches = (nparts + most - 1) / most;
-      const int lists = (nparts + launches - 1) / launches;
+      const int lists = lists_at_once(w, nparts);
       for (int r = 0; r < nparts; r += lists) {
         z.range = starts ? starts + r : nullptr;
         z.lists = std::min(lists, nparts - r);
@@ -495,6 +504,107 @@ int forward_pairs(const g3pcf_problem& p, const Ws& w, void* ws, double* zeta, i
           return hip_fail(e, "degenerate-triangle correction");
       }
     }
+  }
+  return G3PCF_OK;
+}
+
+// The problem of one catalogue of a batch.
+g3pcf_problem catalogue_of(const g3pcf_problem& p, int64_t first, int64_t n) {
+  g3pcf_problem q = p;
+  q.n = n;
+  q.pos = static_cast<const char*>(p.pos) + size_t(first) * (p.pos_dtype == G3PCF_F32 ? 12 : 24);
+  q.w = p.w + first;
+  q.primary_mask = p.primary_mask ? p.primary_mask + first : nullptr;
+  return q;
+}
+
+// How many catalogues from c on go through forward_group together (in cats; 0 or
+// 1: not in a group): small ones, whose rows, cell starts and heads the workspace
+// of the whole call holds beside each other.  Not where the counts are asked for
+// (a wait per catalogue) or the degenerate triangles are taken out.
+int batch_group(const g3pcf_problem& p, const Ws& w, const int64_t* offsets, int ncat, int c,
+                BatchCat* cats) {
+  if (p.pairs_out || p.distinct) return 0;
+  const int64_t cells = int64_t(w.cell_count - w.cell_start) / 4 + w.grid.ncell + 1;
+  const int64_t heads = int64_t(2 * radix_hist_ints(p.n)) * 4 / int64_t(sizeof(Counters));
+  const int most = int(std::min<int64_t>({kBatchGroup, heads, ncat - c}));
+  int m = 0;
+  int64_t at = 0;
+  for (; m < most; ++m) {
+    BatchCat& k = cats[m];
+    k.first = offsets[c + m];
+    k.n = offsets[c + m + 1] - k.first;
+    k.cells_at = at;
+    if (k.n > kBatchN || k.first + k.n - cats[0].first > w.PB) break;
+    k.grid = make_grid(catalogue_of(p, k.first, k.n));
+    at += k.grid.ncell + 1;
+    if (k.grid.ncell > 4 * kBatchN || at > cells) break;
+  }
+  return m;
+}
+
+// zeta of a group of a batch's catalogues: one launch of the cell stage, their pair
+// kernels, and one of the Gram products.  w: the plan of the whole call, whose
+// per-galaxy buffers the catalogues share out as the galaxies lie.
+int forward_group(const g3pcf_problem& p, const Ws& w, void* ws, const BatchCat* cats, int m,
+                  double* zeta, hipStream_t st) {
+  const int fp64 = (p.pair_prec == G3PCF_PREC_FP64);
+  const int64_t base = cats[0].first, rows = cats[m - 1].first + cats[m - 1].n - base;
+  if (rows == 0) return G3PCF_OK;
+  hipError_t e;
+  Counters* head = at<Counters>(ws, w.rhist);
+  int* plist = at<int>(ws, w.plist);
+  {
+    StageScope sc(p.trace, G3PCF_STAGE_CELLS, st);
+    if ((e = launch_cells_batch(p, cats, m, cell_bufs(w, ws), at<int>(ws, w.flags), plist,
+                                &head->nprim, fp64, st)) != hipSuccess)
+      return hip_fail(e, "cell lists of a batch");
+  }
+  PairArgs a{};
+  {
+    StageScope sc(p.trace, G3PCF_STAGE_PAIRS, st);
+    for (int c = 0; c < m; ++c) {
+      const BatchCat& k = cats[c];
+      if (k.n == 0) continue;
+      Ws v = w;
+      v.grid = k.grid;
+      v.pos4 += size_t(k.first) * (fp64 ? 32 : 16);
+      v.cell_start += size_t(k.cells_at) * 4;
+      v.perm += size_t(k.first) * 4;
+      v.plist += size_t(k.first) * 4;
+      v.flags += size_t(k.first) * 4;
+      v.wsort += size_t(k.first) * 8;
+      v.A += size_t(k.first - base) * w.lay.W * 8;
+      v.counters = w.rhist + size_t(c) * sizeof(Counters);
+      a = PairArgs{};
+      if (int rc = pair_args(catalogue_of(p, k.first, k.n), v, ws, a)) return rc;
+      a.sentinel = int(p.n - k.first);
+      a.p_begin = 0;
+      a.p_count = k.n;
+      a.pairs = nullptr;
+      if ((e = launch_pair_forward(a, fp64, p.basis, false, st)) != hipSuccess)
+        return hip_fail(e, "pair kernel");
+    }
+  }
+  StageScope sc(p.trace, G3PCF_STAGE_ZETA, st);
+  ZetaArgs z{};
+  z.A = at<double>(ws, w.A);
+  z.wsort = at<double>(ws, w.wsort) + base;
+  z.plist = plist + base;
+  z.row_begin = 0;
+  z.lay = w.lay;
+  z.C64 = at<double>(ws, w.C);
+  z.parts = w.parts;
+  z.prec = p.zeta_prec;
+  z.queue = head->xcd[0].queue;
+  const size_t zlen = g3pcf_zeta_len(p.lmax, p.nbins);
+  const int lists = lists_at_once(w, m);
+  for (int c = 0; c < m; c += lists) {
+    z.lists = std::min(lists, m - c);
+    z.cats = &head[c].nprim;
+    z.zeta = zeta + zlen * size_t(c);
+    z.K = cats[c + z.lists - 1].first + cats[c + z.lists - 1].n - cats[c].first;
+    if ((e = launch_zeta_pairblock(z, st)) != hipSuccess) return hip_fail(e, "zeta");
   }
   return G3PCF_OK;
 }
@@ -756,17 +866,20 @@ int g3pcf_forward_batch(const g3pcf_problem* prob, int ncat, const int64_t* offs
   if (!p.accumulate &&
       (e = launch_fill_double(zeta, int64_t(zlen) * ncat, 0.0, st)) != hipSuccess)
     return hip_fail(e, "zeta clear");
-  const size_t pos_row = (p.pos_dtype == G3PCF_F32 ? 4 : 8) * 3;
   int64_t total = 0;
-  // one catalogue after another in the same workspace, in stream order (no
-  // host synchronisation unless pairs_out asks for the counts)
+  // one group or catalogue after another in the same workspace, in stream order
+  // (no host synchronisation unless pairs_out asks for the counts)
+  const Ws all = plan(p, 0);
   for (int c = 0; c < ncat; ++c) {
-    g3pcf_problem q = p;
-    q.n = offsets[c + 1] - offsets[c];
+    BatchCat cats[kBatchGroup];
+    const int m = batch_group(p, all, offsets, ncat, c, cats);
+    if (m > 1) {
+      if ((rc = forward_group(p, all, ws, cats, m, zeta + zlen * size_t(c), st))) return rc;
+      c += m - 1;
+      continue;
+    }
+    g3pcf_problem q = catalogue_of(p, offsets[c], offsets[c + 1] - offsets[c]);
     if (q.n == 0) continue;
-    q.pos = static_cast<const char*>(p.pos) + size_t(offsets[c]) * pos_row;
-    q.w = p.w + offsets[c];
-    q.primary_mask = p.primary_mask ? p.primary_mask + offsets[c] : nullptr;
     int64_t pairs_c = 0;
     q.pairs_out = p.pairs_out ? &pairs_c : nullptr;
     const Ws w = plan(q, 0);

@@ -296,24 +296,28 @@ struct SmallOut {
   int counter_words;
 };
 
-template <typename Real, typename In>
-__global__ __launch_bounds__(kSmallThreads) void k_cells_small(
-    const In* __restrict__ pos, const double* __restrict__ w, int n, GridDev g,
-    const uint8_t* __restrict__ mask, typename Vec4<Real>::T* stage4,
-    typename Vec4<Real>::T* __restrict__ pos4, SmallOut o, Clears z) {
+template <int N>
+struct SmallLds {
+  unsigned short key[N];
+  unsigned short val[2][N];
+  unsigned short hist[kSmallWaves][kRadixDigits];  // then running offsets
+  int wtot[kSmallWaves];
+};
+
+// One workgroup's catalogue of n <= N galaxies; the NaN entries go to nan4.
+template <typename Real, typename In, int N>
+__device__ __forceinline__ void cells_small(SmallLds<N>& lds, const In* __restrict__ pos,
+                                            const double* __restrict__ w, int n, const GridDev& g,
+                                            const uint8_t* __restrict__ mask,
+                                            typename Vec4<Real>::T* stage4,
+                                            typename Vec4<Real>::T* __restrict__ pos4,
+                                            typename Vec4<Real>::T* nan4, const SmallOut& o) {
   using V4 = typename Vec4<Real>::T;
-  __shared__ unsigned short key[kSmallN];
-  __shared__ unsigned short val[2][kSmallN];
-  __shared__ unsigned short hist[kSmallWaves][kRadixDigits];  // then running offsets
-  __shared__ int wtot[kSmallWaves];
+  auto& key = lds.key;
+  auto& val = lds.val;
+  auto& hist = lds.hist;
+  auto& wtot = lds.wtot;
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  if (blockIdx.x > 0) {
-    const int64_t t = int64_t(blockIdx.x - 1) * kSmallThreads + tid;
-    const int64_t step = int64_t(gridDim.x - 1) * kSmallThreads;
-    for (int k = 0; k < z.count; ++k)
-      for (int64_t i = t; i < z.words[k]; i += step) z.at[k][i] = 0;
-    return;
-  }
   for (int i = tid; i < o.counter_words; i += kSmallThreads) o.counters[i] = 0;
   for (int i = tid; i < n; i += kSmallThreads) {
     int c;
@@ -400,7 +404,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_cells_small(
       o.wsort[s] = w[i];
     } else {
       const Real nan = Real(__builtin_nan(""));
-      pos4[s] = V4{nan, nan, nan, nan};
+      nan4[s - n] = V4{nan, nan, nan, nan};
     }
   }
   // cell_start[c] = galaxies in cells below c; a run of cells per thread, the
@@ -449,6 +453,46 @@ __global__ __launch_bounds__(kSmallThreads) void k_cells_small(
     __syncthreads();
   }
   if (tid == 0) *o.nprim = base;
+}
+
+template <typename Real, typename In>
+__global__ __launch_bounds__(kSmallThreads) void k_cells_small(
+    const In* __restrict__ pos, const double* __restrict__ w, int n, GridDev g,
+    const uint8_t* __restrict__ mask, typename Vec4<Real>::T* stage4,
+    typename Vec4<Real>::T* __restrict__ pos4, SmallOut o, Clears z) {
+  __shared__ SmallLds<kSmallN> lds;
+  if (blockIdx.x > 0) {
+    const int64_t t = int64_t(blockIdx.x - 1) * kSmallThreads + threadIdx.x;
+    const int64_t step = int64_t(gridDim.x - 1) * kSmallThreads;
+    for (int k = 0; k < z.count; ++k)
+      for (int64_t i = t; i < z.words[k]; i += step) z.at[k][i] = 0;
+    return;
+  }
+  cells_small<Real, In>(lds, pos, w, n, g, mask, stage4, pos4, pos4 + n, o);
+}
+
+// A workgroup per catalogue of a batch.
+struct BatchGrids {
+  GridDev g[kBatchGroup];
+  int first[kBatchGroup], n[kBatchGroup], ncell[kBatchGroup], cells_at[kBatchGroup];
+};
+static_assert(sizeof(BatchGrids) + sizeof(SmallOut) <= 3584, "kernel arguments");
+
+template <typename Real, typename In>
+__global__ __launch_bounds__(kSmallThreads) void k_cells_batch(
+    const In* __restrict__ pos, const double* __restrict__ w, BatchGrids b,
+    const uint8_t* __restrict__ mask, typename Vec4<Real>::T* stage4,
+    typename Vec4<Real>::T* __restrict__ pos4, typename Vec4<Real>::T* nan4, SmallOut o) {
+  __shared__ SmallLds<kBatchN> lds;
+  const int c = blockIdx.x;
+  const int at = b.first[c];
+  SmallOut oc{o.perm + at,  o.wsort + at, o.cell_start + b.cells_at[c], b.ncell[c],
+              o.flags + at, o.plist + at, o.nprim + c * kCatStride,
+              o.counters + c * kCatStride * 2, kCatStride * 2};
+  cells_small<Real, In>(lds, pos + 3 * int64_t(at), w + at, b.n[c], b.g[c],
+                        mask ? mask + at : nullptr, stage4 + at, pos4 + at, nan4, oc);
+  // (after the barriers that follow the counters' clear)
+  if (threadIdx.x == 0) oc.nprim[kCatFirst] = at - b.first[0];
 }
 
 __global__ void k_fill_int(int* p, int64_t count, int value) {
@@ -681,9 +725,7 @@ static hipError_t radix_sort(const CellBufs& b, int64_t n, int64_t bound, int* o
   return hipSuccess;
 }
 
-hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b,
-                        const Primaries& pr, Clears z, int fp64, hipStream_t st) {
-  const int64_t n = p.n;
+static GridDev grid_dev(const Grid& g) {
   GridDev gd;
   for (int a = 0; a < 3; ++a) {
     gd.nc[a] = g.nc[a];
@@ -692,6 +734,44 @@ hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b
     gd.L[a] = g.L[a];
   }
   gd.periodic = g.periodic;
+  return gd;
+}
+
+hipError_t launch_cells_batch(const g3pcf_problem& p, const BatchCat* cats, int ncat,
+                              const CellBufs& b, int* flags, int* plist, long long* head,
+                              int fp64, hipStream_t st) {
+  BatchGrids bg{};
+  for (int c = 0; c < ncat; ++c) {
+    bg.g[c] = grid_dev(cats[c].grid);
+    bg.first[c] = int(cats[c].first);
+    bg.n[c] = int(cats[c].n);
+    bg.ncell[c] = int(cats[c].grid.ncell);
+    bg.cells_at[c] = int(cats[c].cells_at);
+  }
+  SmallOut o{b.perm, b.wsort, b.cell_start, 0, flags, plist, head, reinterpret_cast<int*>(head), 0};
+  auto go = [&](auto real, auto in) {
+    using Real = decltype(real);
+    using In = decltype(in);
+    using V = typename Vec4<Real>::T;
+    V* pos4 = static_cast<V*>(b.pos4);
+    hipLaunchKernelGGL((k_cells_batch<Real, In>), dim3(unsigned(ncat)), dim3(kSmallThreads), 0,
+                       st, static_cast<const In*>(p.pos), p.w, bg, p.primary_mask,
+                       static_cast<V*>(b.stage4), pos4, pos4 + p.n, o);
+  };
+  if (fp64) {
+    if (p.pos_dtype == G3PCF_F64) go(double(), double());
+    else go(double(), float());
+  } else {
+    if (p.pos_dtype == G3PCF_F64) go(float(), double());
+    else go(float(), float());
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b,
+                        const Primaries& pr, Clears z, int fp64, hipStream_t st) {
+  const int64_t n = p.n;
+  const GridDev gd = grid_dev(g);
   // n <= kSmallN galaxies: one launch (the grid has at most 4 n cells)
   if (n > 0 && n <= kSmallN && g.ncell <= 4 * kSmallN) {
     SmallOut o{b.perm, b.wsort, b.cell_start, int(g.ncell), pr.flags, pr.plist, pr.nprim,

@@ -247,6 +247,25 @@ struct Primaries {
 // 700, 40 at 4096, 52 at 6000 and 66 at 8192 galaxies, against 56 us for the
 // general path's launches at any of these sizes.
 constexpr int kSmallN = 6144;
+// Catalogues of a batch of at most kBatchN galaxies take the cell stage together,
+// a workgroup each (16 of about 8192: 1160 us of kernels one after the other, 100 us
+// in one launch), and their Gram products (see ZetaArgs::cats): the call 4.50 and
+// 3.67 ms.  Cell ids of 16 bits (the grid has at most 4 n cells) and the workgroup's
+// LDS, 104 KB here, set the limit.
+constexpr int kBatchN = 16384;
+constexpr int kBatchGroup = 16;
+// Head of a catalogue of a group: kCatStride 8-byte words, the first its primaries
+// and word kCatFirst its first row in the group; the rest its pair kernels' counters.
+constexpr int kCatStride = 72;
+constexpr int kCatFirst = 2;
+struct BatchCat {
+  Grid grid;
+  int64_t first, n;          // galaxies first..first + n - 1 of the call's catalogue
+  int64_t cells_at;          // its cell_start in b.cell_start
+};
+hipError_t launch_cells_batch(const g3pcf_problem& p, const BatchCat* cats, int ncat,
+                              const CellBufs& b, int* flags, int* plist, long long* head,
+                              int fp64, hipStream_t st);
 // The cell list, the primary list and the pass's clears.
 hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b,
                         const Primaries& pr, Clears z, int fp64, hipStream_t st);
@@ -295,7 +314,8 @@ struct ZetaArgs {
   const int* plist;
   const long long* nprim;
   const int* range;          // parts of the list that are summed (device, `lists` + 1 of them), or NULL
-  int lists;                 // parts of the list (1 without `range`), at most kZetaLists
+  const long long* cats;     // or heads of the catalogues whose rows, lists and weights follow each other
+  int lists;                 // parts of the list (1 without `range` or `cats`), at most kZetaLists
   long long row_begin;       // global primary index of A row 0
   long long K;               // rows of the pair-block (upper bound)
   RowLayout lay;

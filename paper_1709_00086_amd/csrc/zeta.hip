@@ -51,7 +51,10 @@ static_assert(kZetaLists <= kWave, "a lane per list part");
 __device__ __forceinline__ GramBlocks gram_blocks(const ZetaArgs& z) {
   const int lane = threadIdx.x % kWave;
   GramBlocks g{};
-  if (lane < z.lists) {
+  if (z.cats && lane < z.lists) {
+    g.count = int(z.cats[lane * kCatStride]);
+    g.first = int(z.cats[lane * kCatStride + kCatFirst]);
+  } else if (lane < z.lists) {
     long long first;
     g.count = int(valid_rows(z.nprim, z.range ? z.range + lane : nullptr, z.row_begin, z.K, first));
     g.first = int(first);
@@ -276,6 +279,7 @@ __device__ __forceinline__ void gram_tile(const ZetaArgs& z, const MDims& d, Ope
   const int W = d.W[m];
   const double* A = z.A + (long long)first * z.lay.W + d.off[m];
   const int* plist = z.plist + z.row_begin + first;
+  const double* wsort = z.wsort + (z.cats ? first : 0);
 
   // staging: thread -> column tid % 128 of both panels, a quarter of the step's
   // rows (the same for a whole wave, so the rows' weights come by readlane)
@@ -289,7 +293,7 @@ __device__ __forceinline__ void gram_tile(const ZetaArgs& z, const MDims& d, Ope
   };
   auto index = [&](int kb) { return plist[min(kb + min(lane, kStep - 1), r1 - 1)]; };
   auto load = [&](Stage& g, int kb, int idx) {
-    g.w = z.wsort[idx];
+    g.w = wsort[idx];
 #pragma unroll
     for (int q = 0; q < kRows; ++q) {
       const double* row = A + min(kb + kRows * rg + q, r1 - 1) * (long long)z.lay.W;

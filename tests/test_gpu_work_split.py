@@ -222,3 +222,33 @@ def test_regions_of_very_different_sizes(dev, nregions):
         ref = oracle.zeta(cat, primary_mask=(region == r).astype(np.uint8))
         assert np.abs(z[r] - ref).max() <= 1e-10 * scale, r
     assert not z[nregions - 1].any()
+
+
+@pytest.mark.parametrize("precision,basis", [("fp64", "spin"), ("fp32", "spin"),
+                                             ("fp64", "cartesian")])
+@pytest.mark.parametrize("sizes", [[300, 200], [1, 0, 63, 64, 0, 65, 2], [700] * 20,
+                                   [16383, 16384, 16385, 40, 3000]])
+@pytest.mark.parametrize("masked", [False, True])
+def test_catalogues_of_a_batch_together(dev, sizes, masked, precision, basis):
+    """Fewest and more catalogues than a group holds, empty ones, and the sizes
+    around its largest.  Each against a call of its own (FP64 1e-10, FP32 1e-5 of
+    max|zeta|), with a mask that leaves some without primaries."""
+    say(f"case batch {sizes} {masked} {precision} {basis}")
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    cat = C.uniform(int(off[-1]), 300.0, seed=77, dtype=np.float64, weights="uniform",
+                    rmax=30.0, nbins=4, lmax=5)
+    mask = (np.random.default_rng(78).uniform(size=cat.n) < 0.3).astype(np.uint8)
+    mask[:off[1]] = 0
+    pos, w = on(dev, cat)
+    mt = torch.from_numpy(mask).to(dev) if masked else None
+    cfg = cfg_of(cat, precision, basis=basis)
+    z = api.zeta_batch(pos, w, cfg, off, primary_mask=mt).cpu().numpy()
+    scale = np.abs(z).max()
+    for c, n in enumerate(sizes):
+        a, b = int(off[c]), int(off[c + 1])
+        if n == 0:
+            assert not z[c].any()
+            continue
+        ref = api.zeta(pos[a:b], w[a:b], cfg,
+                       primary_mask=mt[a:b].contiguous() if masked else None).cpu().numpy()
+        assert np.abs(z[c] - ref).max() <= (1e-10 if precision == "fp64" else 1e-5) * scale, c
