@@ -253,8 +253,8 @@ int g3pcf_forward_regions(const g3pcf_problem* prob, const int32_t* region, int 
  * catalogues).  offsets: HOST [ncat+1], offsets[0] = 0, non-decreasing,
  * offsets[ncat] = n.  zeta: device [ncat][g3pcf_zeta_len] doubles.  ws: at
  * least g3pcf_workspace_bytes(prob, 0) bytes for the whole batch; the
- * catalogues run one after another in it on `stream`.  pairs_out (if set): the
- * pairs of all catalogues (one wait per catalogue).  alm must be NULL.
+ * catalogues share it on `stream`, small ones in groups, larger ones one after
+ * another.  pairs_out (if set): the pairs of all catalogues (one wait per catalogue).  alm must be NULL.
  * Errors as g3pcf_forward, and G3PCF_EINVAL for ncat outside 1..2^20 or
  * inconsistent offsets. */
 int g3pcf_forward_batch(const g3pcf_problem* prob, int ncat, const int64_t* offsets,

@@ -35,8 +35,15 @@
 // which the later chunks replay (a repeated search if the list overflowed).
 //
 // The adjoint kernel runs the same search and, per accepted pair, evaluates
-// the shell's adjoint polynomial in FP64 and adds it to the secondary's
-// gradient with one atomic (FP32 on the FP32 path, FP64 on the FP64 path).
+// the shell's adjoint polynomial and adds it to the secondary's gradient with one
+// atomic (both in FP32 on the FP32 path, in FP64 on the FP64 path).
+//
+// What bounds it: dense shells, the issue of the accumulation's multiply-adds
+// (524,288 primaries of 35135 pairs, FP32 spin: 105.3 ms with 121 sums a lane and
+// three waves per SIMD, 100 to 104 with split sums and four); the adjoint, the
+// rate of the atomic adds (151.7 -> 144.6 ms); sparse shells, the instructions
+// and the waits of a search (100,000 primaries of 2640 pairs in 10 shells: 8.9 ->
+// 3.5 ms; 131,072 of 274 pairs in 16 catalogues: 5.5 -> 2.6 ms).
 //
 // Included by the pairs_*.hip files, which instantiate the kernels (it opens an
 // anonymous namespace).
@@ -287,7 +294,9 @@ struct Bin64 {
 };
 
 // Occupancy target per kernel (waves per SIMD); the register budget is
-// 512 / target per lane, so every accumulator chunk must fit.
+// 512 / target per lane, so every accumulator chunk must fit.  FP32 spin: the split
+// sums leave room for four, where a multiply-add issues every 2.5 cycles against 3.4
+// with three waves; the cartesian chunks and the FP64 sums have no room for more.
 template <typename Real, int BASIS, bool ADJOINT, int DEG>
 struct Occ {
   static constexpr bool kF32 = std::is_same<Real, float>::value;

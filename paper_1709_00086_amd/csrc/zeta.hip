@@ -93,7 +93,7 @@ __device__ __forceinline__ GramBlocks gram_blocks(const ZetaArgs& z) {
 // instructions that convert and split them (BF16x3, 2^19 rows of 1210: 7.9 GB staged
 // in 2.6 ms, 3.0 TB/s; the MFMAs alone 0.55 ms).  With 64 x 64 macro tiles every
 // column was staged in up to five workgroups; 128-wide panels stage it in at most
-// three, and tiles below the diagonal or past the last column are left out (395 of
+// three, and tiles below the diagonal or past the last column are left out (438 of
 // 16 x 16 a block at lmax 10 and 10 shells instead of 688).  The rows of a step are
 // read two steps ahead and its row numbers three, without a branch around a load:
 // with a wait for the weights (row number, then weight, then lane reads) in every
