@@ -61,6 +61,9 @@ ADJ_FLOPS_PER_PAIR_FP32 = 314
 # for m >= 1; sum of squares 166,100.  The zeta stage's algorithmic work is the
 # full square Gram, 2 x 166,100 flops per primary.
 ZETA_FLOPS_PER_PRIMARY = 2 * 166100
+# What the Gram kernel issues of it (per product of operands): the 16 x 16 tiles on
+# and above the diagonal, in pairs below each other, 438 of them.
+ZETA_ISSUED_PER_PRIMARY = 438 * 512
 
 WORKLOADS = {
     "c1": "config1",
@@ -366,7 +369,7 @@ def main():
                     help="summarise rocprofv3 CSV output instead of running (no GPU)")
     ap.add_argument("--counters", nargs="*", default=[])
     ap.add_argument("--kernel-stats", nargs="*", default=[])
-    ap.add_argument("--kernel-regex", default=r"k_pairs<float, 1, false, 10, false, false>")
+    ap.add_argument("--kernel-regex", default=r"k_pairs<float, 1, false, 10, false, false, 0>")
     ap.add_argument("--label", default=None)
     ap.add_argument("--copy-mib", type=int, default=0)
     ap.add_argument("--commands", nargs="*", default=None)
@@ -586,9 +589,10 @@ def main():
         # BF16x3 does six bfloat16 products per FP32-equivalent product
         key, work = {_lib.PREC_FP32: ("fp32_mfma_tflops", 1), _lib.PREC_FP64: ("fp64_mfma_tflops", 1),
                      _lib.PREC_BF16X3: ("bf16_mfma_tflops", 6)}[zp]
+        issued = zfl * work * ZETA_ISSUED_PER_PRIMARY / ZETA_FLOPS_PER_PRIMARY
         out["zeta_stage"] = {"ms_per_pass": zeta_launch_ms, "tflops_full_square": zfl,
-                             "mfma_tflops": zfl * work,
-                             "frac_of_mfma_peak": zfl * work / PEAK[key], "peak": key}
+                             "mfma_tflops": issued,
+                             "frac_of_mfma_peak": issued / PEAK[key], "peak": key}
 
     # the same seeded primary sample for the errors, the FP64 comparison and the
     # CPU baseline

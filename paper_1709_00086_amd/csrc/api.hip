@@ -560,31 +560,28 @@ int forward_group(const g3pcf_problem& p, const Ws& w, void* ws, const BatchCat*
                                 &head->nprim, fp64, st)) != hipSuccess)
       return hip_fail(e, "cell lists of a batch");
   }
-  PairArgs a{};
-  {
+  for (int c = 0; c < m; ++c) {
+    const BatchCat& k = cats[c];
+    if (k.n == 0) continue;
+    Ws v = w;
+    v.grid = k.grid;
+    v.pos4 += size_t(k.first) * (fp64 ? 32 : 16);
+    v.cell_start += size_t(k.cells_at) * 4;
+    v.perm += size_t(k.first) * 4;
+    v.plist += size_t(k.first) * 4;
+    v.flags += size_t(k.first) * 4;
+    v.wsort += size_t(k.first) * 8;
+    v.A += size_t(k.first - base) * w.lay.W * 8;
+    v.counters = w.rhist + size_t(c) * sizeof(Counters);
     StageScope sc(p.trace, G3PCF_STAGE_PAIRS, st);
-    for (int c = 0; c < m; ++c) {
-      const BatchCat& k = cats[c];
-      if (k.n == 0) continue;
-      Ws v = w;
-      v.grid = k.grid;
-      v.pos4 += size_t(k.first) * (fp64 ? 32 : 16);
-      v.cell_start += size_t(k.cells_at) * 4;
-      v.perm += size_t(k.first) * 4;
-      v.plist += size_t(k.first) * 4;
-      v.flags += size_t(k.first) * 4;
-      v.wsort += size_t(k.first) * 8;
-      v.A += size_t(k.first - base) * w.lay.W * 8;
-      v.counters = w.rhist + size_t(c) * sizeof(Counters);
-      a = PairArgs{};
-      if (int rc = pair_args(catalogue_of(p, k.first, k.n), v, ws, a)) return rc;
-      a.sentinel = int(p.n - k.first);
-      a.p_begin = 0;
-      a.p_count = k.n;
-      a.pairs = nullptr;
-      if ((e = launch_pair_forward(a, fp64, p.basis, false, st)) != hipSuccess)
-        return hip_fail(e, "pair kernel");
-    }
+    PairArgs a{};
+    if (int rc = pair_args(catalogue_of(p, k.first, k.n), v, ws, a)) return rc;
+    a.sentinel = int(p.n - k.first);
+    a.p_begin = 0;
+    a.p_count = k.n;
+    a.pairs = nullptr;
+    if ((e = launch_pair_forward(a, fp64, p.basis, false, st)) != hipSuccess)
+      return hip_fail(e, "pair kernel");
   }
   StageScope sc(p.trace, G3PCF_STAGE_ZETA, st);
   ZetaArgs z{};
