@@ -543,9 +543,9 @@ RowLayout make_layout(int lmax, int nb) {
 // partials few where there are many rows; a small pair-block is cut into more,
 // until the macro tiles times the blocks give every CU, which holds one workgroup
 // at a time, about two (a tile's 4096 rows are one serial chain of 128 steps: the
-// Gram products of 16 catalogues of 8192 took 4.55 ms in blocks of 4096 rows and take
-// 0.91 ms in 27; three or six workgroups a CU 3 to 8% more of the whole call, and
-// the sum over the blocks grows with them).
+// Gram products of 16 catalogues of 8192, one launch each, took 4.55 ms in blocks of
+// 4096 rows and 0.91 ms in 27 blocks; three or six workgroups a CU took the whole call
+// 3 to 8% longer, the sum over the blocks growing with them).
 int zeta_parts(const RowLayout& L, long long PB) {
   const long long tiles = make_mdims(L).mt[L.lmax + 1];
   const long long fill = (2 * 256 + tiles - 1) / tiles;
