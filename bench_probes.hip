@@ -6,7 +6,7 @@
 //           all operands in vector registers, or one multiplicand in a scalar
 //           register, at 1 to 8 waves per SIMD (occupancy set through LDS);
 //           reports cycles per wave-level FMA per SIMD at 2.4 GHz.
-//   accum   the pair kernel's spin accumulation alone (SpinSplit::add, one
+//   accum   the pair kernel's spin accumulation alone (SpinSums::add, one
 //           synthetic unit vector per lane per step) at 3 and 4 waves per SIMD.
 //   count   one launch that issues exactly 2^20 wave-level FP32 FMAs, to check
 //           what SQ_INSTS_VALU_FMA_F32 reads under rocprofv3.
@@ -48,12 +48,9 @@ __global__ __launch_bounds__(256) void k_fma(float* out, int iters, float a0, fl
   out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_accum(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_accum(
     float* out, int iters, float c, float s) {
-  typedef Exchange<float, true> X;
-  __shared__ __attribute__((aligned(16))) float xch[4][X::kReals];
-  const int lane = threadIdx.x % kWave;
-  SpinSplit<float, kDeg, false> a;
+  SpinSums<kDeg, false> a;
   a.zero();
   float x = 0.6f + threadIdx.x * 1e-4f, y = 0.48f, z = 0.64f;
   const float w = 1.0f + threadIdx.x * 1e-5f;
@@ -61,14 +58,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const float nx = fma_r(x, c, -(y * s)), ny = fma_r(x, s, y * c);
     x = nx;
     y = ny;
-    a.add(x, y, z, w, xch[threadIdx.x / kWave], lane);
-    X::fence();
+    a.add(x, y, z, w);
   }
-  float s0[kDeg + 1], sm[decltype(a)::NP];
-  a.unpack(s0, sm);
   float t = 0.f;
-  for (int i = 0; i <= kDeg; ++i) t += s0[i];
-  for (int i = 0; i < decltype(a)::NP; ++i) t += sm[i];
+#pragma unroll
+  for (int i = 0; i < decltype(a)::NT; ++i) t += a.acc[i];
   out[blockIdx.x * blockDim.x + threadIdx.x] = t;
 }
 
@@ -228,9 +222,9 @@ int main(int argc, char** argv) {
     for (int w : {3, 4, 8}) fma_rate<16, true>(out, w);
   }
   if (all || !std::strcmp(mode, "accum")) {
-    // 164 VALU instructions per step: the accumulation's 159 and the
-    // synthetic vector's 5 (counted in the compiled loop)
-    for (int w : {3, 4}) accum_rate(out, "spin", w, 187);
+    // 164 VALU instructions per step: the accumulation's 159 (the T_n of the
+    // constant z leave the loop) and the synthetic vector's 5
+    for (int w : {3, 4}) accum_rate(out, "spin", w, 164);
   }
   if (all || !std::strcmp(mode, "count")) {
     // 1024 waves x (4 iterations x 256 FMAs in the loop + 18 outside it: the

@@ -306,149 +306,6 @@ __device__ __forceinline__ void swap_halves(float& a, float& b) {
 }
 __device__ __forceinline__ void swap_halves(double& a, double& b) { b = swap32_d(a, b); }
 
-// Register pairs.  An FP32 multiply-add issues in about 2.5 cycles a SIMD where
-// its three source registers are not all even or all odd numbered, and in 4.4
-// where they are (measured; the register file has two banks).  Values held in
-// the halves of an aligned pair have a known parity: the empty statement makes
-// the compiler keep the two in one.  FP64 operands are pairs already.
-typedef float pair_f __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void keep_pair(float& even, float& odd) {
-  pair_f p = {even, odd};
-  asm("" : "+v"(p));
-  even = p.x;
-  odd = p.y;
-}
-__device__ __forceinline__ void keep_pair(double&, double&) {}
-
-// T_1..T_N of one lane, T_n in a register of n's parity; (D + 1)-entry arrays
-// with T_0 unused.
-template <int N, typename Real, int D>
-__device__ __forceinline__ void pair_up(Real (&t)[D]) {
-  static_for<N / 2>([&](auto kc) {
-    constexpr int n = 2 * (decltype(kc)::value + 1);
-    if constexpr (n + 1 <= N) keep_pair(t[n], t[n + 1]);
-  });
-}
-// Rows of sums (or coefficients) over n = 0..N, entries (1, 2), (3, 4), ... in
-// register pairs: entry n in a register of the other parity than T_n's.  The
-// pairs are kept as vectors, so that they stay in their registers around a loop.
-template <int N, typename Real>
-struct Row;
-template <int N>
-struct Row<N, float> {
-  float first;                         // n = 0
-  pair_f pairs[N / 2 > 0 ? N / 2 : 1]; // (1, 2), (3, 4), ...
-  float last;                          // n = N if N is odd
-  template <int n>
-  __device__ __forceinline__ float get() const {
-    if constexpr (n == 0) return first;
-    else if constexpr (n == N && (N & 1)) return last;
-    else if constexpr (n & 1) return pairs[(n - 1) / 2].x;
-    else return pairs[(n - 1) / 2].y;
-  }
-  template <int n>
-  __device__ __forceinline__ void set(float v) {
-    if constexpr (n == 0) first = v;
-    else if constexpr (n == N && (N & 1)) last = v;
-    else if constexpr (n & 1) pairs[(n - 1) / 2].x = v;
-    else pairs[(n - 1) / 2].y = v;
-  }
-  __device__ __forceinline__ void keep() {
-    static_for<N / 2>([&](auto kc) { asm("" : "+v"(pairs[decltype(kc)::value])); });
-  }
-};
-template <int N>
-struct Row<N, double> {
-  double v[N + 1];
-  template <int n>
-  __device__ __forceinline__ double get() const {
-    return v[n];
-  }
-  template <int n>
-  __device__ __forceinline__ void set(double x) {
-    v[n] = x;
-  }
-  __device__ __forceinline__ void keep() {}
-};
-
-// The rows m = 1..D (n = 0..D - m).
-template <int M, int D, typename Real>
-struct Rows {
-  Row<D - M, Real> row;
-  Rows<M + 1, D, Real> rest;
-  template <int m>
-  __device__ __forceinline__ auto& at() {
-    if constexpr (m == M)
-      return row;
-    else
-      return rest.template at<m>();
-  }
-  template <int m>
-  __device__ __forceinline__ const auto& at() const {
-    if constexpr (m == M)
-      return row;
-    else
-      return rest.template at<m>();
-  }
-};
-template <int D, typename Real>
-struct Rows<D, D, Real> {
-  Row<0, Real> row;
-  template <int m>
-  __device__ __forceinline__ auto& at() {
-    return row;
-  }
-  template <int m>
-  __device__ __forceinline__ const auto& at() const {
-    return row;
-  }
-};
-
-// The half waves' operands.  For m >= 1 a register holds the real part of
-// something in the lower half of the wave and the imaginary part in the upper;
-// the 64 pairs are then taken 32 at a time, each by both halves, which need the
-// pair's z and powers (x - i y)^m: in LDS every lane leaves what they follow
-// from, and reads it for its half's part of a lower pair (lane mod 32) and of
-// an upper one.  (Exchanging registers by permlane32_swap costs 8.3 cycles each,
-// and 19 of them a wave of pairs, against none here.)  The real and the
-// imaginary parts c_m of w (x - i y)^m both follow
-//   c_{m+1} = 2 x c_m - (x^2 + y^2) c_{m-1}.
-template <typename Real>
-struct Half {
-  Real z, z2, x2, rho;  // z, 2 z, 2 x, x^2 + y^2
-  Real c0, c1;          // c_0, c_1: of the real part [w | 0], [w x | -w y]
-};
-// kWeighted: with w; else w = 1 (c_0 is then known, and takes no room).
-template <typename Real, bool kWeighted>
-struct Exchange {
-  static constexpr int kReals = (kWeighted ? 8 : 6) * kWave;  // per wave
-  typedef Real V4r __attribute__((ext_vector_type(4)));
-  typedef Real V2r __attribute__((ext_vector_type(2)));
-  static __device__ __forceinline__ void put(Real* s, int lane, Real x, Real y, Real z, Real w) {
-    reinterpret_cast<V4r*>(s)[lane] = V4r{z, z + z, x + x, fma_r(y, y, x * x)};
-    if constexpr (kWeighted)
-      reinterpret_cast<V4r*>(s)[kWave + lane] = V4r{w, w * x, Real(0), -(w * y)};
-    else
-      reinterpret_cast<V2r*>(s)[2 * kWave + lane] = V2r{x, -y};
-  }
-  // upper: pairs 32..63 instead of 0..31
-  static __device__ __forceinline__ Half<Real> get(const Real* s, int lane, bool upper) {
-    const int p = (lane & 31) + (upper ? 32 : 0), half = lane >> 5;
-    const V4r a = reinterpret_cast<const V4r*>(s)[p];
-    if constexpr (kWeighted) {
-      const V2r c = reinterpret_cast<const V2r*>(s)[2 * (kWave + p) + half];
-      return Half<Real>{a.x, a.y, a.z, a.w, c.x, c.y};
-    } else {
-      const Real c = s[4 * kWave + 2 * p + half];
-      return Half<Real>{a.x, a.y, a.z, a.w, half ? Real(0) : Real(1), c};
-    }
-  }
-  static __device__ __forceinline__ void fence() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-  }
-};
-
 // T_1..T_N of z, given 2 z too, by their three-term recurrence
 // T_{n+1} = 2 z T_n - T_{n-1} (one FMA each).  In this basis the
 // coefficients of the spherical harmonics do not cancel: those of the powers
@@ -465,101 +322,81 @@ __device__ __forceinline__ void chebyshev_z2(Real z, Real z2, Real (&tn)[D]) {
   });
 }
 
+// c = (x - i y) c, two multiply-adds and two products.  The power's real part
+// alone follows 2 x c_m - (x^2 + y^2) c_{m-1} with half the operations, but the
+// rounding errors of that recurrence grow with m (random directions, FP32: 2.0
+// times those of the product at m = 3, 3.6 at 6, 5.7 at 10).
+template <typename Real>
+__device__ __forceinline__ void times_xy(Real& re, Real& im, Real x, Real y) {
+  const Real r = fma_r(re, x, im * y);
+  im = fma_r(im, x, -(re * y));
+  re = r;
+}
+
+// Degenerate-triangle sums that ride along with the spin sums: deg[n] += w^2
+// T_n(z), n <= 2 D, given T_1..T_D.
+template <int D, typename Real, int N>
+__device__ __forceinline__ void add_degenerate(Real (&deg)[N], const Real (&t)[D + 1], Real z,
+                                               Real w) {
+  const Real w2 = w * w, z2 = z + z;
+  deg[0] += w2;
+  static_for<D>([&](auto nc) {
+    constexpr int n = decltype(nc)::value + 1;
+    deg[n] = fma_r(w2, t[n], deg[n]);
+  });
+  Real p0 = t[D - 1], p1 = t[D];
+  static_for<D>([&](auto nc) {
+    constexpr int n = decltype(nc)::value + D + 1;
+    const Real p2 = fma_r(z2, p1, -p0);
+    deg[n] = fma_r(w2, p2, deg[n]);
+    p0 = p1;
+    p1 = p2;
+  });
+}
+
 // Spin sums S_{m,n} = sum w (u_x - i u_y)^m T_n(u_z), m + n <= D, with T_n the
 // Chebyshev polynomials (the conversion to a_lm uses the spin-Chebyshev table).
-//
-// For m >= 1 the lower half of the wave holds the real part of S_{m,n} and the
-// upper half the imaginary part, in one register: 66 accumulators instead of
-// 121 at D = 10, four waves per SIMD instead of three, and the same number of
-// multiply-adds as with one pair per lane.  Degrees 4, 6 and 8 hold 15, 28 and 45:
-// 100,003 primaries with 20 shells at l_max 4 took 8.0 ms carried to degree 10 and
-// take 3.3 ms.
-template <typename Real, int D, bool DISTINCT>
-struct SpinSplit {
+// FP32: every lane carries all (D + 1)^2 sums of its own pairs, in term order.
+// (Real and imaginary parts in either half of a wave, as in FP64 below, fit four
+// waves a SIMD at D = 10 instead of three, but a lane then sums twice as many pairs:
+// the errors of S_{m,0}, m = 1..3, over 20,000 pairs were 1.4 to 1.5 times these.  The
+// fourth wave is worth 11 to 13% where the search counts, 16 catalogues of 8192
+// in 3.66 against 4.18 ms, and nothing on dense catalogues.  Degrees 4, 6 and 8 have
+// four waves either way and are up to 8% faster unsplit.)
+template <int D, bool DISTINCT>
+struct SpinSums {
+  static constexpr int NT = (D + 1) * (D + 1);
   static constexpr int ND = DISTINCT ? 2 * D + 1 : 1;
-  Row<D, Real> acc0;        // m = 0, one pair per lane
-  Rows<1, D, Real> acc;     // Re | Im
-  Real deg[ND];             // sum w^2 T_n(u_z), n <= 2 D (degenerate triangles)
+  float acc[NT];
+  float deg[ND];            // sum w^2 T_n(u_z), n <= 2 D (degenerate triangles)
 
   __device__ __forceinline__ void zero() {
-    static_for<D + 1>([&](auto nc) { acc0.template set<decltype(nc)::value>(Real(0)); });
-    static_for<D>([&](auto mc) {
-      constexpr int m = decltype(mc)::value + 1;
-      static_for<D - m + 1>(
-          [&](auto nc) { acc.template at<m>().template set<decltype(nc)::value>(Real(0)); });
-    });
 #pragma unroll
-    for (int i = 0; i < ND; ++i) deg[i] = Real(0);
+    for (int i = 0; i < NT; ++i) acc[i] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < ND; ++i) deg[i] = 0.0f;
   }
 
-  // 32 pairs, both halves of the wave
-  __device__ __forceinline__ void add_half(const Half<Real>& h) {
-    Real t[D + 1];
-    chebyshev_z2<D - 1>(h.z, h.z2, t);
-    pair_up<D - 1>(t);
-    Real c0 = h.c0, c1 = h.c1;
-    static_for<D>([&](auto mc) {
-      constexpr int m = decltype(mc)::value + 1;
-      auto& r = acc.template at<m>();
-      r.template set<0>(r.template get<0>() + c1);
-      static_for<D - m>([&](auto nc) {
-        constexpr int n = decltype(nc)::value + 1;
-        r.template set<n>(fma_r(c1, t[n], r.template get<n>()));
-      });
-      if constexpr (m < D) {
-        const Real c2 = fma_r(h.x2, c1, -(h.rho * c0));
-        c0 = c1;
-        c1 = c2;
-      }
-    });
-  }
-
-  __device__ __forceinline__ void add(Real x, Real y, Real z, Real w, Real* xch, int lane) {
-    Exchange<Real, true>::put(xch, lane, x, y, z, w);
-    static_for<D>([&](auto mc) { acc.template at<decltype(mc)::value + 1>().keep(); });
-    acc0.keep();
-    // m = 0 (and the degenerate sums) while the exchange is under way
-    Real t[D + 1];
+  __device__ __forceinline__ void add(float x, float y, float z, float w) {
+    float t[D + 1];
     chebyshev_z2<D>(z, z + z, t);
-    pair_up<D>(t);
-    acc0.template set<0>(acc0.template get<0>() + w);
+    acc[0] += w;
     static_for<D>([&](auto nc) {
       constexpr int n = decltype(nc)::value + 1;
-      acc0.template set<n>(fma_r(w, t[n], acc0.template get<n>()));
+      acc[n] = fma_r(w, t[n], acc[n]);
     });
-    if constexpr (DISTINCT) {
-      const Real w2 = w * w, z2 = z + z;
-      deg[0] += w2;
-      static_for<D>([&](auto nc) {
-        constexpr int n = decltype(nc)::value + 1;
-        deg[n] = fma_r(w2, t[n], deg[n]);
-      });
-      Real p0 = t[D - 1], p1 = t[D];
-      static_for<D>([&](auto nc) {
-        constexpr int n = decltype(nc)::value + D + 1;
-        const Real p2 = fma_r(z2, p1, -p0);
-        deg[n] = fma_r(w2, p2, deg[n]);
-        p0 = p1;
-        p1 = p2;
-      });
-    }
-    Exchange<Real, true>::fence();
-    add_half(Exchange<Real, true>::get(xch, lane, false));
-    add_half(Exchange<Real, true>::get(xch, lane, true));
-  }
-
-  // The sums as plain arrays: m = 0 by n, and the rest in pair order.
-  static constexpr int NP = D * (D + 1) / 2;  // (m >= 1, n) pairs
-  __device__ __forceinline__ void unpack(Real (&s0)[D + 1], Real (&s)[NP]) const {
-    static_for<D + 1>([&](auto nc) {
-      constexpr int n = decltype(nc)::value;
-      s0[n] = acc0.template get<n>();
-    });
+    if constexpr (DISTINCT) add_degenerate<D>(deg, t, z, w);
+    float cr = w * x, ci = -(w * y);  // w (x - i y)^m
     static_for<D>([&](auto mc) {
       constexpr int m = decltype(mc)::value + 1;
-      static_for<D - m + 1>([&](auto nc) {
-        constexpr int n = decltype(nc)::value;
-        s[spin_pair_c<D>(m, n)] = acc.template at<m>().template get<n>();
+      if constexpr (m > 1) times_xy(cr, ci, x, y);
+      float* a = acc + spin_term_c<D>(m, 0, 0);
+      a[0] += cr;
+      a[1] += ci;
+      static_for<D - m>([&](auto nc) {
+        constexpr int n = decltype(nc)::value + 1;
+        a[2 * n] = fma_r(cr, t[n], a[2 * n]);
+        a[2 * n + 1] = fma_r(ci, t[n], a[2 * n + 1]);
       });
     });
   }
@@ -571,52 +408,176 @@ struct SpinSplit {
 // spherical harmonics do not cancel (those of z^n do, by two to three orders
 // of magnitude at l = 10), so FP32 evaluation keeps close to FP32 accuracy.
 // The coefficients are the same for every pair (one set per primary and
-// shell) and are held in vector registers, for m >= 1 those of the real parts
-// in the lower half of the wave and those of the imaginary parts in the upper
-// (66 registers instead of 121 at D = 10, split as the sums of SpinSplit are):
-// each half evaluates its part of all 64 pairs, and one exchange at the end adds
-// the two.
+// shell) and are held in vector registers: a multiply-add with a scalar-register
+// operand issues more slowly than one with three vector registers.
+template <int D>
+struct SpinPoly {
+  static constexpr int NT = (D + 1) * (D + 1);
+  float g[NT];
+
+  template <typename Ptr>
+  __device__ __forceinline__ void load(Ptr gc, int) {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) g[i] = gc[i];
+  }
+
+  __device__ __forceinline__ float eval(float x, float y, float z) const {
+    float t[D + 1];
+    chebyshev_z2<D>(z, z + z, t);
+    float total = g[0];
+    static_for<D>([&](auto nc) {
+      constexpr int n = decltype(nc)::value + 1;
+      total = fma_r(g[n], t[n], total);
+    });
+    float cr = x, ci = -y;  // (x - i y)^m
+    static_for<D>([&](auto mc) {
+      constexpr int m = decltype(mc)::value + 1;
+      if constexpr (m > 1) times_xy(cr, ci, x, y);
+      const float* a = g + spin_term_c<D>(m, 0, 0);
+      float hr = a[0], hi = a[1];
+      static_for<D - m>([&](auto nc) {
+        constexpr int n = decltype(nc)::value + 1;
+        hr = fma_r(a[2 * n], t[n], hr);
+        hi = fma_r(a[2 * n + 1], t[n], hi);
+      });
+      total = fma_r(cr, hr, fma_r(ci, hi, total));
+    });
+    return total;
+  }
+};
+
+// The half waves' operands.  For m >= 1 a register holds the real part of
+// something in the lower half of the wave and the imaginary part in the upper;
+// the 64 pairs are then taken 32 at a time, each by both halves, which need the
+// pair's z and powers (x - i y)^m: in LDS every lane leaves what they follow
+// from, and reads it for its half's part of a lower pair (lane mod 32) and of
+// an upper one.  Each half carries the power's other part too: with s = y in the
+// lower half and -y in the upper, both follow
+//   own' = own x + other s,   other' = other x - own s.
+template <typename Real>
+struct Half {
+  Real z, x, s;
+  Real own, other;  // of w (x - i y), or of x - i y
+};
+// kWeighted: with w.
+template <typename Real, bool kWeighted>
+struct Exchange {
+  static constexpr int kReals = (kWeighted ? 8 : 4) * kWave;  // per wave
+  typedef Real V2r __attribute__((ext_vector_type(2)));
+  typedef Real V4r __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ void put(Real* s, int lane, Real x, Real y, Real z, Real w) {
+    reinterpret_cast<V4r*>(s)[lane] = V4r{z, x, y, -y};
+    // (the fourth is not read)
+    if constexpr (kWeighted)
+      reinterpret_cast<V4r*>(s)[kWave + lane] = V4r{w * x, -(w * y), w * x, Real(0)};
+  }
+  // upper: pairs 32..63 instead of 0..31
+  static __device__ __forceinline__ Half<Real> get(const Real* s, int lane, bool upper) {
+    const int p = (lane & 31) + (upper ? 32 : 0), half = lane >> 5;
+    const V2r a = reinterpret_cast<const V2r*>(s)[2 * p];
+    const Real sy = s[4 * p + 2 + half];
+    if constexpr (kWeighted) {
+      const Real* c = s + 4 * (kWave + p) + half;
+      return Half<Real>{a.x, a.y, sy, c[0], c[1]};
+    } else {
+      return Half<Real>{a.x, a.y, sy, half ? sy : a.y, half ? a.y : -sy};
+    }
+  }
+  static __device__ __forceinline__ void fence() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+  }
+};
+
+// The same sums in FP64, of which a lane holds no 121.  For m >= 1 the lower half of the wave holds the real
+// part of S_{m,n} and the upper half the imaginary part, in one register: 66
+// accumulators instead of 121 at D = 10, which fit two waves per SIMD at once.
+template <int D, bool DISTINCT>
+struct SpinSplit {
+  static constexpr int ND = DISTINCT ? 2 * D + 1 : 1;
+  static constexpr int NP = D * (D + 1) / 2;  // (m >= 1, n) pairs
+  double acc0[D + 1];       // m = 0, one pair per lane
+  double acc[NP];           // Re | Im
+  double deg[ND];           // sum w^2 T_n(u_z), n <= 2 D (degenerate triangles)
+
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int i = 0; i <= D; ++i) acc0[i] = 0.0;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) acc[i] = 0.0;
+#pragma unroll
+    for (int i = 0; i < ND; ++i) deg[i] = 0.0;
+  }
+
+  // 32 pairs, both halves of the wave
+  __device__ __forceinline__ void add_half(const Half<double>& h) {
+    double t[D + 1];
+    chebyshev_z2<D - 1>(h.z, h.z + h.z, t);
+    double own = h.own, other = h.other;
+    static_for<D>([&](auto mc) {
+      constexpr int m = decltype(mc)::value + 1;
+      if constexpr (m > 1) times_xy(own, other, h.x, h.s);
+      double* a = acc + spin_pair_c<D>(m, 0);
+      a[0] += own;
+      static_for<D - m>([&](auto nc) {
+        constexpr int n = decltype(nc)::value + 1;
+        a[n] = fma_r(own, t[n], a[n]);
+      });
+    });
+  }
+
+  __device__ __forceinline__ void add(double x, double y, double z, double w, double* xch,
+                                      int lane) {
+    Exchange<double, true>::put(xch, lane, x, y, z, w);
+    // m = 0 (and the degenerate sums) while the exchange is under way
+    double t[D + 1];
+    chebyshev_z2<D>(z, z + z, t);
+    acc0[0] += w;
+    static_for<D>([&](auto nc) {
+      constexpr int n = decltype(nc)::value + 1;
+      acc0[n] = fma_r(w, t[n], acc0[n]);
+    });
+    if constexpr (DISTINCT) add_degenerate<D>(deg, t, z, w);
+    Exchange<double, true>::fence();
+    add_half(Exchange<double, true>::get(xch, lane, false));
+    add_half(Exchange<double, true>::get(xch, lane, true));
+  }
+};
+
+// The same polynomial (FP64, and FP32 at D = 10) with the coefficients split as the
+// sums of SpinSplit are (66 registers instead of 121 at D = 10, so four waves a SIMD
+// in FP32: 100,003 primaries of 2640 pairs 5.8 ms, at three waves and unsplit 6.3):
+// each half of the wave evaluates its part of all 64 pairs, and one exchange at the
+// end adds the two.
 template <typename Real, int D>
 struct SplitPoly {
-  Row<D, Real> g0;
-  Rows<1, D, Real> g;
+  static constexpr int NP = D * (D + 1) / 2;
+  Real g0[D + 1], g[NP];
 
   // gc: the (D + 1)^2 coefficients in term order
   template <typename Ptr>
   __device__ __forceinline__ void load(Ptr gc, int lane) {
     const int part = lane >> 5;
-    static_for<D + 1>([&](auto nc) {
-      constexpr int n = decltype(nc)::value;
-      g0.template set<n>(gc[n]);
-    });
-    static_for<D>([&](auto mc) {
-      constexpr int m = decltype(mc)::value + 1;
-      static_for<D - m + 1>([&](auto nc) {
-        constexpr int n = decltype(nc)::value;
-        g.template at<m>().template set<n>(gc[D + 1 + 2 * spin_pair_c<D>(m, n) + part]);
-      });
-    });
+#pragma unroll
+    for (int i = 0; i <= D; ++i) g0[i] = gc[i];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) g[i] = gc[D + 1 + 2 * i + part];
   }
 
   __device__ __forceinline__ Real eval_half(const Half<Real>& h) const {
     Real t[D + 1];
-    chebyshev_z2<D - 1>(h.z, h.z2, t);
-    pair_up<D - 1>(t);
-    Real c0 = h.c0, c1 = h.c1, sum = Real(0);
+    chebyshev_z2<D - 1>(h.z, h.z + h.z, t);
+    Real own = h.own, other = h.other, sum = Real(0);
     static_for<D>([&](auto mc) {
       constexpr int m = decltype(mc)::value + 1;
-      const auto& r = g.template at<m>();
-      Real v = r.template get<0>();
+      if constexpr (m > 1) times_xy(own, other, h.x, h.s);
+      const Real* a = g + spin_pair_c<D>(m, 0);
+      Real v = a[0];
       static_for<D - m>([&](auto nc) {
         constexpr int n = decltype(nc)::value + 1;
-        v = fma_r(r.template get<n>(), t[n], v);
+        v = fma_r(a[n], t[n], v);
       });
-      sum = m == 1 ? c1 * v : fma_r(c1, v, sum);
-      if constexpr (m < D) {
-        const Real c2 = fma_r(h.x2, c1, -(h.rho * c0));
-        c0 = c1;
-        c1 = c2;
-      }
+      sum = m == 1 ? own * v : fma_r(own, v, sum);
     });
     return sum;
   }
@@ -624,15 +585,12 @@ struct SplitPoly {
   // the polynomial of the lane's own pair
   __device__ __forceinline__ Real eval(Real x, Real y, Real z, Real* xch, int lane) {
     Exchange<Real, false>::put(xch, lane, x, y, z, Real(1));
-    static_for<D>([&](auto mc) { g.template at<decltype(mc)::value + 1>().keep(); });
-    g0.keep();
     Real t[D + 1];
     chebyshev_z2<D>(z, z + z, t);
-    pair_up<D>(t);
-    Real total = g0.template get<0>();
+    Real total = g0[0];
     static_for<D>([&](auto nc) {
       constexpr int n = decltype(nc)::value + 1;
-      total = fma_r(g0.template get<n>(), t[n], total);
+      total = fma_r(g0[n], t[n], total);
     });
     Exchange<Real, false>::fence();
     Real sa = eval_half(Exchange<Real, false>::get(xch, lane, false));
@@ -695,13 +653,16 @@ template <typename Real>
 struct Chunks<Real, kBasisDeg, kDeg> {
   using type = ChunkList<DegChunk<Real>>;
 };
+template <typename Real, int DEG, bool DISTINCT>
+using SpinOf =
+    std::conditional_t<sizeof(Real) == 4, SpinSums<DEG, DISTINCT>, SpinSplit<DEG, DISTINCT>>;
 template <typename Real, int DEG>
 struct Chunks<Real, G3PCF_BASIS_SPIN, DEG> {
-  using type = ChunkList<SpinSplit<Real, DEG, false>>;
+  using type = ChunkList<SpinOf<Real, DEG, false>>;
 };
 template <typename Real, int DEG>
 struct Chunks<Real, kBasisSpinDeg, DEG> {
-  using type = ChunkList<SpinSplit<Real, DEG, true>>;
+  using type = ChunkList<SpinOf<Real, DEG, true>>;
 };
 
 template <class... C, typename F>

@@ -39,11 +39,11 @@
 // atomic (both in FP32 on the FP32 path, in FP64 on the FP64 path).
 //
 // What bounds it: dense shells, the issue of the accumulation's multiply-adds
-// (524,288 primaries of 35135 pairs, FP32 spin: 105.3 ms with 121 sums a lane and
-// three waves per SIMD, 100 to 104 with split sums and four); the adjoint, the
-// rate of the atomic adds (151.7 -> 144.6 ms); sparse shells, the instructions
-// and the waits of a search (100,000 primaries of 2640 pairs in 10 shells: 8.9 ->
-// 3.5 ms; 131,072 of 274 pairs in 16 catalogues: 5.5 -> 2.6 ms).
+// (524,288 primaries of 35135 pairs, FP32 spin: 99 ms at 121 sums a lane and three
+// waves per SIMD); the adjoint, the rate of the atomic adds (151.7 -> 144 ms with
+// more stripes, see run); sparse shells, the instructions and the waits of a search
+// (100,000 primaries of 2640 pairs in 10 shells: 8.9 -> 4.0 ms; 131,072 of 274 pairs
+// in 16 catalogues: 5.5 -> 3.1 ms).
 //
 // Included by the pairs_*.hip files, which instantiate the kernels (it opens an
 // anonymous namespace).
@@ -103,14 +103,14 @@ template <typename Real>
 constexpr int kList = sizeof(Real) == 4 ? kListMost32 : kListMost64;
 constexpr int kOutBufList = 3 * kWave;  // terms that may wait beside the list
 
-template <typename Real, bool SPILL, bool SPINT, bool SPIN, bool ADJ, bool LISTED>
+template <typename Real, bool SPILL, bool SPINT, bool SPLIT, bool ADJ, bool LISTED>
 struct WaveLds {
   using V = typename V4<Real>::T;
-  static constexpr int kExchange = SPIN ? int(Exchange<Real, !ADJ>::kReals * sizeof(Real)) : 0;
-  // FP32 spin kernels have 10 KB a wave (four waves per SIMD): with the list the
+  static constexpr int kExchange = SPLIT ? int(Exchange<Real, !ADJ>::kReals * sizeof(Real)) : 0;
+  // FP32 adjoints have 10 KB a wave (four waves per SIMD): with the list the
   // exchange and the waiting terms go into the run table, which is not in use
   // while the list is read
-  static constexpr bool kInRuns = LISTED && SPIN && sizeof(Real) == 4;
+  static constexpr bool kInRuns = LISTED && SPINT;
   static constexpr int kOut = SPINT ? (LISTED ? kOutBufList : kOutBuf) : 0;  // waves of terms
   static constexpr int kEntries = kList<Real>;
   static constexpr int kListBytes = LISTED ? kEntries * int(sizeof(V)) : 0;
@@ -294,16 +294,22 @@ struct Bin64 {
 };
 
 // Occupancy target per kernel (waves per SIMD); the register budget is
-// 512 / target per lane, so every accumulator chunk must fit.  FP32 spin: the split
-// sums leave room for four, where a multiply-add issues every 2.5 cycles against 3.4
-// with three waves; the cartesian chunks and the FP64 sums have no room for more.
+// 512 / target per lane, so every accumulator chunk must fit: four waves for the 81
+// FP32 sums (or coefficients) of degree 8 and below, three for the 121 sums of degree
+// 10 and for the cartesian chunks of 91 to 99, two for FP64.  kSplit: sums or
+// coefficients in the halves of a wave, those of FP64 and the FP32 adjoint's of degree
+// 10, which then also runs at four waves.
 template <typename Real, int BASIS, bool ADJOINT, int DEG>
 struct Occ {
   static constexpr bool kF32 = std::is_same<Real, float>::value;
   static constexpr bool kSpinT = ADJOINT && kF32;
-  static constexpr int value = (BASIS == kBasisDeg)                ? (kF32 ? 4 : 2)
-                               : (BASIS == G3PCF_BASIS_CARTESIAN) ? (kF32 ? 3 : 2)
-                               : kF32 ? 4 : 2;
+  static constexpr bool kSplit = (BASIS == G3PCF_BASIS_SPIN || BASIS == kBasisSpinDeg) &&
+                                 (!kF32 || (ADJOINT && DEG == kDeg));
+  static constexpr int value = !kF32                               ? 2
+                               : (BASIS == kBasisDeg)              ? 4
+                               : (BASIS == G3PCF_BASIS_CARTESIAN) ? 3
+                               : DEG == kDeg && !kSplit            ? 3
+                                                                   : 4;
 };
 
 template <class... C>
@@ -331,9 +337,11 @@ struct PairKernel {
   // FP32 adjoint: terms wait in LDS for their atomic additions
   static constexpr bool kSpinT = Occ<Real, BASIS, ADJOINT, DEG>::kSpinT;
   static constexpr bool kSpin = BASIS == G3PCF_BASIS_SPIN || BASIS == kBasisSpinDeg;
+  // real and imaginary parts in the halves of a wave
+  static constexpr bool kSplit = Occ<Real, BASIS, ADJOINT, DEG>::kSplit;
   using CL = typename Chunks<Real, BASIS, DEG>::type;
   static constexpr bool kMulti = !ADJOINT && n_chunks(CL{}) > 1;
-  using Lds = WaveLds<Real, kMulti, kSpinT, kSpin, ADJOINT, kListed>;
+  using Lds = WaveLds<Real, kMulti, kSpinT, kSplit, ADJOINT, kListed>;
   // the waves of the occupancy target fit a CU's LDS (the waves' first items are
   // dealt out in advance, so all of them have to run at once)
   static_assert(sizeof(Lds) * 4 * Occ<Real, BASIS, ADJOINT, DEG>::value <= 160 * 1024, "LDS");
@@ -968,7 +976,7 @@ struct PairKernel {
         Chunk ch;
         ch.zero();
         auto add_unit = [&](Real ux, Real uy, Real uz, Real w) {
-          if constexpr (kSpin)
+          if constexpr (kSplit)
             ch.add(ux, uy, uz, w, W.xch(), lane);
           else
             ch.add(ux, uy, uz, w);
@@ -995,13 +1003,16 @@ struct PairKernel {
           if (first) got = g;
         }
         first = false;
-        if constexpr (kSpin) {
+        if constexpr (kSplit) {
           reduce_split(W, ch);
         } else {
-          // a cartesian chunk's sums (or the degenerate ones) after the last's
+          // a chunk's sums after the last's
           const int wl = lane_here();
-          fold_plain<Chunk::NT>(sums(W) + base, ch.acc, wl >> 4,
-                                ((wl >> 3) & 1) | ((wl >> 1) & 2), (wl & 3) == 0, wl);
+          const int row = wl >> 4, grp = ((wl >> 3) & 1) | ((wl >> 1) & 2);
+          const bool leader = (wl & 3) == 0;
+          fold_plain<Chunk::NT>(sums(W) + base, ch.acc, row, grp, leader, wl);
+          if constexpr (BASIS == kBasisSpinDeg)
+            fold_plain<Chunk::ND>(sums(W) + kSpinTerms, ch.deg, row, grp, leader, wl);
           base += Chunk::NT;
         }
       });
@@ -1023,7 +1034,7 @@ struct PairKernel {
       Real* coef = coef_stage(W);
       shell_coefficients(a, W, coef, row, b);
       wave_lds_fence();
-      SplitPoly<Real, DEG> poly;
+      std::conditional_t<kSplit, SplitPoly<Real, DEG>, SpinPoly<DEG>> poly;
       poly.load(coef, lane);
       wave_lds_fence();
       if constexpr (kSpinT) {
@@ -1044,7 +1055,11 @@ struct PairKernel {
                                  }
                                  Real ux, uy, uz;
                                  unit(P, e, ux, uy, uz);
-                                 const float v = poly.eval(ux, uy, uz, W.xch(), lane_here());
+                                 float v;
+                                 if constexpr (kSplit)
+                                   v = poly.eval(ux, uy, uz, W.xch(), lane_here());
+                                 else
+                                   v = poly.eval(ux, uy, uz);
                                  W.out()[nout + lane_here()] = make_int2(
                                      valid ? unpack_index(e.w) : -1, __float_as_int(wp * v));
                                  nout += kWave;
@@ -1322,11 +1337,10 @@ struct PairKernel {
   // fold into rows Re q, Re q + 1, Im q, Im q + 1; those of m = 0 fold by four.
   // Four such results share the last steps, and one lane of each quad stores.
   static __device__ __forceinline__ void reduce_split(Lds& W,
-                                                      SpinSplit<Real, DEG, BASIS == kBasisSpinDeg>& ch) {
-    using Chunk = SpinSplit<Real, DEG, BASIS == kBasisSpinDeg>;
+                                                      SpinSplit<DEG, BASIS == kBasisSpinDeg>& ch) {
+    using Chunk = SpinSplit<DEG, BASIS == kBasisSpinDeg>;
     constexpr int NP = Chunk::NP;
-    Real s0[DEG + 1], s[NP];
-    ch.unpack(s0, s);
+    const auto& s = ch.acc;
     Real* M = sums(W);
     const int lane = lane_here();
     const int row = lane >> 4;
@@ -1348,7 +1362,7 @@ struct PairKernel {
       const int q = g + 2 * grp + (row & 1);
       if (leader && q < NP) M[DEG + 1 + 2 * q + (row >> 1)] = tot;
     }
-    fold_plain<DEG + 1>(M, s0, row, grp, leader, lane);
+    fold_plain<DEG + 1>(M, ch.acc0, row, grp, leader, lane);
     if constexpr (BASIS == kBasisSpinDeg)
       fold_plain<Chunk::ND>(M + kSpinTerms, ch.deg, row, grp, leader, lane);
   }
