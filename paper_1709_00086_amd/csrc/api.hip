@@ -69,6 +69,7 @@ struct Ws {
   int64_t PB;   // primaries per pair-block
   int spill_cap;  // spill-list entries per wave (0: none)
   int parts;    // partial Gram products of a pair-block
+  int room;     // of several small catalogues' pair-blocks (batches), at least `parts`
   bool deg_fused;  // distinct: the pair kernel also collects the degenerate sums
   Grid grid;
   RowLayout lay;
@@ -116,7 +117,8 @@ Ws plan(const g3pcf_problem& p, int backward, int64_t pb_max = kPairBlockMax,
   w.A = take(size_t(w.PB) * w.lay.W * 8);
   // the compact layout's pair-blocks are one block of kZetaBlock rows
   w.parts = compact ? 4 : zeta_parts(w.lay, w.PB);
-  w.C = take(size_t(w.parts) * sum_wm2(w.lay) * 8);
+  w.room = compact ? w.parts : zeta_room(w.lay, w.PB);
+  w.C = take(size_t(w.room) * sum_wm2(w.lay) * 8);
   // degenerate triangles: per-shell Legendre sums and their per-workgroup partials
   const bool deg = !backward && p.distinct;
   w.degD = take(deg ? size_t(p.nbins) * (2 * p.lmax + 1) * 8 : 0);
@@ -215,10 +217,12 @@ struct Counters {
   long long nprim;
   unsigned long long inputs_hash;  // backward: fingerprint of its inputs (a_lm store check)
   long long first;                 // first row among its group's (catalogues of a batch)
-  long long pad[5];
+  long long parts;                 // and its Gram blocks
+  long long pad[4];
   XcdCounters xcd[kQueues];
 };
-static_assert(sizeof(Counters) == kCatStride * 8 && offsetof(Counters, first) == kCatFirst * 8,
+static_assert(sizeof(Counters) == kCatStride * 8 && offsetof(Counters, first) == kCatFirst * 8 &&
+                  offsetof(Counters, parts) == kCatParts * 8,
               "head of a catalogue of a group");
 static_assert(sizeof(Counters) <= kCountersBytes, "counters block");
 
@@ -426,8 +430,8 @@ int forward_tables(const g3pcf_problem& p) {
 }
 
 // List parts of `n` that one launch of the Gram products takes: so many that each
-// has four blocks of partials on average (16 catalogues of 8192: 4.08 ms of the
-// whole call with two, 3.67 with three or four, 3.70 with eight).
+// has four blocks of partials on average (27 regions of 3700 primaries in one
+// launch each: 5.3 ms of the whole call, in five launches 4.0).
 int lists_at_once(const Ws& w, int n) {
   const int most = std::max(1, std::min(kZetaLists, w.parts / 4));
   const int launches = (n + most - 1) / most;
@@ -535,6 +539,7 @@ int batch_group(const g3pcf_problem& p, const Ws& w, const int64_t* offsets, int
     k.first = offsets[c + m];
     k.n = offsets[c + m + 1] - k.first;
     k.cells_at = at;
+    k.parts = std::max(1, zeta_parts(w.lay, k.n));
     if (k.n > kBatchN || k.first + k.n - cats[0].first > w.PB) break;
     k.grid = make_grid(catalogue_of(p, k.first, k.n));
     at += k.grid.ncell + 1;
@@ -591,13 +596,16 @@ int forward_group(const g3pcf_problem& p, const Ws& w, void* ws, const BatchCat*
   z.row_begin = 0;
   z.lay = w.lay;
   z.C64 = at<double>(ws, w.C);
-  z.parts = w.parts;
   z.prec = p.zeta_prec;
   z.queue = head->xcd[0].queue;
   const size_t zlen = g3pcf_zeta_len(p.lmax, p.nbins);
-  const int lists = lists_at_once(w, m);
-  for (int c = 0; c < m; c += lists) {
-    z.lists = std::min(lists, m - c);
+  // every catalogue in the blocks that a call of its own would cut it into, so that
+  // its sums are the same bits; as many catalogues a launch as there is room for
+  for (int c = 0; c < m; c += z.lists) {
+    z.lists = z.parts = 0;
+    while (z.lists < std::min(kZetaLists, m - c) &&
+           (z.lists == 0 || z.parts + cats[c + z.lists].parts <= w.room))
+      z.parts += cats[c + z.lists++].parts;
     z.cats = &head[c].nprim;
     z.zeta = zeta + zlen * size_t(c);
     z.K = cats[c + z.lists - 1].first + cats[c + z.lists - 1].n - cats[c].first;

@@ -474,7 +474,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_cells_small(
 // A workgroup per catalogue of a batch.
 struct BatchGrids {
   GridDev g[kBatchGroup];
-  int first[kBatchGroup], n[kBatchGroup], ncell[kBatchGroup], cells_at[kBatchGroup];
+  int first[kBatchGroup], n[kBatchGroup], ncell[kBatchGroup], cells_at[kBatchGroup],
+      parts[kBatchGroup];
 };
 static_assert(sizeof(BatchGrids) + sizeof(SmallOut) <= 3584, "kernel arguments");
 
@@ -492,7 +493,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_cells_batch(
   cells_small<Real, In>(lds, pos + 3 * int64_t(at), w + at, b.n[c], b.g[c],
                         mask ? mask + at : nullptr, stage4 + at, pos4 + at, nan4, oc);
   // (after the barriers that follow the counters' clear)
-  if (threadIdx.x == 0) oc.nprim[kCatFirst] = at - b.first[0];
+  if (threadIdx.x == 0) {
+    oc.nprim[kCatFirst] = at - b.first[0];
+    oc.nprim[kCatParts] = b.parts[c];
+  }
 }
 
 __global__ void k_fill_int(int* p, int64_t count, int value) {
@@ -747,6 +751,7 @@ hipError_t launch_cells_batch(const g3pcf_problem& p, const BatchCat* cats, int 
     bg.n[c] = int(cats[c].n);
     bg.ncell[c] = int(cats[c].grid.ncell);
     bg.cells_at[c] = int(cats[c].cells_at);
+    bg.parts[c] = cats[c].parts;
   }
   SmallOut o{b.perm, b.wsort, b.cell_start, 0, flags, plist, head, reinterpret_cast<int*>(head), 0};
   auto go = [&](auto real, auto in) {

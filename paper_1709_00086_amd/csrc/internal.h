@@ -254,14 +254,16 @@ constexpr int kSmallN = 6144;
 // LDS, 104 KB here, set the limit.
 constexpr int kBatchN = 16384;
 constexpr int kBatchGroup = 16;
-// Head of a catalogue of a group: kCatStride 8-byte words, the first its primaries
-// and word kCatFirst its first row in the group; the rest its pair kernels' counters.
+// Head of a catalogue of a group: kCatStride 8-byte words, the first its primaries,
+// word kCatFirst its first row in the group and kCatParts the Gram blocks a call of its
+// own has room for; the rest its pair kernels' counters.
 constexpr int kCatStride = 72;
-constexpr int kCatFirst = 2;
+constexpr int kCatFirst = 2, kCatParts = 3;
 struct BatchCat {
   Grid grid;
   int64_t first, n;          // galaxies first..first + n - 1 of the call's catalogue
   int64_t cells_at;          // its cell_start in b.cell_start
+  int parts;                 // see kCatParts
 };
 hipError_t launch_cells_batch(const g3pcf_problem& p, const BatchCat* cats, int ncat,
                               const CellBufs& b, int* flags, int* plist, long long* head,
@@ -320,7 +322,8 @@ struct ZetaArgs {
   long long K;               // rows of the pair-block (upper bound)
   RowLayout lay;
   double* C64;               // [parts][sum W_m^2] per-block Gram products (FP64)
-  int parts;                 // blocks the partials have room for (>= K / kZetaBlock and `lists`)
+  int parts;                 // blocks the partials have room for (>= K / kZetaBlock and `lists`);
+                             // with `cats` the sum of theirs
   double* zeta;              // one a list part
   int prec;
   int* queue;                // the pair kernel's primary counters, cleared for its next launch
@@ -329,6 +332,8 @@ struct ZetaArgs {
 hipError_t launch_zeta_pairblock(const ZetaArgs& z, hipStream_t st);
 // Blocks (partial Gram products) of a pair-block of at most PB primaries.
 int zeta_parts(const RowLayout& L, long long PB);
+// Partials that a workspace holds for a pair-block of at most PB primaries.
+int zeta_room(const RowLayout& L, long long PB);
 
 // Adjoint helpers
 struct AdjArgs {

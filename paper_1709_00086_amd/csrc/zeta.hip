@@ -40,7 +40,8 @@ __device__ __forceinline__ long long valid_rows(const long long* nprim, const in
 // of kZetaRowsMin).  Only the device knows how many primaries there are (a mask
 // may leave few of the rows the launch covers, a region's part may hold any number
 // of them), so the blocks are dealt out here, one list part a lane; the workgroups
-// past the last block leave at once.
+// past the last block leave at once.  The catalogues of a batch are each cut as in a
+// call of their own.
 struct GramBlocks {
   int first, count;  // rows of the lane's list part
   int rows;          // rows of a block of the lane's list part
@@ -51,19 +52,27 @@ static_assert(kZetaLists <= kWave, "a lane per list part");
 __device__ __forceinline__ GramBlocks gram_blocks(const ZetaArgs& z) {
   const int lane = threadIdx.x % kWave;
   GramBlocks g{};
-  if (z.cats && lane < z.lists) {
-    g.count = int(z.cats[lane * kCatStride]);
-    g.first = int(z.cats[lane * kCatStride + kCatFirst]);
-  } else if (lane < z.lists) {
-    long long first;
-    g.count = int(valid_rows(z.nprim, z.range ? z.range + lane : nullptr, z.row_begin, z.K, first));
-    g.first = int(first);
-  }
-  int all = g.count;
+  // blocks that `all` rows are cut into
+  int share = z.parts - z.lists + 1, all;
+  if (z.cats) {
+    if (lane < z.lists) {
+      g.count = int(z.cats[lane * kCatStride]);
+      g.first = int(z.cats[lane * kCatStride + kCatFirst]);
+      share = int(z.cats[lane * kCatStride + kCatParts]);
+    }
+    all = g.count;
+  } else {
+    if (lane < z.lists) {
+      long long first;
+      g.count =
+          int(valid_rows(z.nprim, z.range ? z.range + lane : nullptr, z.row_begin, z.K, first));
+      g.first = int(first);
+    }
+    // sum of ceil(count / rows) <= ceil(all / rows) + lists - 1 <= parts
+    all = g.count;
 #pragma unroll
-  for (int o = 1; o < kWave; o *= 2) all += __shfl_xor(all, o);
-  // sum of ceil(count / rows) <= ceil(all / rows) + lists - 1 <= parts
-  const int share = z.parts - z.lists + 1;
+    for (int o = 1; o < kWave; o *= 2) all += __shfl_xor(all, o);
+  }
   auto whole = [](int r) {
     return max(r + kZetaRowsMin - 1, kZetaRowsMin) / kZetaRowsMin * kZetaRowsMin;
   };
@@ -546,12 +555,17 @@ RowLayout make_layout(int lmax, int nb) {
 // Gram products of 16 catalogues of 8192, one launch each, took 4.55 ms in blocks of
 // 4096 rows and 0.91 ms in 27 blocks; three or six workgroups a CU took the whole call
 // 3 to 8% longer, the sum over the blocks growing with them).
-int zeta_parts(const RowLayout& L, long long PB) {
+static int zeta_blocks(const RowLayout& L, long long PB, int times) {
   const long long tiles = make_mdims(L).mt[L.lmax + 1];
-  const long long fill = (2 * 256 + tiles - 1) / tiles;
+  const long long fill = times * ((2 * 256 + tiles - 1) / tiles);
   const long long least = (PB + kZetaBlock - 1) / kZetaBlock;
   return int(std::max(least, std::min(fill, (PB + kZetaRowsMin - 1) / kZetaRowsMin)));
 }
+
+int zeta_parts(const RowLayout& L, long long PB) { return zeta_blocks(L, PB, 1); }
+
+// Four times as many where a batch's small catalogues can fill them.
+int zeta_room(const RowLayout& L, long long PB) { return zeta_blocks(L, PB, 4); }
 
 // All blocks of a pair-block (z.K rows at most).
 hipError_t launch_zeta_pairblock(const ZetaArgs& z, hipStream_t st) {
