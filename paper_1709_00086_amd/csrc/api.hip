@@ -66,6 +66,7 @@ struct Ws {
       plist, scan, counters, spill, A, C, gsort, gsort32, mht, hrows, degD, degP, degX;
   size_t scan_bytes;
   size_t total;
+  int64_t blocks_at;  // see CellBufs::blocks
   int64_t PB;   // primaries per pair-block
   int spill_cap;  // spill-list entries per wave (0: none)
   int parts;    // partial Gram products of a pair-block
@@ -102,11 +103,13 @@ Ws plan(const g3pcf_problem& p, int backward, int64_t pb_max = kPairBlockMax,
   w.perm = take(size_t(n) * 4);
   w.tmp_perm = take(size_t(n) * 4);
   w.rkey = take(size_t(n) * 4);
-  w.rhist = take(size_t(2 * nhist) * 4);
+  // (also the heads of a batch's group of catalogues)
+  w.rhist = take(std::max(size_t(2 * nhist) * 4, size_t(kBatchGroup) * kCatStride * 8));
   w.wsort = take(size_t(n) * 8);
   w.cell_start = take(size_t(ncell + 1) * 4);
   w.cell_count = take(size_t(ncell + 1) * 4);
   w.flags = take(size_t(2 * (n + 1)) * 4);
+  w.blocks_at = n + 1;
   w.plist = take(size_t(n) * 4);
   w.scan = take(w.scan_bytes);
   w.counters = take(kCountersBytes);
@@ -218,11 +221,14 @@ struct Counters {
   unsigned long long inputs_hash;  // backward: fingerprint of its inputs (a_lm store check)
   long long first;                 // first row among its group's (catalogues of a batch)
   long long parts;                 // and its Gram blocks
-  long long pad[4];
+  GroupTable groups;
+  int pad[4];
   XcdCounters xcd[kQueues];
 };
 static_assert(sizeof(Counters) == kCatStride * 8 && offsetof(Counters, first) == kCatFirst * 8 &&
-                  offsetof(Counters, parts) == kCatParts * 8,
+                  offsetof(Counters, parts) == kCatParts * 8 &&
+                  offsetof(Counters, groups) == kCatGroups * 8 &&
+                  offsetof(Counters, xcd) % 64 == 0,
               "head of a catalogue of a group");
 static_assert(sizeof(Counters) <= kCountersBytes, "counters block");
 
@@ -238,6 +244,9 @@ CellBufs cell_bufs(const Ws& w, void* ws) {
   b.perm = at<int>(ws, w.perm);
   b.hist = at<int>(ws, w.rhist);
   b.wsort = at<double>(ws, w.wsort);
+  // (the second half of the flags is free until the primary list)
+  b.blocks = at<int>(ws, w.flags) + w.blocks_at;
+  b.groups = &at<Counters>(ws, w.counters)->groups;
   b.scan_tmp = at<void>(ws, w.scan);
   b.scan_bytes = w.scan_bytes;
   return b;
@@ -252,53 +261,9 @@ int stage_catalogue(const g3pcf_problem& p, const Ws& w, void* ws, const Clears&
   Counters* c = at<Counters>(ws, w.counters);
   Primaries pr{p.primary_mask, primaries ? at<int>(ws, w.flags) : nullptr, at<int>(ws, w.plist),
                &c->nprim, reinterpret_cast<int*>(c), int(sizeof(Counters) / 4)};
-  const hipError_t e = launch_cells(p, w.grid, b, pr, z, fp64, st);
+  const hipError_t e = launch_cells(p, w.grid, shell_plan(p, w.grid), b, pr, z, fp64, st);
   if (e != hipSuccess) return hip_fail(e, "cell list");
   return G3PCF_OK;
-}
-
-// Neighbouring shells whose expected pairs (at the catalogue's mean density)
-// fit the list together make one group: a search costs a wave about 10 us of
-// waiting however little it finds (16 catalogues of 8192 with 274 pairs a
-// primary: 5.5 ms of pair kernels shell by shell, 2.6 ms in groups; FP64 step of
-// 4096 with 137 pairs: 422 and 250 us).  Not where every shell of every primary
-// can have a wave of its own.  A group of one shell is searched into the list
-// only for the cartesian basis, whose later chunks then read it again.  Depends
-// on the catalogue and the settings alone, so that every entry point sums a
-// shell's pairs in the same order.
-void shell_groups(const g3pcf_problem& p, PairArgs& a) {
-  const bool cart = p.basis == G3PCF_BASIS_CARTESIAN;
-  const bool fp64 = p.pair_prec == G3PCF_PREC_FP64;
-  const double most = fp64 ? kListMean64 : kListMean32;
-  const double dr = p.rmax / p.nbins;
-  const double per = double(p.n) / (p.box[0] * p.box[1] * p.box[2]) * 4.0 / 3.0 * M_PI * dr * dr * dr;
-  auto expected = [&](int b0, int b1) {  // shells b0..b1
-    return per * (std::pow(b1 + 1.0, 3) - std::pow(double(b0), 3));
-  };
-  // nor on a tight axis (few cells, and the kernels would double)
-  const bool tight = a.tight[0] || a.tight[1] || a.tight[2];
-  bool single = p.n * p.nbins <= kPairWaves || tight;
-  if (!single) {
-    // the second launch costs each primary about as much as two searches
-    int searches = 0;
-    for (int b = 0, e; b < p.nbins; b = e + 1, ++searches)
-      for (e = b; e + 1 < p.nbins && expected(b, e + 1) <= most;) ++e;
-    single = p.nbins - searches < kListSaves && !cart;
-  }
-  a.ngroup = a.nsingle = 0;
-  for (int lists = 0; lists < 2; ++lists) {
-    for (int b = 0; b < p.nbins;) {
-      int e = b;  // last shell of the group
-      while (!single && e + 1 < p.nbins && expected(b, e + 1) <= most) ++e;
-      if (lists == int(e > b || (cart && !tight && expected(b, e) <= most))) {
-        a.group_lo[a.ngroup] = b;
-        a.group_hi[a.ngroup++] = e;
-      }
-      b = e + 1;
-    }
-    if (lists == 0) a.nsingle = a.ngroup;
-  }
-  a.primary_terms = 1;
 }
 
 int pair_args(const g3pcf_problem& p, const Ws& w, void* ws, PairArgs& a) {
@@ -336,7 +301,10 @@ int pair_args(const g3pcf_problem& p, const Ws& w, void* ws, PairArgs& a) {
     a.r2_lo[b] = (b == 0) ? 0.0f : std::nextafter(t0, 0.0f);
     a.r2_hi[b] = (b + 1 == p.nbins) ? float(p.rmax * p.rmax) : float(e1 * e1);
   }
-  shell_groups(p, a);
+  const ShellPlan sp = shell_plan(p, w.grid);
+  a.lists = sp.lists;
+  a.groups = &c->groups;
+  a.list_mean = sp.most;
   a.nbins = p.nbins;
   a.lmax = p.lmax;
   a.los = p.los;
@@ -523,15 +491,14 @@ g3pcf_problem catalogue_of(const g3pcf_problem& p, int64_t first, int64_t n) {
 }
 
 // How many catalogues from c on go through forward_group together (in cats; 0 or
-// 1: not in a group): small ones, whose rows, cell starts and heads the workspace
-// of the whole call holds beside each other.  Not where the counts are asked for
+// 1: not in a group): small ones, whose rows and cell starts the workspace of the
+// whole call holds beside each other.  Not where the counts are asked for
 // (a wait per catalogue) or the degenerate triangles are taken out.
 int batch_group(const g3pcf_problem& p, const Ws& w, const int64_t* offsets, int ncat, int c,
                 BatchCat* cats) {
   if (p.pairs_out || p.distinct) return 0;
   const int64_t cells = int64_t(w.cell_count - w.cell_start) / 4 + w.grid.ncell + 1;
-  const int64_t heads = int64_t(2 * radix_hist_ints(p.n)) * 4 / int64_t(sizeof(Counters));
-  const int most = int(std::min<int64_t>({kBatchGroup, heads, ncat - c}));
+  const int most = std::min(kBatchGroup, ncat - c);
   int m = 0;
   int64_t at = 0;
   for (; m < most; ++m) {
@@ -541,7 +508,9 @@ int batch_group(const g3pcf_problem& p, const Ws& w, const int64_t* offsets, int
     k.cells_at = at;
     k.parts = std::max(1, zeta_parts(w.lay, k.n));
     if (k.n > kBatchN || k.first + k.n - cats[0].first > w.PB) break;
-    k.grid = make_grid(catalogue_of(p, k.first, k.n));
+    const g3pcf_problem q = catalogue_of(p, k.first, k.n);
+    k.grid = make_grid(q);
+    k.plan = shell_plan(q, k.grid);
     at += k.grid.ncell + 1;
     if (k.grid.ncell > 4 * kBatchN || at > cells) break;
   }

@@ -88,6 +88,68 @@ __device__ __forceinline__ typename Vec4<Real>::T staged(const In* __restrict__ 
   return v4;
 }
 
+// ---- groups of shells ----
+// Quotients of small numbers: x / d with inv about 1 / d, exact below 2^16 (an integer
+// division is some thirty instructions).
+__device__ __forceinline__ float about_inverse(int d) { return __builtin_amdgcn_rcpf(float(d)); }
+__device__ __forceinline__ int quotient(int x, float inv) { return int((float(x) + 0.5f) * inv); }
+
+__device__ __forceinline__ float wave_total(float v) {
+  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
+// The table, by one wave: lane b finds how far a group from shell b on may reach, then
+// the groups follow one another.  A galaxy shares its block with density x volume +
+// excess others on average, and its run of cells too: the density of the footprint,
+// and what clusters smaller than a run add.  blocks, runs: these averages times n.
+__device__ __forceinline__ void form_groups(const ShellPlan& sp, float blocks, float runs,
+                                            GroupTable* out) {
+  const int lane = threadIdx.x % kWave;
+  const float in_block = blocks / sp.n, in_run = runs / sp.n;
+  // (cells wider than R_max: a block is a run, and nothing is known)
+  const float crowd = sp.in_block > 1.5f * sp.in_run
+                          ? fmaxf(1.0f, (in_block - in_run) / (sp.in_block - sp.in_run))
+                          : 1.0f;
+  const float density = sp.density * crowd;
+  const float excess = fmaxf(0.0f, in_run - crowd * sp.in_run);
+  auto fits = [&](int b, int last) {  // the pairs in shells b..last
+    const float u = float(last + 1), v = float(b);
+    return density * (u * u * u - v * v * v) + (b == 0 ? excess : 0.0f) <= sp.most;
+  };
+  int e = lane;
+  while (e + 1 < sp.nbins && fits(lane, e + 1)) ++e;
+  // a shell of its own goes through the list where that leaves nothing to the second
+  // launch, or for the cartesian basis, whose later chunks then read it again
+  const bool dense = !fits(sp.nbins - 1, sp.nbins - 1) || !fits(0, 0);
+  const bool listed = e > lane || ((sp.cart || !dense) && fits(lane, lane));
+  int searches = 0;
+  for (int b = 0; b < sp.nbins; b = __builtin_amdgcn_readlane(e, b) + 1) ++searches;
+  // (whole clusters of galaxies come and go in the shells of one primary and another:
+  // lists that hold the mean overflow)
+  const bool single = !sp.cart && (sp.nbins - searches < (dense ? kListSavesDense : kListSaves) ||
+                                   excess > kListClusters);
+  if (single) e = lane;
+  int at = 0, nsingle = 0;
+  for (int lists = 0; lists < 2; ++lists) {
+    for (int b = 0; b < sp.nbins;) {
+      const int last = __builtin_amdgcn_readlane(e, b);
+      if (__builtin_amdgcn_readlane(int(listed && !single), b) == lists) {
+        if (lane == 0) out->range[at] = b | last << 8;
+        ++at;
+      }
+      b = last + 1;
+    }
+    if (lists == 0) nsingle = at;
+  }
+  if (lane == 0) {
+    out->ngroup = at;
+    out->nsingle = nsingle;
+    out->density = density;
+    out->excess = excess;
+  }
+}
+
 template <typename Real, typename In>
 __global__ void k_assign(const In* __restrict__ pos, const double* __restrict__ w, int64_t n,
                          GridDev g, typename Vec4<Real>::T* __restrict__ out4,
@@ -192,12 +254,87 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_scatter(
   }
 }
 
+// What the table follows from: the galaxies of the blocks of cells, a wave a block and a
+// row of cells a lane, and those of the runs of cells in some rows, a wave a row and a
+// run a lane (C and C (C - 1) summed over a row's runs).  (Atomic counts as the cells
+// are assigned took 7 us for 16384 galaxies, 26 where they crowd into a fifth of the
+// blocks; these take about two.)
+__device__ __forceinline__ void count_blocks(const ShellPlan& sp,
+                                             const int* __restrict__ cell_start,
+                                             int* __restrict__ blocks) {
+  const int waves = int(gridDim.x * blockDim.x / kWave), lane = threadIdx.x % kWave;
+  const int wave = int((blockIdx.x * blockDim.x + threadIdx.x) / kWave);
+  for (int b = wave; b < sp.blocks; b += waves) {
+    const int row = b / sp.count[0], bx = b - row * sp.count[0];
+    const int bz = row / sp.count[1], by = row - bz * sp.count[1];
+    const int x0 = bx * sp.side[0], x1 = min(x0 + sp.side[0], sp.nc[0]);
+    const int y0 = by * sp.side[1], ny = min(sp.side[1], sp.nc[1] - y0);
+    const int z0 = bz * sp.side[2], nz = min(sp.side[2], sp.nc[2] - z0);
+    int c = 0;
+    for (int r = lane; r < ny * nz; r += kWave) {
+      const int z = r / ny;
+      const int* row0 = cell_start + ((z0 + z) * sp.nc[1] + y0 + r - z * ny) * sp.nc[0];
+      c += row0[x1] - row0[x0];
+    }
+    for (int off = kWave / 2; off > 0; off >>= 1) c += __shfl_xor(c, off);
+    if (lane == 0) blocks[b] = c;
+  }
+  int* sums = blocks + kCrowdBlocks;
+  const int rows = sp.nc[1] * sp.nc[2];
+  for (int i = wave; i < sp.rows; i += waves) {
+    const int* row0 = cell_start + int64_t(i) * rows / sp.rows * sp.nc[0];
+    float c1 = 0.0f, c2 = 0.0f;
+    for (int x = lane * sp.run; x < sp.nc[0]; x += kWave * sp.run) {
+      const float c = float(row0[min(x + sp.run, sp.nc[0])] - row0[x]);
+      c1 += c;
+      c2 += c * (c - 1.0f);
+    }
+    c1 = wave_total(c1);
+    c2 = wave_total(c2);
+    if (lane == 0) {
+      sums[2 * i] = __float_as_int(c1);
+      sums[2 * i + 1] = __float_as_int(c2);
+    }
+  }
+}
+
+// The table from these, in the last workgroup (of 256) of a launch that has one more
+// for it; true there.
+__device__ __forceinline__ bool groups_workgroup(const ShellPlan& sp,
+                                                 const int* __restrict__ blocks,
+                                                 GroupTable* __restrict__ groups) {
+  if (!sp.lists || blockIdx.x + 1 < gridDim.x) return false;
+  __shared__ float part[3][256 / kWave];
+  float v[3] = {0.0f, 0.0f, 0.0f};
+  for (int i = threadIdx.x; i < sp.blocks; i += 256) {
+    const float c = float(blocks[i]);
+    v[0] += c * (c - 1.0f);
+  }
+  const int* sums = blocks + kCrowdBlocks;
+  for (int i = threadIdx.x; i < sp.rows; i += 256) {
+    v[1] += __int_as_float(sums[2 * i]);
+    v[2] += __int_as_float(sums[2 * i + 1]);
+  }
+  for (int k = 0; k < 3; ++k) {
+    v[k] = wave_total(v[k]);
+    if (threadIdx.x % kWave == 0) part[k][threadIdx.x / kWave] = v[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    for (int k = 0; k < 3; ++k) v[k] = part[k][0] + part[k][1] + part[k][2] + part[k][3];
+    form_groups(sp, v[0], v[2] / fmaxf(v[1], 1.0f) * sp.n, groups);
+  }
+  return true;
+}
+
 // Cell-order arrays from the sorted original indices, and the kSentinel NaN
-// entries after them.
+// entries after them; the blocks' counts, where shells may be searched together.
 template <typename V4>
-__global__ void k_gather_sorted(const V4* __restrict__ in4, const int* __restrict__ perm,
-                                int64_t n, const double* __restrict__ w,
-                                V4* __restrict__ out4, double* __restrict__ wsort) {
+__global__ __launch_bounds__(256) void k_gather_sorted(
+    const V4* __restrict__ in4, const int* __restrict__ perm, int64_t n,
+    const double* __restrict__ w, V4* __restrict__ out4, double* __restrict__ wsort, ShellPlan sp,
+    const int* __restrict__ cell_start, int* __restrict__ blocks) {
+  if (sp.lists) count_blocks(sp, cell_start, blocks);
   const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (s >= n) {
     if (s < n + kSentinel) {
@@ -213,8 +350,11 @@ __global__ void k_gather_sorted(const V4* __restrict__ in4, const int* __restric
 }
 
 // primary flag of the galaxy in cell-order slot s
-__global__ void k_primary_flags(const uint8_t* __restrict__ mask, const int* __restrict__ perm,
-                                int64_t n, int* __restrict__ flags) {
+__global__ __launch_bounds__(256) void k_primary_flags(
+    const uint8_t* __restrict__ mask, const int* __restrict__ perm, int64_t n,
+    int* __restrict__ flags, ShellPlan sp, const int* __restrict__ blocks,
+    GroupTable* __restrict__ groups) {
+  if (groups_workgroup(sp, blocks, groups)) return;
   const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (s > n) return;
   flags[s] = s < n && mask[perm[s]] != 0 ? 1 : 0;
@@ -250,13 +390,21 @@ __global__ void k_region_starts(const int* __restrict__ keys, int64_t n, int nre
 }
 
 // every galaxy a primary
-__global__ void k_primary_all(int* __restrict__ flags, int64_t n, int* __restrict__ plist,
-                              long long* __restrict__ nprim) {
+__global__ __launch_bounds__(256) void k_primary_all(
+    int* __restrict__ flags, int64_t n, int* __restrict__ plist, long long* __restrict__ nprim,
+    ShellPlan sp, const int* __restrict__ blocks, GroupTable* __restrict__ groups) {
+  if (groups_workgroup(sp, blocks, groups)) return;
   const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (s > n) return;
   flags[s] = 0;
   if (s == n) *nprim = n;
   else plist[s] = int(s);
+}
+
+// the table alone
+__global__ __launch_bounds__(256) void k_groups(ShellPlan sp, const int* __restrict__ blocks,
+                                                GroupTable* __restrict__ groups) {
+  groups_workgroup(sp, blocks, groups);
 }
 
 // (the flags are left zero)
@@ -294,20 +442,26 @@ struct SmallOut {
   long long* nprim;
   int* counters;             // zeroed
   int counter_words;
+  GroupTable* groups;
 };
 
 template <int N>
 struct SmallLds {
   unsigned short key[N];
   unsigned short val[2][N];
-  unsigned short hist[kSmallWaves][kRadixDigits];  // then running offsets
+  union {
+    unsigned short hist[kSmallWaves][kRadixDigits];  // then running offsets
+    int blocks[kCrowdBlocks];                        // before them
+  };
   int wtot[kSmallWaves];
+  float wsum[2][kSmallWaves];                      // the table's sums
 };
 
 // One workgroup's catalogue of n <= N galaxies; the NaN entries go to nan4.
 template <typename Real, typename In, int N>
 __device__ __forceinline__ void cells_small(SmallLds<N>& lds, const In* __restrict__ pos,
                                             const double* __restrict__ w, int n, const GridDev& g,
+                                            const ShellPlan& sp,
                                             const uint8_t* __restrict__ mask,
                                             typename Vec4<Real>::T* stage4,
                                             typename Vec4<Real>::T* __restrict__ pos4,
@@ -319,11 +473,35 @@ __device__ __forceinline__ void cells_small(SmallLds<N>& lds, const In* __restri
   auto& wtot = lds.wtot;
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   for (int i = tid; i < o.counter_words; i += kSmallThreads) o.counters[i] = 0;
+  const float per_x = about_inverse(sp.nc[0]), per_y = about_inverse(sp.nc[1]);
+  if (sp.lists) {
+    for (int i = tid; i < sp.blocks; i += kSmallThreads) lds.blocks[i] = 0;
+    __syncthreads();
+  }
+  const float bx = about_inverse(sp.side[0]), by = about_inverse(sp.side[1]),
+              bz = about_inverse(sp.side[2]);
   for (int i = tid; i < n; i += kSmallThreads) {
     int c;
     stage4[i] = staged<Real, In>(pos, w, i, g, c);
     key[i] = (unsigned short)c;
     val[0][i] = (unsigned short)i;
+    if (sp.lists) {
+      const int row = quotient(c, per_x), z = quotient(row, per_y);
+      const int b = (quotient(z, bz) * sp.count[1] + quotient(row - z * sp.nc[1], by)) *
+                        sp.count[0] + quotient(c - row * sp.nc[0], bx);
+      atomicAdd(&lds.blocks[b], 1);
+    }
+  }
+  if (sp.lists) {
+    __syncthreads();
+    float sum = 0.0f;
+    for (int i = tid; i < sp.blocks; i += kSmallThreads) {
+      const float c = float(lds.blocks[i]);
+      sum += c * (c - 1.0f);
+    }
+    sum = wave_total(sum);
+    if (lane == 0) lds.wsum[0][wave] = sum;
+    __syncthreads();
   }
   const int chunk = (n + kSmallThreads - 1) / kSmallThreads * kWave;  // per wave
   const int c0 = wave * chunk, c1 = min(n, c0 + chunk);
@@ -407,10 +585,33 @@ __device__ __forceinline__ void cells_small(SmallLds<N>& lds, const In* __restri
       nan4[s - n] = V4{nan, nan, nan, nan};
     }
   }
+  auto cell_at = [&](int s) { return int(key[order[s]]); };
+  if (sp.lists) {
+    // pairs that share a run of cells: from each galaxy on, at most a wave of them
+    const int per_row = (sp.nc[0] + sp.run - 1) / sp.run;
+    const float per_run = about_inverse(sp.run);
+    auto run_at = [&](int s) {
+      const int c = cell_at(s), row = quotient(c, per_x);
+      return row * per_row + quotient(c - row * sp.nc[0], per_run);
+    };
+    float sum = 0.0f;
+    for (int s = tid; s < n; s += kSmallThreads) {
+      const int r = run_at(s), end = min(n, s + kWave);
+      for (int t = s + 1; t < end && run_at(t) == r; ++t) sum += 2.0f;
+    }
+    sum = wave_total(sum);
+    if (lane == 0) lds.wsum[1][wave] = sum;
+    __syncthreads();
+    if (wave == kSmallWaves - 1) {
+      float v[2] = {0.0f, 0.0f};
+      for (int u = 0; u < kSmallWaves; ++u)
+        for (int k = 0; k < 2; ++k) v[k] += lds.wsum[k][u];
+      form_groups(sp, v[0], v[1], o.groups);
+    }
+  }
   // cell_start[c] = galaxies in cells below c; a run of cells per thread, the
   // next start found by doubling steps
   const int per = (o.ncell + 1 + kSmallThreads - 1) / kSmallThreads;
-  auto cell_at = [&](int s) { return int(key[order[s]]); };
   int s = 0;
   for (int c = tid * per; c < min((tid + 1) * per, o.ncell + 1); ++c) {
     int step = c == tid * per ? n : 1;  // the thread's first cell: a plain bisection
@@ -457,7 +658,7 @@ __device__ __forceinline__ void cells_small(SmallLds<N>& lds, const In* __restri
 
 template <typename Real, typename In>
 __global__ __launch_bounds__(kSmallThreads) void k_cells_small(
-    const In* __restrict__ pos, const double* __restrict__ w, int n, GridDev g,
+    const In* __restrict__ pos, const double* __restrict__ w, int n, GridDev g, ShellPlan sp,
     const uint8_t* __restrict__ mask, typename Vec4<Real>::T* stage4,
     typename Vec4<Real>::T* __restrict__ pos4, SmallOut o, Clears z) {
   __shared__ SmallLds<kSmallN> lds;
@@ -468,12 +669,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_cells_small(
       for (int64_t i = t; i < z.words[k]; i += step) z.at[k][i] = 0;
     return;
   }
-  cells_small<Real, In>(lds, pos, w, n, g, mask, stage4, pos4, pos4 + n, o);
+  cells_small<Real, In>(lds, pos, w, n, g, sp, mask, stage4, pos4, pos4 + n, o);
 }
 
 // A workgroup per catalogue of a batch.
 struct BatchGrids {
   GridDev g[kBatchGroup];
+  ShellPlan plan[kBatchGroup];
   int first[kBatchGroup], n[kBatchGroup], ncell[kBatchGroup], cells_at[kBatchGroup],
       parts[kBatchGroup];
 };
@@ -489,8 +691,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_cells_batch(
   const int at = b.first[c];
   SmallOut oc{o.perm + at,  o.wsort + at, o.cell_start + b.cells_at[c], b.ncell[c],
               o.flags + at, o.plist + at, o.nprim + c * kCatStride,
-              o.counters + c * kCatStride * 2, kCatStride * 2};
-  cells_small<Real, In>(lds, pos + 3 * int64_t(at), w + at, b.n[c], b.g[c],
+              o.counters + c * kCatStride * 2, kCatStride * 2,
+              reinterpret_cast<GroupTable*>(o.nprim + c * kCatStride + kCatGroups)};
+  cells_small<Real, In>(lds, pos + 3 * int64_t(at), w + at, b.n[c], b.g[c], b.plan[c],
                         mask ? mask + at : nullptr, stage4 + at, pos4 + at, nan4, oc);
   // (after the barriers that follow the counters' clear)
   if (threadIdx.x == 0) {
@@ -690,6 +893,71 @@ Grid make_grid(const g3pcf_problem& p) {
   return g;
 }
 
+// Which shells may be searched together.  Neighbouring shells whose expected pairs fit
+// the list make one group: a search costs a wave about 10 us of waiting however little
+// it finds (16 catalogues of 8192 with 274 pairs a primary: 5.5 ms of pair kernels shell
+// by shell, 2.6 ms in groups; FP64 step of 4096 with 137 pairs: 422 and 250 us).  Not
+// where every shell of every primary can have a wave of its own.  The pairs expected
+// follow from the density around the galaxies, which is the mean over the declared box
+// or (a footprint that fills part of it, clusters) more: the device measures it with
+// the cell list and forms the groups (see form_groups).  Taking the mean as it stands,
+// lists overflowed for most primaries of such catalogues, and everything was searched
+// twice (16384 galaxies in the lowest fifth of their box, 849 pairs, l_max 4: 630 us of
+// the call; shell by shell 411).  Where even the mean leaves no groups worth a second
+// launch, nothing is measured.  Depends on the catalogue and the settings alone, so
+// that every entry point sums a shell's pairs in the same order.
+ShellPlan shell_plan(const g3pcf_problem& p, const Grid& g) {
+  ShellPlan sp{};
+  sp.nbins = p.nbins;
+  sp.cart = p.basis == G3PCF_BASIS_CARTESIAN;
+  const double most = p.pair_prec == G3PCF_PREC_FP64 ? kListMean64 : kListMean32;
+  const double dr = p.rmax / p.nbins;
+  const double density =
+      double(p.n) / (p.box[0] * p.box[1] * p.box[2]) * 4.0 / 3.0 * M_PI * dr * dr * dr;
+  auto cube = [](double x) { return x * x * x; };
+  int searches = 0;
+  for (int b = 0, e; b < p.nbins; b = e + 1, ++searches)
+    for (e = b; e + 1 < p.nbins && density * (cube(e + 2) - cube(b)) <= most;) ++e;
+  const int least =
+      density * (cube(p.nbins) - cube(p.nbins - 1.0)) > most ? kListSavesDense : kListSaves;
+  // nor on a tight axis (few cells, and the kernels would double)
+  if (p.n * p.nbins <= kPairWaves || g.tight[0] || g.tight[1] || g.tight[2] ||
+      (sp.cart ? density > most : p.nbins - searches < least))
+    return sp;
+  sp.lists = 1;
+  sp.density = float(density);
+  // (a uniform catalogue's measured density is a few per cent off its mean)
+  sp.most = float(kListSlack * most);
+  int64_t count[3];
+  for (int a = 0; a < 3; ++a)
+    sp.side[a] = std::max(1, std::min(g.nc[a], int(std::lround(p.rmax * g.inv_s[a]))));
+  for (;;) {
+    for (int a = 0; a < 3; ++a) count[a] = (g.nc[a] + sp.side[a] - 1) / sp.side[a];
+    if (count[0] * count[1] * count[2] <= kCrowdBlocks) break;
+    for (int a = 0; a < 3; ++a) sp.side[a] += std::max(1, sp.side[a] / 8);
+  }
+  // chances of two points of the box to share a block, and a run of cells
+  auto share = [](int side, int nc) {
+    const int whole = nc / side, rest = nc % side;
+    return (double(whole) * side * side + double(rest) * rest) / (double(nc) * nc);
+  };
+  double in_block = 1.0;
+  for (int a = 0; a < 3; ++a) {
+    in_block *= share(sp.side[a], g.nc[a]);
+    sp.nc[a] = g.nc[a];
+    sp.count[a] = int(count[a]);
+  }
+  // (runs of R_max / 8, as long as a cell is wide unless the grid is coarse)
+  sp.run = std::max(1, int(std::lround(0.125 * p.rmax * g.inv_s[0])));
+  const double in_run = share(sp.run, g.nc[0]) / (double(g.nc[1]) * g.nc[2]);
+  sp.blocks = sp.count[0] * sp.count[1] * sp.count[2];
+  sp.rows = std::min(kCrowdBlocks, g.nc[1] * g.nc[2]);
+  sp.n = float(p.n);
+  sp.in_block = float(double(p.n - 1) * in_block);
+  sp.in_run = float(double(p.n - 1) * in_run);
+  return sp;
+}
+
 size_t radix_hist_ints(int64_t n) {
   const int64_t ntiles = std::max<int64_t>(1, (n + kRadixTile - 1) / kRadixTile);
   return size_t(ntiles) * kRadixDigits;
@@ -747,13 +1015,15 @@ hipError_t launch_cells_batch(const g3pcf_problem& p, const BatchCat* cats, int 
   BatchGrids bg{};
   for (int c = 0; c < ncat; ++c) {
     bg.g[c] = grid_dev(cats[c].grid);
+    bg.plan[c] = cats[c].plan;
     bg.first[c] = int(cats[c].first);
     bg.n[c] = int(cats[c].n);
     bg.ncell[c] = int(cats[c].grid.ncell);
     bg.cells_at[c] = int(cats[c].cells_at);
     bg.parts[c] = cats[c].parts;
   }
-  SmallOut o{b.perm, b.wsort, b.cell_start, 0, flags, plist, head, reinterpret_cast<int*>(head), 0};
+  SmallOut o{b.perm, b.wsort, b.cell_start, 0,      flags,
+             plist,  head,    reinterpret_cast<int*>(head), 0, nullptr};
   auto go = [&](auto real, auto in) {
     using Real = decltype(real);
     using In = decltype(in);
@@ -773,14 +1043,39 @@ hipError_t launch_cells_batch(const g3pcf_problem& p, const BatchCat* cats, int 
   return hipGetLastError();
 }
 
-hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b,
-                        const Primaries& pr, Clears z, int fp64, hipStream_t st) {
+// Primary list (cell order): galaxies in the mask (NULL: all).  Leaves flags zero
+// (see PairArgs::overflow).  Also forms the table of groups.
+static hipError_t launch_primaries(const uint8_t* mask, int64_t n, const ShellPlan& sp,
+                                   const CellBufs& b, int* flags, int* plist, long long* nprim,
+                                   hipStream_t st) {
+  const unsigned nb = blocks_for(n + 1, 256), table = sp.lists ? 1 : 0;
+  if (!mask) {
+    hipLaunchKernelGGL(k_primary_all, dim3(nb + table), dim3(256), 0, st, flags, n, plist, nprim,
+                       sp, b.blocks, b.groups);
+    return hipGetLastError();
+  }
+  // (the blocks' counts are read before the scan writes over them)
+  hipLaunchKernelGGL(k_primary_flags, dim3(nb + table), dim3(256), 0, st, mask, b.perm, n, flags,
+                     sp, b.blocks, b.groups);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // positions: exclusive scan into flags + (n + 1)
+  int* pos = flags + (n + 1);
+  if ((e = launch_scan(flags, pos, n + 1, b.scan_tmp, b.scan_bytes, st)) != hipSuccess)
+    return e;
+  hipLaunchKernelGGL(k_primary_list, dim3(nb), dim3(256), 0, st, flags, pos, n, plist, nprim);
+  return hipGetLastError();
+}
+
+hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const ShellPlan& sp,
+                        const CellBufs& b, const Primaries& pr, Clears z, int fp64,
+                        hipStream_t st) {
   const int64_t n = p.n;
   const GridDev gd = grid_dev(g);
   // n <= kSmallN galaxies: one launch (the grid has at most 4 n cells)
   if (n > 0 && n <= kSmallN && g.ncell <= 4 * kSmallN) {
     SmallOut o{b.perm, b.wsort, b.cell_start, int(g.ncell), pr.flags, pr.plist, pr.nprim,
-               pr.counters, pr.counter_words};
+               pr.counters, pr.counter_words, b.groups};
     int64_t words = 0;
     for (int k = 0; k < z.count; ++k) words += z.words[k];
     const unsigned grid = 1u + unsigned(std::min<int64_t>(255, blocks_for(words, kSmallThreads * 4)));
@@ -789,7 +1084,7 @@ hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b
       using In = decltype(in);
       using V = typename Vec4<Real>::T;
       hipLaunchKernelGGL((k_cells_small<Real, In>), dim3(grid), dim3(kSmallThreads), 0, st,
-                         static_cast<const In*>(p.pos), p.w, int(n), gd, pr.mask,
+                         static_cast<const In*>(p.pos), p.w, int(n), gd, sp, pr.mask,
                          static_cast<V*>(b.stage4), static_cast<V*>(b.pos4), o, z);
     };
     if (fp64) {
@@ -839,14 +1134,18 @@ hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b
   if (fp64)
     hipLaunchKernelGGL((k_gather_sorted<double4>), dim3(ng), dim3(256), 0, st,
                        static_cast<const double4*>(b.stage4), b.perm, n, p.w,
-                       static_cast<double4*>(b.pos4), b.wsort);
+                       static_cast<double4*>(b.pos4), b.wsort, sp, b.cell_start, b.blocks);
   else
     hipLaunchKernelGGL((k_gather_sorted<float4>), dim3(ng), dim3(256), 0, st,
                        static_cast<const float4*>(b.stage4), b.perm, n, p.w,
-                       static_cast<float4*>(b.pos4), b.wsort);
-  if ((e = hipGetLastError()) != hipSuccess || !pr.flags) return e;
-  return launch_primaries(pr.mask, b.perm, n, pr.flags, pr.plist, pr.nprim, b.scan_tmp,
-                          b.scan_bytes, st);
+                       static_cast<float4*>(b.pos4), b.wsort, sp, b.cell_start, b.blocks);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (!pr.flags) {
+    if (!sp.lists) return hipSuccess;
+    hipLaunchKernelGGL(k_groups, dim3(1), dim3(256), 0, st, sp, b.blocks, b.groups);
+    return hipGetLastError();
+  }
+  return launch_primaries(pr.mask, n, sp, b, pr.flags, pr.plist, pr.nprim, st);
 }
 
 hipError_t launch_region_primaries(const uint8_t* mask, const int32_t* region, int region0,
@@ -860,25 +1159,6 @@ hipError_t launch_region_primaries(const uint8_t* mask, const int32_t* region, i
   if ((e = radix_sort(b, n, int64_t(nregions) + 1, plist, &keys, st)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_region_starts, dim3(blocks_for(int64_t(nregions) + 1, 256)), dim3(256), 0,
                      st, keys, n, nregions, starts, nprim);
-  return hipGetLastError();
-}
-
-hipError_t launch_primaries(const uint8_t* mask, const int* perm, int64_t n, int* flags,
-                            int* plist, long long* nprim, void* scan_tmp, size_t scan_tmp_bytes_,
-                            hipStream_t st) {
-  const unsigned nb = blocks_for(n + 1, 256);
-  if (!mask) {
-    hipLaunchKernelGGL(k_primary_all, dim3(nb), dim3(256), 0, st, flags, n, plist, nprim);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(k_primary_flags, dim3(nb), dim3(256), 0, st, mask, perm, n, flags);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // positions: exclusive scan into flags + (n + 1)
-  int* pos = flags + (n + 1);
-  if ((e = launch_scan(flags, pos, n + 1, scan_tmp, scan_tmp_bytes_, st)) != hipSuccess)
-    return e;
-  hipLaunchKernelGGL(k_primary_list, dim3(nb), dim3(256), 0, st, flags, pos, n, plist, nprim);
   return hipGetLastError();
 }
 

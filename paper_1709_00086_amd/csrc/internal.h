@@ -49,8 +49,8 @@ constexpr int kZetaLists = 32;
 // the 8 XCDs round-robin), each counter on its own 64-byte line.
 constexpr int kQueues = 8;
 constexpr int kQueueStride = 16;
-// further counters on the same line: of either kernel's groups of shells searched
-// together, of such groups that overflowed, and all three of the adjoint
+// further words on the same line: the counter of either kernel's groups of shells
+// searched together, whether any of their shells overflowed, and all three of the adjoint
 constexpr int kQueueListed = 1, kQueueOverflow = 2, kQueueAdjoint = 3, kQueueKinds = 6;
 // Persistent waves of the pair kernel: as many as its occupancy lets run at
 // once on the 256 CUs' SIMDs, at most kPairWaves.
@@ -61,16 +61,25 @@ constexpr int kPairWaves = 4 * kSimds;
 // at once).
 constexpr long long kSplitBelow = 4 * kPairWaves;
 // Pairs the list of a group of shells searched together holds (LDS decides, see
-// WaveLds), and pairs expected in a group: about five standard deviations fewer;
-// a group that holds still more (clustered galaxies) is searched again, shell by
-// shell.  (16 catalogues of 8192, FP32: 6.03 ms a call at a mean of 70, 5.22 at
+// WaveLds), and pairs expected in a group: about five standard deviations fewer.  Where
+// a primary has still more, the search ends early and fewer shells are searched
+// together, at the density it found; a shell that does not fit by itself is left to the
+// launch of the single shells.  (16 catalogues of 8192, FP32: 6.03 ms a call at a mean of 70, 5.22 at
 // 130, 5.05 at 150, 4.99 at 180; FP64 step of 4096: 0.68 ms at 70, 0.63 at 100,
 // 0.79 at 130, where lists overflow.  Longer lists for the cartesian kernels,
 // 368 pairs at a mean of 275, were no gain: 3.24 against 2.85 ms for 40,000
 // galaxies.)
 constexpr int kListMost32 = 224, kListMost64 = 128;
 constexpr double kListMean32 = 150.0, kListMean64 = 85.0;
-constexpr int kListSaves = 3;  // searches a primary that the groups have to save
+constexpr double kListSlack = 1.06;  // over the mean, in the measured density's favour
+constexpr float kListClusters = 25.0f;  // size of clusters above which nothing is listed
+// Searches a primary that the groups have to save: where every shell fits a list, and
+// where some do not and a second launch searches them.  (100,000 primaries of 818 pairs,
+// four saved and five dense shells, l_max 4: 1517 us forward and 2600 the adjoint,
+// against 1575 and 2216 shell by shell; 16384 of 274 in a fifth of the box, four saved:
+// 450 against 411.  100,003 of 503 in 20 shells, eight saved and ten dense ones: 3.5 ms
+// against 3.9.)
+constexpr int kListSaves = 3, kListSavesDense = 5;
 // Spill-list entries per wave: a shell's secondaries kept for the later
 // accumulator chunks of a multi-chunk basis.
 constexpr int kSpillCap = 1 << 14;
@@ -160,6 +169,34 @@ struct RowLayout {
 
 RowLayout make_layout(int lmax, int nb);
 
+// Groups of neighbouring shells: first the nsingle ones of a shell of its own, then
+// those searched together.
+struct GroupTable {
+  int ngroup, nsingle;
+  float density;             // pairs expected per dr^3 of volume (dr: width of a shell),
+  float excess;              // and besides them in the innermost shells
+  int range[kMaxBins];       // first shell of the group | last << 8
+};
+// How a catalogue's table is formed (host part).
+struct ShellPlan {
+  int lists;                 // 0: no table
+  int nbins;
+  int cart;
+  float density;             // at the catalogue's mean over the declared box
+  float most;                // pairs expected in a group at most
+  // blocks of cells of about R_max, and runs of cells along x of about R_max / 8: from
+  // the galaxies that share one with a galaxy follows the density around galaxies
+  int nc[3];                 // cells along each axis
+  int side[3], count[3];     // cells of a block and blocks along each axis
+  int blocks, rows;          // blocks, and rows of cells whose runs are counted
+  int run;                   // cells of a run
+  float n;                   // galaxies
+  float in_block, in_run;    // others that share a galaxy's in a uniform catalogue
+};
+constexpr int kCrowdBlocks = 2048;
+constexpr int kCrowdWords = 3 * kCrowdBlocks;  // counts, and two sums a row
+ShellPlan shell_plan(const g3pcf_problem& p, const Grid& g);
+
 // Arguments of the pair kernels (forward accumulation and adjoint scatter).
 struct PairArgs {
   const void* pos4;          // [n + kSentinel] (x, y, z, w) in cell order, float4 or double4
@@ -182,12 +219,13 @@ struct PairArgs {
   // FP32 shell test: shell b holds r^2 with r2_lo[b] < r^2 < r2_hi[b] (floats
   // next to the squared shell edges, so the shells partition the floats)
   float r2_lo[kMaxBins], r2_hi[kMaxBins];
-  // groups of neighbouring shells, group g being shells group_lo[g]..group_hi[g]:
-  // first the nsingle ones of a shell of its own, then those searched together
-  int ngroup, nsingle;
-  int group_lo[kMaxBins], group_hi[kMaxBins];
-  unsigned* overflow;        // [*nprim] per primary the groups (bits) that did not fit the list
-  int primary_terms;         // adjoint: this launch adds the primaries' own terms
+  // whether shells may be searched together: which are is in the table (device);
+  // without, every shell is a group of its own
+  int lists;
+  const GroupTable* groups;
+  float list_mean;           // pairs expected in shells searched together, at most
+  unsigned* overflow;        // [*nprim] per primary the shells (bits) that did not fit the
+                             // list, from the launch of groups to the one after it
   int nbins;
   int lmax;
   int los;                   // 0 z, 1 observer
@@ -219,6 +257,8 @@ struct CellBufs {
   int* perm;           // [n] out: cell-order slot -> input index
   int* hist;           // [2 radix_hist_ints(n)] scratch: digit counts and offsets
   double* wsort;       // [n] out: FP64 weights in cell order
+  int* blocks;         // [kCrowdWords] scratch (n > kSmallN): see ShellPlan
+  GroupTable* groups;  // out, where a ShellPlan asks for it
   void* scan_tmp;      // scan scratch for max(ncell + 1, n + 1, radix_hist_ints(n)) entries
   size_t scan_bytes;
 };
@@ -247,6 +287,7 @@ struct Primaries {
 // 700, 40 at 4096, 52 at 6000 and 66 at 8192 galaxies, against 56 us for the
 // general path's launches at any of these sizes.
 constexpr int kSmallN = 6144;
+static_assert(kCrowdWords <= kSmallN + 2, "half of the flags of a larger catalogue");
 // Catalogues of a batch of at most kBatchN galaxies take the cell stage together,
 // a workgroup each (16 of about 8192: 1160 us of kernels one after the other, 100 us
 // in one launch), and their Gram products (see ZetaArgs::cats): the call 4.50 and
@@ -256,11 +297,13 @@ constexpr int kBatchN = 16384;
 constexpr int kBatchGroup = 16;
 // Head of a catalogue of a group: kCatStride 8-byte words, the first its primaries,
 // word kCatFirst its first row in the group and kCatParts the Gram blocks a call of its
-// own has room for; the rest its pair kernels' counters.
-constexpr int kCatStride = 72;
-constexpr int kCatFirst = 2, kCatParts = 3;
+// own has room for, from kCatGroups on its GroupTable; the rest its pair kernels'
+// counters.
+constexpr int kCatStride = 88;  // (whole lines of 64 bytes)
+constexpr int kCatFirst = 2, kCatParts = 3, kCatGroups = 4;
 struct BatchCat {
   Grid grid;
+  ShellPlan plan;
   int64_t first, n;          // galaxies first..first + n - 1 of the call's catalogue
   int64_t cells_at;          // its cell_start in b.cell_start
   int parts;                 // see kCatParts
@@ -268,15 +311,11 @@ struct BatchCat {
 hipError_t launch_cells_batch(const g3pcf_problem& p, const BatchCat* cats, int ncat,
                               const CellBufs& b, int* flags, int* plist, long long* head,
                               int fp64, hipStream_t st);
-// The cell list, the primary list and the pass's clears.
-hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const CellBufs& b,
-                        const Primaries& pr, Clears z, int fp64, hipStream_t st);
-// Primary list (cell order): galaxies in the mask (NULL: all).  Leaves flags zero
-// (see PairArgs::overflow).
-hipError_t launch_primaries(const uint8_t* mask, const int* perm, int64_t n, int* flags,
-                            int* plist, long long* nprim, void* scan_tmp, size_t scan_tmp_bytes,
-                            hipStream_t st);
-// The same for the galaxies with region0 <= region[i] < region0 + nregions, by
+// The cell list, the table of groups of shells, the primary list and the pass's clears.
+hipError_t launch_cells(const g3pcf_problem& p, const Grid& g, const ShellPlan& sp,
+                        const CellBufs& b, const Primaries& pr, Clears z, int fp64,
+                        hipStream_t st);
+// Primary list for the galaxies with region0 <= region[i] < region0 + nregions, by
 // region and within one in cell order: region r's are plist[starts[r - region0]] to
 // plist[starts[r - region0 + 1] - 1].  nregions <= n; starts shares flags' second
 // half.

@@ -27,7 +27,7 @@
 //   4. reduces the per-lane partials once per (primary, shell) with DPP and
 //      converts the shell's monomial sums to a_lm in FP64.
 // Sparse neighbouring shells are searched together: a group of shells that is
-// expected to hold few pairs (PairArgs::group) is searched once, into a list in
+// expected to hold few pairs (GroupTable) is searched once, into a list in
 // LDS, and steps 2 and 3 then read the list for each of its shells.
 // No neighbour list ever leaves the compute unit.  A basis whose sums do not
 // fit in registers at once is accumulated in chunks: the first chunk's
@@ -326,13 +326,15 @@ constexpr int n_chunks(ChunkList<C...>) {
 // KIND: kKindSingle, every group of shells is one shell, whose pairs are
 // accumulated as its search finds them; kKindListed, the launch's groups are
 // searched into the list; kKindAfter, as the first, after a launch of the
-// second: also the groups that did not fit the list.  (A kernel that does more
+// second: also the shells that did not fit the list.  (A kernel that does more
 // than the first needs registers for it: 4 to 7% slower on a large catalogue.)
 enum { kKindSingle, kKindListed, kKindAfter };
 template <typename Real, int BASIS, bool ADJOINT, int DEG, bool kRot, bool kMin, int KIND>
 struct PairKernel {
   static constexpr bool kListed = KIND == kKindListed;
   using V = typename V4<Real>::T;
+  // (constant memory: read into scalar registers)
+  using Groups = const __attribute__((address_space(4))) GroupTable*;
   static constexpr bool kF32 = std::is_same<Real, float>::value;
   // FP32 adjoint: terms wait in LDS for their atomic additions
   static constexpr bool kSpinT = Occ<Real, BASIS, ADJOINT, DEG>::kSpinT;
@@ -635,8 +637,9 @@ struct PairKernel {
   }
 
   // One search of the shells b..b_last over the annulus [r0, r1).
-  // kListed: the accepted pairs are written to the list (those past its end are
-  // only counted).  Else b = b_last, and every one is
+  // kListed: the accepted pairs are written to the list; a search that finds more
+  // than it holds ends early, and `whole` is then about how many pairs there are.
+  // Else b = b_last, and every one is
   // appended to the LDS ring as (separation, weight or index), and every full
   // wave of pairs is handed to consume(entry, index, valid) (one pair per
   // lane; the index only with SPILL); the
@@ -646,7 +649,7 @@ struct PairKernel {
   static __device__ __forceinline__ unsigned search(const PairArgs& a, Lds& W,
                                                     const V* __restrict__ pos4, const Primary& P,
                                                     int b, int b_last, double r0, double r1,
-                                                    Consume&& consume) {
+                                                    float& whole, Consume&& consume) {
     const int lane = threadIdx.x % kWave;
     const int* __restrict__ cs = a.cell_start;
     int c0[3] = {0, 0, 0}, c1[3] = {0, 0, 0};
@@ -784,6 +787,18 @@ struct PairKernel {
         qa = load_galaxy(pos4, ja);
         if constexpr (ADJOINT) __builtin_amdgcn_s_setprio(1);
         step(qb, refb, jb, v0 + kWave);
+        if constexpr (kListed) {
+          if (accepted > unsigned(Lds::kEntries)) {
+            // the rows go through the sphere from its lowest z up: at a fraction q of
+            // them, 3 q^2 - 2 q^3 of its volume
+            const float rows = float(rb) + float(min(nrows - rb, kWave)) *
+                                               (float(min(v0 + 2 * kWave, total)) / float(total));
+            const float q = fminf(rows / float(nrows), 1.0f);
+            whole = float(accepted) / (q * q * (3.0f - 2.0f * q));
+            rb = nrows;
+            break;
+          }
+        }
       }
       wave_lds_fence();
     }
@@ -949,7 +964,8 @@ struct PairKernel {
       list_shell(a, W, b, found, consume);
       return 0;
     } else {
-      return search<MINIMG, false>(a, W, pos4, P, b, b, r0, r1, consume);
+      float whole;
+      return search<MINIMG, false>(a, W, pos4, P, b, b, r0, r1, whole, consume);
     }
   }
 
@@ -988,8 +1004,9 @@ struct PairKernel {
         };
         if (kMulti && !kListed && first && cap > 0) {
           int nsp = 0;
+          float whole;
           got = search<MINIMG, kMulti && !kListed>(
-              a, W, pos4, P, b, b, r0, r1, [&](const V& e, int j, bool valid) {
+              a, W, pos4, P, b, b, r0, r1, whole, [&](const V& e, int j, bool valid) {
                 if (valid && nsp + lane < cap) sp[nsp + lane] = j;
                 nsp += __popcll(ballot(valid));
                 add(e);
@@ -1123,18 +1140,25 @@ struct PairKernel {
     // counters in one load before it adds to another's (4096 waves that each
     // tried all eight counters in turn took 60 us to end).
     // groups of this launch: the searched together, or the single shells; then,
-    // where some primary's list overflowed, also all groups again (the shells of
-    // those that did)
-    int mine = a.nsingle;
-    if constexpr (kListed) {
-      mine = a.ngroup - a.nsingle;
-    } else if constexpr (KIND == kKindAfter) {
-      bool any = false;
-      if (lane < kQueues) any = a.queue[lane * kQueueStride + (kListed ? kQueueOverflow - kQueueListed : kQueueOverflow)] != 0;
-      if (ballot(any) != 0) mine = a.ngroup;
+    // where a shell of some primary did not fit the list, also all groups again (for
+    // those shells)
+    int mine = nb, nsingle = nb;
+    bool terms = true;  // adjoint: this launch adds the primaries' own terms
+    const Groups table = (Groups)(a.groups);
+    if constexpr (KIND != kKindSingle) {
+      const int ngroup = table->ngroup;
+      mine = nsingle = table->nsingle;
+      if constexpr (kListed) {
+        mine = ngroup - nsingle;
+      } else {
+        bool any = false;
+        if (lane < kQueues) any = a.queue[lane * kQueueStride + kQueueOverflow] != 0;
+        if (ballot(any) != 0) mine = ngroup;
+        terms = nsingle == ngroup;  // (else the launch of groups did)
+      }
     }
     if (mine == 0) return;
-    const int g_first = kListed ? a.nsingle : 0;
+    const int g_first = kListed ? nsingle : 0;
     const int per = NP < kSplitBelow ? mine : 1;  // items of a primary
     const int grid = int(gridDim.x);
     const long long share = (NP + kQueues - 1) / kQueues;
@@ -1249,7 +1273,7 @@ struct PairKernel {
       double w_prim = 0.0;
       if constexpr (ADJOINT) {
         w_prim = a.wsort[slot];
-        if (item == 0 && a.primary_terms) primary_term(a, row, slot);
+        if (item == 0 && terms) primary_term(a, row, slot);
       }
 
       // annulus of a shell, widened by the search margin on both sides
@@ -1259,36 +1283,76 @@ struct PairKernel {
       };
       int next = items;
       const int first = share_waves(x);
-      unsigned over = 0;
+      unsigned over = 0;  // shells left to the launch of the single shells
+      // pairs of this primary per dr^3 of volume: the catalogue's mean, until a search
+      // finds more
+      float dens = kListed ? table->density : 0.0f;
       if constexpr (KIND == kKindAfter) {
-        if (mine > a.nsingle) over = unsigned(uniform_int(int(a.overflow[a.p_begin + qi])));
+        if (mine > nsingle) over = unsigned(uniform_int(int(a.overflow[a.p_begin + qi])));
       }
       for (int g = g_hi; g >= g_lo; --g) {
         // every shell is a group of its own where none are searched together
-        const int b0 = KIND == kKindSingle ? g : uniform_int(a.group_lo[g]);
-        const int b1 = KIND == kKindSingle ? g : uniform_int(a.group_hi[g]);
+        const int range = KIND == kKindSingle ? g | g << 8 : uniform_int(table->range[g]);
+        const int b0 = range & 255, b1 = range >> 8;
+        if constexpr (KIND == kKindAfter) {
+          // the mask is left clear for the next kernel: which shells overflow depends on
+          // the windows in which a search that ends early took its candidates
+          const unsigned mask = over & ((2u << b1) - (1u << b0));
+          if (g >= nsingle && mask && lane == 0) atomicAnd(a.overflow + a.p_begin + qi, ~mask);
+        }
         // the wave's next item is asked for before its last group
         if (g == g_lo && items > first && lane == 0)
           next = first + atomicAdd(a.queue + x * kQueueStride, 1);
-        int found = 0;
-        if constexpr (kListed) {
-          found = int(search<kF32 && kMin, false>(a, W, pos4, P, b0, b1, inner(b0), outer(b1),
-                                                  [](const V&, int, bool) {}));
-          if (found > Lds::kEntries) {
-            // left to the launch of the single shells
-            if (lane == 0) {
-              atomicOr(a.overflow + a.p_begin + qi, 1u << g);
-              atomicAdd(a.queue + x * kQueueStride + (kListed ? kQueueOverflow - kQueueListed : kQueueOverflow), 1);
+        // KIND == kKindListed: the group's outermost shells that the list is expected
+        // to hold, or one, then the next ones
+        for (int top = b1; top >= b0;) {
+          int low = b0, found = 0;
+          if constexpr (kListed) {
+            auto volume = [&](int c) {  // of the shells c..top, in dr^3
+              const float u = float(top + 1), v = float(c);
+              return u * u * u - v * v * v;
+            };
+            auto expected = [&](int c) {
+              return dens * volume(c) + (c == 0 ? table->excess : 0.0f);
+            };
+            low = top;
+            while (low > b0 && expected(low - 1) <= a.list_mean) --low;
+            low = uniform_int(low);
+            found = Lds::kEntries + 1;
+            if (expected(low) <= float(Lds::kEntries)) {
+              float whole = 0.0f;
+              found = int(search<kF32 && kMin, false>(a, W, pos4, P, low, top, inner(low),
+                                                      outer(top), whole,
+                                                      [](const V&, int, bool) {}));
+              if (found > Lds::kEntries) {
+                dens = fmaxf(dens, uniform_real(
+                                       (whole - (low == 0 ? table->excess : 0.0f)) / volume(low)));
+                if (low < top) continue;
+              }
             }
-            continue;
+            if (found > Lds::kEntries) {
+              // left to the launch of the single shells
+              over |= 1u << top;
+              --top;
+              continue;
+            }
+            my_pairs += unsigned(found);
           }
-          my_pairs += unsigned(found);
-        } else if constexpr (KIND == kKindAfter) {
-          if (g >= a.nsingle && ((over >> g) & 1u) == 0) continue;
+          for (int bb = top; bb >= low; --bb) {
+            const int b = uniform_int(bb);  // in a scalar register throughout the shell
+            if constexpr (KIND == kKindAfter) {
+              if (g >= nsingle && ((over >> b) & 1u) == 0) continue;
+            }
+            my_pairs += shell(a, W, pos4, P, b, inner(b), outer(b), found, row, w_prim, sp);
+          }
+          top = low - 1;
         }
-        for (int bb = b1; bb >= b0; --bb) {
-          const int b = uniform_int(bb);  // in a scalar register throughout the shell
-          my_pairs += shell(a, W, pos4, P, b, inner(b), outer(b), found, row, w_prim, sp);
+      }
+      if constexpr (kListed) {
+        if (over && lane == 0) {
+          // (in a launch of single groups, another wave may hold the primary too)
+          atomicOr(a.overflow + a.p_begin + qi, over);
+          a.queue[x * kQueueStride + kQueueOverflow - kQueueListed] = 1;
         }
       }
       t = uniform_int(__shfl(next, 0));
@@ -1533,7 +1597,7 @@ template <typename Real, int BASIS, bool ADJOINT, int DEG, bool ROT, bool MIN, i
 hipError_t launch_groups(const PairArgs& a, hipStream_t st) {
   // a wave per primary, or per primary and group where they may be handed out so;
   // no more than run at once (the waves' first items are dealt out in advance)
-  const long long items = a.p_count < kSplitBelow ? a.p_count * a.ngroup : a.p_count;
+  const long long items = a.p_count < kSplitBelow ? a.p_count * a.nbins : a.p_count;
   const long long want = (items + kWavesPerBlock - 1) / kWavesPerBlock;
   constexpr int kWaves = Occ<Real, BASIS, ADJOINT, DEG>::value * kSimds;
   static_assert(kWaves <= kPairWaves, "spill lists of every wave");
@@ -1549,18 +1613,17 @@ hipError_t launch_groups(const PairArgs& a, hipStream_t st) {
 }
 
 // The groups of sparse shells, then the single shells (a tight box has no groups:
-// see shell_groups in api.hip).
+// see shell_plan in cells.hip).
 template <typename Real, int BASIS, bool ADJOINT, int DEG, bool ROT, bool MIN>
 hipError_t launch_mode(const PairArgs& a, hipStream_t st) {
   if constexpr (!MIN) {
-    if (a.nsingle < a.ngroup) {
-      PairArgs after = a, listed = a;
+    if (a.lists) {
+      PairArgs listed = a;
       listed.queue += kQueueListed;
-      after.primary_terms = 0;
       const hipError_t e =
           launch_groups<Real, BASIS, ADJOINT, DEG, ROT, MIN, kKindListed>(listed, st);
       if (e != hipSuccess) return e;
-      return launch_groups<Real, BASIS, ADJOINT, DEG, ROT, MIN, kKindAfter>(after, st);
+      return launch_groups<Real, BASIS, ADJOINT, DEG, ROT, MIN, kKindAfter>(a, st);
     }
   }
   return launch_groups<Real, BASIS, ADJOINT, DEG, ROT, MIN, kKindSingle>(a, st);
