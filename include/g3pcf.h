@@ -96,7 +96,8 @@ typedef enum {
   G3PCF_STAGE_ZETA = 2,         /* Gram products on MFMA + FP64 accumulation       */
   G3PCF_STAGE_ADJ_COEF = 3,     /* adjoint: U, V, H and monomial coefficients      */
   G3PCF_STAGE_PAIR_ADJOINT = 4, /* adjoint pair kernel: polynomial + scatter        */
-  G3PCF_STAGE_DISTINCT = 5      /* degenerate-triangle pass, sums and correction   */
+  G3PCF_STAGE_DISTINCT = 5      /* degenerate-triangle sums and correction (with the
+                                   cartesian basis also their pass over the pairs) */
 } g3pcf_stage;
 
 /* Opaque record of per-stage GPU time.  Created on the current device. */
@@ -136,7 +137,8 @@ typedef struct {
                               secondary on both sides, b1 = b2).  1: leave them
                               out, i.e. subtract sum_i w_i sum_j w_j^2
                               conj(Y_lm(u_ij)) Y_l'm(u_ij) at b1 = b2 = b_ij
-                              (a second pass over the pairs; forward only:
+                              (with the cartesian basis a second pass over the
+                              pairs, with the spin basis in the same; forward only:
                               g3pcf_backward returns G3PCF_EUNSUPPORTED)     */
   void* alm;               /* DEVICE buffer or NULL: the a_lm store, i.e. the
                               forward pass's a_lm kept for the backward pass (the
@@ -249,7 +251,7 @@ int g3pcf_forward_regions(const g3pcf_problem* prob, const int32_t* region, int 
  * paper's downstream use (Sec. 6.1): catalogue c is the galaxies
  * [offsets[c], offsets[c+1]) of prob's arrays (positions, weights and, if set,
  * primary_mask), and its zeta goes to zeta + c * g3pcf_zeta_len, computed as
- * g3pcf_forward would for that catalogue alone (pairs never cross
+ * g3pcf_forward would for that catalogue alone, to the bit (pairs never cross
  * catalogues).  offsets: HOST [ncat+1], offsets[0] = 0, non-decreasing,
  * offsets[ncat] = n.  zeta: device [ncat][g3pcf_zeta_len] doubles.  ws: at
  * least g3pcf_workspace_bytes(prob, 0) bytes for the whole batch; the
@@ -290,7 +292,7 @@ int g3pcf_isotropic(int lmax, int nbins, const double* zeta, double* iso, void* 
 
 /* Diagnostic, host only, no device use: the degenerate-triangle term
  * conj(Y_lm(u)) Y_l'm(u) (real; it depends on u_z alone) as the library's
- * distinct = 1 correction represents it, a Legendre series in u_z.
+ * distinct = 1 correction represents it, a Chebyshev series in u_z.
  * out: HOST array [lmax+1][lmax+1][lmax+1] as [m][l][l'], zero where l < m or
  * l' < m.  Returns G3PCF_OK or G3PCF_EINVAL (lmax outside 0..10, NULL). */
 int g3pcf_degenerate_term(int lmax, double uz, double* out);

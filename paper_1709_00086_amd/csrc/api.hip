@@ -122,7 +122,7 @@ Ws plan(const g3pcf_problem& p, int backward, int64_t pb_max = kPairBlockMax,
   w.parts = compact ? 4 : zeta_parts(w.lay, w.PB);
   w.room = compact ? w.parts : zeta_room(w.lay, w.PB);
   w.C = take(size_t(w.room) * sum_wm2(w.lay) * 8);
-  // degenerate triangles: per-shell Legendre sums and their per-workgroup partials
+  // degenerate triangles: per-shell Chebyshev sums and their per-workgroup partials
   const bool deg = !backward && p.distinct;
   w.degD = take(deg ? size_t(p.nbins) * (2 * p.lmax + 1) * 8 : 0);
   w.degP = take(deg ? deg_partial_doubles(w.PB, p.nbins, p.lmax) * 8 : 0);
@@ -398,8 +398,8 @@ int forward_tables(const g3pcf_problem& p) {
 }
 
 // List parts of `n` that one launch of the Gram products takes: so many that each
-// has four blocks of partials on average (27 regions of 3700 primaries in one
-// launch each: 5.3 ms of the whole call, in five launches 4.0).
+// has four blocks of partials on average (27 regions of 3700 primaries: 1.84 ms of
+// Gram products and their sums in one launch each, 0.74 in five).
 int lists_at_once(const Ws& w, int n) {
   const int most = std::max(1, std::min(kZetaLists, w.parts / 4));
   const int launches = (n + most - 1) / most;
@@ -800,8 +800,9 @@ int g3pcf_forward_regions(const g3pcf_problem* prob, const int32_t* region, int 
   // pair kernel; then the Gram products of up to kZetaLists regions in a launch.  (As
   // many regions at a time as there are galaxies: their starts share the scan's
   // space.)  27 regions of 3700 primaries as passes of their own took 8.0 ms, of
-  // which 4.9 in pair kernels and 1.4 in waits for each region's count; with a Gram
-  // launch per region 5.3 ms, 1.84 of them Gram products and their sums, now 0.78 of 4.0.
+  // which 4.9 in pair kernels and 1.4 in waits for each region's count; now 4.5, of which
+  // 3.9 in the pair kernel and 0.74 in Gram products and their sums (1.84 with a launch
+  // per region).
   Counters* c = at<Counters>(ws, w.counters);
   int* flags = at<int>(ws, w.flags);
   int* starts = flags + (p.n + 1);
@@ -832,7 +833,8 @@ int g3pcf_forward_batch(const g3pcf_problem* prob, int ncat, const int64_t* offs
     if (offsets[c + 1] < offsets[c]) return fail(G3PCF_EINVAL, "offsets must not decrease");
   if (prob->alm) return fail(G3PCF_EINVAL, "alm store is not kept per catalogue (set it to NULL)");
   const g3pcf_problem& p = *prob;
-  if ((rc = check_workspace(plan(p, 0), ws, ws_bytes))) return rc;
+  const Ws all = plan(p, 0);
+  if ((rc = check_workspace(all, ws, ws_bytes))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = forward_tables(p))) return rc;
   const size_t zlen = g3pcf_zeta_len(p.lmax, p.nbins);
@@ -843,7 +845,6 @@ int g3pcf_forward_batch(const g3pcf_problem* prob, int ncat, const int64_t* offs
   int64_t total = 0;
   // one group or catalogue after another in the same workspace, in stream order
   // (no host synchronisation unless pairs_out asks for the counts)
-  const Ws all = plan(p, 0);
   for (int c = 0; c < ncat; ++c) {
     BatchCat cats[kBatchGroup];
     const int m = batch_group(p, all, offsets, ncat, c, cats);

@@ -895,8 +895,8 @@ Grid make_grid(const g3pcf_problem& p) {
 
 // Which shells may be searched together.  Neighbouring shells whose expected pairs fit
 // the list make one group: a search costs a wave about 10 us of waiting however little
-// it finds (16 catalogues of 8192 with 274 pairs a primary: 5.5 ms of pair kernels shell
-// by shell, 2.6 ms in groups; FP64 step of 4096 with 137 pairs: 422 and 250 us).  Not
+// it finds (16 catalogues of 8192 with 274 pairs a primary: 5.5 ms a call shell by
+// shell, 4.1 in groups; FP64 step of 4096 with 137 pairs: 802 and 607 us).  Not
 // where every shell of every primary can have a wave of its own.  The pairs expected
 // follow from the density around the galaxies, which is the mean over the declared box
 // or (a footprint that fills part of it, clusters) more: the device measures it with

@@ -64,11 +64,11 @@ constexpr long long kSplitBelow = 4 * kPairWaves;
 // WaveLds), and pairs expected in a group: about five standard deviations fewer.  Where
 // a primary has still more, the search ends early and fewer shells are searched
 // together, at the density it found; a shell that does not fit by itself is left to the
-// launch of the single shells.  (16 catalogues of 8192, FP32: 6.03 ms a call at a mean of 70, 5.22 at
-// 130, 5.05 at 150, 4.99 at 180; FP64 step of 4096: 0.68 ms at 70, 0.63 at 100,
-// 0.79 at 130, where lists overflow.  Longer lists for the cartesian kernels,
-// 368 pairs at a mean of 275, were no gain: 3.24 against 2.85 ms for 40,000
-// galaxies.)
+// launch of the single shells.  (16 catalogues of 8192, FP32: 4.74 ms a call at a mean
+// of 70, 4.12 at 130, 4.10 at 150, 4.08 at 180, where a few lists overflow even in
+// a uniform catalogue; FP64 step of 4096: 0.61 ms at 70 and at 85, 0.62 at 100, 0.66
+// at 130.  Longer lists for the cartesian kernels, 368 pairs at a mean of 275, were no
+// gain: 3.24 against 2.85 ms for 40,000 galaxies.)
 constexpr int kListMost32 = 224, kListMost64 = 128;
 constexpr double kListMean32 = 150.0, kListMean64 = 85.0;
 constexpr double kListSlack = 1.06;  // over the mean, in the measured density's favour
@@ -78,7 +78,7 @@ constexpr float kListClusters = 25.0f;  // size of clusters above which nothing 
 // four saved and five dense shells, l_max 4: 1517 us forward and 2600 the adjoint,
 // against 1575 and 2216 shell by shell; 16384 of 274 in a fifth of the box, four saved:
 // 450 against 411.  100,003 of 503 in 20 shells, eight saved and ten dense ones: 3.5 ms
-// against 3.9.)
+// against 3.7.)
 constexpr int kListSaves = 3, kListSavesDense = 5;
 // Spill-list entries per wave: a shell's secondaries kept for the later
 // accumulator chunks of a multi-chunk basis.
@@ -289,9 +289,9 @@ struct Primaries {
 constexpr int kSmallN = 6144;
 static_assert(kCrowdWords <= kSmallN + 2, "half of the flags of a larger catalogue");
 // Catalogues of a batch of at most kBatchN galaxies take the cell stage together,
-// a workgroup each (16 of about 8192: 1160 us of kernels one after the other, 100 us
-// in one launch), and their Gram products (see ZetaArgs::cats): the call 4.50 and
-// 3.67 ms.  Cell ids of 16 bits (the grid has at most 4 n cells) and the workgroup's
+// a workgroup each (16 of about 8192: 1160 us of kernels one after the other, 104 us
+// in one launch), and their Gram products (see ZetaArgs::cats): the call 5.02 and
+// 4.07 ms.  Cell ids of 16 bits (the grid has at most 4 n cells) and the workgroup's
 // LDS, 104 KB here, set the limit.
 constexpr int kBatchN = 16384;
 constexpr int kBatchGroup = 16;

@@ -42,8 +42,8 @@
 // (524,288 primaries of 35135 pairs, FP32 spin: 99 ms at 121 sums a lane and three
 // waves per SIMD); the adjoint, the rate of the atomic adds (151.7 -> 144 ms with
 // more stripes, see run); sparse shells, the instructions and the waits of a search
-// (100,000 primaries of 2640 pairs in 10 shells: 8.9 -> 4.0 ms; 131,072 of 274 pairs
-// in 16 catalogues: 5.5 -> 3.1 ms).
+// (100,000 primaries of 2640 pairs in 10 shells: 8.9 -> 3.9 ms; 131,072 of 274 pairs
+// in 16 catalogues: 5.5 -> 3.0 ms).
 //
 // Included by the pairs_*.hip files, which instantiate the kernels (it opens an
 // anonymous namespace).
@@ -905,18 +905,17 @@ struct PairKernel {
   }
 
   // Stream `count` spilled secondaries of a shell, one per lane, into
-  // body(unit vector, weight, index, valid).  Two batches alternate so that
+  // body(unit vector, weight; 0 past the end).  Two batches alternate so that
   // the next batch's gathers and the batch after that's indices are in flight
   // while one batch is used.
   template <bool MINIMG, typename Body>
-  static __device__ __forceinline__ void replay_all(const PairArgs& a,
-                                                    const V* __restrict__ pos4,
-                                                    const Primary& P, const int* __restrict__ sp,
-                                                    int count, Body&& body) {
+  static __device__ __forceinline__ void replay(const PairArgs& a, const V* __restrict__ pos4,
+                                                const Primary& P, const int* __restrict__ sp,
+                                                int count, Body&& body) {
     if (count <= 0) return;
     const int lane = threadIdx.x % kWave;
     const int last = count - 1;
-    auto use = [&](const V& q, int j, int base) {
+    auto use = [&](const V& q, int base) {
       const bool valid = base + lane < count;
       Real d[3];
       separation<MINIMG>(a, P, q, d);
@@ -926,31 +925,19 @@ struct PairKernel {
       e.z = valid ? d[2] : Real(1);
       Real ux, uy, uz;
       unit(P, e, ux, uy, uz);
-      body(ux, uy, uz, valid ? q.w : Real(0), j, valid);
+      body(ux, uy, uz, valid ? q.w : Real(0));
     };
     int ja = sp[min(lane, last)];
     int jb = sp[min(kWave + lane, last)];
     V qa = load_galaxy(pos4, ja);
     for (int base = 0; base < count; base += 2 * kWave) {
       const V qb = load_galaxy(pos4, jb);
-      const int jn = sp[min(base + 2 * kWave + lane, last)];
-      use(qa, ja, base);
-      ja = jn;
+      ja = sp[min(base + 2 * kWave + lane, last)];
+      use(qa, base);
       qa = load_galaxy(pos4, ja);
-      const int jbb = jb;
       jb = sp[min(base + 3 * kWave + lane, last)];
-      use(qb, jbb, base + kWave);
+      use(qb, base + kWave);
     }
-  }
-
-  template <bool MINIMG, typename Body>
-  static __device__ __forceinline__ void replay(const PairArgs& a, const V* __restrict__ pos4,
-                                                const Primary& P, const int* __restrict__ sp,
-                                                int count, Body&& body) {
-    replay_all<MINIMG>(a, pos4, P, sp, count,
-                            [&](Real ux, Real uy, Real uz, Real w, int, bool) {
-                              body(ux, uy, uz, w);
-                            });
   }
 
   // The pairs of shell b to consume: by a search of its own, or (kListed) from
