@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void k_fma(float* out, int iters, float a0, fl
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_accum(
     float* out, int iters, float c, float s) {
-  SpinSums<kDeg, false> a;
+  SpinSums<float, kDeg, false> a;
   a.zero();
   float x = 0.6f + threadIdx.x * 1e-4f, y = 0.48f, z = 0.64f;
   const float w = 1.0f + threadIdx.x * 1e-5f;

@@ -356,29 +356,30 @@ __device__ __forceinline__ void add_degenerate(Real (&deg)[N], const Real (&t)[D
 
 // Spin sums S_{m,n} = sum w (u_x - i u_y)^m T_n(u_z), m + n <= D, with T_n the
 // Chebyshev polynomials (the conversion to a_lm uses the spin-Chebyshev table).
-// FP32: every lane carries all (D + 1)^2 sums of its own pairs, in term order.
-// (Real and imaginary parts in either half of a wave, as in FP64 below, fit four
-// waves a SIMD at D = 10 instead of three, but a lane then sums twice as many pairs:
+// Every lane carries all (D + 1)^2 sums of its own pairs, in term order.
+// (Real and imaginary parts in either half of a wave, as in FP64 at D = 10 below, fit
+// four FP32 waves a SIMD at D = 10 instead of three, but a lane then sums twice as many pairs:
 // the errors of S_{m,0}, m = 1..3, over 20,000 pairs were 1.4 to 1.5 times these.  The
 // fourth wave is worth 11 to 13% where the search counts, 16 catalogues of 8192
 // in 3.66 against 4.18 ms, and nothing on dense catalogues.  Degrees 4, 6 and 8 have
-// four waves either way and are up to 8% faster unsplit.)
-template <int D, bool DISTINCT>
+// four waves either way and are up to 8% faster unsplit, in FP64 up to 7%, sparse
+// catalogues at D = 8 4% slower.)
+template <typename Real, int D, bool DISTINCT>
 struct SpinSums {
   static constexpr int NT = (D + 1) * (D + 1);
   static constexpr int ND = DISTINCT ? 2 * D + 1 : 1;
-  float acc[NT];
-  float deg[ND];            // sum w^2 T_n(u_z), n <= 2 D (degenerate triangles)
+  Real acc[NT];
+  Real deg[ND];            // sum w^2 T_n(u_z), n <= 2 D (degenerate triangles)
 
   __device__ __forceinline__ void zero() {
 #pragma unroll
-    for (int i = 0; i < NT; ++i) acc[i] = 0.0f;
+    for (int i = 0; i < NT; ++i) acc[i] = Real(0);
 #pragma unroll
-    for (int i = 0; i < ND; ++i) deg[i] = 0.0f;
+    for (int i = 0; i < ND; ++i) deg[i] = Real(0);
   }
 
-  __device__ __forceinline__ void add(float x, float y, float z, float w) {
-    float t[D + 1];
+  __device__ __forceinline__ void add(Real x, Real y, Real z, Real w) {
+    Real t[D + 1];
     chebyshev_z2<D>(z, z + z, t);
     acc[0] += w;
     static_for<D>([&](auto nc) {
@@ -386,11 +387,11 @@ struct SpinSums {
       acc[n] = fma_r(w, t[n], acc[n]);
     });
     if constexpr (DISTINCT) add_degenerate<D>(deg, t, z, w);
-    float cr = w * x, ci = -(w * y);  // w (x - i y)^m
+    Real cr = w * x, ci = -(w * y);  // w (x - i y)^m
     static_for<D>([&](auto mc) {
       constexpr int m = decltype(mc)::value + 1;
       if constexpr (m > 1) times_xy(cr, ci, x, y);
-      float* a = acc + spin_term_c<D>(m, 0, 0);
+      Real* a = acc + spin_term_c<D>(m, 0, 0);
       a[0] += cr;
       a[1] += ci;
       static_for<D - m>([&](auto nc) {
@@ -410,10 +411,10 @@ struct SpinSums {
 // The coefficients are the same for every pair (one set per primary and
 // shell) and are held in vector registers: a multiply-add with a scalar-register
 // operand issues more slowly than one with three vector registers.
-template <int D>
+template <typename Real, int D>
 struct SpinPoly {
   static constexpr int NT = (D + 1) * (D + 1);
-  float g[NT];
+  Real g[NT];
 
   template <typename Ptr>
   __device__ __forceinline__ void load(Ptr gc, int) {
@@ -421,20 +422,20 @@ struct SpinPoly {
     for (int i = 0; i < NT; ++i) g[i] = gc[i];
   }
 
-  __device__ __forceinline__ float eval(float x, float y, float z) const {
-    float t[D + 1];
+  __device__ __forceinline__ Real eval(Real x, Real y, Real z) const {
+    Real t[D + 1];
     chebyshev_z2<D>(z, z + z, t);
-    float total = g[0];
+    Real total = g[0];
     static_for<D>([&](auto nc) {
       constexpr int n = decltype(nc)::value + 1;
       total = fma_r(g[n], t[n], total);
     });
-    float cr = x, ci = -y;  // (x - i y)^m
+    Real cr = x, ci = -y;  // (x - i y)^m
     static_for<D>([&](auto mc) {
       constexpr int m = decltype(mc)::value + 1;
       if constexpr (m > 1) times_xy(cr, ci, x, y);
-      const float* a = g + spin_term_c<D>(m, 0, 0);
-      float hr = a[0], hi = a[1];
+      const Real* a = g + spin_term_c<D>(m, 0, 0);
+      Real hr = a[0], hi = a[1];
       static_for<D - m>([&](auto nc) {
         constexpr int n = decltype(nc)::value + 1;
         hr = fma_r(a[2 * n], t[n], hr);
@@ -489,7 +490,7 @@ struct Exchange {
   }
 };
 
-// The same sums in FP64, of which a lane holds no 121.  For m >= 1 the lower half of the wave holds the real
+// The same sums at D = 10 in FP64, of which a lane holds no 121.  For m >= 1 the lower half of the wave holds the real
 // part of S_{m,n} and the upper half the imaginary part, in one register: 66
 // accumulators instead of 121 at D = 10, which fit two waves per SIMD at once.
 template <int D, bool DISTINCT>
@@ -544,11 +545,10 @@ struct SpinSplit {
   }
 };
 
-// The same polynomial (FP64, and FP32 at D = 10) with the coefficients split as the
-// sums of SpinSplit are (66 registers instead of 121 at D = 10, so four waves a SIMD
-// in FP32: 100,003 primaries of 2640 pairs 5.8 ms, at three waves and unsplit 6.3):
-// each half of the wave evaluates its part of all 64 pairs, and one exchange at the
-// end adds the two.
+// The same polynomial with the coefficients split as the sums of SpinSplit are (66
+// registers instead of 121 at D = 10, so four waves a SIMD in FP32: 100,003 primaries
+// of 2640 pairs 5.8 ms, at three waves and unsplit 6.3): each half of the wave evaluates
+// its part of all 64 pairs, and one exchange at the end adds the two.
 template <typename Real, int D>
 struct SplitPoly {
   static constexpr int NP = D * (D + 1) / 2;
@@ -654,8 +654,8 @@ struct Chunks<Real, kBasisDeg, kDeg> {
   using type = ChunkList<DegChunk<Real>>;
 };
 template <typename Real, int DEG, bool DISTINCT>
-using SpinOf =
-    std::conditional_t<sizeof(Real) == 4, SpinSums<DEG, DISTINCT>, SpinSplit<DEG, DISTINCT>>;
+using SpinOf = std::conditional_t<sizeof(Real) == 4 || DEG != kDeg, SpinSums<Real, DEG, DISTINCT>,
+                                  SpinSplit<DEG, DISTINCT>>;
 template <typename Real, int DEG>
 struct Chunks<Real, G3PCF_BASIS_SPIN, DEG> {
   using type = ChunkList<SpinOf<Real, DEG, false>>;

@@ -297,14 +297,16 @@ struct Bin64 {
 // 512 / target per lane, so every accumulator chunk must fit: four waves for the 81
 // FP32 sums (or coefficients) of degree 8 and below, three for the 121 sums of degree
 // 10 and for the cartesian chunks of 91 to 99, two for FP64.  kSplit: sums or
-// coefficients in the halves of a wave, those of FP64 and the FP32 adjoint's of degree
-// 10, which then also runs at four waves.
+// coefficients in the halves of a wave: the sums only where they fit no other way (FP64,
+// degree 10: see SpinSums), the coefficients where that is faster (FP32 of degree 10,
+// which then also runs at four waves; FP64 of degrees 8 and 10: 30,003 primaries of
+// 2383 pairs at l_max 8 2.5 against 3.0 ms, at l_max 6 2.1 against 2.0 unsplit).
 template <typename Real, int BASIS, bool ADJOINT, int DEG>
 struct Occ {
   static constexpr bool kF32 = std::is_same<Real, float>::value;
   static constexpr bool kSpinT = ADJOINT && kF32;
   static constexpr bool kSplit = (BASIS == G3PCF_BASIS_SPIN || BASIS == kBasisSpinDeg) &&
-                                 (!kF32 || (ADJOINT && DEG == kDeg));
+                                 DEG >= (ADJOINT ? (kF32 ? 10 : 8) : (kF32 ? kDeg + 1 : 10));
   static constexpr int value = !kF32                               ? 2
                                : (BASIS == kBasisDeg)              ? 4
                                : (BASIS == G3PCF_BASIS_CARTESIAN) ? 3
@@ -1038,7 +1040,7 @@ struct PairKernel {
       Real* coef = coef_stage(W);
       shell_coefficients(a, W, coef, row, b);
       wave_lds_fence();
-      std::conditional_t<kSplit, SplitPoly<Real, DEG>, SpinPoly<DEG>> poly;
+      std::conditional_t<kSplit, SplitPoly<Real, DEG>, SpinPoly<Real, DEG>> poly;
       poly.load(coef, lane);
       wave_lds_fence();
       if constexpr (kSpinT) {
@@ -1074,7 +1076,11 @@ struct PairKernel {
                                [&](const V& e, int, bool valid) {
                                  Real ux, uy, uz;
                                  unit(P, e, ux, uy, uz);
-                                 const double v = poly.eval(ux, uy, uz, W.xch(), lane_here());
+                                 double v;
+                                 if constexpr (kSplit)
+                                   v = poly.eval(ux, uy, uz, W.xch(), lane_here());
+                                 else
+                                   v = poly.eval(ux, uy, uz);
                                  if (valid)
                                    unsafeAtomicAdd(&a.grad_w[unpack_index(e.w)], w_prim * v);
                                });
