@@ -455,6 +455,12 @@ struct SpinPoly {
 // an upper one.  Each half carries the power's other part too: with s = y in the
 // lower half and -y in the upper, both follow
 //   own' = own x + other s,   other' = other x - own s.
+__device__ __forceinline__ float flip(float v, int lane) {  // -v in the upper half
+  return __uint_as_float(__float_as_uint(v) ^ (unsigned(lane & 32) << 26));
+}
+__device__ __forceinline__ double flip(double v, int lane) {
+  return __longlong_as_double(__double_as_longlong(v) ^ ((long long)(lane & 32) << 58));
+}
 template <typename Real>
 struct Half {
   Real z, x, s;
@@ -464,19 +470,18 @@ struct Half {
 template <typename Real, bool kWeighted>
 struct Exchange {
   static constexpr int kReals = (kWeighted ? 8 : 4) * kWave;  // per wave
-  typedef Real V2r __attribute__((ext_vector_type(2)));
   typedef Real V4r __attribute__((ext_vector_type(4)));
   static __device__ __forceinline__ void put(Real* s, int lane, Real x, Real y, Real z, Real w) {
-    reinterpret_cast<V4r*>(s)[lane] = V4r{z, x, y, -y};
-    // (the fourth is not read)
+    // (the fourth of either is not read)
+    reinterpret_cast<V4r*>(s)[lane] = V4r{z, x, y, Real(0)};
     if constexpr (kWeighted)
       reinterpret_cast<V4r*>(s)[kWave + lane] = V4r{w * x, -(w * y), w * x, Real(0)};
   }
   // upper: pairs 32..63 instead of 0..31
   static __device__ __forceinline__ Half<Real> get(const Real* s, int lane, bool upper) {
     const int p = (lane & 31) + (upper ? 32 : 0), half = lane >> 5;
-    const V2r a = reinterpret_cast<const V2r*>(s)[2 * p];
-    const Real sy = s[4 * p + 2 + half];
+    const V4r a = reinterpret_cast<const V4r*>(s)[p];
+    const Real sy = flip(a.z, lane);
     if constexpr (kWeighted) {
       const Real* c = s + 4 * (kWave + p) + half;
       return Half<Real>{a.x, a.y, sy, c[0], c[1]};
